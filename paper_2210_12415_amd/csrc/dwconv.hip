@@ -7,9 +7,10 @@
 // the data layout decides how wide the accesses are.
 //
 //  * vector kernel: bf16 tensors whose channel is contiguous in runs of at
-//    least eight on activations, weights and output (NHWC or NCHW[x]c with
-//    channel-last weights): a thread owns eight channels of one output pixel,
-//    every access is 16 bytes;
+//    least eight on activations and output (NHWC or NCHW[x]c), with
+//    channel-last weights or weights whose taps lie side by side (OHWI, OIHW):
+//    a thread owns eight channels of one output pixel, every access to the
+//    activations is 16 bytes
 //    (3x3 filters without dilation get a register-tiled version of it);
 //  * row kernel: bf16 tensors whose width is contiguous on activations and
 //    output (NCHW), 3x3 filters with padding 1 along the width: a thread owns
@@ -20,13 +21,14 @@
 //    threads run along the output's contiguous dimension.
 #include <hip/hip_runtime.h>
 
-#include "igemm.h"
+#include "igemm_dma.h"
 #include "ops.h"
 
 namespace alt {
 namespace {
 
 constexpr int kDwThreads = 256;
+constexpr int kDwCols = 4;    // output columns per thread of the 3x3 vector kernel
 
 struct DwParams {
     const void *x, *w;
@@ -34,8 +36,11 @@ struct DwParams {
     void *y;
     int32_t N, C, H, W, R, S, OH, OW;
     int32_t stride_h, stride_w, pad_h, pad_w, dil_h, dil_w;
-    int32_t epilogue, in_bf16, out_bf16, chan_fast;
+    int32_t epilogue, in_bf16, out_bf16, chan_fast, w_taps;
     Dim2 xn, xc, xh, xw, wo, wr, ws, yn, yk, yh, yw;
+    // 3x3 vector kernel: threads, the divisions of a thread's index, sizes of the tensors
+    uint32_t items, x_bytes, y_bytes;
+    FastDiv fd_c8, fd_owb, fd_ohb;
 };
 
 __device__ __forceinline__ float load_elem(const void *p, int64_t off, int bf16)
@@ -119,7 +124,15 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams 
                 const int iw = ow * p.stride_w - p.pad_w + fs * p.dil_w;
                 if ((unsigned)iw >= (unsigned)p.W) continue;
                 const w4_t xv = *(const w4_t *)((const uint16_t *)p.x + xb + dim2_off(p.xh, ih) + dim2_off(p.xw, iw));
-                const w4_t wv = *(const w4_t *)((const uint16_t *)p.w + wb + dim2_off(p.wr, fr) + dim2_off(p.ws, fs));
+                w4_t wv;
+                if (p.w_taps) {                     // the taps of a channel side by side: element by element
+                    const uint16_t *we = (const uint16_t *)p.w + (int64_t)c * p.R * p.S + fr * p.S + fs;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        wv[q] = (uint32_t)we[(int64_t)2 * q * p.R * p.S] | ((uint32_t)we[(int64_t)(2 * q + 1) * p.R * p.S] << 16);
+                } else {
+                    wv = *(const w4_t *)((const uint16_t *)p.w + wb + dim2_off(p.wr, fr) + dim2_off(p.ws, fs));
+                }
                 lo += __builtin_bit_cast(f4_t, xv << 16) * __builtin_bit_cast(f4_t, wv << 16);
                 hi += __builtin_bit_cast(f4_t, xv & 0xffff0000u) * __builtin_bit_cast(f4_t, wv & 0xffff0000u);
             }
@@ -141,90 +154,117 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams 
     }
 }
 
-// The common case of the vector kernel: 3x3 filter, dilation 1, H and W not blocked.  A thread
-// owns eight channels of TW consecutive output pixels of one row: the nine weight vectors are
-// loaded once, and neighbouring outputs share the input columns of their windows, so a thread
-// makes 3 * ((TW - 1) * STRIDE + 3) + 9 loads for TW outputs instead of 18 per output.
-// (At stride 1 the register count is held to four waves per SIMD: the benchmark layers are 3.4
-// waves per SIMD of work, so every thread is then resident at once; at stride 2 the nine input
-// columns of a row do not fit that budget without spilling.)
-template <int STRIDE, int TW>
-__global__ __launch_bounds__(kDwThreads, STRIDE == 1 ? 4 : 3) void dwconv_vec8_3x3_kernel(const DwParams p)
+// The common case of the vector kernel: 3x3 filter, dilation 1, H and W not blocked, tensors below 2 GiB.  A thread
+// owns eight channels of TH x TW output pixels: the filter is loaded once, and neighbouring outputs share the
+// input pixels of their windows, so a thread makes ((TH-1)*STRIDE+3) * ((TW-1)*STRIDE+3) loads for TH*TW outputs.
+// The kernel is bound by memory: all its loads go through a buffer descriptor (a pixel outside the image gets an
+// out-of-range offset and reads zeros), so no branch keeps them from being in flight together.
+// TAPS: the filter lies tap-contiguous (OHWI, OIHW: the nine taps of a channel side by side), so that eight
+// channels' taps are one run of 72 elements; they are loaded as nine vectors and transposed in registers.
+// Consecutive blocks run on one XCD, so that the rows two blocks share come out of one L2.
+// Measured on 16 x 144 x 56 x 56 (29 MB): 10.0 us, 2.9 TB/s; OHWI filters took the element kernel before, 137 us, and
+// filters with the channel innermost a version of this one with a branch per load and one row per thread, 13.0 us.
+template <int STRIDE, int TW, int TH, bool TAPS>
+__global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const DwParams p)
 {
     typedef uint32_t w4_t __attribute__((ext_vector_type(4)));
     typedef float f4_t __attribute__((ext_vector_type(4)));
-    constexpr int NCOL = (TW - 1) * STRIDE + 3;
-    const int C8 = p.C >> 3, OWB = (p.OW + TW - 1) / TW;
-    const int64_t total = (int64_t)p.N * p.OH * OWB * C8;
-    const int64_t sxh = p.xh.si, sxw = p.xw.si, syh = p.yh.si, syw = p.yw.si;
-    for (int64_t e = blockIdx.x * (int64_t)kDwThreads + threadIdx.x; e < total; e += (int64_t)gridDim.x * kDwThreads) {
-        int c, ow0, oh, n;
-        if (total <= 0x7fffffff) {                  // 32-bit divisions cost a fraction of 64-bit ones
-            uint32_t r = (uint32_t)e;
-            c = (int)(r % (uint32_t)C8) * 8; r /= (uint32_t)C8;
-            ow0 = (int)(r % (uint32_t)OWB) * TW; r /= (uint32_t)OWB;
-            oh = (int)(r % (uint32_t)p.OH);
-            n = (int)(r / (uint32_t)p.OH);
-        } else {
-            int64_t r = e;
-            c = (int)(r % C8) * 8; r /= C8;
-            ow0 = (int)(r % OWB) * TW; r /= OWB;
-            oh = (int)(r % p.OH);
-            n = (int)(r / p.OH);
+    constexpr int NCOL = (TW - 1) * STRIDE + 3, NROW = (TH - 1) * STRIDE + 3;
+    const uint32_t e = (uint32_t)igemm_logical_tile((int)gridDim.x) * kDwThreads + threadIdx.x;
+    if (e >= p.items) return;
+    uint32_t r = fast_div(e, p.fd_c8);
+    const int c = (int)(e - r * p.fd_c8.d) * 8;
+    const uint32_t r2 = fast_div(r, p.fd_owb);
+    const int ow0 = (int)(r - r2 * p.fd_owb.d) * TW;
+    const int n = (int)fast_div(r2, p.fd_ohb);
+    const int oh0 = (int)(r2 - (uint32_t)n * p.fd_ohb.d) * TH;
+
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, (int)p.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)p.y_bytes, 0x00020000);
+    w4_t wv[9];                                     // kept packed: unpacked where used, half the registers
+    if constexpr (TAPS) {
+        const w4_t *wp = (const w4_t *)((const uint16_t *)p.w + c * 9);
+        uint32_t raw[36];
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            const w4_t d = wp[v];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) raw[v * 4 + q] = d[q];
         }
-        const uint16_t *xb = (const uint16_t *)p.x + dim2_off(p.xn, n) + dim2_off(p.xc, c);
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {           // channels 2q and 2q + 1 of tap t
+                const int a = 2 * q * 9 + t, b = a + 9;
+                wv[t][q] = __builtin_amdgcn_perm(raw[b / 2], raw[a / 2], ((b & 1) ? 0x07060000u : 0x05040000u) | ((a & 1) ? 0x0302u : 0x0100u));
+            }
+    } else {
         const uint16_t *wb = (const uint16_t *)p.w + dim2_off(p.wo, c);
-        w4_t wv[9];                                 // kept packed: unpacked where used, half the registers
 #pragma unroll
         for (int t = 0; t < 9; ++t) wv[t] = *(const w4_t *)(wb + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3));
-        f4_t lo[TW], hi[TW];
+    }
+    f4_t lo[TH][TW], hi[TH][TW];
 #pragma unroll
-        for (int j = 0; j < TW; ++j) { lo[j] = (f4_t){0.f, 0.f, 0.f, 0.f}; hi[j] = (f4_t){0.f, 0.f, 0.f, 0.f}; }
-        const int ih0 = oh * STRIDE - p.pad_h, iw0 = ow0 * STRIDE - p.pad_w;
+    for (int i = 0; i < TH; ++i)
 #pragma unroll
-        for (int fr = 0; fr < 3; ++fr) {
-            const int ih = ih0 + fr;
-            if ((unsigned)ih >= (unsigned)p.H) continue;
-            const uint16_t *row = xb + ih * sxh;
-            f4_t xlo[NCOL], xhi[NCOL];
+        for (int j = 0; j < TW; ++j) { lo[i][j] = (f4_t){0.f, 0.f, 0.f, 0.f}; hi[i][j] = (f4_t){0.f, 0.f, 0.f, 0.f}; }
+    const int ih0 = oh0 * STRIDE - p.pad_h, iw0 = ow0 * STRIDE - p.pad_w;
+    const int32_t xb = dim2_off32(p.xn, n) + dim2_off32(p.xc, c), sxh = (int32_t)p.xh.si, sxw = (int32_t)p.xw.si;
+    uint32_t col[NCOL];                             // byte offset of each input column, out of range outside the image
 #pragma unroll
-            for (int q = 0; q < NCOL; ++q) {
-                const int iw = iw0 + q;
-                w4_t xv = {0u, 0u, 0u, 0u};
-                if ((unsigned)iw < (unsigned)p.W) xv = *(const w4_t *)(row + iw * sxw);
-                xlo[q] = __builtin_bit_cast(f4_t, xv << 16);
-                xhi[q] = __builtin_bit_cast(f4_t, xv & 0xffff0000u);
-            }
+    for (int q = 0; q < NCOL; ++q)
+        col[q] = (unsigned)(iw0 + q) < (unsigned)p.W ? (uint32_t)(xb + (iw0 + q) * sxw) * 2u : kOutOfRange;
+#pragma unroll
+    for (int fr = 0; fr < NROW; ++fr) {
+        const int ih = ih0 + fr;
+        const bool row_ok = (unsigned)ih < (unsigned)p.H;
+        const uint32_t row = (uint32_t)(ih * sxh) * 2u;
+        w4_t xv[NCOL];
+#pragma unroll
+        for (int q = 0; q < NCOL; ++q)
+            xv[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(row_ok && col[q] != kOutOfRange ? col[q] + row : kOutOfRange), 0, 0);
+        f4_t xlo[NCOL], xhi[NCOL];
+#pragma unroll
+        for (int q = 0; q < NCOL; ++q) {
+            xlo[q] = __builtin_bit_cast(f4_t, xv[q] << 16);
+            xhi[q] = __builtin_bit_cast(f4_t, xv[q] & 0xffff0000u);
+        }
+#pragma unroll
+        for (int i = 0; i < TH; ++i) {
+            const int wr = fr - i * STRIDE;         // this input row's place in output row i's window
+            if (wr < 0 || wr >= 3) continue;
 #pragma unroll
             for (int fs = 0; fs < 3; ++fs) {
-                const f4_t wl = __builtin_bit_cast(f4_t, wv[fr * 3 + fs] << 16);
-                const f4_t wh = __builtin_bit_cast(f4_t, wv[fr * 3 + fs] & 0xffff0000u);
+                const f4_t wl = __builtin_bit_cast(f4_t, wv[wr * 3 + fs] << 16);
+                const f4_t wh = __builtin_bit_cast(f4_t, wv[wr * 3 + fs] & 0xffff0000u);
 #pragma unroll
                 for (int j = 0; j < TW; ++j) {
-                    lo[j] += xlo[j * STRIDE + fs] * wl;
-                    hi[j] += xhi[j * STRIDE + fs] * wh;
+                    lo[i][j] += xlo[j * STRIDE + fs] * wl;
+                    hi[i][j] += xhi[j * STRIDE + fs] * wh;
                 }
             }
         }
-        f4_t blo = {0.f, 0.f, 0.f, 0.f}, bhi = {0.f, 0.f, 0.f, 0.f};
-        if (p.epilogue & ALT_EPI_BIAS) {
-            const f4_t b0 = *(const f4_t *)(p.bias + c), b1 = *(const f4_t *)(p.bias + c + 4);
-            blo = __builtin_shufflevector(b0, b1, 0, 2, 4, 6);
-            bhi = __builtin_shufflevector(b0, b1, 1, 3, 5, 7);
-        }
-        const float floor_ = (p.epilogue & ALT_EPI_RELU) ? 0.f : -INFINITY;
-        uint16_t *yb = (uint16_t *)p.y + dim2_off(p.yn, n) + dim2_off(p.yk, c) + oh * syh;
+    }
+    f4_t blo = {0.f, 0.f, 0.f, 0.f}, bhi = {0.f, 0.f, 0.f, 0.f};
+    if (p.epilogue & ALT_EPI_BIAS) {
+        const f4_t b0 = *(const f4_t *)(p.bias + c), b1 = *(const f4_t *)(p.bias + c + 4);
+        blo = __builtin_shufflevector(b0, b1, 0, 2, 4, 6);
+        bhi = __builtin_shufflevector(b0, b1, 1, 3, 5, 7);
+    }
+    const float floor_ = (p.epilogue & ALT_EPI_RELU) ? 0.f : -INFINITY;
+    const int32_t yb = dim2_off32(p.yn, n) + dim2_off32(p.yk, c), syh = (int32_t)p.yh.si, syw = (int32_t)p.yw.si;
+#pragma unroll
+    for (int i = 0; i < TH; ++i)
 #pragma unroll
         for (int j = 0; j < TW; ++j) {
-            if (ow0 + j >= p.OW) break;
-            const f4_t a = __builtin_elementwise_max(lo[j] + blo, (f4_t){floor_, floor_, floor_, floor_});
-            const f4_t b = __builtin_elementwise_max(hi[j] + bhi, (f4_t){floor_, floor_, floor_, floor_});
+            const bool ok = ow0 + j < p.OW && oh0 + i < p.OH;
+            const f4_t a = __builtin_elementwise_max(lo[i][j] + blo, (f4_t){floor_, floor_, floor_, floor_});
+            const f4_t b = __builtin_elementwise_max(hi[i][j] + bhi, (f4_t){floor_, floor_, floor_, floor_});
             w4_t out;
 #pragma unroll
             for (int q = 0; q < 4; ++q) out[q] = f32x2_to_bf16x2(a[q], b[q]);
-            *(w4_t *)(yb + (ow0 + j) * syw) = out;
+            __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + (oh0 + i) * syh + (ow0 + j) * syw) * 2u : kOutOfRange), 0, 0);
         }
-    }
 }
 
 // bf16 in and out, width contiguous, 3x3 without dilation, padding 1 along the width, W and OW multiples of TW
@@ -339,13 +379,36 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
     p.yn = q.yn; p.yk = q.yk; p.yh = q.yh; p.yw = q.yw;
     p.chan_fast = q.yk.si == 1;
     const Dim2 xo[3] = {q.xn, q.xh, q.xw}, wo_[2] = {q.wr, q.ws}, yo[3] = {q.yn, q.yh, q.yw};
-    const bool vec = p.in_bf16 && p.out_bf16 && chan_runs_of_8(q.xc, C, xo, 3) && chan_runs_of_8(q.wo, C, wo_, 2) &&
+    // filters: eight channels a 16-byte run per tap, or (taps) the taps of a channel side by side
+    const bool taps = q.wo.f >= C && q.wo.si == q.R * q.S && q.wr.f >= q.R && q.wr.si == q.S && q.ws.f >= q.S && q.ws.si == 1;
+    const bool vec = p.in_bf16 && p.out_bf16 && chan_runs_of_8(q.xc, C, xo, 3) && (taps || chan_runs_of_8(q.wo, C, wo_, 2)) &&
                      chan_runs_of_8(q.yk, C, yo, 3) && (uintptr_t)q.x % 16 == 0 && (uintptr_t)q.w % 16 == 0 &&
                      (uintptr_t)q.y % 16 == 0 && (!(q.epilogue & ALT_EPI_BIAS) || (uintptr_t)q.bias % 16 == 0);
-    constexpr int kTW = 4;
     const bool k3x3 = vec && q.R == 3 && q.S == 3 && q.dil_h == 1 && q.dil_w == 1 && q.stride_h == q.stride_w &&
                       (q.stride_h == 1 || q.stride_h == 2) && q.xh.f >= q.H && q.xw.f >= q.W && q.yh.f >= q.OH &&
-                      q.yw.f >= q.OW;
+                      q.yw.f >= q.OW && N * C * q.H * q.W < (1 << 30) && N * C * q.OH * q.OW < (1 << 30);
+    if (k3x3) {
+        // Rows per thread.  Two share their windows' rows (24 loads for eight outputs against 36) where one row each
+        // would make more threads than the chip holds one wave of per SIMD: 16 x 144 x 56 x 56 takes 10.0 us with two
+        // and 11.5 with one, but 1 x 144 x 56 x 56 4.8 and 3.9.  At stride 2 they share one row of three, and the
+        // registers they take cost more than that (16 x 96 x 112 x 112: 23 us with two, 12.0 with one).
+        const int64_t items1 = N * q.OH * ((q.OW + kDwCols - 1) / kDwCols) * (C / 8);
+        const int th = q.stride_h == 1 && items1 >= 65536 ? 2 : 1;
+        const uint32_t owb = (uint32_t)(q.OW + kDwCols - 1) / kDwCols, ohb = (uint32_t)(q.OH + th - 1) / th;
+        p.fd_c8 = make_fastdiv((uint32_t)C / 8);
+        p.fd_owb = make_fastdiv(owb);
+        p.fd_ohb = make_fastdiv(ohb);
+        p.items = (uint32_t)(N * ohb * owb * (C / 8));
+        p.x_bytes = (uint32_t)(N * C * q.H * q.W * 2);
+        p.y_bytes = (uint32_t)(N * C * q.OH * q.OW * 2);
+        auto kern = th == 2            ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 2, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 2, false>)
+                    : q.stride_h == 1 ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 1, false>)
+                                      : (taps ? dwconv_vec8_3x3_kernel<2, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<2, kDwCols, 1, false>);
+        hipLaunchKernelGGL(kern, dim3((p.items + kDwThreads - 1) / kDwThreads), dim3(kDwThreads), 0, st, p);
+        ALT_CHECK_HIP(h, hipGetLastError());
+        return ALT_OK;
+    }
+    p.w_taps = taps && !chan_runs_of_8(q.wo, C, wo_, 2);
     const Dim2 xr[3] = {q.xn, q.xc, q.xh}, yr[3] = {q.yn, q.yk, q.yh};
     const bool rows = !vec && p.in_bf16 && p.out_bf16 && q.R == 3 && q.S == 3 && q.dil_h == 1 && q.dil_w == 1 &&
                       q.stride_h == q.stride_w && (q.stride_h == 1 || q.stride_h == 2) && q.pad_w == 1 && q.xw.si == 1 &&
@@ -356,14 +419,12 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
     const bool rows8 = rows && q.W % 8 == 0 && q.OW % 8 == 0 && rows_of(8, xr, 3) && rows_of(8, yr, 3) &&
                        (uintptr_t)q.x % 16 == 0 && (uintptr_t)q.y % 16 == 0;
     const int64_t work = rows ? N * C * q.OH * (q.OW / (rows8 ? 8 : 4))
-                       : k3x3 ? N * q.OH * ((q.OW + kTW - 1) / kTW) * (C / 8) : N * q.OH * q.OW * (vec ? C / 8 : C);
+                            : N * q.OH * q.OW * (vec ? C / 8 : C);
     const unsigned blocks = (unsigned)std::min<int64_t>((work + kDwThreads - 1) / kDwThreads, 256 * 64);
     if (rows8 && q.stride_h == 1) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<1, 8>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (rows8) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<2, 8>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (rows && q.stride_h == 1) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<1, 4>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (rows) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<2, 4>), dim3(blocks), dim3(kDwThreads), 0, st, p);
-    else if (k3x3 && q.stride_h == 1) hipLaunchKernelGGL((dwconv_vec8_3x3_kernel<1, kTW>), dim3(blocks), dim3(kDwThreads), 0, st, p);
-    else if (k3x3) hipLaunchKernelGGL((dwconv_vec8_3x3_kernel<2, kTW>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (vec) hipLaunchKernelGGL(dwconv_vec8_kernel, dim3(blocks), dim3(kDwThreads), 0, st, p);
     else hipLaunchKernelGGL(dwconv_elem_kernel, dim3(blocks), dim3(kDwThreads), 0, st, p);
     ALT_CHECK_HIP(h, hipGetLastError());

@@ -1,0 +1,53 @@
+"""GPU parity at the edges of the kernels' ranges: remainders of tiles, the smallest and the largest extents, every branch
+of a dispatch rule.  Integer-valued inputs make every partial sum exact, so results are compared bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2210_12415_amd as alt
+from gpu_util import canary_dev, canary_ok, dev, from_layout, host, to_layout
+from workloads import f32_to_bf16_bits, small_ints_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def h():
+    return alt.Handle()
+
+
+def check_conv(h, N, C, H, W, K, R, stride=1, pad=0, dil=1, groups=1, layouts=("NHWC", "OHWI", "NHWC"), dtype=alt.BF16,
+               out_dtype=None, epilogue=True, variant=-1, S=None):
+    """One convolution of small integers under the library's own choice of kernel (or `variant`), against the oracle."""
+    S = R if S is None else S
+    out_dtype = dtype if out_dtype is None else out_dtype
+    bits = lambda a: f32_to_bf16_bits(a) if dtype == alt.BF16 else a
+    x, w = small_ints_f32(41, (N, C, H, W), -3, 3), small_ints_f32(42, (K, C // groups, R, S), -3, 3)
+    b = small_ints_f32(43, (K,), -20, 20)
+    more = dict(bias=b, relu=True) if epilogue else {}
+    ref = oracle.conv2d(x, w, stride=stride, pad=pad, dil=dil, groups=groups, out_bf16=out_dtype == alt.BF16, **more)
+    xl, wl, yl = layouts
+    d = alt.conv_desc(N, C, H, W, K, R, S, stride=stride, dil=dil, in_dtype=dtype, out_dtype=out_dtype, groups=groups,
+                      epilogue=alt.EPI_BIAS | alt.EPI_RELU if epilogue else 0, variant=variant, x_layout="NCHW->" + xl,
+                      w_layout="OIHW->" + wl, y_layout="NCHW->" + yl)
+    d.pad_h, d.pad_w = pad if isinstance(pad, tuple) else (pad, pad)
+    np_out = np.uint16 if out_dtype == alt.BF16 else np.float32
+    whole, y = canary_dev(ref.size, np_out)
+    ws_bytes = h.conv2d_workspace_size(d)
+    ws = dev(np.zeros(max(1, ws_bytes // 4), np.float32))
+    print("conv", N, C, H, W, K, R, S, stride, pad, dil, groups, layouts, flush=True)
+    h.conv2d(d, dev(to_layout(bits(x), "NCHW", xl)), dev(to_layout(bits(w), "OIHW", wl)), y, bias=dev(b) if epilogue else None,
+             workspace=ws if ws_bytes else None, ws_bytes=ws_bytes)
+    got = from_layout(host(y, np_out), ref.shape, "NCHW", yl)
+    assert canary_ok(whole, ref.size), "wrote outside y"
+    assert np.array_equal(got, ref)
+
+
+# widths of 4 * n and with one column over, one or two rows per thread (two from 65536 threads on), an odd last row, one
+# vector of channels; 5x5 runs on the general vector kernel
+@pytest.mark.parametrize("N,C,H,W,R,stride,pad", [
+    (2, 8, 7, 9, 3, 1, 1), (1, 24, 6, 4, 3, 1, (0, 1)), (2, 256, 65, 61, 3, 1, 1), (3, 40, 8, 13, 3, 2, 1), (1, 16, 3, 3, 3, 1, 0),
+    (2, 24, 9, 10, 5, 1, 2), (1, 72, 11, 7, 3, 2, (1, 0))])
+@pytest.mark.parametrize("wl", ["OHWI", "OIHW", "HWIO"])
+def test_depthwise_vector_kernels(h, N, C, H, W, R, stride, pad, wl):
+    check_conv(h, N, C, H, W, C, R, stride, pad, groups=C, layouts=("NHWC", wl, "NHWC"))
