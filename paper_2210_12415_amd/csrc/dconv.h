@@ -88,7 +88,17 @@ struct DconvParams {
     Div32 d_ihw;                  // division by H*W (channel-planar kernel, blocked activations)
     // Channel-blocked tensors (N C/b H W b, b = 1 << blk, at least 8): 0 = channels contiguous per pixel (NHWC)
     int32_t x_blk, y_blk;
+    // streaming kernel over filter taps (dstream.h, TAPS): depth taps T, depth extents and the parameters of its
+    // direction (T = D = OD = 1 for two-dimensional problems); stride and dil above are the height's
+    int32_t T, D, OD, stride_d, pad_d, dil_d, stride_w, dil_w;
+    int32_t taps, strided;        // T * R * S; whether output pixel m is not simply input pixel m
+    int32_t c16, kq;              // 16-byte chunks per tap (a pixel's channels), and of the whole reduction
+    uint32_t x_pix, w_row;        // bytes of an input pixel and of a filter row (T * R * S * C elements)
+    uint32_t tap_d, tap_h, tap_w; // bytes between taps
+    uint32_t x_shift;             // bytes from the first tap of output pixel 0 to x
+    Div32 d_c16, d_rs, d_s, d_od; // divisions by c16, R * S, S, OD
 };
+constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
 
 // Element offset of channel `ch` of input pixel g (= img * H*W + hw) under the activations' layout.
 __device__ __forceinline__ uint32_t dconv_in_elem(const DconvParams &p, int g, int ch)

@@ -165,7 +165,7 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
         return no("operand of 2 GiB or more");
     if ((int64_t)p.M * K * 4 >= 0x7fffffff) return no("output too large for 32-bit offsets");
     if (K % 4 || (p.epilogue & ALT_EPI_BIAS && (uintptr_t)p.bias % 16)) return no("streaming kernel stores four output columns at a time");
-    const size_t lds = dstream_lds_bytes(k.BM, k.BN, k.BK, k.prefetch + 1, k.wgm, k.wgn, k.kw);
+    const size_t lds = dstream_lds_bytes(k.BM, k.BN, k.BK * 2, k.prefetch + 1, k.wgm, k.wgn, k.kw);
     if (lds > 160 * 1024) return no("stages do not fit LDS");
     if (dstream_banded(k.BM, k.BN, k.wgn, k.kw) && splitk > 1) return no("tiles this large take no split-K");
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
@@ -192,6 +192,92 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     d.OH = p.H; d.OW = p.W; d.x_blk = x_blk; d.y_blk = y_blk;
     d.d_ihw = make_div32((uint32_t)(p.H * p.W));
     d.x_bstride = p.x_bstride * 2; d.w_bstride = p.w_bstride * 2; d.y_bstride = p.y_bstride * osz;
+    *out = d;
+    *lds_bytes = lds;
+    return true;
+}
+
+// The same for a streaming kernel over filter taps (dstream.h, TAPS): any filter of up to ten taps per direction, any
+// stride, dilation and padding, dense NHWC activations and output with OHWI weights, a pixel's channels a whole number of
+// 16-byte chunks; and matrix products whose K is one, with B as NK or (bt) KN.
+static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
+{
+    auto no = [&](const char *m) { if (why) *why = m; return false; };
+    const IgemmParams &p = pb.p;
+    const int es = (int)dtype_size(pb.dtype), epc = 16 / es;
+    const int64_t C = p.C, H = p.H, W = p.W, OH = p.OH, OW = p.OW, K = p.Nc, R = p.R, S = p.S, N = p.M / (OH * OW);
+    if (R > kTapBits || S > kTapBits) return no("filters of more than ten taps in one direction");
+    if (C % epc) return no("a pixel's channels are not a whole number of 16-byte chunks");
+    int x_blk = 0, y_blk = 0;
+    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, N, &x_blk) || x_blk) return no("activations are not dense NHWC");
+    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH, OW, N, &y_blk) || (y_blk && p.batch > 1)) return no("output is not dense NHWC or N K/b H W b");
+    if (k.bt) {
+        if (R * S != 1 || !(dense(p.wo, K, 1) && dense(p.wi, C, K))) return no("B is not dense with N contiguous");
+        if (K % 8) return no("row-major B is loaded eight columns at a time");
+    } else if (!(dense(p.wi, C, 1) && dense(p.ws, S, C) && dense(p.wr, R, S * C) && dense(p.wo, K, R * S * C))) {
+        return no("weights are not dense OHWI");
+    }
+    const int64_t osz = p.out_bf16 ? 2 : 4;
+    if ((uintptr_t)p.x % 16 || (uintptr_t)p.w % 16 || (uintptr_t)p.y % 16) return no("operands are not 16-byte aligned");
+    if (p.batch > 1 && ((p.x_bstride * es) % 16 || (p.w_bstride * es) % 16 || (p.y_bstride * osz) % 16))
+        return no("batch entries are not 16-byte aligned");
+    if (p.batch > 65535) return no("too many batch entries for one launch");
+    if (pb.groups > 1) return no("a group's channels are not dense");
+    if (p.addend && p.batch > 1) return no("the fused sum is not built for batched problems");
+    if (splitk < 1 || (splitk > 1 && p.batch > 1)) return no("split-K is not built for batched problems");
+    const int64_t pix = C * es, shift = ((int64_t)p.pad_h * W + p.pad_w) * pix;
+    if (pb.x_elems * es + shift >= 0x7fffffff || pb.w_elems * es >= 0x7fffffff || p.y_bytes == 0) return no("operand of 2 GiB or more");
+    if ((int64_t)p.M * pix + shift >= 0x7fffffff && R * S == 1 && p.stride_h == 1) return no("operand of 2 GiB or more");
+    if ((int64_t)p.M * K * 4 >= 0x7fffffff) return no("output too large for 32-bit offsets");
+    if (K % 4 || ((p.epilogue & ALT_EPI_BIAS) && (uintptr_t)p.bias % 16)) return no("streaming kernel stores four output columns at a time");
+    const int64_t reach = ((R - 1) * (int64_t)p.dil_h * W + (S - 1) * (int64_t)p.dil_w) * pix;
+    if (reach + shift >= 0x3fffffff) return no("filter reaches too far");
+    const int cpr = k.BK * es / 16;
+    const int64_t kq = R * S * C / epc, steps = (kq + cpr - 1) / cpr, slices = (int64_t)splitk * k.kw;
+    if (k.taps == kTapsUniform && (C % k.BK || steps % slices)) return no("K steps do not divide the channels and the slices evenly");
+    const int64_t nk = (steps + slices - 1) / slices;
+    if ((slices - 1) * nk >= steps) return no("split factor leaves an empty slice");
+    const size_t lds = dstream_lds_bytes(k.BM, k.BN, k.BK * es, k.prefetch + 1, k.wgm, k.wgn, k.kw);
+    if (lds > 160 * 1024) return no("stages do not fit LDS");
+    if (dstream_banded(k.BM, k.BN, k.wgn, k.kw) && splitk > 1) return no("tiles this large take no split-K");
+    const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
+    if (splitk > 1 && (int64_t)tiles_m * tiles_n > kDconvMaxTiles) return no("too many output tiles for the split-K counters");
+    if ((int64_t)tiles_m * tiles_n * splitk > 0x7fffffff) return no("grid too large");
+    if (!out) return true;
+    DconvParams d;
+    std::memset(&d, 0, sizeof d);
+    d.x = p.x; d.w = p.w; d.bias = p.bias; d.y = p.y; d.addend = p.addend;
+    d.x_bytes = p.x_bytes; d.w_bytes = p.w_bytes; d.y_bytes = p.y_bytes;
+    d.partial_bytes = (uint32_t)((int64_t)p.M * K * 4);
+    d.M = p.M; d.Nc = p.Nc; d.C = p.C; d.Cs = p.C;
+    d.H = p.H; d.W = p.W; d.R = p.R; d.S = p.S; d.pad_h = p.pad_h; d.pad_w = p.pad_w;
+    d.OH = p.OH; d.OW = p.OW; d.stride = p.stride_h; d.dil = p.dil_h; d.stride_w = p.stride_w; d.dil_w = p.dil_w;
+    d.T = d.D = d.OD = d.stride_d = d.dil_d = 1;
+    d.tiles_m = tiles_m; d.tiles_n = tiles_n; d.splitk = splitk;
+    d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | (p.out_bf16 ? kDconvOutBf16 : 0);
+    d.d_hw = make_div32((uint32_t)(OH * OW));
+    d.d_w = make_div32((uint32_t)OW);
+    d.d_tm = make_div32((uint32_t)tiles_m);
+    d.d_tn = make_div32((uint32_t)tiles_n);
+    d.d_sk = make_div32((uint32_t)splitk);
+    d.d_od = make_div32(1);
+    d.ncc = (int32_t)nk;
+    d.bk = k.BK;
+    d.taps = (int32_t)(R * S);
+    d.strided = !(R * S == 1 && OH == H && OW == W && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 0 && p.pad_w == 0);
+    d.c16 = (int32_t)(C / epc); d.kq = (int32_t)kq;
+    d.d_c16 = make_div32((uint32_t)d.c16);
+    d.d_rs = make_div32((uint32_t)(R * S));
+    d.d_s = make_div32((uint32_t)S);
+    d.x_pix = (uint32_t)pix;
+    d.w_row = (uint32_t)(R * S * pix);
+    d.tap_h = (uint32_t)(p.dil_h * W * pix);
+    d.tap_w = (uint32_t)(p.dil_w * pix);
+    d.x_shift = (uint32_t)shift;
+    d.batch = p.batch;
+    d.y_blk = y_blk;
+    d.d_ihw = make_div32((uint32_t)(H * W));
+    d.x_bstride = p.x_bstride * es; d.w_bstride = p.w_bstride * es; d.y_bstride = p.y_bstride * osz;
     *out = d;
     *lds_bytes = lds;
     return true;
@@ -263,6 +349,7 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
 bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
 {
     if (k.stream == 2) return dplanar_setup(pb, k, splitk, out, lds_bytes, why);
+    if (k.taps) return dtaps_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream) return dstream_setup(pb, k, splitk, out, lds_bytes, why);
     auto no = [&](const char *m) { if (why) *why = m; return false; };
     const IgemmParams &p = pb.p;

@@ -41,3 +41,21 @@
                                     ALT_BF16, BM, BN, BK, LOAD_VEC, LOAD_VEC, NS - 1, 1, 0, nullptr,             \
                                     &dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, true>, WGM, WGN, KW, 1, 1}),   \
          true)
+
+// the streaming kernel over filter taps: MODE kTapsUniform (named taps) or kTapsRagged (named rtaps), T and TNAME the element type
+#define ALT_DTAPS_(T, TNAME, DT, BM, BN, WGM, WGN, KW, NS, BK, MODE, MNAME)                                      \
+    const bool reg_dtaps_##TNAME##_##BM##x##BN##x##BK##_w##WGM##x##WGN##x##KW##_s##NS##_##MNAME =                \
+        (igemm_register(IgemmLaunch{#TNAME "_" #BM "x" #BN "x" #BK "_" #MNAME "_w" #WGM "x" #WGN "x" #KW "_s" #NS, \
+                                    DT, BM, BN, BK, LOAD_VEC, LOAD_VEC, NS - 1, 1, 0, nullptr,                   \
+                                    &dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, false, MODE, T>, WGM, WGN, KW, 1, 0, MODE}), \
+         true)
+#define ALT_DTAPS(BM, BN, WGM, WGN, KW, NS, BK) ALT_DTAPS_(bf16_tag, bf16, ALT_BF16, BM, BN, WGM, WGN, KW, NS, BK, kTapsUniform, taps)
+#define ALT_DRTAPS(BM, BN, WGM, WGN, KW, NS, BK) ALT_DTAPS_(bf16_tag, bf16, ALT_BF16, BM, BN, WGM, WGN, KW, NS, BK, kTapsRagged, rtaps)
+#define ALT_DRTAPS_F32(BM, BN, WGM, WGN, KW, NS, BK) ALT_DTAPS_(float, f32, ALT_F32, BM, BN, WGM, WGN, KW, NS, BK, kTapsRagged, rtaps)
+// ragged K with B stored [K][N]
+#define ALT_DRSTREAM_KN(BM, BN, WGM, WGN, KW, NS, BK)                                                            \
+    const bool reg_drstream_kn_##BM##x##BN##x##BK##_w##WGM##x##WGN##x##KW##_s##NS =                              \
+        (igemm_register(IgemmLaunch{"bf16_" #BM "x" #BN "x" #BK "_rtapskn_w" #WGM "x" #WGN "x" #KW "_s" #NS,      \
+                                    ALT_BF16, BM, BN, BK, LOAD_VEC, LOAD_VEC, NS - 1, 1, 0, nullptr,             \
+                                    &dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, true, kTapsRagged>, WGM, WGN, KW, 1, 1, kTapsRagged}), \
+         true)

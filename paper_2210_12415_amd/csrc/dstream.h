@@ -15,27 +15,45 @@
 // stages (no registers in between); everything else is the machinery of the direct
 // convolution (dconv.h): asynchronous fragment reads that run ahead of the MFMAs,
 // K groups inside the workgroup, the fused split-K tail, the shared epilogue.
+//
+// The same kernel is an implicit-GEMM convolution (TAPS): the reduction then runs over the
+// filter's taps and, inside a tap, the input channels, exactly as an OHWI filter row lies in
+// memory, so that the B operand stays a plain K-contiguous matrix and only the address of
+// A's 16-byte chunks changes.  A chunk never straddles two taps (a pixel's channels are a
+// whole number of chunks).  Each row of the tile keeps the byte offset of its window's first
+// tap and a mask of the filter rows, columns and depths that fall inside the image; a load of
+// a tap outside gets an out-of-range offset and reads zeros.
+//   kTapsUniform: the channels are a multiple of the K step, so that a step lies inside one
+//     tap: its offset and selector are wave-uniform (scalar registers).
+//   kTapsRagged: any channel count that is a multiple of a chunk: every lane finds the tap of
+//     its own chunk (three divisions per K step, not per load).  The last step is filled up
+//     with zeros, so it also covers matrix products whose K is not a multiple of the K step.
+// T = float runs on the fp32 matrix instructions: a K step is BK floats, a 16-byte chunk four.
 #pragma once
 
 #include "dconv.h"
 
 namespace alt {
 
+enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2 };
+
 // KW groups of WGM x WGN waves; group kg handles channels [kg, kg + 1) * Cs / KW of the
-// workgroup's slice in steps of BK (64 or 32), through a ring of NS stages of its own.
+// workgroup's slice in steps of BK (64 or 32; half of that for float), through a ring of NS stages of its own.
 // While a step computes, NS - 2 later stages are in flight: deep rings of small stages
 // (BK = 32) cover the load latency with the same LDS as shallow rings of large ones.
-template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false>
+template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false, int TAPS = kNoTaps, typename T = bf16_tag>
 __global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM) * (BN / WGN) / 64, WGM * WGN * KW))
 void dstream_kernel(const DconvParams p)
 {
+    constexpr int ES = ElemTraits<T>::SIZE;                // bytes per element
+    constexpr int BKB = BK * ES;                           // bytes of a K step per row
     constexpr int NWG = WGM * WGN;                         // waves per K group
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
     constexpr int TM = WTM / 32, TN = WTN / 32;
-    constexpr int NKC = BK / 16;
-    constexpr int CPR = BK / 8;                            // 16-byte chunks per tile row of a stage
-    constexpr int RP = 256 / (BK * 2);                     // tile rows per 256 bytes of LDS
-    constexpr int A_STAGE = BM * BK * 2, B_STAGE = BN * BK * 2;     // bytes: [rows][CPR chunks of 16 B]
+    constexpr int NKC = BKB / 32;                          // k chunks: 16 bytes of k per lane, two lane halves
+    constexpr int CPR = BKB / 16;                          // 16-byte chunks per tile row of a stage
+    constexpr int RP = 256 / BKB;                     // tile rows per 256 bytes of LDS
+    constexpr int A_STAGE = BM * BKB, B_STAGE = BN * BKB;     // bytes: [rows][CPR chunks of 16 B]
     constexpr int STAGE = A_STAGE + B_STAGE;
     constexpr int RING = NS * STAGE;
     constexpr int NLA = A_STAGE / 1024 / NWG, NLB = B_STAGE / 1024 / NWG;   // wave-loads per wave per stage
@@ -43,7 +61,8 @@ void dstream_kernel(const DconvParams p)
     static_assert(WTM % 32 == 0 && WTN % 32 == 0 && TM >= 1 && TN >= 1, "wave tile");
     static_assert(A_STAGE % (1024 * NWG) == 0 && B_STAGE % (1024 * NWG) == 0 && NLA >= 1 && NLB >= 1,
                   "a stage is a whole number of wave-loads per wave");
-    static_assert(BK == 64 || BK == 32, "K step");
+    static_assert(BKB == 128 || BKB == 64, "K step");
+    static_assert(ES == 2 || (!BT && TAPS == kTapsRagged), "fp32: built for ragged taps, which cover the rest");
     static_assert(NS >= 3 && (NS - 1) * LPS < 60, "pipeline depth against the vmcnt range");
     static_assert((NS * NKC) % 4 == 0, "a round over the stages is a whole number of fragment-buffer cycles");
     constexpr int RB = BT ? 2 : 1;                         // LDS reads per B fragment
@@ -76,41 +95,125 @@ void dstream_kernel(const DconvParams p)
     const int m0 = mt * BM, n0 = nt * BN;
     const int bz = blockIdx.y;                             // batch entry
 
-    const i32x4_t x_rsrc = make_rsrc((const char *)p.x + (int64_t)bz * p.x_bstride, p.x_bytes);
+    const i32x4_t x_rsrc = TAPS ? make_rsrc((const char *)p.x + (int64_t)bz * p.x_bstride - p.x_shift, p.x_bytes + p.x_shift)
+                                : make_rsrc((const char *)p.x + (int64_t)bz * p.x_bstride, p.x_bytes);
     const i32x4_t w_rsrc = make_rsrc((const char *)p.w + (int64_t)bz * p.w_bstride, p.w_bytes);
 
     // ---- loads: slot s = (i*NWG + wq)*64 + lane of an operand's stage holds chunk (s % CPR) ^ swz(row) of
     // row s / CPR (rows that share LDS banks, RP apart, get different chunk orders)
     const int nk = p.ncc;                                  // K steps of a group
+    const int step0 = (split * KW + kg) * nk;              // the group's first K step (TAPS: of the whole reduction)
     const uint32_t k_off0 = (uint32_t)(split * p.Cs + kg * (nk * BK)) * 2u;
     uint32_t a_voff[NLA], b_voff[NLB];
+    uint32_t a_mask[TAPS ? NLA : 1];                       // bit r, kTapBits + s, 2 * kTapBits + t: that tap row, column, depth is inside
 #pragma unroll
     for (int i = 0; i < NLA; ++i) {
         const int s = (i * NWG + wq) * 64 + lane;
         const int row = s / CPR, c = (s % CPR) ^ ((row / RP) & (CPR - 1));
         const int m = m0 + row;
-        // (blocked activations: a K step is BK / block whole blocks, so the chunk's place inside the step and the
-        // step's distance are both fixed)
-        a_voff[i] = m < p.M ? dconv_in_elem(p, m, split * p.Cs + kg * (nk * BK) + c * 8) * 2u : kOutOfRange;
+        if constexpr (TAPS) {
+            // (the descriptor starts pad rows, columns and slices before x, so that no offset is negative)
+            a_mask[i] = 0;
+            a_voff[i] = (uint32_t)m * p.x_pix;
+            if (m >= p.M) {
+            } else if (p.taps == 1) {
+                a_mask[i] = 1u | (1u << kTapBits) | (1u << 2 * kTapBits);
+            }
+            if (p.taps > 1 || p.strided) {
+                const uint32_t img = div32((uint32_t)m, p.d_hw), q = (uint32_t)m - img * (uint32_t)(p.OH * p.OW);
+                const uint32_t oh = div32(q, p.d_w), ow = q - oh * (uint32_t)p.OW;
+                const uint32_t n = div32(img, p.d_od), od = img - n * (uint32_t)p.OD;
+                a_voff[i] = ((n * (uint32_t)p.D + od * (uint32_t)p.stride_d) * (uint32_t)(p.H * p.W) +
+                             oh * (uint32_t)(p.stride * p.W) + ow * (uint32_t)p.stride_w) * p.x_pix;
+                if (m < p.M) {
+                    uint32_t mask = 0;
+                    const int ih0 = (int)oh * p.stride - p.pad_h, iw0 = (int)ow * p.stride_w - p.pad_w, id0 = (int)od * p.stride_d - p.pad_d;
+                    for (int r = 0; r < p.R; ++r) mask |= (unsigned)(ih0 + r * p.dil) < (unsigned)p.H ? 1u << r : 0u;
+                    for (int q2 = 0; q2 < p.S; ++q2) mask |= (unsigned)(iw0 + q2 * p.dil_w) < (unsigned)p.W ? 1u << (kTapBits + q2) : 0u;
+                    for (int d = 0; d < p.T; ++d) mask |= (unsigned)(id0 + d * p.dil_d) < (unsigned)p.D ? 1u << (2 * kTapBits + d) : 0u;
+                    a_mask[i] = mask;
+                }
+            }
+            if constexpr (TAPS == kTapsUniform) a_voff[i] += (uint32_t)c * 16u;
+        } else {
+            // (blocked activations: a K step is BK / block whole blocks, so the chunk's place inside the step and the
+            // step's distance are both fixed)
+            a_voff[i] = m < p.M ? dconv_in_elem(p, m, split * p.Cs + kg * (nk * BK) + c * 8) * 2u : kOutOfRange;
+        }
     }
 #pragma unroll
     for (int i = 0; i < NLB; ++i) {
         const int s = (i * NWG + wq) * 64 + lane;
         if constexpr (BT) {
             // slot s of the stage: row k = s / CPRB, chunk position s % CPRB, which holds chunk position ^ swz(k)
+            // (ragged K: rows past the last one lie past the end of B and read zeros)
             const int k = s / CPRB, c = (s % CPRB) ^ swz_b(k);
             const int n = n0 + c * 8;
-            b_voff[i] = n < p.Nc ? (uint32_t)((split * p.Cs + kg * (nk * BK) + k) * p.Nc + n) * 2u : kOutOfRange;
+            b_voff[i] = n < p.Nc ? (uint32_t)((TAPS ? step0 * BK + k : split * p.Cs + kg * (nk * BK) + k) * p.Nc + n) * 2u : kOutOfRange;
         } else {
             const int row = s / CPR, c = (s % CPR) ^ ((row / RP) & (CPR - 1));
             const int n = n0 + row;
-            b_voff[i] = n < p.Nc ? (uint32_t)(n * p.C) * 2u + k_off0 + (uint32_t)c * 16u : kOutOfRange;
+            if constexpr (TAPS == kTapsRagged) b_voff[i] = n < p.Nc ? (uint32_t)n * p.w_row : kOutOfRange;
+            else if constexpr (TAPS == kTapsUniform) b_voff[i] = n < p.Nc ? (uint32_t)n * p.w_row + (uint32_t)step0 * BKB + (uint32_t)c * 16u : kOutOfRange;
+            else b_voff[i] = n < p.Nc ? (uint32_t)(n * p.C) * 2u + k_off0 + (uint32_t)c * 16u : kOutOfRange;
         }
     }
+    // ragged taps: this lane's chunk of every row it loads (the same for all its loads and both operands)
+    static_assert(TAPS != kTapsRagged || (NWG * 64 / CPR / RP) % CPR == 0, "a lane's loads sit in one chunk column");
+    const uint32_t chunk0 = (uint32_t)step0 * CPR + (uint32_t)((lane % CPR) ^ ((((wq * 64 + lane) / CPR) / RP) & (CPR - 1)));
+    // uniform taps: the tap the load cursor stands on and the chunk inside it
+    int u_t = 0, u_r = 0, u_s = 0, u_c = 0;
+    if constexpr (TAPS == kTapsUniform) {
+        const uint32_t q = (uint32_t)step0 * CPR, tap = div32(q, p.d_c16);
+        u_c = (int)(q - tap * (uint32_t)p.c16);
+        const uint32_t td = div32(tap, p.d_rs), rs = tap - td * (uint32_t)(p.R * p.S), tr = div32(rs, p.d_s);
+        u_t = (int)td; u_r = (int)tr; u_s = (int)(rs - tr * (uint32_t)p.S);
+    }
+    // what a step adds to A's and B's offsets, and the mask bits it needs
+    uint32_t add_a = 0, add_b = 0, sel = 0;
+    auto step_address = [&](int step) {                    // step: of this group, 0 .. nk - 1 (ragged: any)
+        if constexpr (TAPS == kTapsUniform) {
+            add_a = (uint32_t)u_t * p.tap_d + (uint32_t)u_r * p.tap_h + (uint32_t)u_s * p.tap_w + (uint32_t)u_c * 16u;
+            sel = (1u << u_r) | (1u << (kTapBits + u_s)) | (1u << (2 * kTapBits + u_t));
+            add_b = (uint32_t)step * BKB;
+        } else if constexpr (TAPS == kTapsRagged) {
+            const uint32_t q = chunk0 + (uint32_t)step * CPR;
+            sel = 1u | (1u << kTapBits) | (1u << 2 * kTapBits);
+            add_b = add_a = q * 16u;
+            if (p.taps > 1) {
+                const uint32_t tap = div32(q, p.d_c16), td = div32(tap, p.d_rs), rs = tap - td * (uint32_t)(p.R * p.S);
+                const uint32_t tr = div32(rs, p.d_s), tc = rs - tr * (uint32_t)p.S;
+                add_a = td * p.tap_d + tr * p.tap_h + tc * p.tap_w + (q - tap * (uint32_t)p.c16) * 16u;
+                sel = (1u << tr) | (1u << (kTapBits + tc)) | (1u << (2 * kTapBits + td));
+            }
+            if (q >= (uint32_t)p.kq) { sel = 0x80000000u; add_b = kOutOfRange; }     // past the last chunk: zeros
+        }
+    };
+    auto next_tap = [&]() {                                // uniform taps: one K step further
+        u_c += CPR;
+        const int ws = u_c == p.c16 ? 1 : 0;
+        u_c = ws ? 0 : u_c;
+        u_s += ws;
+        const int wr = u_s == p.S ? 1 : 0;
+        u_s = wr ? 0 : u_s;
+        u_r += wr;
+        const int wt = u_r == p.R ? 1 : 0;
+        u_r = wt ? 0 : u_r;
+        u_t += wt;
+    };
+    auto load_a = [&](int i, uint32_t soff, uint32_t dst) {
+        // (added in a vector register: a wave-uniform offset larger than a small tensor would wrap the hardware's range check)
+        if constexpr (TAPS) dma_load16_s(x_rsrc, (a_mask[i] & sel) == sel ? a_voff[i] + add_a : kOutOfRange, 0u, dst);
+        else dma_load16_s(x_rsrc, a_voff[i], soff, dst);
+    };
+    auto load_b = [&](int i, uint32_t soff, uint32_t dst) {
+        if constexpr (TAPS == kTapsRagged && !BT) dma_load16_s(w_rsrc, (b_voff[i] | add_b) & kOutOfRange ? kOutOfRange : b_voff[i] + add_b, 0u, dst);
+        else dma_load16_s(w_rsrc, b_voff[i], soff, dst);
+    };
     // byte distance between consecutive K steps of B: BK columns of a row, or BK rows; of A: BK channels of a
     // pixel, or BK / block channel blocks (planes of H*W pixels)
-    const uint32_t b_step = BT ? (uint32_t)(BK * p.Nc) * 2u : (uint32_t)(BK * 2);
-    const uint32_t a_step = p.x_blk ? (uint32_t)(BK * p.H * p.W) * 2u : (uint32_t)(BK * 2);
+    const uint32_t b_step = BT ? (uint32_t)(BK * p.Nc) * 2u : (uint32_t)BKB;
+    const uint32_t a_step = p.x_blk ? (uint32_t)(BK * p.H * p.W) * 2u : (uint32_t)BKB;
     const uint32_t ring0 = lds0 + kg * RING;
     const uint32_t ldsW = ring0 + wq * 1024;
     // load cursor: K step `lstep` goes to stage `lstage`; past the last step the last one is
@@ -119,10 +222,12 @@ void dstream_kernel(const DconvParams p)
     auto issue_stage = [&]() {
         const uint32_t soff = (uint32_t)min(lstep, nk - 1) * a_step, soff_b = (uint32_t)min(lstep, nk - 1) * b_step;
         const uint32_t dst = ldsW + lstage * STAGE;
+        step_address(min(lstep, nk - 1));
 #pragma unroll
-        for (int i = 0; i < NLA; ++i) dma_load16_s(x_rsrc, a_voff[i], soff, dst + i * (NWG * 1024));
+        for (int i = 0; i < NLA; ++i) load_a(i, soff, dst + i * (NWG * 1024));
 #pragma unroll
-        for (int i = 0; i < NLB; ++i) dma_load16_s(w_rsrc, b_voff[i], soff_b, dst + A_STAGE + i * (NWG * 1024));
+        for (int i = 0; i < NLB; ++i) load_b(i, soff_b, dst + A_STAGE + i * (NWG * 1024));
+        if constexpr (TAPS == kTapsUniform) { if (lstep + 1 < nk) next_tap(); }
         ++lstep;
         lstage = lstage + 1 == NS ? 0 : lstage + 1;
     };
@@ -138,7 +243,7 @@ void dstream_kernel(const DconvParams p)
             const int r = wm * WTM + i * 32 + (lane & 31);
             const uint32_t swz = ((r / RP) & (CPR - 1)) * 16;
 #pragma unroll
-            for (int kc = 0; kc < NKC; ++kc) a_rd[i][kc] = ring0 + r * (BK * 2) + ((kc * 32 + khalf) ^ swz);
+            for (int kc = 0; kc < NKC; ++kc) a_rd[i][kc] = ring0 + r * BKB + ((kc * 32 + khalf) ^ swz);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -153,7 +258,7 @@ void dstream_kernel(const DconvParams p)
                 const int r = wn * WTN + j * 32 + (lane & 31);
                 const uint32_t swz = ((r / RP) & (CPR - 1)) * 16;
 #pragma unroll
-                for (int kc = 0; kc < NKC; ++kc) b_rd[j][kc] = ring0 + A_STAGE + r * (BK * 2) + ((kc * 32 + khalf) ^ swz);
+                for (int kc = 0; kc < NKC; ++kc) b_rd[j][kc] = ring0 + A_STAGE + r * BKB + ((kc * 32 + khalf) ^ swz);
             }
         }
     }
@@ -232,8 +337,21 @@ void dstream_kernel(const DconvParams p)
     auto issue_one = [&](int i) {                          // load i of the stage the cursor is on
         const uint32_t soff = (uint32_t)min(lstep, nk - 1) * a_step, soff_b = (uint32_t)min(lstep, nk - 1) * b_step;
         const uint32_t dst = ldsW + lstage * STAGE;
-        if (i < NLA) dma_load16_s(x_rsrc, a_voff[i], soff, dst + i * (NWG * 1024));
-        else dma_load16_s(w_rsrc, b_voff[i - NLA], soff_b, dst + A_STAGE + (i - NLA) * (NWG * 1024));
+        if (i == 0) step_address(min(lstep, nk - 1));
+        if (i < NLA) load_a(i, soff, dst + i * (NWG * 1024));
+        else load_b(i - NLA, soff_b, dst + A_STAGE + (i - NLA) * (NWG * 1024));
+    };
+    auto mma = [&](floatx16_t &c, const u32x4_t &b, const u32x4_t &a) {
+        if constexpr (ES == 2) {
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, b), __builtin_bit_cast(bf16x8_t, a), c, 0, 0, 0);
+        } else {
+            // (each instruction takes one float of each lane half: k = 4 * half + j of the chunk pair, for both operands)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_t fb = __builtin_bit_cast(f32x4_t, b), fa = __builtin_bit_cast(f32x4_t, a);
+                c = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[j], c, 0, 0, 0);
+            }
+        }
     };
     // GEND: the look-ahead reads k chunks below GEND only (0: no limit, the NK kernels); FIRST: this step
     // issues its own first D chunks
@@ -256,9 +374,7 @@ void dstream_kernel(const DconvParams p)
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, bf[buf][j]),
-                                                                            __builtin_bit_cast(bf16x8_t, af[buf][i]),
-                                                                            acc[i][j], 0, 0, 0);
+                        mma(acc[i][j], bf[buf][j], af[buf][i]);
             });
         } else {
             static_for<NKC>([&](auto KC) {
@@ -273,9 +389,7 @@ void dstream_kernel(const DconvParams p)
                     constexpr int i = decltype(IR)::value;
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, bf[buf][j]),
-                                                                            __builtin_bit_cast(bf16x8_t, af[buf][i]),
-                                                                            acc[i][j], 0, 0, 0);
+                        mma(acc[i][j], bf[buf][j], af[buf][i]);
                     __builtin_amdgcn_sched_barrier(0);
                     static_for<RPS>([&](auto RR) {
                         constexpr int r = i * RPS + decltype(RR)::value;
@@ -289,6 +403,7 @@ void dstream_kernel(const DconvParams p)
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
+            if constexpr (TAPS == kTapsUniform) { if (lstep + 1 < nk) next_tap(); }
             ++lstep;
             lstage = lstage + 1 == NS ? 0 : lstage + 1;
         }
@@ -347,20 +462,20 @@ inline bool dstream_banded(int BM, int BN, int waves_n, int kw)
     return (size_t)kw * BM * (BN + 8 * waves_n) * 4 + 16 > 160 * 1024;
 }
 
-inline size_t dstream_lds_bytes(int BM, int BN, int bk, int NS, int waves_m, int waves_n, int kw)
+inline size_t dstream_lds_bytes(int BM, int BN, int step_bytes, int NS, int waves_m, int waves_n, int kw)
 {
-    const size_t main_loop = (size_t)kw * NS * (BM + BN) * bk * 2;
+    const size_t main_loop = (size_t)kw * NS * (BM + BN) * step_bytes;
     const size_t staging = dstream_banded(BM, BN, waves_n, kw)
         ? (size_t)waves_m * waves_n * 32 * (BN / waves_n + 4) * 4
         : (size_t)kw * BM * (BN + 8 * waves_n) * 4 + 16;
     return main_loop > staging ? main_loop : staging;
 }
 
-template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false>
+template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false, int TAPS = kNoTaps, typename T = bf16_tag>
 hipError_t dstream_launch(const DconvParams &p, size_t lds, hipStream_t st)
 {
     if (p.bk != BK) return hipErrorInvalidValue;
-    auto kern = dstream_kernel<BM, BN, WGM, WGN, KW, NS, BK, BT>;
+    auto kern = dstream_kernel<BM, BN, WGM, WGN, KW, NS, BK, BT, TAPS, T>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);

@@ -660,6 +660,7 @@ struct IgemmLaunch {
     int stream = 0;           // 1: both operands stream through LDS (dstream.h: 1x1 filters and GEMMs of any depth);
                               // 2: channel-planar operands converted on the way into LDS (dplanar.h)
     int bt = 0;               // streaming kernel: 1 = B stored [K][N] (row-major), read through LDS transpose reads
+    int taps = 0;             // streaming kernel over filter taps: kTapsUniform or kTapsRagged
 };
 
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, int AMODE, int BMODE, int PF>

@@ -107,8 +107,8 @@ bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igemm
         if (out) {
             IgemmParams p = p0;
             p.splitk = splitk;
-            p.ksteps_total = p.R * p.S * (p.C / 64);
-            p.ksteps_per_split = p.ksteps_total / splitk;
+            p.ksteps_total = k.taps ? (p.R * p.S * p.C + k.BK - 1) / k.BK : p.R * p.S * (p.C / 64);
+            p.ksteps_per_split = (p.ksteps_total + splitk - 1) / splitk;
             p.tiles_m = (p.M + k.BM - 1) / k.BM;
             p.tiles_n = (p.Nc + k.BN - 1) / k.BN;
             *out = p;
@@ -164,18 +164,23 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         // as their LDS allows.  Clocks at 2.2 GHz, scaled to the unit of the estimate below
         // (about 45 per microsecond).
         const int waves = k.kw * k.wgm * k.wgn;
-        const double lds = (double)k.kw * (k.prefetch + 1) * (k.BM + k.BN) * k.BK * 2;
+        const double es = k.dtype == ALT_BF16 ? 2.0 : 4.0;
+        const double lds = (double)k.kw * (k.prefetch + 1) * (k.BM + k.BN) * k.BK * es;
         const double stage = (double)k.kw * k.BM * (k.BN + 8.0 * k.wgn) * 4;
         const int per_cu = std::max(1, (int)(160.0 * 1024 / std::max(lds, stage)));
         const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
         const double rounds = std::ceil(blocks / (256.0 * per_cu));
-        const double steps = (double)p.C / p.splitk / k.kw / k.BK;
-        const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * 8.0 * (waves >= 8 ? 1.7 : 2.0);
-        const double bytes = (double)k.kw * (k.BM + k.BN) * k.BK * 2 / 45.0;
+        const double steps = k.taps ? std::ceil((double)p.ksteps_per_split / k.kw) : (double)p.C / p.splitk / k.kw / k.BK;
+        // (fp32 matrix instructions do a sixteenth of the products per clock)
+        const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * (k.dtype == ALT_BF16 ? 8.0 : 128.0) * (waves >= 8 ? 1.7 : 2.0);
+        const double bytes = (double)k.kw * (k.BM + k.BN) * k.BK * es / 45.0;
         const double clk = rounds * (steps * (std::max(mfma, bytes) + 120.0) + 6000.0);
         // (halved like the direct kernels' estimate below: wherever one of these kernels applies it
         // has beaten the implicit-GEMM kernels, whose estimate is optimistic)
-        return 0.5 * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 : 0.0));
+        // The kernels over filter taps fetch a pixel once per tap, so where the patch-resident or the plain streaming
+        // kernels cover the problem (bf16, channels a multiple of 64) those come first.
+        const double taps = k.taps && k.dtype == ALT_BF16 && p.C % 64 == 0 ? 3.0 : 1.0;
+        return taps * 0.5 * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 : 0.0));
     }
     if (k.launch_direct && k.stream == 2) {
         // Channel-planar kernel: a workgroup converts its patch on the way in (about 20 bytes per clock

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import paper_2210_12415_amd as alt
-from gpu_util import canary_dev, canary_ok, dev, from_layout, host, to_layout
+from gpu_util import applicable_variants, canary_dev, canary_ok, dev, from_layout, host, to_layout
 from workloads import f32_to_bf16_bits, small_ints_f32
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +51,60 @@ def check_conv(h, N, C, H, W, K, R, stride=1, pad=0, dil=1, groups=1, layouts=("
 @pytest.mark.parametrize("wl", ["OHWI", "OIHW", "HWIO"])
 def test_depthwise_vector_kernels(h, N, C, H, W, R, stride, pad, wl):
     check_conv(h, N, C, H, W, C, R, stride, pad, groups=C, layouts=("NHWC", wl, "NHWC"))
+
+
+TAPS_CASES = [
+    # N, C, H, W, K, R, S, stride, pad, dil
+    (2, 64, 9, 7, 64, 3, 3, 1, 1, 1),          # one K step per tap, rows that end inside a tile
+    (1, 24, 12, 11, 40, 3, 3, 1, 1, 1),        # a chunk column crosses taps inside a K step
+    (3, 8, 5, 6, 12, 3, 3, 2, 1, 1),           # one chunk per tap, stride 2, narrow output
+    (2, 40, 10, 9, 72, 1, 1, 1, 0, 1),         # 1x1, K of 1.25 steps
+    (2, 24, 7, 9, 144, 1, 1, 2, 0, 1),         # 1x1 at stride 2
+    (1, 96, 8, 8, 100, 5, 5, 1, 4, 2),         # dilation, more padding than same-size
+    (1, 128, 6, 5, 256, 1, 7, 1, (0, 3), 1),   # one-dimensional filter
+    (1, 16, 4, 4, 32, 3, 3, 1, 8, 8),          # a filter that reaches past the whole image
+    (1, 192, 16, 15, 132, 3, 3, 1, 1, 1),
+    (4, 160, 1, 1, 36, 1, 1, 1, 0, 1),         # a handful of rows
+]
+
+
+@pytest.mark.parametrize("dtype", [alt.BF16, alt.F32])
+@pytest.mark.parametrize("case", TAPS_CASES, ids=lambda c: "_".join(str(v) for v in c))
+def test_tap_kernels_every_variant(h, case, dtype):
+    """The streaming kernels over filter taps (names with _taps_ or _rtaps_): every tile shape that takes the problem, without
+    and with the smallest split-K factor, bit for bit."""
+    N, C, H, W, K, R, S, stride, pad, dil = case
+    d = alt.conv_desc(N, C, H, W, K, R, S, stride=stride, dil=dil, in_dtype=dtype, out_dtype=dtype, x_layout="NCHW->NHWC",
+                      w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+    d.pad_h, d.pad_w = pad if isinstance(pad, tuple) else (pad, pad)
+    seen = set()
+    for v, name in applicable_variants(h, d):
+        base, k = name.rsplit("_k", 1)
+        if "taps_" not in name or (base, k != "1") in seen:
+            continue
+        seen.add((base, k != "1"))
+        check_conv(h, N, C, H, W, K, R, stride, pad, dil, S=S, dtype=dtype, variant=v)
+    assert len(seen) >= 3
+
+
+@pytest.mark.parametrize("bl", ["NK", "KN"])
+@pytest.mark.parametrize("M,N,K", [(70, 64, 8), (129, 136, 72), (37, 200, 1304), (300, 72, 104)])
+def test_products_with_ragged_depth_every_variant(h, bl, M, N, K):
+    """Products whose K is no multiple of a K step on the kernels named _rtaps_ (B as NK) and _rtapskn_ (B as KN)."""
+    A, B = small_ints_f32(51, (M, K), -3, 3), small_ints_f32(52, (K, N), -3, 3)
+    ref = oracle.gemm(A, B)
+    a, b = dev(f32_to_bf16_bits(A)), dev(f32_to_bf16_bits(np.ascontiguousarray(B.T) if bl == "NK" else B))
+    d = alt.gemm_desc(M, N, K, b_layout="KN->" + bl)
+    seen = 0
+    for v, name in applicable_variants(h, d, "gemm"):
+        if "rtaps" not in name:
+            continue
+        seen += 1
+        d.variant = v
+        ws_bytes = h.gemm_workspace_size(d)
+        whole, C = canary_dev(M * N, np.float32)
+        print("gemm", M, N, K, bl, name, flush=True)
+        h.gemm(d, a, b, C, workspace=dev(np.zeros(max(1, ws_bytes // 4), np.float32)), ws_bytes=ws_bytes)
+        got = host(C, np.float32).reshape(M, N)
+        assert canary_ok(whole, M * N) and np.array_equal(got, ref), name
+    assert seen >= 4
