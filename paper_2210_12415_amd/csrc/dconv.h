@@ -97,6 +97,10 @@ struct DconvParams {
     uint32_t tap_d, tap_h, tap_w; // bytes between taps
     uint32_t x_shift;             // bytes from the first tap of output pixel 0 to x
     Div32 d_c16, d_rs, d_s, d_od; // divisions by c16, R * S, S, OD
+    // kernel for images of few channels (dstem.h): element strides of the filter; there tiles_m counts tiles of 16 x 16 pixels,
+    // tiles_n and splitk a row's and an image's, with d_w and d_hw their divisions; d_c16, d_rs, d_s divide by a patch row's pieces,
+    // a channel's patch rows and R
+    int32_t wst_o, wst_i, wst_r, wst_s;
 };
 constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
 

@@ -4,6 +4,7 @@
 #include <mutex>
 
 #include "dplanar.h"
+#include "dstem.h"
 #include "dstream.h"
 #include "ops.h"
 
@@ -344,11 +345,61 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     return true;
 }
 
+// The same for the kernel over images of few channels (dstem.h): NCHW activations, filters of up to eight columns under any
+// unblocked layout, NHWC or channel-blocked bf16 output.
+static bool dstem_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
+{
+    auto no = [&](const char *m) { if (why) *why = m; return false; };
+    const IgemmParams &p = pb.p;
+    if (pb.dtype != ALT_BF16 || !p.out_bf16) return no("kernel for few channels is bf16 in and out");
+    if (p.batch != 1 || pb.groups > 1 || splitk != 1 || p.addend) return no("kernel for few channels takes no batch, groups, split-K or fused sum");
+    const int64_t C = p.C, H = p.H, W = p.W, OH = p.OH, OW = p.OW, K = p.Nc, R = p.R, S = p.S, N = p.M / (OH * OW);
+    if (C > 4 || S > 8 || C * R > 2 * k.prefetch || p.dil_h != 1 || p.dil_w != 1) return no("more channels, taps or dilation than the kernel for few channels holds");
+    if (!(dense(p.xw, W, 1) && dense(p.xh, H, W) && dense(p.xc, C, H * W) && dense(p.xn, N, C * H * W))) return no("activations are not dense NCHW");
+    if (!dense(p.wo, K, C * R * S) || (K > 1 && p.wo.si != C * R * S) || p.wi.f < C || p.wr.f < R || p.ws.f < S)
+        return no("filter is not dense with the output channel outermost");
+    int y_blk = 0;
+    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH, OW, N, &y_blk)) return no("output is not dense NHWC or N K/b H W b");
+    if (K % 8 || (uintptr_t)p.y % 16) return no("output is stored eight channels at a time");
+    if (pb.x_elems * 2 >= 0x7fffffff || p.y_bytes == 0 || pb.w_elems >= 0x7fffffff || C * N * H * W > 0x7fffff00) return no("operand of 2 GiB or more");
+    if (C * N * H * W < 8 || pb.w_elems > 0x3fffffff) return no("images of fewer than eight elements");
+    const int PCH = dstem_pieces(p.stride_w), PR = dstem_rows(p.stride_h, (int)R);
+    const int64_t pieces = (int64_t)dstem_copies(p.stride_w) * C * PR * PCH;
+    if (pieces > kStemMaxLoads * 256) return no("patch does not fit the registers it is loaded through");
+    const int patch = dstem_patch_bytes(k.BN / 32, (int)(C * R * S), (int)pieces);
+    const size_t lds = dstem_lds_bytes(2 * k.prefetch, k.BN / 32, patch);
+    if (lds > 64 * 1024) return no("patch does not fit LDS");
+    const int64_t tw = (OW + kStemTile - 1) / kStemTile, th = (OH + kStemTile - 1) / kStemTile;
+    if (tw * th * N > 0x7fffffff - 4096 || (K + k.BN - 1) / k.BN > 65535) return no("grid too large");
+    if (!out) return true;
+    DconvParams d;
+    std::memset(&d, 0, sizeof d);
+    d.x = p.x; d.w = p.w; d.bias = p.bias; d.y = p.y;
+    d.y_bytes = p.y_bytes;
+    d.M = p.M; d.Nc = p.Nc; d.C = p.C; d.H = p.H; d.W = p.W; d.R = p.R; d.S = p.S; d.pad_h = p.pad_h; d.pad_w = p.pad_w;
+    d.OH = p.OH; d.OW = p.OW; d.stride = p.stride_h; d.stride_w = p.stride_w;
+    d.in_px = (int32_t)(N * H * W);
+    d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | kDconvOutBf16;
+    d.tiles_m = (int32_t)(tw * th * N); d.tiles_n = (int32_t)tw; d.splitk = (int32_t)th;
+    d.d_w = make_div32((uint32_t)tw);
+    d.d_hw = make_div32((uint32_t)th);
+    d.d_c16 = make_div32((uint32_t)PCH);
+    d.d_rs = make_div32((uint32_t)PR);
+    d.d_s = make_div32((uint32_t)R);
+    d.ncc = patch;
+    d.wst_o = (int32_t)(C * R * S); d.wst_i = (int32_t)p.wi.si; d.wst_r = (int32_t)p.wr.si; d.wst_s = (int32_t)p.ws.si;
+    d.y_blk = y_blk;
+    *out = d;
+    *lds_bytes = lds;
+    return true;
+}
+
 // Fills the launch parameters of direct kernel `k` for `pb` split into `splitk`
 // channel slices, or says why the kernel does not cover the problem.
 bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
 {
     if (k.stream == 2) return dplanar_setup(pb, k, splitk, out, lds_bytes, why);
+    if (k.stream == 3) return dstem_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.taps) return dtaps_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream) return dstream_setup(pb, k, splitk, out, lds_bytes, why);
     auto no = [&](const char *m) { if (why) *why = m; return false; };
@@ -423,7 +474,7 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
 
 hipError_t dconv_run(const IgemmLaunch &k, DconvParams d, size_t lds, float *partial, hipStream_t st)
 {
-    if (d.splitk > 1) {
+    if (d.splitk > 1 && k.stream != 3) {
         uint32_t *base = nullptr;
         hipError_t e = dconv_counters(&base);
         if (e != hipSuccess) return e;

@@ -108,3 +108,18 @@ def test_products_with_ragged_depth_every_variant(h, bl, M, N, K):
         got = host(C, np.float32).reshape(M, N)
         assert canary_ok(whole, M * N) and np.array_equal(got, ref), name
     assert seen >= 4
+
+
+# tiles that end inside an image in both directions, one to four channels, odd and even strides (odd ones read a second, shifted
+# copy of the patch), filters of one to eight columns, output channels that leave part of a 32-channel tile empty
+@pytest.mark.parametrize("N,C,H,W,K,R,S,stride,pad", [
+    (2, 3, 37, 41, 64, 7, 7, 2, 3), (1, 3, 16, 16, 8, 3, 3, 2, 1), (1, 1, 9, 50, 40, 5, 5, 1, 2), (2, 4, 33, 20, 96, 3, 3, 1, 1),
+    (1, 3, 70, 66, 104, 7, 7, 2, 3), (1, 2, 21, 23, 32, 3, 8, 2, 4), (3, 3, 8, 8, 64, 1, 1, 1, 0), (1, 2, 40, 36, 48, 5, 6, 3, 0)])
+@pytest.mark.parametrize("wl,yl", [("OHWI", "NHWC"), ("OIHW", "NCHW8c")])
+def test_few_channel_kernels_every_variant(h, N, C, H, W, K, R, S, stride, pad, wl, yl):
+    d = alt.conv_desc(N, C, H, W, K, R, S, stride=stride, pad=pad, in_dtype=alt.BF16, out_dtype=alt.BF16, w_layout="OIHW->" + wl,
+                      y_layout="NCHW->" + yl)
+    few = [v for v, n in applicable_variants(h, d) if "_few_" in n]
+    assert few and "_few_" in h.conv2d_variant_name(d, -1)
+    for v in few:
+        check_conv(h, N, C, H, W, K, R, stride, pad, S=S, layouts=("NCHW", wl, yl), variant=v)
