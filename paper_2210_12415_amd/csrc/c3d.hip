@@ -21,6 +21,7 @@
 // result a last kernel moves into place; no inserted zeros are multiplied.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <string>
 
 #include "common.h"
@@ -368,9 +369,25 @@ alt_status_t run3d(alt_handle_t h, const Problem3d &pr, const void *x, const voi
     const alt_conv_desc_t &f = pr.f;
     const int elsz = (int)dtype_size(f.in_dtype);
     const size_t xu_bytes = gathered_bytes(pr);
+    // (the workspace that the unfolded input takes is asked for on either way: which one runs depends on the buffers' alignment)
     if (!workspace || ws_bytes < xu_bytes)
         return fail(h, ALT_WORKSPACE_TOO_SMALL, "%s: the workspace must hold the depth-unfolded input (%zu bytes)", who, xu_bytes);
     if ((uintptr_t)workspace % 16) return fail(h, ALT_INVALID_ARG, "%s: workspace must be 16-byte aligned", who);
+    if (pr.zd == 1 && pr.zh == 1 && pr.zw == 1) {
+        TapsCall c;
+        std::memset(&c, 0, sizeof c);
+        c.f = f;
+        for (int i = 0; i < 4; ++i) c.xs[i] = pr.xs[i];
+        const bool shaped = alt_conv2d_output_shape(&f, c.ys) == ALT_OK;
+        c.C = pr.C; c.K = f.K;
+        c.v.T = (int32_t)(f.C / pr.C); c.v.D = (int32_t)pr.D; c.v.OD = (int32_t)pr.OD;
+        c.v.stride_d = pr.sd; c.v.pad_d = pr.pd; c.v.dil_d = pr.dd;
+        c.v.sd = c.v.sh = c.v.sw = 1;
+        c.v.taps[0] = c.v.T; c.v.taps[1] = (int32_t)f.R; c.v.taps[2] = (int32_t)f.S;
+        bool done = false;
+        const alt_status_t cs = shaped ? taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, (hipStream_t)stream, &done) : ALT_OK;
+        if (done) return cs;
+    }
     GatherParams p;
     const int64_t us[4] = {f.N, f.C, f.H, f.W};
     std::string err;
@@ -434,8 +451,27 @@ alt_status_t run_subpixel3d(alt_handle_t h, const alt_conv3d_desc_t *d, const Su
     if ((uintptr_t)workspace % 16 || (uintptr_t)y % 16) return fail(h, ALT_INVALID_ARG, "alt_conv3d_transpose: workspace and y must be 16-byte aligned");
     if ((q.epilogue & ALT_EPI_BIAS) && !bias) return fail(h, ALT_INVALID_ARG, "alt_conv3d_transpose: ALT_EPI_BIAS without a bias");
     hipStream_t st = (hipStream_t)stream;
-    float *bias_m = (float *)((char *)workspace + yb);
     alt_status_t st_;
+    const int32_t strides[3] = {d->stride_d, q.stride_h, q.stride_w}, pads[3] = {d->pad_d, q.pad_h, q.pad_w};
+    const int32_t dils[3] = {d->dil_d, q.dil_h, q.dil_w};
+    const int64_t taps[3] = {d->T, q.R, q.S};
+    Volume v;
+    std::memset(&v, 0, sizeof v);
+    if (phase_taps(strides, pads, dils, taps, &v)) {
+        TapsCall c;
+        std::memset(&c, 0, sizeof c);
+        c.f = s.pr.f;
+        for (int i = 0; i < 4; ++i) c.xs[i] = s.pr.xs[i];
+        c.ys[0] = q.N * s.ad.outq * d->stride_d; c.ys[1] = q.K; c.ys[2] = s.ah.outq * q.stride_h; c.ys[3] = s.aw.outq * q.stride_w;
+        c.C = q.C; c.K = q.K;
+        c.v = v;
+        c.v.T = s.ad.taps; c.v.D = (int32_t)d->D; c.v.OD = (int32_t)s.ad.outq;
+        c.v.stride_d = 1; c.v.pad_d = s.ad.pad; c.v.dil_d = 1;
+        bool done = false;
+        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, st, &done);
+        if (done) return st_;
+    }
+    float *bias_m = (float *)((char *)workspace + yb);
     if (q.epilogue & ALT_EPI_BIAS)
         if ((st_ = phase_bias(h, bias, bias_m, q.K, s.pr.f.K, st)) != ALT_OK) return st_;
     st_ = run3d(h, s.pr, x, w_packed, (q.epilogue & ALT_EPI_BIAS) ? bias_m : nullptr, workspace, (char *)workspace + yb + bb,

@@ -95,6 +95,14 @@ struct DconvParams {
     int32_t c16, kq;              // 16-byte chunks per tap (a pixel's channels), and of the whole reduction
     uint32_t x_pix, w_row;        // bytes of an input pixel and of a filter row (T * R * S * C elements)
     uint32_t tap_d, tap_h, tap_w; // bytes between taps
+    uint32_t wtap_d, wtap_h, wtap_w;   // bytes between the taps of a filter row
+    int32_t w_dense;              // whether a filter row holds its taps in the order (depth, row, column)
+    // output phases of a transposed convolution (dstream.h; one per blockIdx.y): the phase's taps are T x R x S of the common
+    // window, from tap (phase + ph_pad) / stride + ph_first of each direction on; its outputs lie y_pd, y_ph, y_pw elements after
+    // those of the phase before (depth, row, column) and y_img, y_row, y_pix apart (y_blk = kOutPhases)
+    int32_t phases, ph_sh, ph_sw, ph_pad_d, ph_pad_h, ph_pad_w, ph_first_d, ph_first_h, ph_first_w;
+    uint32_t y_pd, y_ph, y_pw, y_img, y_row, y_pix;
+    Div32 d_phw, d_phd, d_phh, d_phs;  // divisions by stride_h * stride_w and the strides of the depth, rows and columns
     uint32_t x_shift;             // bytes from the first tap of output pixel 0 to x
     Div32 d_c16, d_rs, d_s, d_od; // divisions by c16, R * S, S, OD
     // kernel for images of few channels (dstem.h): element strides of the filter; there tiles_m counts tiles of 16 x 16 pixels,
@@ -102,6 +110,7 @@ struct DconvParams {
     // a channel's patch rows and R
     int32_t wst_o, wst_i, wst_r, wst_s;
 };
+constexpr int kOutPhases = -1;    // y_blk of an output written phase by phase
 constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
 
 // Element offset of channel `ch` of input pixel g (= img * H*W + hw) under the activations' layout.
@@ -119,6 +128,10 @@ __device__ __forceinline__ uint32_t dconv_out_elem(const DconvParams &p, int m, 
     if (p.y_blk == 0) return (uint32_t)(m * p.Nc + n);
     const int ohw = p.OH * p.OW;
     const int img = (int)div32((uint32_t)m, p.d_hw), q = m - img * ohw;
+    if (p.y_blk == kOutPhases) {
+        const uint32_t oh = div32((uint32_t)q, p.d_w), ow = (uint32_t)q - oh * (uint32_t)p.OW;
+        return (uint32_t)img * p.y_img + oh * p.y_row + ow * p.y_pix + (uint32_t)n;
+    }
     return (uint32_t)(img * (p.Nc * ohw) + ((((n >> p.y_blk) * ohw + q) << p.y_blk) | (n & ((1 << p.y_blk) - 1))));
 }
 

@@ -206,16 +206,21 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     auto no = [&](const char *m) { if (why) *why = m; return false; };
     const IgemmParams &p = pb.p;
     const int es = (int)dtype_size(pb.dtype), epc = 16 / es;
-    const int64_t C = p.C, H = p.H, W = p.W, OH = p.OH, OW = p.OW, K = p.Nc, R = p.R, S = p.S, N = p.M / (OH * OW);
-    if (R > kTapBits || S > kTapBits) return no("filters of more than ten taps in one direction");
+    const int64_t C = p.C, H = p.H, W = p.W, OH = p.OH, OW = p.OW, K = p.Nc, R = p.R, S = p.S;
+    // (a volume's slices are images; D = OD = T = 1 without one)
+    const Volume &v = pb.v;
+    const int64_t D = v.T ? v.D : 1, OD = v.T ? v.OD : 1, T = v.T ? v.T : 1, N = p.M / (OH * OW * OD), NX = N * D, NY = N * OD;
+    const int sd = v.T ? v.sd : 1, sh = v.T ? v.sh : 1, sw = v.T ? v.sw : 1, phases = sd * sh * sw;
+    const int64_t nT = phases > 1 ? v.taps[0] : T, nR = phases > 1 ? v.taps[1] : R, nS = phases > 1 ? v.taps[2] : S;
+    if (T > kTapBits || R > kTapBits || S > kTapBits) return no("filters of more than ten taps in one direction");
     if (C % epc) return no("a pixel's channels are not a whole number of 16-byte chunks");
     int x_blk = 0, y_blk = 0;
-    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, N, &x_blk) || x_blk) return no("activations are not dense NHWC");
-    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH, OW, N, &y_blk) || (y_blk && p.batch > 1)) return no("output is not dense NHWC or N K/b H W b");
+    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, NX, &x_blk) || x_blk) return no("activations are not dense NHWC");
+    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH * sh, OW * sw, NY * sd, &y_blk) || (y_blk && p.batch > 1)) return no("output is not dense NHWC or N K/b H W b");
     if (k.bt) {
-        if (R * S != 1 || !(dense(p.wo, K, 1) && dense(p.wi, C, K))) return no("B is not dense with N contiguous");
+        if (v.T || R * S != 1 || !(dense(p.wo, K, 1) && dense(p.wi, C, K))) return no("B is not dense with N contiguous");
         if (K % 8) return no("row-major B is loaded eight columns at a time");
-    } else if (!(dense(p.wi, C, 1) && dense(p.ws, S, C) && dense(p.wr, R, S * C) && dense(p.wo, K, R * S * C))) {
+    } else if (!(dense(p.wi, T * C, 1) && dense(p.ws, S, T * C) && dense(p.wr, R, S * T * C) && dense(p.wo, phases * K, R * S * T * C))) {
         return no("weights are not dense OHWI");
     }
     const int64_t osz = p.out_bf16 ? 2 : 4;
@@ -226,15 +231,15 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     if (pb.groups > 1) return no("a group's channels are not dense");
     if (p.addend && p.batch > 1) return no("the fused sum is not built for batched problems");
     if (splitk < 1 || (splitk > 1 && p.batch > 1)) return no("split-K is not built for batched problems");
-    const int64_t pix = C * es, shift = ((int64_t)p.pad_h * W + p.pad_w) * pix;
+    const int64_t pix = C * es, shift = ((v.T ? v.pad_d * H * W : 0) + (int64_t)p.pad_h * W + p.pad_w) * pix;
     if (pb.x_elems * es + shift >= 0x7fffffff || pb.w_elems * es >= 0x7fffffff || p.y_bytes == 0) return no("operand of 2 GiB or more");
     if ((int64_t)p.M * pix + shift >= 0x7fffffff && R * S == 1 && p.stride_h == 1) return no("operand of 2 GiB or more");
-    if ((int64_t)p.M * K * 4 >= 0x7fffffff) return no("output too large for 32-bit offsets");
+    if ((int64_t)p.M * phases * K * 4 >= 0x7fffffff) return no("output too large for 32-bit offsets");
     if (K % 4 || ((p.epilogue & ALT_EPI_BIAS) && (uintptr_t)p.bias % 16)) return no("streaming kernel stores four output columns at a time");
-    const int64_t reach = ((R - 1) * (int64_t)p.dil_h * W + (S - 1) * (int64_t)p.dil_w) * pix;
+    const int64_t reach = ((v.T ? (T - 1) * (int64_t)v.dil_d * H * W : 0) + (R - 1) * (int64_t)p.dil_h * W + (S - 1) * (int64_t)p.dil_w) * pix;
     if (reach + shift >= 0x3fffffff) return no("filter reaches too far");
     const int cpr = k.BK * es / 16;
-    const int64_t kq = R * S * C / epc, steps = (kq + cpr - 1) / cpr, slices = (int64_t)splitk * k.kw;
+    const int64_t kq = nT * nR * nS * C / epc, steps = (kq + cpr - 1) / cpr, slices = (int64_t)splitk * k.kw;
     if (k.taps == kTapsUniform && (C % k.BK || steps % slices)) return no("K steps do not divide the channels and the slices evenly");
     const int64_t nk = (steps + slices - 1) / slices;
     if ((slices - 1) * nk >= steps) return no("split factor leaves an empty slice");
@@ -251,9 +256,10 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     d.x_bytes = p.x_bytes; d.w_bytes = p.w_bytes; d.y_bytes = p.y_bytes;
     d.partial_bytes = (uint32_t)((int64_t)p.M * K * 4);
     d.M = p.M; d.Nc = p.Nc; d.C = p.C; d.Cs = p.C;
-    d.H = p.H; d.W = p.W; d.R = p.R; d.S = p.S; d.pad_h = p.pad_h; d.pad_w = p.pad_w;
+    d.H = p.H; d.W = p.W; d.R = (int32_t)nR; d.S = (int32_t)nS; d.pad_h = p.pad_h; d.pad_w = p.pad_w;
     d.OH = p.OH; d.OW = p.OW; d.stride = p.stride_h; d.dil = p.dil_h; d.stride_w = p.stride_w; d.dil_w = p.dil_w;
     d.T = d.D = d.OD = d.stride_d = d.dil_d = 1;
+    if (v.T) { d.T = (int32_t)nT; d.D = v.D; d.OD = v.OD; d.stride_d = v.stride_d; d.pad_d = v.pad_d; d.dil_d = v.dil_d; }
     d.tiles_m = tiles_m; d.tiles_n = tiles_n; d.splitk = splitk;
     d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | (p.out_bf16 ? kDconvOutBf16 : 0);
     d.d_hw = make_div32((uint32_t)(OH * OW));
@@ -261,20 +267,38 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     d.d_tm = make_div32((uint32_t)tiles_m);
     d.d_tn = make_div32((uint32_t)tiles_n);
     d.d_sk = make_div32((uint32_t)splitk);
-    d.d_od = make_div32(1);
+    d.d_od = make_div32((uint32_t)OD);
     d.ncc = (int32_t)nk;
     d.bk = k.BK;
-    d.taps = (int32_t)(R * S);
-    d.strided = !(R * S == 1 && OH == H && OW == W && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 0 && p.pad_w == 0);
+    d.taps = (int32_t)(nT * nR * nS);
+    d.strided = v.T || !(R * S == 1 && OH == H && OW == W && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 0 && p.pad_w == 0);
     d.c16 = (int32_t)(C / epc); d.kq = (int32_t)kq;
     d.d_c16 = make_div32((uint32_t)d.c16);
-    d.d_rs = make_div32((uint32_t)(R * S));
-    d.d_s = make_div32((uint32_t)S);
+    d.d_rs = make_div32((uint32_t)(nR * nS));
+    d.d_s = make_div32((uint32_t)nS);
     d.x_pix = (uint32_t)pix;
-    d.w_row = (uint32_t)(R * S * pix);
+    d.w_row = (uint32_t)(R * S * T * pix);
     d.tap_h = (uint32_t)(p.dil_h * W * pix);
     d.tap_w = (uint32_t)(p.dil_w * pix);
+    if (v.T) d.tap_d = (uint32_t)(v.dil_d * H * W * pix);
+    d.wtap_d = (uint32_t)pix;
+    d.wtap_h = (uint32_t)(S * T * pix);
+    d.wtap_w = (uint32_t)(T * pix);
+    d.w_dense = T == 1 && phases == 1;
     d.x_shift = (uint32_t)shift;
+    if (phases > 1) {
+        d.phases = phases;
+        d.ph_sh = sh; d.ph_sw = sw;
+        d.ph_pad_d = v.pad[0]; d.ph_pad_h = v.pad[1]; d.ph_pad_w = v.pad[2];
+        d.ph_first_d = v.pad_d + 1 - v.taps[0]; d.ph_first_h = p.pad_h + 1 - v.taps[1]; d.ph_first_w = p.pad_w + 1 - v.taps[2];
+        d.d_phw = make_div32((uint32_t)(sh * sw)); d.d_phd = make_div32((uint32_t)sd);
+        d.d_phh = make_div32((uint32_t)sh); d.d_phs = make_div32((uint32_t)sw);
+        d.y_pw = (uint32_t)K; d.y_ph = (uint32_t)(OW * sw * K); d.y_pd = (uint32_t)(OH * sh * OW * sw * K);
+        d.y_pix = sw * d.y_pw; d.y_row = sh * d.y_ph; d.y_img = sd * d.y_pd;
+        // (the last phase's outputs end where the tensor does)
+        d.y_bytes = p.y_bytes - (uint32_t)(((sd - 1) * (int64_t)d.y_pd + (sh - 1) * (int64_t)d.y_ph + (sw - 1) * (int64_t)d.y_pw) * osz);
+        y_blk = kOutPhases;
+    }
     d.batch = p.batch;
     d.y_blk = y_blk;
     d.d_ihw = make_div32((uint32_t)(H * W));

@@ -28,6 +28,10 @@
 //   kTapsRagged: any channel count that is a multiple of a chunk: every lane finds the tap of
 //     its own chunk (three divisions per K step, not per load).  The last step is filled up
 //     with zeros, so it also covers matrix products whose K is not a multiple of the K step.
+// The depth of a 3-D convolution is one more direction of taps, so that its input is read where it lies.  A transposed
+// convolution in its sub-pixel form is one such launch with the output phases along blockIdx.y: each phase walks the taps of
+// the merged filter that are its own (the others are zeros: three of four in a 4x4 filter at stride 2, seven of eight
+// in 4x4x4 of the 27 x 8 of the common window) and stores its pixels into the interleaved output.
 // T = float runs on the fp32 matrix instructions: a K step is BK floats, a 16-byte chunk four.
 #pragma once
 
@@ -93,7 +97,20 @@ void dstream_kernel(const DconvParams p)
         nt = rest - split * p.tiles_n;
     }
     const int m0 = mt * BM, n0 = nt * BN;
-    const int bz = blockIdx.y;                             // batch entry
+    const int bz = blockIdx.y;                             // batch entry, or output phase
+    // the phase's first tap in the common window (depth, row, column) and the offset of its first output
+    int f_d = 0, f_h = 0, f_w = 0;
+    int64_t y_phase = 0;
+    if constexpr (TAPS) {
+        if (p.phases > 1) {
+            const uint32_t pd = div32((uint32_t)bz, p.d_phw), phw = (uint32_t)bz - pd * (uint32_t)(p.ph_sh * p.ph_sw);
+            const uint32_t ph = div32(phw, p.d_phs), pw = phw - ph * (uint32_t)p.ph_sw;
+            f_d = (int)div32(pd + (uint32_t)p.ph_pad_d, p.d_phd) + p.ph_first_d;
+            f_h = (int)div32(ph + (uint32_t)p.ph_pad_h, p.d_phh) + p.ph_first_h;
+            f_w = (int)div32(pw + (uint32_t)p.ph_pad_w, p.d_phs) + p.ph_first_w;
+            y_phase = (int64_t)(pd * p.y_pd + ph * p.y_ph + pw * p.y_pw) * (p.flags & kDconvOutBf16 ? 2 : 4);
+        }
+    }
 
     const i32x4_t x_rsrc = TAPS ? make_rsrc((const char *)p.x + (int64_t)bz * p.x_bstride - p.x_shift, p.x_bytes + p.x_shift)
                                 : make_rsrc((const char *)p.x + (int64_t)bz * p.x_bstride, p.x_bytes);
@@ -124,10 +141,12 @@ void dstream_kernel(const DconvParams p)
                 const uint32_t oh = div32(q, p.d_w), ow = q - oh * (uint32_t)p.OW;
                 const uint32_t n = div32(img, p.d_od), od = img - n * (uint32_t)p.OD;
                 a_voff[i] = ((n * (uint32_t)p.D + od * (uint32_t)p.stride_d) * (uint32_t)(p.H * p.W) +
-                             oh * (uint32_t)(p.stride * p.W) + ow * (uint32_t)p.stride_w) * p.x_pix;
+                             oh * (uint32_t)(p.stride * p.W) + ow * (uint32_t)p.stride_w) * p.x_pix +
+                            (uint32_t)f_d * p.tap_d + (uint32_t)f_h * p.tap_h + (uint32_t)f_w * p.tap_w;
                 if (m < p.M) {
                     uint32_t mask = 0;
-                    const int ih0 = (int)oh * p.stride - p.pad_h, iw0 = (int)ow * p.stride_w - p.pad_w, id0 = (int)od * p.stride_d - p.pad_d;
+                    const int ih0 = (int)oh * p.stride - p.pad_h + f_h, iw0 = (int)ow * p.stride_w - p.pad_w + f_w;
+                    const int id0 = (int)od * p.stride_d - p.pad_d + f_d;
                     for (int r = 0; r < p.R; ++r) mask |= (unsigned)(ih0 + r * p.dil) < (unsigned)p.H ? 1u << r : 0u;
                     for (int q2 = 0; q2 < p.S; ++q2) mask |= (unsigned)(iw0 + q2 * p.dil_w) < (unsigned)p.W ? 1u << (kTapBits + q2) : 0u;
                     for (int d = 0; d < p.T; ++d) mask |= (unsigned)(id0 + d * p.dil_d) < (unsigned)p.D ? 1u << (2 * kTapBits + d) : 0u;
@@ -153,8 +172,10 @@ void dstream_kernel(const DconvParams p)
         } else {
             const int row = s / CPR, c = (s % CPR) ^ ((row / RP) & (CPR - 1));
             const int n = n0 + row;
-            if constexpr (TAPS == kTapsRagged) b_voff[i] = n < p.Nc ? (uint32_t)n * p.w_row : kOutOfRange;
-            else if constexpr (TAPS == kTapsUniform) b_voff[i] = n < p.Nc ? (uint32_t)n * p.w_row + (uint32_t)step0 * BKB + (uint32_t)c * 16u : kOutOfRange;
+            if constexpr (TAPS) {
+                b_voff[i] = n < p.Nc ? (uint32_t)n * p.w_row + (uint32_t)f_d * p.wtap_d + (uint32_t)f_h * p.wtap_h + (uint32_t)f_w * p.wtap_w +
+                                           (TAPS == kTapsUniform ? (uint32_t)c * 16u : 0u) : kOutOfRange;
+            }
             else b_voff[i] = n < p.Nc ? (uint32_t)(n * p.C) * 2u + k_off0 + (uint32_t)c * 16u : kOutOfRange;
         }
     }
@@ -175,7 +196,7 @@ void dstream_kernel(const DconvParams p)
         if constexpr (TAPS == kTapsUniform) {
             add_a = (uint32_t)u_t * p.tap_d + (uint32_t)u_r * p.tap_h + (uint32_t)u_s * p.tap_w + (uint32_t)u_c * 16u;
             sel = (1u << u_r) | (1u << (kTapBits + u_s)) | (1u << (2 * kTapBits + u_t));
-            add_b = (uint32_t)step * BKB;
+            add_b = (uint32_t)u_t * p.wtap_d + (uint32_t)u_r * p.wtap_h + (uint32_t)u_s * p.wtap_w + (uint32_t)u_c * 16u;
         } else if constexpr (TAPS == kTapsRagged) {
             const uint32_t q = chunk0 + (uint32_t)step * CPR;
             sel = 1u | (1u << kTapBits) | (1u << 2 * kTapBits);
@@ -183,7 +204,9 @@ void dstream_kernel(const DconvParams p)
             if (p.taps > 1) {
                 const uint32_t tap = div32(q, p.d_c16), td = div32(tap, p.d_rs), rs = tap - td * (uint32_t)(p.R * p.S);
                 const uint32_t tr = div32(rs, p.d_s), tc = rs - tr * (uint32_t)p.S;
-                add_a = td * p.tap_d + tr * p.tap_h + tc * p.tap_w + (q - tap * (uint32_t)p.c16) * 16u;
+                const uint32_t in_tap = (q - tap * (uint32_t)p.c16) * 16u;
+                add_a = td * p.tap_d + tr * p.tap_h + tc * p.tap_w + in_tap;
+                if (!p.w_dense) add_b = td * p.wtap_d + tr * p.wtap_h + tc * p.wtap_w + in_tap;
                 sel = (1u << tr) | (1u << (kTapBits + tc)) | (1u << (2 * kTapBits + td));
             }
             if (q >= (uint32_t)p.kq) { sel = 0x80000000u; add_b = kOutOfRange; }     // past the last chunk: zeros
@@ -207,7 +230,8 @@ void dstream_kernel(const DconvParams p)
         else dma_load16_s(x_rsrc, a_voff[i], soff, dst);
     };
     auto load_b = [&](int i, uint32_t soff, uint32_t dst) {
-        if constexpr (TAPS == kTapsRagged && !BT) dma_load16_s(w_rsrc, (b_voff[i] | add_b) & kOutOfRange ? kOutOfRange : b_voff[i] + add_b, 0u, dst);
+        if constexpr (TAPS == kTapsUniform) dma_load16_s(w_rsrc, b_voff[i], add_b, dst);
+        else if constexpr (TAPS == kTapsRagged && !BT) dma_load16_s(w_rsrc, (b_voff[i] | add_b) & kOutOfRange ? kOutOfRange : b_voff[i] + add_b, 0u, dst);
         else dma_load16_s(w_rsrc, b_voff[i], soff, dst);
     };
     // byte distance between consecutive K steps of B: BK columns of a row, or BK rows; of A: BK channels of a
@@ -448,10 +472,10 @@ void dstream_kernel(const DconvParams p)
     if constexpr (kBandedEpilogue<BM, BN, WGN, KW>) {
         static_assert(KW == 1, "banded epilogue: one K group");
         dconv_epilogue_banded<BM, BN, WGM, WGN>(p, acc, smem_u4, lane, wave, wm, wn, m0, n0,
-                                                (char *)p.y + (int64_t)bz * p.y_bstride);
+                                                (char *)p.y + (int64_t)bz * p.y_bstride + y_phase);
     } else {
         dconv_epilogue<BM, BN, WGM, WGN, KW>(p, acc, smem_u4, t, lane, wave, kg, wq, wm, wn, m0, n0, mt, nt, split,
-                                             (char *)p.y + (int64_t)bz * p.y_bstride);
+                                             (char *)p.y + (int64_t)bz * p.y_bstride + y_phase);
     }
 }
 

@@ -5,6 +5,15 @@
 
 namespace alt {
 
+// What the kernels over filter taps add to a 2-D problem: a depth direction, whose taps lie beside the channels in a filter
+// row ((r, s), (t, c): the filter alt_conv3d packs), and the output phases of a transposed convolution in its sub-pixel form.
+// All zero for an ordinary problem.
+struct Volume {
+    int32_t T, D, OD, stride_d, pad_d, dil_d;   // T = 0: an ordinary problem
+    int32_t sd, sh, sw;                         // phases per direction (1: none); then per direction:
+    int32_t pad[3], taps[3];                    // the operator's own padding and the taps of one phase
+};
+
 // One conv/gemm call reduced to what the implicit-GEMM kernels need.
 struct Problem {
     IgemmParams p;
@@ -14,6 +23,16 @@ struct Problem {
     int64_t x_elems, w_elems;              // elements of one batch entry of each operand
     int64_t groups;                        // convolution groups (1 for ordinary problems and products)
     bool depthwise;                        // groups = C = K: runs on dwconv.hip, p describes the whole tensors
+    Volume v;
+};
+
+// A 3-D or transposed convolution as the kernels over filter taps read it: `f` the merged or depth-unfolded 2-D problem, over
+// whose weights they run, xs and ys the extents of the tensors where they lie.
+struct TapsCall {
+    alt_conv_desc_t f;
+    int64_t xs[4], ys[4];
+    int64_t C, K;                          // channels of a tap, output channels of a phase
+    Volume v;
 };
 
 extern const int kSplitFactors[];
@@ -43,6 +62,11 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
 // eltwise.hip
 alt_status_t eltwise_add(alt_handle_t h, int dtype, int64_t numel, const void *a, const void *b, void *y, int relu,
                          hipStream_t st);
+
+// ops.hip: runs the call on a kernel over filter taps and says so in *done, or leaves it alone (a layout, size or alignment these
+// kernels do not take, or a variant of the 2-D problem asked for by number)
+alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
+                      size_t ws_bytes, hipStream_t st, bool *done);
 
 alt_status_t conv_problem(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w,
                           const float *bias, void *y, Problem *pb);

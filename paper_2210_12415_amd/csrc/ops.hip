@@ -101,13 +101,15 @@ bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igemm
     auto no = [&](const char *m) { if (why) *why = m; return false; };
     const IgemmParams &p0 = pb.p;
     if (k.dtype != pb.dtype) return no("element type");
+    if (pb.v.T && !k.taps) return no("depth taps and output phases are built into the kernels over filter taps only");
     if (p0.addend && !k.launch_direct) return no("the fused sum is built into the tile kernels only");
     if (k.launch_direct) {
         if (!dconv_setup(pb, k, splitk, nullptr, nullptr, why)) return false;
         if (out) {
             IgemmParams p = p0;
             p.splitk = splitk;
-            p.ksteps_total = k.taps ? (p.R * p.S * p.C + k.BK - 1) / k.BK : p.R * p.S * (p.C / 64);
+            const int64_t taps = pb.v.T ? (int64_t)pb.v.taps[0] * pb.v.taps[1] * pb.v.taps[2] : (int64_t)p.R * p.S;
+            p.ksteps_total = (int32_t)(k.taps ? (taps * p.C + k.BK - 1) / k.BK : p.R * p.S * (p.C / 64));
             p.ksteps_per_split = (p.ksteps_total + splitk - 1) / splitk;
             p.tiles_m = (p.M + k.BM - 1) / k.BM;
             p.tiles_n = (p.Nc + k.BN - 1) / k.BN;
@@ -546,6 +548,59 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
     memo_store(h, d, sizeof *d, sig, ws_limit, pb, v);
     return igemm_run(h, pb, v, workspace, ws_bytes, (hipStream_t)stream);
 }
+
+}  // extern "C"
+
+namespace alt {
+// (a depth-unfolded copy of the input costs T times its traffic, a merged filter sh*sw (sd*sh*sw) times the products that are not
+// zeros, and its result one more pass into place: 128 channels, 3x3x3 on 8x28x28 at batch 2 took 48 us that way and T3D
+// 128 -> 64, 4x4x4 at stride 2 on the same volume 128 us; so these kernels run whatever they cover)
+alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
+                      size_t ws_bytes, hipStream_t st, bool *done)
+{
+    *done = false;
+    if (c.f.variant >= 0 || !x || !w || !y || ((c.f.epilogue & ALT_EPI_BIAS) && !bias)) return ALT_OK;
+    const size_t ws_limit = workspace ? ws_bytes : 0;
+    const unsigned sig = align_sig(x, w, bias, y) | 1u << 31;
+    Problem pb;
+    int v = -1;
+    if (MemoEntry *m = memo_find(h, &c, sizeof c, sig, ws_limit)) {
+        pb = m->pb;
+        v = m->variant;
+    } else {
+        BoundLayout bx, by;
+        Dim2 dx[4], dy[4];
+        std::string err;
+        bool ok = conv_problem(h, &c.f, x, w, bias, y, &pb) == ALT_OK && pb.groups <= 1 &&
+                  bind_layout(&c.f.x_layout, 4, c.xs, &bx, &err) == ALT_OK && bind_layout(&c.f.y_layout, 4, c.ys, &by, &err) == ALT_OK &&
+                  layout_to_dim2(bx, dx) && layout_to_dim2(by, dy);
+        if (ok) {
+            const int64_t es = (int64_t)dtype_size(c.f.in_dtype), os = (int64_t)dtype_size(c.f.out_dtype);
+            IgemmParams &p = pb.p;
+            pb.v = c.v;
+            p.xn = dx[0]; p.xc = dx[1]; p.xh = dx[2]; p.xw = dx[3];
+            p.yn = dy[0]; p.yk = dy[1]; p.yh = dy[2]; p.yw = dy[3];
+            p.C = (int32_t)c.C;
+            p.Nc = (int32_t)c.K;
+            p.batch = c.v.sd * c.v.sh * c.v.sw;
+            pb.x_elems = bx.numel;
+            pb.w_elems = (int64_t)c.K * c.f.C * c.f.R * c.f.S;
+            p.x_bstride = 0; p.w_bstride = pb.w_elems; p.y_bstride = 0;
+            p.x_bytes = (uint32_t)std::min<int64_t>(pb.x_elems * es, 0x7fffffff);
+            p.w_bytes = (uint32_t)std::min<int64_t>(pb.w_elems * es, 0x7fffffff);
+            p.y_bytes = by.numel * 4 < 0x7fffffff ? (uint32_t)(by.numel * os) : 0;
+            v = igemm_default_variant(pb, ws_limit);
+        }
+        memo_store(h, &c, sizeof c, sig, ws_limit, pb, v);
+    }
+    if (v < 0) return ALT_OK;
+    *done = true;
+    pb.p.x = x; pb.p.w = w; pb.p.bias = bias; pb.p.y = y;
+    return igemm_run(h, pb, v, workspace, ws_bytes, st);
+}
+}  // namespace alt
+
+extern "C" {
 
 alt_status_t alt_conv2d(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w, const float *bias,
                         void *y, void *workspace, size_t ws_bytes, void *stream)

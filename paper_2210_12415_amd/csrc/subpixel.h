@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "ops.h"
+
 namespace alt {
 
 struct PhaseAxis {
@@ -37,6 +39,19 @@ inline PhaseAxis phase_axis(int64_t in, int64_t taps, int stride, int pad, int d
     a.outq = out / stride;
     a.ok = in + 2 * (int64_t)a.pad - a.taps + 1 == a.outq;
     return a;
+}
+
+// Whether every phase of every direction has the same number of neighbouring taps (extents that are multiples of the strides,
+// no dilation), so that a kernel can walk a phase's own taps; fills the directions (depth, rows, columns) of `v` if so.
+inline bool phase_taps(const int32_t stride[3], const int32_t pad[3], const int32_t dil[3], const int64_t taps[3], Volume *v)
+{
+    for (int i = 0; i < 3; ++i) {
+        if (taps[i] % stride[i] || (dil[i] != 1 && taps[i] > 1) || taps[i] / stride[i] > 64) return false;
+        v->pad[i] = pad[i];
+        v->taps[i] = (int32_t)(taps[i] / stride[i]);
+    }
+    v->sd = stride[0]; v->sh = stride[1]; v->sw = stride[2];
+    return true;
 }
 
 }  // namespace alt

@@ -8,6 +8,8 @@
 // expanded input per call, into the workspace), then alt_conv2d does the work.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
+
 #include <string>
 
 #include "common.h"
@@ -393,8 +395,25 @@ alt_status_t run_subpixel(alt_handle_t h, const alt_conv_desc_t *d, const SubPix
     if ((uintptr_t)workspace % 16 || (uintptr_t)y % 16) return fail(h, ALT_INVALID_ARG, "alt_conv2d_transpose: workspace and y must be 16-byte aligned");
     if ((d->epilogue & ALT_EPI_BIAS) && !bias) return fail(h, ALT_INVALID_ARG, "alt_conv2d_transpose: ALT_EPI_BIAS without a bias");
     hipStream_t st = (hipStream_t)stream;
-    float *bias_m = (float *)((char *)workspace + yb);
     alt_status_t st_;
+    const int32_t strides[3] = {1, d->stride_h, d->stride_w}, pads[3] = {0, d->pad_h, d->pad_w}, dils[3] = {1, d->dil_h, d->dil_w};
+    const int64_t taps[3] = {1, d->R, d->S};
+    Volume v;
+    std::memset(&v, 0, sizeof v);
+    if (phase_taps(strides, pads, dils, taps, &v)) {
+        TapsCall c;
+        std::memset(&c, 0, sizeof c);
+        c.f = s.f;
+        c.xs[0] = d->N; c.xs[1] = d->C; c.xs[2] = d->H; c.xs[3] = d->W;
+        c.ys[0] = d->N; c.ys[1] = d->K; c.ys[2] = s.ah.outq * d->stride_h; c.ys[3] = s.aw.outq * d->stride_w;
+        c.C = d->C; c.K = d->K;
+        c.v = v;
+        c.v.T = c.v.D = c.v.OD = c.v.stride_d = c.v.dil_d = 1;
+        bool done = false;
+        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, st, &done);
+        if (done) return st_;
+    }
+    float *bias_m = (float *)((char *)workspace + yb);
     if (d->epilogue & ALT_EPI_BIAS)
         if ((st_ = phase_bias(h, bias, bias_m, d->K, s.f.K, st)) != ALT_OK) return st_;
     st_ = alt_conv2d(h, &s.f, x, w_packed, (d->epilogue & ALT_EPI_BIAS) ? bias_m : nullptr, workspace,
