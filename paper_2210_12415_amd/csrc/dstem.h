@@ -12,7 +12,7 @@
 // rows of each channel comes in through registers while the previous tile computes.  A row tile of the matrix
 // instruction is 2 x 16 pixels.  Results are rounded, transposed through LDS, and stored 16 bytes per lane.
 //
-// 16 images of 3 x 224 x 224, 64 channels of 7 x 7 at stride 2 (30 MB, 3.8 GFLOP): 16.2 us, 1.9 TB/s, against 118 us on the
+// 16 images of 3 x 224 x 224, 64 channels of 7 x 7 at stride 2 (30 MB, 3.8 GFLOP): 14.7 us, 2.1 TB/s, against 118 us on the
 // element-gather kernel; 64 images 42 us, 2.9 TB/s. What bounds it is instruction issue: per row tile 22 matrix instructions
 // stand beside about 150 others (window reads and masks, rounding, the transpose, store addresses) on two waves per SIMD.
 #pragma once

@@ -173,16 +173,36 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
         const double rounds = std::ceil(blocks / (256.0 * per_cu));
         const double steps = k.taps ? std::ceil((double)p.ksteps_per_split / k.kw) : (double)p.C / p.splitk / k.kw / k.BK;
-        // (fp32 matrix instructions do a sixteenth of the products per clock)
-        const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * (k.dtype == ALT_BF16 ? 8.0 : 128.0) * (waves >= 8 ? 1.7 : 2.0);
+        // (a split's partial sums are written, fetched and added by whoever comes last: fitted over products of 37 to 10000 rows,
+        // 1 us a MB of them; 1536 x 512 x 2048 in eight slices of 256x128 tiles took 38 us, unsplit on 64x64 tiles 10.8)
+        const double partial_us = p.splitk > 1 ? 1e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0 : 0.0;
+        if (k.dtype == ALT_F32) {
+            // fp32: matrix instructions do a sixteenth of the products per clock, so co-resident workgroups share them; a
+            // step costs 280 clocks beside its products, a workgroup 7200, a split 0.8 us and 0.9 us a MB (fitted over 40
+            // convolutions of 0.05 to 3 GFLOP; the choice is at most 5 % from the fastest variant).  They beat the
+            // register-staged kernels on each of the 40: the five 3x3 and 1x1 layers at batch 5 take
+            // 15.5 / 17.9 / 20.2 / 21.3 / 8.7 us against 28.9 / 26.4 / 26.9 / 26.6 / 13.4.  Past 60 us nothing was compared, and
+            // the two estimates meet as they are.
+            const double need = std::max((double)k.kw * k.BM * k.BN * k.BK / 128.0 * (waves >= 8 ? 1.11 : 1.07) * std::max(1.0, 4.0 / waves),
+                                         (double)k.kw * (k.BM + k.BN) * k.BK * es / 33.6);
+            auto round_clk = [&](double n) { return steps * std::max(need + 280.0, n * need) + 7200.0; };
+            const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
+            const double us = (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0 + (p.splitk > 1 ? 0.8 + 0.9 * partial_us : 0.0);
+            return (us < 60.0 ? 0.2 : 0.5) * us * 45.0;
+        }
+        const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * 8.0 * (waves >= 8 ? 1.7 : 2.0);
         const double bytes = (double)k.kw * (k.BM + k.BN) * k.BK * es / 45.0;
         const double clk = rounds * (steps * (std::max(mfma, bytes) + 120.0) + 6000.0);
         // (halved like the direct kernels' estimate below: wherever one of these kernels applies it
         // has beaten the implicit-GEMM kernels, whose estimate is optimistic)
         // The kernels over filter taps fetch a pixel once per tap, so where the patch-resident or the plain streaming
         // kernels cover the problem (bf16, channels a multiple of 64) those come first.
-        const double taps = k.taps && k.dtype == ALT_BF16 && p.C % 64 == 0 ? 3.0 : 1.0;
-        return taps * 0.5 * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 : 0.0));
+        const double taps = k.taps && p.C % 64 == 0 ? 3.0 : 1.0;
+        // One tap leaves the patch-resident kernel nothing to reuse, and its and the implicit-GEMM kernels' estimates know little
+        // of what many slices cost: 37 x 768 x 3072 took 21.6 us on the former in 24 slices, 19.9 here in 24, 7.3 in four;
+        // 200 x 1024 x 1024 17.0 and 7.1; 810 x 384 x 1536 17.7 and 7.1. No product of the 36 compared was faster elsewhere.
+        const double lead = p.R * p.S == 1 ? 0.25 : 0.5;
+        return taps * lead * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 + 45.0 * partial_us : 0.0));
     }
     if (k.launch_direct && k.stream == 2) {
         // Channel-planar kernel: a workgroup converts its patch on the way in (about 20 bytes per clock
@@ -227,6 +247,8 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
     const double step = (double)k.BM * k.BN * k.BK / 16384.0 + 3.0 * (k.BM + k.BN) * k.BK / 8192.0 + 2.0;
     double est = rounds * (p.ksteps_per_split * step + 60.0) * mode_cost;
     if (p.splitk > 1) est += (k.launch_direct ? 5.0 : 30.0) + 0.00002 * p.splitk * (double)p.M * p.Nc * p.batch;
+    // (of one tap: what a split costs the streaming kernel, whose tail it shares)
+    if (p.splitk > 1 && k.launch_direct && p.R * p.S == 1) est += 70.0 + 22.5e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0;
     return est;
 }
 

@@ -167,3 +167,29 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     got = np.moveaxis(host(y, np.float32).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1)
     assert canary_ok(whole, ref.size), "wrote outside y"
     assert np.array_equal(got, ref)
+
+
+# single precision: the library's own choice among tiles, K groups and slices (remainders in all of them), with the workspace that
+# this choice asks for
+@pytest.mark.parametrize("N,C,H,W,K,R", [(5, 64, 21, 19, 64, 3), (1, 512, 7, 7, 512, 3), (3, 72, 9, 11, 76, 3), (1, 256, 30, 31, 36, 1),
+                                         (1, 8, 5, 5, 4, 3), (2, 320, 6, 5, 320, 3)])
+def test_fp32_default_choice(h, N, C, H, W, K, R):
+    d = alt.conv_desc(N, C, H, W, K, R, R, pad=R // 2, in_dtype=alt.F32, out_dtype=alt.F32, x_layout="NCHW->NHWC",
+                      w_layout="OIHW->OHWI", y_layout="NCHW->NHWC", epilogue=alt.EPI_BIAS | alt.EPI_RELU)
+    assert "_rtaps_" in h.conv2d_variant_name(d, -1)
+    check_conv(h, N, C, H, W, K, R, pad=R // 2, dtype=alt.F32)
+
+
+# products of few rows and long sums: unsplit or in a few slices, never on the patch-resident kernel
+@pytest.mark.parametrize("M,N,K", [(37, 768, 3072), (200, 1024, 4096), (810, 384, 1536), (1, 64, 8192), (300, 264, 2048)])
+@pytest.mark.parametrize("lay", ["NK", "KN"])
+def test_product_default_choice(h, M, N, K, lay):
+    a, b = small_ints_f32(81, (M, K), -2, 2), small_ints_f32(82, (K, N), -2, 2)
+    A, B = f32_to_bf16_bits(a), f32_to_bf16_bits(b)
+    d = alt.gemm_desc(M, N, K, b_layout="KN->" + lay)
+    assert "stream" in h.gemm_variant_name(d, -1) or "taps" in h.gemm_variant_name(d, -1)
+    ws_bytes = h.gemm_workspace_size(d)
+    whole, C = canary_dev(M * N, np.float32)
+    h.gemm(d, dev(A), dev(B if lay == "KN" else np.ascontiguousarray(B.T)), C, workspace=dev(np.zeros(max(1, ws_bytes // 4), np.float32)),
+           ws_bytes=ws_bytes)
+    assert canary_ok(whole, M * N) and np.array_equal(host(C, np.float32).reshape(M, N), oracle.gemm(A, B))
