@@ -344,7 +344,7 @@ __device__ __forceinline__ bool dconv_epilogue_tail(const DconvParams &p, uint4 
     }
 
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y, 0, (int)p.y_bytes, 0x00020000);
-    const float relu_floor = (p.flags & ALT_EPI_RELU) ? 0.f : -INFINITY;
+    const float floor_ = relu_floor(p.flags & ALT_EPI_RELU);
     const bool out_bf16 = p.flags & kDconvOutBf16;
     float bv[CW];
 #pragma unroll
@@ -385,7 +385,7 @@ __device__ __forceinline__ bool dconv_epilogue_tail(const DconvParams &p, uint4 
         }
         float o[CW];
 #pragma unroll
-        for (int q = 0; q < CW; ++q) o[q] = fmaxf(vs[it][q / 4][q % 4] + bv[q] + ad[q], relu_floor);
+        for (int q = 0; q < CW; ++q) o[q] = fmaxf(vs[it][q / 4][q % 4] + bv[q] + ad[q], floor_);
         if (CW == 8 || out_bf16) {                         // (eight columns per lane are only used for bf16 output)
             uint32_t w[CW / 2];
 #pragma unroll
@@ -478,7 +478,7 @@ __device__ __forceinline__ void dconv_epilogue_banded(const DconvParams &p, floa
     float *stg = (float *)smem_u4 + wave * (32 * SP);
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y, 0, (int)p.y_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc((void *)p.addend, 0, (int)p.y_bytes, 0x00020000);
-    const float relu_floor = (p.flags & ALT_EPI_RELU) ? 0.f : -INFINITY;
+    const float floor_ = relu_floor(p.flags & ALT_EPI_RELU);
     const bool wide = (p.flags & kDconvOutBf16) && p.Nc % 8 == 0;      // eight bf16 columns per lane
     auto band = [&](auto cw, int i) {
         constexpr int CW = decltype(cw)::value;
@@ -530,7 +530,7 @@ __device__ __forceinline__ void dconv_epilogue_banded(const DconvParams &p, floa
                 for (int q = 0; q < 4; ++q) ad[q] = z[q];
             }
 #pragma unroll
-            for (int q = 0; q < CW; ++q) o[q] = fmaxf(o[q] + bv[q] + ad[q], relu_floor);
+            for (int q = 0; q < CW; ++q) o[q] = fmaxf(o[q] + bv[q] + ad[q], floor_);
             if (CW == 8 || (p.flags & kDconvOutBf16)) {
                 uint32_t w[CW / 2];
 #pragma unroll

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void dstem_kernel(const DconvParams p)
         const uint32_t c = div32((uint32_t)q, p.d_s);
         off[kc] = q < chunks ? ((int)c * PR + (q - (int)c * p.R)) * pitch : -1;
     }
-    const float floor_ = (p.flags & ALT_EPI_RELU) ? 0.f : -INFINITY;
+    const float floor_ = relu_floor(p.flags & ALT_EPI_RELU);
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, (int)p.y_bytes, 0x00020000);
     const int odd = (pcol * p.stride_w) & 1;
     constexpr int SP = TN * 64 + 16;                       // staging pitch of a pixel in bytes

@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
         blo = __builtin_shufflevector(b0, b1, 0, 2, 4, 6);
         bhi = __builtin_shufflevector(b0, b1, 1, 3, 5, 7);
     }
-    const float floor_ = (p.epilogue & ALT_EPI_RELU) ? 0.f : -INFINITY;
+    const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
     const int32_t yb = dim2_off32(p.yn, n) + dim2_off32(p.yk, c), syh = (int32_t)p.yh.si, syw = (int32_t)p.yw.si;
 #pragma unroll
     for (int i = 0; i < TH; ++i)
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_rows_3x3_kernel(const DwPar
                 for (int j = 0; j < TW; ++j) acc[j] += xv[j * STRIDE + fs] * wq[fr * 3 + fs];
         }
         const float bias = (p.epilogue & ALT_EPI_BIAS) ? p.bias[c] : 0.f;
-        const float floor_ = (p.epilogue & ALT_EPI_RELU) ? 0.f : -INFINITY;
+        const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
         wv_t out;
 #pragma unroll
         for (int q = 0; q < TW / 2; ++q)

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kEltThreads) void eltwise_add_kernel(const void *a,
     typedef uint32_t w4_t __attribute__((ext_vector_type(4)));
     typedef float f4_t __attribute__((ext_vector_type(4)));
     constexpr int EPV = 16 / ELSZ;
-    const float floor_ = relu ? 0.f : -INFINITY;
+    const float floor_ = relu_floor(relu);
     const int64_t n16 = numel / EPV;
     for (int64_t v = blockIdx.x * (int64_t)kEltThreads + threadIdx.x; v < n16; v += (int64_t)gridDim.x * kEltThreads) {
         // (whole-vector arithmetic: element-wise float views of a loaded vector are miscompiled

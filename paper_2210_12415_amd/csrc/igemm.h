@@ -141,6 +141,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
     return (uint16_t)(((w & 0x7fffffffu) > 0x7f800000u) ? quiet : rounded);
 }
 
+// What a result is raised to before it is stored: 0 under ReLU, else NaN, which a maximum passes over (it returns the operand
+// that is a number), so that every value stays as it is, NaN among them; -inf in its place would turn a NaN into -inf.
+__device__ __forceinline__ float relu_floor(bool relu) { return relu ? 0.f : __builtin_nanf(""); }
+
 // Two fp32 -> bf16 conversions (round to nearest even, NaN kept quiet) packed into one
 // dword, lo in the low half: one hardware conversion instruction on gfx950.
 __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi)
@@ -228,7 +232,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams &p, floatx16_t 
             }
         // straight-line store loops (no branch per element, so the compiler's
         // wait-count bookkeeping never makes a store wait for the one before it)
-        const float relu_floor = (p.epilogue & ALT_EPI_RELU) ? 0.f : -INFINITY;
+        const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
         const int mode = to_partial ? 0 : (p.out_bf16 ? 2 : 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -255,7 +259,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams &p, floatx16_t 
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
-                        const float v = fmaxf(acc[i][j][e] + bv, relu_floor);
+                        const float v = fmaxf(acc[i][j][e] + bv, floor_);
                         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rsrc, (int)voff[i][e], 0, 0);
                     }
             } else {
@@ -263,7 +267,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams &p, floatx16_t 
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
-                        const float v = fmaxf(acc[i][j][e] + bv, relu_floor);
+                        const float v = fmaxf(acc[i][j][e] + bv, floor_);
                         __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_rne(v), rsrc, (int)voff[i][e], 0, 0);
                     }
             }
