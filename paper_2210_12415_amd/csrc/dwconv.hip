@@ -36,7 +36,7 @@ struct DwParams {
     void *y;
     int32_t N, C, H, W, R, S, OH, OW;
     int32_t stride_h, stride_w, pad_h, pad_w, dil_h, dil_w;
-    int32_t epilogue, in_bf16, out_bf16, chan_fast, w_taps;
+    int32_t epilogue, in_bf16, out_bf16, chan_fast;
     Dim2 xn, xc, xh, xw, wo, wr, ws, yn, yk, yh, yw;
     // 3x3 vector kernel: threads, the divisions of a thread's index, sizes of the tensors
     uint32_t items, x_bytes, y_bytes;
@@ -101,7 +101,10 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_elem_kernel(const DwParams 
     }
 }
 
-// bf16 in and out, eight consecutive channels per thread (one 16-byte access per tensor and tap).
+// bf16 in and out, eight consecutive channels per thread (one 16-byte access per tensor and tap).  TAPS: the taps of a channel
+// lie side by side, so a tap's eight filter values are loaded one by one.  (A template: the choice made inside the loop over
+// the taps cost filters with the channel innermost 13 to 20 %, 26 x 568 x 40 x 40 under 5x5 156 us against 133.)
+template <bool TAPS>
 __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams p)
 {
     typedef uint32_t w4_t __attribute__((ext_vector_type(4)));
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams 
                 if ((unsigned)iw >= (unsigned)p.W) continue;
                 const w4_t xv = *(const w4_t *)((const uint16_t *)p.x + xb + dim2_off(p.xh, ih) + dim2_off(p.xw, iw));
                 w4_t wv;
-                if (p.w_taps) {                     // the taps of a channel side by side: element by element
+                if constexpr (TAPS) {
                     const uint16_t *we = (const uint16_t *)p.w + (int64_t)c * p.R * p.S + fr * p.S + fs;
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
@@ -381,9 +384,10 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
     const Dim2 xo[3] = {q.xn, q.xh, q.xw}, wo_[2] = {q.wr, q.ws}, yo[3] = {q.yn, q.yh, q.yw};
     // filters: eight channels a 16-byte run per tap, or (taps) the taps of a channel side by side
     const bool taps = q.wo.f >= C && q.wo.si == q.R * q.S && q.wr.f >= q.R && q.wr.si == q.S && q.ws.f >= q.S && q.ws.si == 1;
-    const bool vec = p.in_bf16 && p.out_bf16 && chan_runs_of_8(q.xc, C, xo, 3) && (taps || chan_runs_of_8(q.wo, C, wo_, 2)) &&
-                     chan_runs_of_8(q.yk, C, yo, 3) && (uintptr_t)q.x % 16 == 0 && (uintptr_t)q.w % 16 == 0 &&
-                     (uintptr_t)q.y % 16 == 0 && (!(q.epilogue & ALT_EPI_BIAS) || (uintptr_t)q.bias % 16 == 0);
+    const bool wchan = chan_runs_of_8(q.wo, C, wo_, 2);
+    bool vec = p.in_bf16 && p.out_bf16 && chan_runs_of_8(q.xc, C, xo, 3) && (taps || wchan) && chan_runs_of_8(q.yk, C, yo, 3) &&
+               (uintptr_t)q.x % 16 == 0 && (uintptr_t)q.w % 16 == 0 && (uintptr_t)q.y % 16 == 0 &&
+               (!(q.epilogue & ALT_EPI_BIAS) || (uintptr_t)q.bias % 16 == 0);
     const bool k3x3 = vec && q.R == 3 && q.S == 3 && q.dil_h == 1 && q.dil_w == 1 && q.stride_h == q.stride_w &&
                       (q.stride_h == 1 || q.stride_h == 2) && q.xh.f >= q.H && q.xw.f >= q.W && q.yh.f >= q.OH &&
                       q.yw.f >= q.OW && N * C * q.H * q.W < (1 << 30) && N * C * q.OH * q.OW < (1 << 30);
@@ -408,7 +412,12 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
         ALT_CHECK_HIP(h, hipGetLastError());
         return ALT_OK;
     }
-    p.w_taps = taps && !chan_runs_of_8(q.wo, C, wo_, 2);
+    // Filters whose taps lie side by side, beyond 3x3: a thread of the vector kernel loads eight scattered filter values per tap,
+    // which pays once the element kernel's eight times as many threads fill the chip (5x5 at stride 2: 1 x 480 x 28 x 28, 11760
+    // vectors, 17.4 us against 12.2; 2 x 120 x 75 x 75, 43320, 17.1 and 16.9; 1 x 360 x 70 x 70, 55125, 17.6 and 23.7), or where
+    // 8, 16 or 32 channels let a wave's lanes share the values (5 x 8 x 67 x 67, 22445 vectors, 10.0 and 12.3).
+    const int64_t vectors = N * q.OH * q.OW * (C / 8);
+    if (!wchan && vectors < 49152 && C != 8 && C != 16 && C != 32) vec = false;
     const Dim2 xr[3] = {q.xn, q.xc, q.xh}, yr[3] = {q.yn, q.yk, q.yh};
     const bool rows = !vec && p.in_bf16 && p.out_bf16 && q.R == 3 && q.S == 3 && q.dil_h == 1 && q.dil_w == 1 &&
                       q.stride_h == q.stride_w && (q.stride_h == 1 || q.stride_h == 2) && q.pad_w == 1 && q.xw.si == 1 &&
@@ -425,7 +434,8 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
     else if (rows8) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<2, 8>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (rows && q.stride_h == 1) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<1, 4>), dim3(blocks), dim3(kDwThreads), 0, st, p);
     else if (rows) hipLaunchKernelGGL((dwconv_rows_3x3_kernel<2, 4>), dim3(blocks), dim3(kDwThreads), 0, st, p);
-    else if (vec) hipLaunchKernelGGL(dwconv_vec8_kernel, dim3(blocks), dim3(kDwThreads), 0, st, p);
+    else if (vec && wchan) hipLaunchKernelGGL(dwconv_vec8_kernel<false>, dim3(blocks), dim3(kDwThreads), 0, st, p);
+    else if (vec) hipLaunchKernelGGL(dwconv_vec8_kernel<true>, dim3(blocks), dim3(kDwThreads), 0, st, p);
     else hipLaunchKernelGGL(dwconv_elem_kernel, dim3(blocks), dim3(kDwThreads), 0, st, p);
     ALT_CHECK_HIP(h, hipGetLastError());
     return ALT_OK;

@@ -42,6 +42,16 @@ def canary_ok(whole, n, pad=64):
     return bool((whole[:pad] == ref).all().item() and (whole[pad + n:] == ref).all().item())
 
 
+def kernels_run(call):
+    """Names of the kernels that call() launches, in order."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    events = [e for e in prof.events() if e.device_type == torch.profiler.DeviceType.CUDA]
+    return [e.name for e in sorted(events, key=lambda e: e.time_range.start)]
+
+
 def to_layout(a_logical, logical_name, physical_name):
     """Physical flat buffer of a logical array under 'LOGICAL->PHYSICAL' (oracle)."""
     shape = a_logical.shape

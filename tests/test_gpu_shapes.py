@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import paper_2210_12415_amd as alt
-from gpu_util import applicable_variants, canary_dev, canary_ok, dev, from_layout, host, to_layout
+from gpu_util import applicable_variants, canary_dev, canary_ok, dev, from_layout, host, kernels_run, to_layout
 from workloads import f32_to_bf16_bits, small_ints_f32
 
 pytestmark = pytest.mark.gpu
@@ -51,6 +51,16 @@ def check_conv(h, N, C, H, W, K, R, stride=1, pad=0, dil=1, groups=1, layouts=("
 @pytest.mark.parametrize("wl", ["OHWI", "OIHW", "HWIO"])
 def test_depthwise_vector_kernels(h, N, C, H, W, R, stride, pad, wl):
     check_conv(h, N, C, H, W, C, R, stride, pad, groups=C, layouts=("NHWC", wl, "NHWC"))
+
+
+# depth-wise filters beyond 3x3 on both sides of the rule that chooses between the vector and the element kernel
+@pytest.mark.parametrize("N,C,H,W,R,stride,wl,kernel", [
+    (1, 24, 9, 10, 5, 1, "OHWI", "elem"), (2, 40, 31, 30, 5, 2, "OIHW", "elem"), (3, 16, 9, 10, 5, 1, "OIHW", "vec8_kernel<true>"),
+    (1, 32, 7, 12, 7, 1, "OHWI", "vec8_kernel<true>"), (4, 40, 51, 49, 5, 1, "OHWI", "vec8_kernel<true>"),
+    (1, 24, 9, 10, 5, 1, "HWIO", "vec8_kernel<false>"), (4, 40, 51, 49, 5, 1, "HWIO", "vec8_kernel<false>")])
+def test_depthwise_kernel_by_filter_layout_and_size(h, N, C, H, W, R, stride, wl, kernel):
+    ran = kernels_run(lambda: check_conv(h, N, C, H, W, C, R, stride, R // 2, groups=C, layouts=("NHWC", wl, "NHWC")))
+    assert [k for k in ran if "dwconv_" + kernel in k], ran
 
 
 TAPS_CASES = [
