@@ -157,6 +157,37 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams 
     }
 }
 
+// The outputs of thread `t` of the 3x3 vector kernel, one after the other and over the taps inside the image alone.
+template <int STRIDE, int TW, int TH>
+__device__ __forceinline__ void dw_3x3_inside(const DwParams &p, uint32_t t)
+{
+    asm volatile("" : "+v"(t));                     // (decoded anew: nothing of the item stays in registers for this)
+    const uint32_t e = (uint32_t)igemm_logical_tile((int)gridDim.x) * kDwThreads + t;
+    uint32_t r = fast_div(e, p.fd_c8);
+    const int c = (int)(e - r * p.fd_c8.d) * 8;
+    const uint32_t r2 = fast_div(r, p.fd_owb);
+    const int ow0 = (int)(r - r2 * p.fd_owb.d) * TW;
+    const int n = (int)fast_div(r2, p.fd_ohb);
+    const int oh0 = (int)(r2 - (uint32_t)n * p.fd_ohb.d) * TH;
+    const int ih0 = oh0 * STRIDE - p.pad_h, iw0 = ow0 * STRIDE - p.pad_w;
+    if (ih0 >= 0 && iw0 >= 0 && ih0 + (TH - 1) * STRIDE + 3 <= p.H && iw0 + (TW - 1) * STRIDE + 3 <= p.W) return;
+    const int32_t xb = dim2_off32(p.xn, n), yb = dim2_off32(p.yn, n);
+    for (int o = 0; o < TH * TW * 8; ++o) {
+        const int oh = oh0 + (o >> 3) / TW, ow = ow0 + (o >> 3) % TW, k = c + (o & 7);
+        if (oh >= p.OH || ow >= p.OW) continue;
+        float acc = 0.f;
+        for (int t = 0; t < 9; ++t) {
+            const int ih = oh * STRIDE - p.pad_h + t / 3, iw = ow * STRIDE - p.pad_w + t % 3;
+            if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
+            acc += load_elem(p.x, xb + dim2_off32(p.xc, k) + ih * p.xh.si + iw * p.xw.si, 1) *
+                   load_elem(p.w, dim2_off(p.wo, k) + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3), 1);
+        }
+        if (p.epilogue & ALT_EPI_BIAS) acc += p.bias[k];
+        acc = fmaxf(acc, relu_floor(p.epilogue & ALT_EPI_RELU));
+        ((uint16_t *)p.y)[yb + dim2_off32(p.yk, k) + oh * p.yh.si + ow * p.yw.si] = f32_to_bf16_rne(acc);
+    }
+}
+
 // The common case of the vector kernel: 3x3 filter, dilation 1, H and W not blocked, tensors below 2 GiB.  A thread
 // owns eight channels of TH x TW output pixels: the filter is loaded once, and neighbouring outputs share the
 // input pixels of their windows, so a thread makes ((TH-1)*STRIDE+3) * ((TW-1)*STRIDE+3) loads for TH*TW outputs.
@@ -256,18 +287,26 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
     }
     const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
     const int32_t yb = dim2_off32(p.yn, n) + dim2_off32(p.yk, c), syh = (int32_t)p.yh.si, syw = (int32_t)p.yw.si;
+    float probe = 0.f;                              // NaN once a sum is
 #pragma unroll
     for (int i = 0; i < TH; ++i)
 #pragma unroll
         for (int j = 0; j < TW; ++j) {
             const bool ok = ow0 + j < p.OW && oh0 + i < p.OH;
-            const f4_t a = __builtin_elementwise_max(lo[i][j] + blo, (f4_t){floor_, floor_, floor_, floor_});
-            const f4_t b = __builtin_elementwise_max(hi[i][j] + bhi, (f4_t){floor_, floor_, floor_, floor_});
+            const f4_t sa = lo[i][j] + blo, sb = hi[i][j] + bhi;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) probe = __builtin_elementwise_maximum(__builtin_elementwise_maximum(probe, sa[q]), sb[q]);
+            const f4_t a = __builtin_elementwise_max(sa, (f4_t){floor_, floor_, floor_, floor_});
+            const f4_t b = __builtin_elementwise_max(sb, (f4_t){floor_, floor_, floor_, floor_});
             w4_t out;
 #pragma unroll
             for (int q = 0; q < 4; ++q) out[q] = f32x2_to_bf16x2(a[q], b[q]);
             __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + (oh0 + i) * syh + (ow0 + j) * syw) * 2u : kOutOfRange), 0, 0);
         }
+    // A tap outside the image is no part of the sum, but the zeros read for it were multiplied, and zero times an infinite or NaN
+    // filter value is NaN.  Where a sum came out NaN, the outputs of a thread at the border are taken again over the taps inside
+    // and stored over those above.
+    if (probe != probe) dw_3x3_inside<STRIDE, TW, TH>(p, threadIdx.x);
 }
 
 // bf16 in and out, width contiguous, 3x3 without dilation, padding 1 along the width, W and OW multiples of TW

@@ -65,3 +65,20 @@ def test_element_wise_sum_keeps_nan_and_infinity(h, dtype):
     whole, y = canary_dev(n, np_t)
     h.eltwise_add(dtype, n, dev(bits(a)), dev(bits(b)), y)
     assert canary_ok(whole, n) and np.array_equal(f32(host(y, np_t)), ref, equal_nan=True)
+
+
+# a filter value that meets nothing but the surroundings of the image leaves no trace at the border, whatever it is; one row, one
+# column and one image corner per case are covered by no more than a tap or two
+@pytest.mark.parametrize("out_dtype", [alt.BF16, alt.F32])
+@pytest.mark.parametrize("wl", ["OHWI", "OIHW", "HWIO"])
+@pytest.mark.parametrize("N,C,H,W,R,stride,pad", [(2, 24, 7, 9, 3, 1, 1), (2, 256, 65, 61, 3, 1, 1), (1, 16, 8, 13, 3, 2, 2), (2, 8, 6, 6, 5, 1, 2)])
+def test_depthwise_taps_outside_the_image_do_not_count(h, N, C, H, W, R, stride, pad, wl, out_dtype):
+    x, w = small_ints_f32(66, (N, C, H, W), -3, 3), small_ints_f32(67, (C, 1, R, R), -3, 3)
+    b = small_ints_f32(68, (C,), -20, 20)
+    w[::5, 0, 0, 0], w[1::5, 0, R - 1, R // 2], w[2::5, 0, R // 2, R - 1], x[0, C - 1, 2, 3] = np.inf, -np.inf, np.nan, np.nan
+    ref = oracle.conv2d(x, w, stride=stride, pad=pad, groups=C, bias=b, out_bf16=out_dtype == alt.BF16)
+    assert np.isinf(f32(ref)).any() and np.isnan(f32(ref)).any() and np.isfinite(f32(ref)[:, ::5]).any()
+    layouts = ("NHWC", wl, "NHWC")
+    d = alt.conv_desc(N, C, H, W, C, R, R, stride=stride, pad=pad, groups=C, in_dtype=alt.BF16, out_dtype=out_dtype, epilogue=alt.EPI_BIAS,
+                      x_layout="NCHW->NHWC", w_layout="OIHW->" + wl, y_layout="NCHW->NHWC")
+    assert conv(h, d, x, w, b, layouts, ref)
