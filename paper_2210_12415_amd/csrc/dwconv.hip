@@ -188,8 +188,8 @@ __device__ __forceinline__ void dw_3x3_inside(const DwParams &p, uint32_t t)
     }
 }
 
-// The common case of the vector kernel: 3x3 filter, dilation 1, H and W not blocked, tensors below 2 GiB.  A thread
-// owns eight channels of TH x TW output pixels: the filter is loaded once, and neighbouring outputs share the
+// The common case of the vector kernel: 3x3 filter, dilation 1, H and W not blocked, tensors below 2 GiB a launch.  A
+// thread owns eight channels of TH x TW output pixels: the filter is loaded once, and neighbouring outputs share the
 // input pixels of their windows, so a thread makes ((TH-1)*STRIDE+3) * ((TW-1)*STRIDE+3) loads for TH*TW outputs.
 // The kernel is bound by memory: all its loads go through a buffer descriptor (a pixel outside the image gets an
 // out-of-range offset and reads zeros), so no branch keeps them from being in flight together.
@@ -427,9 +427,14 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
     bool vec = p.in_bf16 && p.out_bf16 && chan_runs_of_8(q.xc, C, xo, 3) && (taps || wchan) && chan_runs_of_8(q.yk, C, yo, 3) &&
                (uintptr_t)q.x % 16 == 0 && (uintptr_t)q.w % 16 == 0 && (uintptr_t)q.y % 16 == 0 &&
                (!(q.epilogue & ALT_EPI_BIAS) || (uintptr_t)q.bias % 16 == 0);
+    // Images a launch of the 3x3 vector kernel takes: its offsets are 32 bits, so larger batches (outermost, or the images of a
+    // launch would not lie together) go in several launches below 2 GiB.
+    const int64_t x_image = C * q.H * q.W, y_image = C * q.OH * q.OW;
+    int64_t images = std::min(N, ((1 << 30) - 1) / std::max(x_image, y_image));
+    if (images < N && !(q.xn.f >= N && q.xn.si == x_image && q.yn.f >= N && q.yn.si == y_image)) images = 0;
     const bool k3x3 = vec && q.R == 3 && q.S == 3 && q.dil_h == 1 && q.dil_w == 1 && q.stride_h == q.stride_w &&
                       (q.stride_h == 1 || q.stride_h == 2) && q.xh.f >= q.H && q.xw.f >= q.W && q.yh.f >= q.OH &&
-                      q.yw.f >= q.OW && N * C * q.H * q.W < (1 << 30) && N * C * q.OH * q.OW < (1 << 30);
+                      q.yw.f >= q.OW && images > 0;
     if (k3x3) {
         // Rows per thread.  Two share their windows' rows (24 loads for eight outputs against 36) where one row each
         // would make more threads than the chip holds one wave of per SIMD: 16 x 144 x 56 x 56 takes 10.0 us with two
@@ -441,14 +446,19 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
         p.fd_c8 = make_fastdiv((uint32_t)C / 8);
         p.fd_owb = make_fastdiv(owb);
         p.fd_ohb = make_fastdiv(ohb);
-        p.items = (uint32_t)(N * ohb * owb * (C / 8));
-        p.x_bytes = (uint32_t)(N * C * q.H * q.W * 2);
-        p.y_bytes = (uint32_t)(N * C * q.OH * q.OW * 2);
         auto kern = th == 2            ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 2, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 2, false>)
                     : q.stride_h == 1 ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 1, false>)
                                       : (taps ? dwconv_vec8_3x3_kernel<2, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<2, kDwCols, 1, false>);
-        hipLaunchKernelGGL(kern, dim3((p.items + kDwThreads - 1) / kDwThreads), dim3(kDwThreads), 0, st, p);
-        ALT_CHECK_HIP(h, hipGetLastError());
+        for (int64_t n = 0; n < N; n += images) {
+            const int64_t here = std::min(images, N - n);
+            p.x = (const uint16_t *)q.x + n * x_image;
+            p.y = (uint16_t *)q.y + n * y_image;
+            p.items = (uint32_t)(here * ohb * owb * (C / 8));
+            p.x_bytes = (uint32_t)(here * x_image * 2);
+            p.y_bytes = (uint32_t)(here * y_image * 2);
+            hipLaunchKernelGGL(kern, dim3((p.items + kDwThreads - 1) / kDwThreads), dim3(kDwThreads), 0, st, p);
+            ALT_CHECK_HIP(h, hipGetLastError());
+        }
         return ALT_OK;
     }
     // Filters whose taps lie side by side, beyond 3x3: a thread of the vector kernel loads eight scattered filter values per tap,

@@ -2,6 +2,7 @@
 of a dispatch rule.  Integer-valued inputs make every partial sum exact, so results are compared bit for bit."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2210_12415_amd as alt
@@ -61,6 +62,36 @@ def test_depthwise_vector_kernels(h, N, C, H, W, R, stride, pad, wl):
 def test_depthwise_kernel_by_filter_layout_and_size(h, N, C, H, W, R, stride, wl, kernel):
     ran = kernels_run(lambda: check_conv(h, N, C, H, W, C, R, stride, R // 2, groups=C, layouts=("NHWC", wl, "NHWC")))
     assert [k for k in ran if "dwconv_" + kernel in k], ran
+
+
+def test_depthwise_batch_of_more_than_2_gib(h):
+    """257 images of 4 M elements: the register-tiled kernel takes them in two launches, each below 2 GiB; every image is what the
+    same call makes of a part of the batch, and the images at the seam are the oracle's."""
+    N, C, H = 257, 64, 256
+    x = torch.empty(N * H * H * C, dtype=torch.bfloat16, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(45)
+    for i in range(0, N, 32):
+        part = x[i * H * H * C:(i + 32) * H * H * C]
+        part.copy_(torch.randint(-3, 4, (part.numel(),), generator=gen, dtype=torch.int32, device="cuda"))
+    w = small_ints_f32(46, (C, 1, 3, 3), -3, 3)
+    wd, y = dev(f32_to_bf16_bits(to_layout(w, "OIHW", "OHWI"))), torch.empty_like(x)
+
+    def call(first, count, out):
+        d = alt.conv_desc(count, C, H, H, C, 3, 3, pad=1, groups=C, in_dtype=alt.BF16, out_dtype=alt.BF16, x_layout="NCHW->NHWC",
+                          w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+        h.conv2d(d, x[first * H * H * C:], wd, out)
+
+    ran = kernels_run(lambda: call(0, N, y))
+    assert len(ran) == 2 and all("dwconv_vec8_3x3" in k for k in ran), ran
+    for first, count in ((0, 128), (128, 129)):
+        part = torch.empty(count * H * H * C, dtype=torch.bfloat16, device="cuda")
+        call(first, count, part)
+        assert torch.equal(part.view(torch.int16), y[first * H * H * C:(first + count) * H * H * C].view(torch.int16))
+    for i in (0, 254, 255, 256):
+        image = lambda t: host(t[i * H * H * C:(i + 1) * H * H * C].view(torch.int16), np.uint16)
+        xi = from_layout(image(x), (1, C, H, H), "NCHW", "NHWC")
+        ref = oracle.conv2d((xi.astype(np.uint32) << 16).view(np.float32), w, pad=1, groups=C, out_bf16=True)
+        assert np.array_equal(from_layout(image(y), (1, C, H, H), "NCHW", "NHWC"), ref), i
 
 
 TAPS_CASES = [
