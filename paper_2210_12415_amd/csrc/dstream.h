@@ -28,6 +28,11 @@
 //   kTapsRagged: any channel count that is a multiple of a chunk: every lane finds the tap of
 //     its own chunk (three divisions per K step, not per load).  The last step is filled up
 //     with zeros, so it also covers matrix products whose K is not a multiple of the K step.
+//     What a step needs then depends on the filter, and no step may branch (see step_address), so
+//     there are three of these kernels and the launch takes the simplest that serves: kTapsOne for
+//     one tap (no divisions), kTapsDense for filter rows whose taps lie in the order they are walked
+//     in, kTapsRagged for the rest.  (One kernel with all the arithmetic took 5 to 12 % longer on products
+//     of few K steps: 115 x 1872 x 2344 12.7 us against 11.4.)
 // The depth of a 3-D convolution is one more direction of taps, so that its input is read where it lies.  A transposed
 // convolution in its sub-pixel form is one such launch with the output phases along blockIdx.y: each phase walks the taps of
 // the merged filter that are its own (the others are zeros: three of four in a 4x4 filter at stride 2, seven of eight
@@ -39,7 +44,7 @@
 
 namespace alt {
 
-enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2 };
+enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2, kTapsDense = 3, kTapsOne = 4 };
 
 // KW groups of WGM x WGN waves; group kg handles channels [kg, kg + 1) * Cs / KW of the
 // workgroup's slice in steps of BK (64 or 32; half of that for float), through a ring of NS stages of its own.
@@ -50,6 +55,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM)
 void dstream_kernel(const DconvParams p)
 {
     constexpr int ES = ElemTraits<T>::SIZE;                // bytes per element
+    constexpr bool kRagged = TAPS >= kTapsRagged;
     constexpr int BKB = BK * ES;                           // bytes of a K step per row
     constexpr int NWG = WGM * WGN;                         // waves per K group
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -66,7 +72,7 @@ void dstream_kernel(const DconvParams p)
     static_assert(A_STAGE % (1024 * NWG) == 0 && B_STAGE % (1024 * NWG) == 0 && NLA >= 1 && NLB >= 1,
                   "a stage is a whole number of wave-loads per wave");
     static_assert(BKB == 128 || BKB == 64, "K step");
-    static_assert(ES == 2 || (!BT && TAPS == kTapsRagged), "fp32: built for ragged taps, which cover the rest");
+    static_assert(ES == 2 || (!BT && kRagged), "fp32: built for ragged taps, which cover the rest");
     static_assert(NS >= 3 && (NS - 1) * LPS < 60, "pipeline depth against the vmcnt range");
     static_assert((NS * NKC) % 4 == 0, "a round over the stages is a whole number of fragment-buffer cycles");
     constexpr int RB = BT ? 2 : 1;                         // LDS reads per B fragment
@@ -180,7 +186,7 @@ void dstream_kernel(const DconvParams p)
         }
     }
     // ragged taps: this lane's chunk of every row it loads (the same for all its loads and both operands)
-    static_assert(TAPS != kTapsRagged || (NWG * 64 / CPR / RP) % CPR == 0, "a lane's loads sit in one chunk column");
+    static_assert(!kRagged || (NWG * 64 / CPR / RP) % CPR == 0, "a lane's loads sit in one chunk column");
     const uint32_t chunk0 = (uint32_t)step0 * CPR + (uint32_t)((lane % CPR) ^ ((((wq * 64 + lane) / CPR) / RP) & (CPR - 1)));
     // uniform taps: the tap the load cursor stands on and the chunk inside it
     int u_t = 0, u_r = 0, u_s = 0, u_c = 0;
@@ -197,23 +203,26 @@ void dstream_kernel(const DconvParams p)
             add_a = (uint32_t)u_t * p.tap_d + (uint32_t)u_r * p.tap_h + (uint32_t)u_s * p.tap_w + (uint32_t)u_c * 16u;
             sel = (1u << u_r) | (1u << (kTapBits + u_s)) | (1u << (2 * kTapBits + u_t));
             add_b = (uint32_t)u_t * p.wtap_d + (uint32_t)u_r * p.wtap_h + (uint32_t)u_s * p.wtap_w + (uint32_t)u_c * 16u;
-        } else if constexpr (TAPS == kTapsRagged) {
+        } else if constexpr (kRagged) {
+            // (no branch: steps run with operand reads in flight, and none may stand between such a read and its wait; see below)
             const uint32_t q = chunk0 + (uint32_t)step * CPR;
             sel = 1u | (1u << kTapBits) | (1u << 2 * kTapBits);
             add_b = add_a = q * 16u;
-            if (p.taps > 1) {
+            if constexpr (TAPS != kTapsOne) {
                 const uint32_t tap = div32(q, p.d_c16), td = div32(tap, p.d_rs), rs = tap - td * (uint32_t)(p.R * p.S);
                 const uint32_t tr = div32(rs, p.d_s), tc = rs - tr * (uint32_t)p.S;
                 const uint32_t in_tap = (q - tap * (uint32_t)p.c16) * 16u;
                 add_a = td * p.tap_d + tr * p.tap_h + tc * p.tap_w + in_tap;
-                if (!p.w_dense) add_b = td * p.wtap_d + tr * p.wtap_h + tc * p.wtap_w + in_tap;
+                if constexpr (TAPS == kTapsRagged) add_b = td * p.wtap_d + tr * p.wtap_h + tc * p.wtap_w + in_tap;
                 sel = (1u << tr) | (1u << (kTapBits + tc)) | (1u << (2 * kTapBits + td));
             }
-            if (q >= (uint32_t)p.kq) { sel = 0x80000000u; add_b = kOutOfRange; }     // past the last chunk: zeros
+            const bool past = q >= (uint32_t)p.kq;         // past the last chunk: zeros
+            sel = past ? 0x80000000u : sel;
+            add_b = past ? kOutOfRange : add_b;
         }
     };
-    auto next_tap = [&]() {                                // uniform taps: one K step further
-        u_c += CPR;
+    auto next_tap = [&](bool more) {                       // uniform taps: one K step further, if there is one (no branch)
+        u_c += more ? CPR : 0;
         const int ws = u_c == p.c16 ? 1 : 0;
         u_c = ws ? 0 : u_c;
         u_s += ws;
@@ -231,7 +240,7 @@ void dstream_kernel(const DconvParams p)
     };
     auto load_b = [&](int i, uint32_t soff, uint32_t dst) {
         if constexpr (TAPS == kTapsUniform) dma_load16_s(w_rsrc, b_voff[i], add_b, dst);
-        else if constexpr (TAPS == kTapsRagged && !BT) dma_load16_s(w_rsrc, (b_voff[i] | add_b) & kOutOfRange ? kOutOfRange : b_voff[i] + add_b, 0u, dst);
+        else if constexpr (kRagged && !BT) dma_load16_s(w_rsrc, (b_voff[i] | add_b) & kOutOfRange ? kOutOfRange : b_voff[i] + add_b, 0u, dst);
         else dma_load16_s(w_rsrc, b_voff[i], soff, dst);
     };
     // byte distance between consecutive K steps of B: BK columns of a row, or BK rows; of A: BK channels of a
@@ -243,18 +252,23 @@ void dstream_kernel(const DconvParams p)
     // load cursor: K step `lstep` goes to stage `lstage`; past the last step the last one is
     // loaded again (into stages nobody reads any more), which keeps the load count per step fixed
     int lstep = 0, lstage = 0;
+    // (the next stage's offsets are worked out behind this one's loads, beside the matrix instructions, and not before its own)
+    auto next_stage = [&]() {
+        if constexpr (TAPS == kTapsUniform) next_tap(lstep + 1 < nk);
+        ++lstep;
+        lstage = lstage + 1 == NS ? 0 : lstage + 1;
+        step_address(min(lstep, nk - 1));
+    };
     auto issue_stage = [&]() {
         const uint32_t soff = (uint32_t)min(lstep, nk - 1) * a_step, soff_b = (uint32_t)min(lstep, nk - 1) * b_step;
         const uint32_t dst = ldsW + lstage * STAGE;
-        step_address(min(lstep, nk - 1));
 #pragma unroll
         for (int i = 0; i < NLA; ++i) load_a(i, soff, dst + i * (NWG * 1024));
 #pragma unroll
         for (int i = 0; i < NLB; ++i) load_b(i, soff_b, dst + A_STAGE + i * (NWG * 1024));
-        if constexpr (TAPS == kTapsUniform) { if (lstep + 1 < nk) next_tap(); }
-        ++lstep;
-        lstage = lstage + 1 == NS ? 0 : lstage + 1;
+        next_stage();
     };
+    step_address(0);
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) issue_stage();
 
@@ -361,7 +375,6 @@ void dstream_kernel(const DconvParams p)
     auto issue_one = [&](int i) {                          // load i of the stage the cursor is on
         const uint32_t soff = (uint32_t)min(lstep, nk - 1) * a_step, soff_b = (uint32_t)min(lstep, nk - 1) * b_step;
         const uint32_t dst = ldsW + lstage * STAGE;
-        if (i == 0) step_address(min(lstep, nk - 1));
         if (i < NLA) load_a(i, soff, dst + i * (NWG * 1024));
         else load_b(i - NLA, soff_b, dst + A_STAGE + (i - NLA) * (NWG * 1024));
     };
@@ -427,9 +440,7 @@ void dstream_kernel(const DconvParams p)
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
-            if constexpr (TAPS == kTapsUniform) { if (lstep + 1 < nk) next_tap(); }
-            ++lstep;
-            lstage = lstage + 1 == NS ? 0 : lstage + 1;
+            next_stage();
         }
     };
     int ks0 = 0;
@@ -499,17 +510,25 @@ template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = fa
 hipError_t dstream_launch(const DconvParams &p, size_t lds, hipStream_t st)
 {
     if (p.bk != BK) return hipErrorInvalidValue;
-    auto kern = dstream_kernel<BM, BN, WGM, WGN, KW, NS, BK, BT, TAPS, T>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        attr_set = true;
+    if constexpr (TAPS == kTapsRagged && BT) {
+        return dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, BT, kTapsOne, T>(p, lds, st);
+    } else {
+        if constexpr (TAPS == kTapsRagged) {
+            if (p.taps == 1) return dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, BT, kTapsOne, T>(p, lds, st);
+            if (p.w_dense) return dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, BT, kTapsDense, T>(p, lds, st);
+        }
+        auto kern = dstream_kernel<BM, BN, WGM, WGN, KW, NS, BK, BT, TAPS, T>;
+        static bool attr_set = false;
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        const int tiles = p.tiles_m * p.tiles_n;
+        const unsigned grid = (unsigned)(tiles * p.splitk);
+        hipLaunchKernelGGL(kern, dim3(grid, (unsigned)p.batch), dim3(64 * WGM * WGN * KW), lds, st, p);
+        return hipGetLastError();
     }
-    const int tiles = p.tiles_m * p.tiles_n;
-    const unsigned grid = (unsigned)(tiles * p.splitk);
-    hipLaunchKernelGGL(kern, dim3(grid, (unsigned)p.batch), dim3(64 * WGM * WGN * KW), lds, st, p);
-    return hipGetLastError();
 }
 
 }  // namespace alt

@@ -188,3 +188,24 @@ def test_streaming_kernels_every_step_count(h, bl):
         for v, name in variants:
             got, _ = run_gemm(h, Ab, Bb, "MK", bl, "MN", alt.BF16, variant=v)
             assert np.array_equal(got, ref), (name, steps)
+
+
+@pytest.mark.parametrize("dtype,bl", [(alt.BF16, "NK"), (alt.BF16, "KN"), (alt.F32, "NK")])
+def test_kernels_over_filter_taps_every_step_count(h, dtype, bl):
+    """The same for the streaming kernels over filter taps (_taps_, _rtaps_, _rtapskn_), whose names the test above does not select:
+    whole K steps, and a last one of a single 16-byte chunk."""
+    M, N, step, chunk = (96, 136, 64, 8) if dtype == alt.BF16 else (96, 136, 32, 4)
+    seen = set()
+    for steps in list(range(1, 13)) + [16, 17, 24]:
+        for K in (step * steps, step * (steps - 1) + chunk):
+            A, B = small_ints_f32(331 + steps, (1, M, K), -3, 3), small_ints_f32(431 + steps, (1, K, N), -3, 3)
+            ref = oracle.gemm(A, B)
+            if dtype == alt.BF16:
+                A, B = f32_to_bf16_bits(A), f32_to_bf16_bits(B)
+            d0 = alt.gemm_desc(M, N, K, in_dtype=dtype, a_layout="MK->MK", b_layout="KN->" + bl, c_layout="MN->MN")
+            for v, name in applicable_variants(h, d0, "gemm"):
+                if "taps" in name:
+                    seen.add(name.rsplit("_k", 1)[0])
+                    got, _ = run_gemm(h, A, B, "MK", bl, "MN", dtype, variant=v)
+                    assert np.array_equal(got, ref), (name, K)
+    assert len(seen) >= 4

@@ -1,0 +1,90 @@
+"""Branches of the built streaming kernels (dstream.h), read from their machine code.  Their operand reads from LDS complete behind
+the compiler's back, and the compiler copies registers where paths join: a copy of a register whose read is in flight copies stale
+data.  So the kernels with row-major B may not branch at all between such a read and its wait, and the others not more often
+than the loop over the stages needs."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import paper_2210_12415_amd as alt
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def streaming_kernels(folder):
+    """name -> [(address, operation, operands)] of every streaming kernel in the library."""
+    lib = os.path.join(os.path.dirname(alt.__file__), "libalt.so")
+    os.symlink(lib, os.path.join(folder, "lib.so"))
+    subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=folder, check=True, capture_output=True)
+    out = {}
+    for f in sorted(os.listdir(folder)):
+        path = os.path.join(folder, f)
+        if "gfx950" not in f or b"dstream_kernel" not in open(path, "rb").read():
+            continue
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--demangle", path], check=True, capture_output=True, text=True).stdout
+        code = None
+        for line in text.splitlines():
+            head = re.match(r"^[0-9a-f]+ <(.*)>:$", line)
+            if head:
+                name = re.search(r"dstream_kernel<(.*)>\(", head.group(1))
+                code = out.setdefault(name.group(1), []) if name else None
+            elif code is not None:
+                m = re.match(r"^\s+(\S+)\s*(.*?)\s*//\s*([0-9A-F]+)", line)
+                if m:
+                    code.append((int(m.group(3), 16), m.group(1), m.group(2)))
+    return out
+
+
+def branches_with_reads_in_flight(code):
+    """Indices of the branches of the main loop that some path reaches with operand reads in flight.  (It ends with the last matrix
+    instruction, and a write to LDS opens the epilogue: the compiler keeps the waits of its own reads there.)"""
+    at = {a: i for i, (a, _, _) in enumerate(code)}
+    end = max(i for i, (_, op, _) in enumerate(code) if "mfma" in op)
+    most, todo, found = {}, [(0, 0)], set()
+    while todo:
+        i, reads = todo.pop()
+        if most.get(i, -1) >= reads:
+            continue
+        most[i] = reads
+        address, op, text = code[i]
+        if op == "s_endpgm" or op.startswith("ds_write") or i > end:
+            continue
+        if op.startswith("ds_read"):
+            reads += 1
+        elif op == "s_waitcnt" and "lgkmcnt" in text:
+            reads = min(reads, int(re.search(r"lgkmcnt\((\d+)\)", text).group(1)))
+        elif op == "s_branch" or op.startswith("s_cbranch"):
+            if reads:
+                found.add(i)
+            off = int(text.split()[0])
+            todo.append((at[address + 4 + 4 * (off - 65536 if off >= 32768 else off)], reads))
+            if op == "s_branch":
+                continue
+        todo.append((i + 1, reads))
+    return found
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no disassembler")
+    found = streaming_kernels(str(tmp_path_factory.mktemp("code")))
+    assert len(found) > 40
+    return found
+
+
+def test_row_major_b_kernels_do_not_branch_with_reads_in_flight(kernels):
+    row_major = {n: c for n, c in kernels.items() if n.split(", ")[7] == "true"}
+    assert {n.split(", ")[8] for n in row_major} == {"0", "4"}
+    for name, code in row_major.items():
+        assert not branches_with_reads_in_flight(code), name
+
+
+def test_kernels_over_filter_taps_branch_for_the_stages_alone(kernels):
+    taps = {n: c for n, c in kernels.items() if n.split(", ")[8] != "0"}
+    assert len(taps) >= 20
+    for name, code in taps.items():
+        # the loop over whole rounds, and each step of the last one is entered or left out
+        assert len(branches_with_reads_in_flight(code)) <= 2 * int(name.split(", ")[5]) + 1, name
