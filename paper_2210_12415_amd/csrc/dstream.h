@@ -463,20 +463,16 @@ void dstream_kernel(const DconvParams p)
     }
 
     wait_vmcnt<0>();                                       // the repeated loads past the last step
-    // the look-ahead reads past the last step still land in their registers: tie them to a wait
+    // the look-ahead reads past the last step still land in their registers: tie them to a wait (with BT every read is consumed, and
+    // the ties would only keep registers: 100 bytes a lane spilled in the largest tile)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if constexpr (!BT) {
 #pragma unroll
-    for (int kc = 0; kc < NBUF; ++kc) {
+        for (int kc = 0; kc < NBUF; ++kc) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(af[kc][i]));
+            for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(af[kc][i]));
 #pragma unroll
-        for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(bf[kc][j]));
-        if constexpr (BT) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                asm volatile("" : "+v"(bh[kc][j][0]));
-                asm volatile("" : "+v"(bh[kc][j][1]));
-            }
+            for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(bf[kc][j]));
         }
     }
 
