@@ -914,23 +914,29 @@ def main():
                               x_layout="NCHW->" + xl, w_layout="OIHW->" + wl, y_layout="NCHW->" + xl)
             osh = h.conv2d_transpose_output_shape(d)
             # tune(op, shape) for the transposed operator: the variants of the forward problem it runs as
-            h.tune_conv2d_variants(h.conv2d_transpose_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
             xb = torch.randint(-200, 200, (16 * 128 * 28 * 28,), dtype=torch.int16, device=dev)
             wsrc = torch.randint(-200, 200, (128 * 64 * 16,), dtype=torch.int16, device=dev)
             wb = torch.empty(int(np.prod(h.conv2d_transpose_weight_shape(d))), dtype=torch.int16, device=dev)
             h.pack_weights_transpose(d, wsrc, wb, stream=stream)
             yb = torch.empty(int(np.prod(osh)), dtype=torch.int16, device=dev)
+            run = lambda st: h.conv2d_transpose(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st)
             wsb = h.conv2d_transpose_workspace_size(d)
             wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
-            gr = capture(lambda st: h.conv2d_transpose(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st), 20)
+            gr = capture(run, 20)
+            untuned_us = graph_timed(gr, 20)
+            h.tune_conv2d_variants(h.conv2d_transpose_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
+            wsb = h.conv2d_transpose_workspace_size(d)
+            wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
+            gr = capture(run, 20)
             us = graph_timed(gr, 20)
             del gr, xb, wb, yb, wsd
-            t2d[xl] = dict(us=round(us, 2), nominal_tflops=round(tfl / us / 1e6, 1))
+            t2d[xl] = dict(us=round(us, 2), untuned_us=round(untuned_us, 2), nominal_tflops=round(tfl / us / 1e6, 1))
         extra["conv_transpose_c128_k64_4x4_s2_28x28_b16"] = dict(
             per_layout=t2d, speedup_vs_nchw=round(t2d["NCHW"]["us"] / min(v["us"] for v in t2d.values()), 2),
             form="sub-pixel" if h.conv2d_transpose_weight_shape(d)[0] != 64 else "zero insertion",
             note="sub-pixel form: one stride-1 convolution of x with 4*K output channels into the workspace, then the kernel that "
-                 "moves the four phases into place (and one that replicates the bias when there is one); tuned forward kernel")
+                 "moves the four phases into place (and one that replicates the bias when there is one); tuned forward kernel; "
+                 "untuned_us under NHWC: one launch in place")
 
         # a ResNet3D-18-shaped layer (the C3D of the operator list): 128 -> 128 channels, 3x3x3, 8 slices of 28x28,
         # batch 2; depth unfolded into the channels per call, then the 2-D kernels on 16 images of 384 channels
@@ -941,19 +947,24 @@ def main():
                                 x_layout="NCHW->" + xl, w_layout="OIHW->" + wl, y_layout="NCHW->" + xl)
             osh = h.conv3d_output_shape(d)
             # tune(op, shape) for the 3-D operator: the variants of the 2-D problem it runs as
-            h.tune_conv2d_variants(h.conv3d_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
             xb = torch.randint(-200, 200, (2 * 8 * 128 * 28 * 28,), dtype=torch.int16, device=dev)
             wb = torch.randint(-200, 200, (128 * 128 * 27,), dtype=torch.int16, device=dev)
             yb = torch.empty(int(np.prod(osh)), dtype=torch.int16, device=dev)
+            run = lambda st: h.conv3d(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st)
             wsb = h.conv3d_workspace_size(d)
             wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
-            gr = capture(lambda st: h.conv3d(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st), 20)
+            gr = capture(run, 20)
+            untuned_us = graph_timed(gr, 20)
+            h.tune_conv2d_variants(h.conv3d_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
+            wsb = h.conv3d_workspace_size(d)
+            wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
+            gr = capture(run, 20)
             us = graph_timed(gr, 20)
             del gr, xb, wb, yb, wsd
-            c3d[xl] = dict(us=round(us, 2), nominal_tflops=round(c3fl / us / 1e6, 1))
+            c3d[xl] = dict(us=round(us, 2), untuned_us=round(untuned_us, 2), nominal_tflops=round(c3fl / us / 1e6, 1))
         extra["conv3d_c128_3x3x3_8x28x28_b2"] = dict(
             per_layout=c3d, speedup_vs_nchw=round(c3d["NCHW"]["us"] / min(v["us"] for v in c3d.values()), 2),
-            note="two launches per call (depth unfolding into the workspace, tuned forward kernel)")
+            note="two launches per call (depth unfolding into the workspace, tuned forward kernel); untuned_us under NHWC: one launch on x itself")
 
         # the transposed 3-D operator (T3D): a decoder-shaped 4x4x4 stride-2 layer, 128 -> 64 channels,
         # 4 slices of 14x14 -> 8 slices of 28x28, batch 2
@@ -963,23 +974,28 @@ def main():
             d = alt.conv3d_desc(2, 128, 4, 14, 14, 64, 4, 4, 4, stride=2, pad=1, in_dtype=alt.BF16, out_dtype=alt.BF16,
                                 x_layout="NCHW->" + xl, w_layout="OIHW->" + wl, y_layout="NCHW->" + xl)
             osh = h.conv3d_transpose_output_shape(d)
-            h.tune_conv2d_variants(h.conv3d_transpose_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
             xb = torch.randint(-200, 200, (2 * 4 * 128 * 14 * 14,), dtype=torch.int16, device=dev)
             wsrc = torch.randint(-200, 200, (128 * 64 * 64,), dtype=torch.int16, device=dev)
             wb = torch.empty(int(np.prod(h.conv3d_transpose_weight_shape(d))), dtype=torch.int16, device=dev)
             h.pack_weights3d_transpose(d, wsrc, wb, stream=stream)
             yb = torch.empty(int(np.prod(osh)), dtype=torch.int16, device=dev)
+            run = lambda st: h.conv3d_transpose(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st)
             wsb = h.conv3d_transpose_workspace_size(d)
             wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
-            gr = capture(lambda st: h.conv3d_transpose(d, xb, wb, yb, workspace=wsd, ws_bytes=wsb, stream=st), 20)
+            gr = capture(run, 20)
+            untuned_us = graph_timed(gr, 20)
+            h.tune_conv2d_variants(h.conv3d_transpose_problem(d), arena, arena.numel(), max_trials=0, warmup=3, reps=20)
+            wsb = h.conv3d_transpose_workspace_size(d)
+            wsd = torch.empty(wsb + 16, dtype=torch.uint8, device=dev)
+            gr = capture(run, 20)
             us = graph_timed(gr, 20)
             del gr, xb, wb, yb, wsd
-            t3d[xl] = dict(us=round(us, 2), nominal_tflops=round(t3fl / us / 1e6, 1))
+            t3d[xl] = dict(us=round(us, 2), untuned_us=round(untuned_us, 2), nominal_tflops=round(t3fl / us / 1e6, 1))
         extra["conv3d_transpose_c128_k64_4x4x4_s2_4x14x14_b2"] = dict(
             per_layout=t3d, speedup_vs_nchw=round(t3d["NCHW"]["us"] / min(v["us"] for v in t3d.values()), 2),
             form="sub-pixel" if h.conv3d_transpose_weight_shape(d)[0] != 64 else "zero insertion",
             note="sub-pixel form: one forward 3-D convolution of x with 8*K output channels over the merged 3x3x3 window, then the "
-                 "kernel that moves the eight phases into place")
+                 "kernel that moves the eight phases into place; untuned_us under NHWC: one launch in place")
 
         # a 1-D convolution (C1D: the C2D with H = R = 1): 256 channels, 9 taps, 2048 samples, batch 16, tuned like the others
         c1shape = alt.conv_desc(16, 256, 1, 2048, 256, 1, 9, in_dtype=alt.BF16, out_dtype=alt.BF16)

@@ -385,7 +385,8 @@ alt_status_t run3d(alt_handle_t h, const Problem3d &pr, const void *x, const voi
         c.v.sd = c.v.sh = c.v.sw = 1;
         c.v.taps[0] = c.v.T; c.v.taps[1] = (int32_t)f.R; c.v.taps[2] = (int32_t)f.S;
         bool done = false;
-        const alt_status_t cs = shaped ? taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, (hipStream_t)stream, &done) : ALT_OK;
+        const alt_status_t cs = shaped ? taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, (int64_t)(ws_bytes - xu_bytes),
+                                                  (hipStream_t)stream, &done) : ALT_OK;
         if (done) return cs;
     }
     GatherParams p;
@@ -468,7 +469,8 @@ alt_status_t run_subpixel3d(alt_handle_t h, const alt_conv3d_desc_t *d, const Su
         c.v.T = s.ad.taps; c.v.D = (int32_t)d->D; c.v.OD = (int32_t)s.ad.outq;
         c.v.stride_d = 1; c.v.pad_d = s.ad.pad; c.v.dil_d = 1;
         bool done = false;
-        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, st, &done);
+        const int64_t ws_2d = (int64_t)(ws_bytes - yb - bb) - (s.pr.gather ? (int64_t)gathered_bytes(s.pr) : 0);
+        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, ws_2d, st, &done);
         if (done) return st_;
     }
     float *bias_m = (float *)((char *)workspace + yb);

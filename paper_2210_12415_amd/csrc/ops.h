@@ -64,9 +64,10 @@ alt_status_t eltwise_add(alt_handle_t h, int dtype, int64_t numel, const void *a
                          hipStream_t st);
 
 // ops.hip: runs the call on a kernel over filter taps and says so in *done, or leaves it alone (a layout, size or alignment these
-// kernels do not take, or a variant of the 2-D problem asked for by number)
+// kernels do not take, or a variant of the 2-D problem asked for, by number or by a tuned entry).  ws_2d: bytes of the workspace
+// the 2-D problem would have for itself, negative if its operands do not fit.
 alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
-                      size_t ws_bytes, hipStream_t st, bool *done);
+                      size_t ws_bytes, int64_t ws_2d, hipStream_t st, bool *done);
 
 alt_status_t conv_problem(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w,
                           const float *bias, void *y, Problem *pb);

@@ -524,23 +524,27 @@ static void memo_store(alt_handle_t h, const void *desc, size_t bytes, unsigned 
     else { v[h->memo->next] = std::move(e); h->memo->next = (h->memo->next + 1) % kMemoEntries; }
 }
 
+// The tuned variant of a key, -1 if there is none that runs this problem.
+static int tuned_variant(alt_handle_t h, const Problem &pb, const std::string &key, size_t ws_limit)
+{
+    auto it = h->cache.find(key);
+    if (it == h->cache.end()) return -1;
+    // a cached entry is only trusted if it still applies (pointers may be aligned differently)
+    const auto &tab = igemm_table();
+    const int v = it->second.variant;
+    return v >= 0 && v < (int)tab.size() * kNumSplits &&
+                   igemm_applicable(pb, tab[v / kNumSplits], kSplits[v % kNumSplits], nullptr, nullptr) &&
+                   igemm_workspace(pb, kSplits[v % kNumSplits]) <= ws_limit ? v : -1;
+}
+
 // variant = -1: the cached tuned variant if it applies and its split-K partial
 // sums fit the workspace the caller brought, else the best-estimate variant
 // that fits.
 static int pick_variant(alt_handle_t h, const Problem &pb, int requested, const std::string &key, size_t ws_limit)
 {
     if (requested >= 0) return requested;
-    auto it = h->cache.find(key);
-    if (it != h->cache.end()) {
-        // a cached entry is only trusted if it still applies (pointers may be aligned differently)
-        const auto &tab = igemm_table();
-        int v = it->second.variant;
-        if (v >= 0 && v < (int)tab.size() * kNumSplits &&
-            igemm_applicable(pb, tab[v / kNumSplits], kSplits[v % kNumSplits], nullptr, nullptr) &&
-            igemm_workspace(pb, kSplits[v % kNumSplits]) <= ws_limit)
-            return v;
-    }
-    return igemm_default_variant(pb, ws_limit);
+    const int v = tuned_variant(h, pb, key, ws_limit);
+    return v >= 0 ? v : igemm_default_variant(pb, ws_limit);
 }
 
 static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w, const float *bias,
@@ -578,7 +582,7 @@ namespace alt {
 // zeros, and its result one more pass into place: 128 channels, 3x3x3 on 8x28x28 at batch 2 took 48 us that way and T3D
 // 128 -> 64, 4x4x4 at stride 2 on the same volume 128 us; so these kernels run whatever they cover)
 alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
-                      size_t ws_bytes, hipStream_t st, bool *done)
+                      size_t ws_bytes, int64_t ws_2d, hipStream_t st, bool *done)
 {
     *done = false;
     if (c.f.variant >= 0 || !x || !w || !y || ((c.f.epilogue & ALT_EPI_BIAS) && !bias)) return ALT_OK;
@@ -596,6 +600,8 @@ alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const vo
         bool ok = conv_problem(h, &c.f, x, w, bias, y, &pb) == ALT_OK && pb.groups <= 1 &&
                   bind_layout(&c.f.x_layout, 4, c.xs, &bx, &err) == ALT_OK && bind_layout(&c.f.y_layout, 4, c.ys, &by, &err) == ALT_OK &&
                   layout_to_dim2(bx, dx) && layout_to_dim2(by, dy);
+        // (tuning an operator is tuning its 2-D problem: the winner runs, by the copying path)
+        if (ok && ws_2d >= 0 && tuned_variant(h, pb, conv_key(h, &c.f), (size_t)ws_2d) >= 0) ok = false;
         if (ok) {
             const int64_t es = (int64_t)dtype_size(c.f.in_dtype), os = (int64_t)dtype_size(c.f.out_dtype);
             IgemmParams &p = pb.p;

@@ -410,7 +410,7 @@ alt_status_t run_subpixel(alt_handle_t h, const alt_conv_desc_t *d, const SubPix
         c.v = v;
         c.v.T = c.v.D = c.v.OD = c.v.stride_d = c.v.dil_d = 1;
         bool done = false;
-        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, st, &done);
+        st_ = taps_run(h, c, x, w_packed, bias, y, workspace, ws_bytes, (int64_t)(ws_bytes - yb - bb), st, &done);
         if (done) return st_;
     }
     float *bias_m = (float *)((char *)workspace + yb);

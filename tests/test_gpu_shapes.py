@@ -168,8 +168,8 @@ def test_few_channel_kernels_every_variant(h, N, C, H, W, K, R, S, stride, pad, 
 
 # 3-D and transposed convolutions on the kernels over filter taps: channel counts of whole and of broken K steps (and of one
 # chunk), depth taps beside the channels, output phases of one to four taps per direction, tiles that end inside a phase;
-# the last two have taps that these kernels leave to the copying path (a dilated one, phases of unequal taps)
-@pytest.mark.parametrize("dtype", [alt.BF16, alt.F32])
+# the last two have taps that these kernels leave to the copying path (a dilated one, phases of unequal taps): several launches
+@pytest.mark.parametrize("dtype,out_dtype", [(alt.BF16, alt.F32), (alt.BF16, alt.BF16), (alt.F32, alt.F32)])
 @pytest.mark.parametrize("op,N,C,D,H,W,K,T,R,S,stride,pad,dil", [
     ("c3d", 2, 64, 4, 6, 5, 40, 3, 3, 3, 1, 1, 1), ("c3d", 1, 24, 5, 9, 7, 72, 3, 3, 2, (2, 1, 2), (1, 1, 0), 1),
     ("c3d", 3, 8, 2, 4, 4, 12, 2, 1, 1, 1, (1, 0, 0), 1), ("c3d", 1, 96, 7, 5, 6, 132, 3, 3, 3, 1, (2, 2, 2), 2),
@@ -179,7 +179,7 @@ def test_few_channel_kernels_every_variant(h, N, C, H, W, K, R, S, stride, pad, 
     ("t2d", 3, 48, 1, 9, 7, 36, 1, 4, 4, 2, 1, 1), ("t2d", 1, 64, 1, 20, 19, 136, 1, 8, 4, (4, 2), (2, 1), 1),
     ("t2d", 2, 8, 1, 5, 6, 4, 1, 2, 2, 2, 0, 1), ("t2d", 1, 64, 1, 12, 13, 64, 1, 6, 6, 2, 2, 1), ("t2d", 2, 32, 1, 6, 7, 16, 1, 2, 2, 2, 1, 1),
     ("t2d", 1, 32, 1, 6, 7, 16, 1, 2, 2, 2, 1, 3), ("t3d", 1, 16, 3, 4, 5, 16, 3, 3, 3, 2, 1, 1)])
-def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad, dil, dtype):
+def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad, dil, dtype, out_dtype):
     three = op != "t2d"
     x = small_ints_f32(71, (N, C, D, H, W), -3, 3)
     w = small_ints_f32(72, ((K, C) if op == "c3d" else (C, K)) + (T, R, S), -3, 3)
@@ -187,7 +187,9 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     each = lambda v, first: v if three else (first,) + (v if isinstance(v, tuple) else (v, v))     # a transposed C2D is one slice
     fn = oracle.conv3d if op == "c3d" else oracle.conv3d_transpose
     ref = np.maximum(fn(x, w, stride=each(stride, 1), pad=each(pad, 0), dil=each(dil, 1)) + b[None, :, None, None, None], np.float32(0))
-    lay = dict(in_dtype=dtype, out_dtype=alt.F32, epilogue=alt.EPI_BIAS | alt.EPI_RELU, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI",
+    np_out = np.uint16 if out_dtype == alt.BF16 else np.float32
+    ref = f32_to_bf16_bits(ref) if out_dtype == alt.BF16 else ref
+    lay = dict(in_dtype=dtype, out_dtype=out_dtype, epilogue=alt.EPI_BIAS | alt.EPI_RELU, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI",
                y_layout="NCHW->NHWC")
     if three:
         d = alt.conv3d_desc(N, C, D, H, W, K, T, R, S, stride=stride, pad=pad, dil=dil, **lay)
@@ -200,12 +202,17 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     wshape = (K, C * T, R, S) if op == "c3d" else getattr(h, name + "_weight_shape")(d)
     wd = dev(bits(np.zeros(int(np.prod(wshape)), np.float32)))
     {"c3d": h.pack_weights3d, "t3d": h.pack_weights3d_transpose, "t2d": h.pack_weights_transpose}[op](d, dev(bits(w.reshape(-1))), wd)
-    whole, y = canary_dev(ref.size, np.float32)
+    whole, y = canary_dev(ref.size, np_out)
     ws_bytes = getattr(h, name + "_workspace_size")(d)
     ws = dev(np.zeros(max(4, ws_bytes // 4), np.float32))
     print(op, N, C, D, H, W, K, T, R, S, stride, pad, dil, flush=True)
-    getattr(h, name)(d, dev(bits(np.ascontiguousarray(np.moveaxis(x, 1, -1)).reshape(-1))), wd, y, bias=dev(b), workspace=ws, ws_bytes=ws_bytes)
-    got = np.moveaxis(host(y, np.float32).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1)
+    xd, bd = dev(bits(np.ascontiguousarray(np.moveaxis(x, 1, -1)).reshape(-1))), dev(b)
+    ran = kernels_run(lambda: getattr(h, name)(d, xd, wd, y, bias=bd, workspace=ws, ws_bytes=ws_bytes))
+    if dil == 3 or (op, R, stride) == ("t3d", 3, 2):
+        assert len(ran) > 1, ran
+    else:
+        assert len(ran) == 1 and "dstream_kernel" in ran[0], ran
+    got = np.moveaxis(host(y, np_out).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1)
     assert canary_ok(whole, ref.size), "wrote outside y"
     assert np.array_equal(got, ref)
 

@@ -12,7 +12,7 @@ import oracle
 import paper_2210_12415_amd as alt
 from workloads import CHAIN_LAYERS, bf16_bits_to_f32, f32_to_bf16_bits, normal_f32, small_ints_f32
 
-from gpu_util import TOL, dev, from_layout, host, rel_err, to_layout
+from gpu_util import TOL, dev, from_layout, host, kernels_run, rel_err, to_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -360,3 +360,36 @@ def test_tuning_the_problem_behind_the_transposed_and_3d_operators(h):
     h.conv3d_transpose(dt, dev(xs.reshape(-1)), wdt, yd, workspace=ws, ws_bytes=need)
     assert np.array_equal(host(yd, np.float32).reshape(N, od, oh, ow, K).transpose(0, 4, 1, 2, 3), reft)
 
+
+def test_a_tuned_problem_is_what_its_operator_runs(h):
+    """C3D, T2D and T3D run in place (one launch) until the 2-D problem that the library reports for them is tuned; then the call runs
+    the winner by the copying path, and in place again when the cache is cleared."""
+    h.cache_clear()
+    arena = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    lay = dict(in_dtype=alt.BF16, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+    N, C, D, H, W, K = 2, 64, 4, 9, 7, 32
+    for name, moves, pack, taps, d in (
+            ("conv3d", "c3d_gather", h.pack_weights3d, 27, alt.conv3d_desc(N, C, D, H, W, K, 3, 3, 3, stride=1, pad=1, **lay)),
+            ("conv2d_transpose", "t2d_shuffle", h.pack_weights_transpose, 16, alt.conv_desc(N, C, H, W, K, 4, 4, stride=2, pad=1, **lay)),
+            ("conv3d_transpose", "t2d_shuffle", h.pack_weights3d_transpose, 64, alt.conv3d_desc(N, C, D, H, W, K, 4, 4, 4, stride=2, pad=1, **lay))):
+        f = getattr(h, name + "_problem")(d)
+        weights = getattr(h, name + "_weight_shape")(d) if "transpose" in name else (K, 3 * C, 3, 3)
+        x = dev(f32_to_bf16_bits(small_ints_f32(1211, (N * D * H * W * C,), -3, 3)))
+        w = torch.empty(int(np.prod(weights)), dtype=torch.int16, device="cuda")
+        pack(d, dev(f32_to_bf16_bits(small_ints_f32(1212, (K * C * taps,), -3, 3))), w)
+        shape = getattr(h, name + "_output_shape")(d)
+        ys = [torch.empty(int(np.prod(shape)), dtype=torch.float32, device="cuda") for _ in range(3)]
+
+        def call(y):
+            need = getattr(h, name + "_workspace_size")(d)
+            ws = torch.empty(need // 4 + 4, dtype=torch.float32, device="cuda")
+            return kernels_run(lambda: getattr(h, name)(d, x, w, y, workspace=ws, ws_bytes=need))
+
+        assert [("dstream_kernel" in k) for k in call(ys[0])] == [True]
+        h.tune_conv2d_variants(f, arena, arena.numel(), max_trials=6, warmup=1, reps=2)
+        assert f.variant >= 0 and h.conv2d_variant_name(f, -1) == h.conv2d_variant_name(f, f.variant)
+        ran = call(ys[1])
+        assert len(ran) > 1 and any(moves in k for k in ran), ran
+        h.cache_clear()
+        assert len(call(ys[2])) == 1
+        assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2])
