@@ -269,7 +269,8 @@ alt_status_t alt_conv2d_static(alt_handle_t h, const alt_conv_desc_t *d, const v
  *  - when more than ALT_SPLITK_MAX_STREAMS streams have launched split-K variants on a device,
  *    the next new stream makes the library wait for the device to go idle and release the
  *    sets (those that a graph capture has seen stay bound for good); while a stream is being
- *    captured that wait is not possible and the call returns ALT_UNSUPPORTED;
+ *    captured that wait is not possible: with variant = -1 a variant without slices runs in its
+ *    place, a split-K variant asked for by number returns ALT_UNSUPPORTED;
  *  - a captured graph carries the set of the stream it was captured on: do not replay it
  *    while other split-K launches issued or captured on that same stream are in flight;
  *  - partial tiles and counters are exchanged with device scope (written through to the

@@ -43,9 +43,11 @@ void igemm_analyse(Problem *pb);
 bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why);
 size_t igemm_workspace(const Problem &pb, int splitk);
 double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p);
-int igemm_default_variant(const Problem &pb, size_t ws_limit);
+// (counters = false: among the variants that need no arrival counters)
+int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters = true);
+// (*no_counters: the variant's slices need arrival counters and no set of them is free for the stream)
 alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *workspace, size_t ws_bytes,
-                       hipStream_t st);
+                       hipStream_t st, bool *no_counters = nullptr);
 
 // dconv.hip
 bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes,

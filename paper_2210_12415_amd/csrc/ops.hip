@@ -252,7 +252,7 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
     return est;
 }
 
-int igemm_default_variant(const Problem &pb, size_t ws_limit)
+int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters)
 {
     const auto &tab = igemm_table();
     double best = 1e300;
@@ -260,6 +260,7 @@ int igemm_default_variant(const Problem &pb, size_t ws_limit)
     for (int ki = 0; ki < (int)tab.size(); ++ki)
         for (int si = 0; si < kNumSplits; ++si) {
             IgemmParams p;
+            if (!counters && tab[ki].launch_direct && kSplits[si] > 1) continue;
             if (!igemm_applicable(pb, tab[ki], kSplits[si], &p, nullptr)) continue;
             if (igemm_workspace(pb, kSplits[si]) > ws_limit) continue;
             const double est = igemm_estimate(pb, tab[ki], p);
@@ -269,7 +270,7 @@ int igemm_default_variant(const Problem &pb, size_t ws_limit)
 }
 
 alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *workspace, size_t ws_bytes,
-                       hipStream_t st)
+                       hipStream_t st, bool *no_counters)
 {
     if (!h->has_gpu) return fail(h, ALT_HIP_ERROR, "no GPU device available");
     const auto &tab = igemm_table();
@@ -290,6 +291,7 @@ alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *wor
         if (!dconv_setup(pb, k, splitk, &dp, &lds, &why))
             return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
         hipError_t e = dconv_run(k, dp, lds, (float *)workspace, st);
+        if (e == hipErrorNotReady && no_counters) *no_counters = true;
         if (e == hipErrorNotReady)
             return fail(h, ALT_UNSUPPORTED, "%s: no split-K counter set is free for this stream (%d streams hold one; sets "
                                             "that captured graphs use are never released)", k.name, kDconvSlots);
@@ -547,6 +549,18 @@ static int pick_variant(alt_handle_t h, const Problem &pb, int requested, const 
     return v >= 0 ? v : igemm_default_variant(pb, ws_limit);
 }
 
+// Runs variant v.  Where it was the library's own choice and no set of arrival counters is free for its slices (more streams than
+// sets, under capture), the best variant that needs none takes its place.
+static alt_status_t run_chosen(alt_handle_t h, const Problem &pb, int v, bool own_choice, void *workspace, size_t ws_bytes,
+                               hipStream_t st)
+{
+    bool no_counters = false;
+    const alt_status_t s = igemm_run(h, pb, v, workspace, ws_bytes, st, &no_counters);
+    if (!no_counters || !own_choice) return s;
+    v = igemm_default_variant(pb, workspace ? ws_bytes : 0, false);
+    return v < 0 ? s : igemm_run(h, pb, v, workspace, ws_bytes, st);
+}
+
 static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w, const float *bias,
                                 const void *addend, void *y, void *workspace, size_t ws_bytes, void *stream, const char *who)
 {
@@ -557,7 +571,7 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
     const unsigned sig = align_sig(x, w, bias, y) | (addend ? 1u << 17 : 0u) | ((unsigned)((uintptr_t)addend & 15) << 18);
     if (MemoEntry *m = memo_find(h, d, sizeof *d, sig, ws_limit)) {
         m->pb.p.x = x; m->pb.p.w = w; m->pb.p.bias = bias; m->pb.p.y = y; m->pb.p.addend = addend;
-        return igemm_run(h, m->pb, m->variant, workspace, ws_bytes, (hipStream_t)stream);
+        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
     }
     Problem pb;
     alt_status_t s = conv_problem(h, d, x, w, bias, y, &pb);
@@ -572,7 +586,7 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
     int v = pick_variant(h, pb, d->variant, d->variant >= 0 ? std::string() : conv_key(h, d), ws_limit);
     if (v < 0) return fail(h, ALT_UNSUPPORTED, "%s: no kernel variant applies", who);
     memo_store(h, d, sizeof *d, sig, ws_limit, pb, v);
-    return igemm_run(h, pb, v, workspace, ws_bytes, (hipStream_t)stream);
+    return run_chosen(h, pb, v, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
 }
 
 }  // extern "C"
@@ -624,7 +638,7 @@ alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const vo
     if (v < 0) return ALT_OK;
     *done = true;
     pb.p.x = x; pb.p.w = w; pb.p.bias = bias; pb.p.y = y;
-    return igemm_run(h, pb, v, workspace, ws_bytes, st);
+    return run_chosen(h, pb, v, true, workspace, ws_bytes, st);
 }
 }  // namespace alt
 
@@ -772,7 +786,7 @@ alt_status_t alt_gemm(alt_handle_t h, const alt_gemm_desc_t *d, const void *A, c
     const unsigned sig = align_sig(A, B, nullptr, C);
     if (MemoEntry *m = memo_find(h, d, sizeof *d, sig, ws_limit)) {
         m->pb.p.x = A; m->pb.p.w = B; m->pb.p.y = C;
-        return igemm_run(h, m->pb, m->variant, workspace, ws_bytes, (hipStream_t)stream);
+        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
     }
     Problem pb;
     alt_status_t s = gemm_problem(h, d, A, B, C, &pb);
@@ -780,7 +794,7 @@ alt_status_t alt_gemm(alt_handle_t h, const alt_gemm_desc_t *d, const void *A, c
     int v = pick_variant(h, pb, d->variant, d->variant >= 0 ? std::string() : gemm_key(h, d), ws_limit);
     if (v < 0) return fail(h, ALT_UNSUPPORTED, "alt_gemm: no kernel variant applies");
     memo_store(h, d, sizeof *d, sig, ws_limit, pb, v);
-    return igemm_run(h, pb, v, workspace, ws_bytes, (hipStream_t)stream);
+    return run_chosen(h, pb, v, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
 }
 
 alt_status_t alt_splitk_status(alt_handle_t h, alt_splitk_status_t *out)

@@ -2,6 +2,8 @@
 the fused reduction are bound to streams, so launches in flight on different
 streams never share a set whatever their issue order.  Integer-valued inputs make
 every sum exact: any lost or early-read partial tile shows as a wrong integer."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -107,3 +109,50 @@ def test_split_k_inside_a_captured_graph_replays_exactly(h):
         torch.cuda.synchronize()
         _check(c, y)
     assert h.splitk_status().counters_nonzero == 0
+
+
+def test_default_choice_without_a_free_counter_set(h):
+    """Every counter set bound to a stream, and the call under capture on one more: the library's own choice, which would be a split-K
+    variant, is one without slices then, and replays exactly; the same variant by number is refused."""
+    hip = ctypes.CDLL("libamdhip64.so")
+
+    def stream():
+        out = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(out), 1) == 0
+        return torch.cuda.ExternalStream(out.value)
+
+    N, C, H, K, R = 1, 512, 7, 512, 3
+    x, w = small_ints_f32(930, (N, C, H, H), -3, 3), small_ints_f32(931, (K, C, R, R), -3, 3)
+    ref = oracle.conv2d(x, w, pad=1)
+    d = alt.conv_desc(N, C, H, H, K, R, R, pad=1, in_dtype=alt.F32, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+    chosen = h.conv2d_variant_name(d, -1)
+    assert "taps" in chosen and not chosen.endswith("_k1")
+    xd, wd = dev(to_layout(x, "NCHW", "NHWC")), dev(to_layout(w, "OIHW", "OHWI"))
+    ws_bytes = h.conv2d_workspace_size(d)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    y = torch.empty(ref.size, dtype=torch.float32, device="cuda")
+    call = lambda desc, st: h.conv2d(desc, xd, wd, y, workspace=ws, ws_bytes=ws_bytes, stream=st)
+    streams = []
+    while h.splitk_status().streams_bound < 64:
+        streams.append(stream())
+        call(d, streams[-1])
+        streams[-1].synchronize()
+    side = stream()
+    g = torch.cuda.CUDAGraph()
+    by_number = alt.ConvDesc.from_buffer_copy(bytes(d))
+    by_number.variant = next(v for v, n in applicable_variants(h, d) if n == chosen)
+    with torch.cuda.graph(g, stream=side):
+        with pytest.raises(alt.AltError) as e:
+            call(by_number, side)
+        call(d, side)
+    assert e.value.status == 4
+    for _ in range(4):
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(from_layout(host(y, np.float32), ref.shape, "NCHW", "NHWC"), ref)
+    call(d, side)                               # outside capture: the sets are released, and this stream's is the first
+    torch.cuda.synchronize()
+    assert h.splitk_status().streams_bound < 64
+    assert np.array_equal(from_layout(host(y, np.float32), ref.shape, "NCHW", "NHWC"), ref)
