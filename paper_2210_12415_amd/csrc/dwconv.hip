@@ -183,7 +183,7 @@ __device__ __forceinline__ void dw_3x3_inside(const DwParams &p, uint32_t t)
                    load_elem(p.w, dim2_off(p.wo, k) + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3), 1);
         }
         if (p.epilogue & ALT_EPI_BIAS) acc += p.bias[k];
-        acc = fmaxf(acc, relu_floor(p.epilogue & ALT_EPI_RELU));
+        if (p.epilogue & ALT_EPI_RELU) acc = fmaxf(acc, 0.f);
         ((uint16_t *)p.y)[yb + dim2_off32(p.yk, k) + oh * p.yh.si + ow * p.yw.si] = f32_to_bf16_rne(acc);
     }
 }
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
         blo = __builtin_shufflevector(b0, b1, 0, 2, 4, 6);
         bhi = __builtin_shufflevector(b0, b1, 1, 3, 5, 7);
     }
-    const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
+    const float floor_ = (p.epilogue & ALT_EPI_RELU) ? 0.f : __builtin_nanf("");     // (relu_floor takes a register too many here)
     const int32_t yb = dim2_off32(p.yn, n) + dim2_off32(p.yk, c), syh = (int32_t)p.yh.si, syw = (int32_t)p.yw.si;
     float probe = 0.f;                              // NaN once a sum is
 #pragma unroll

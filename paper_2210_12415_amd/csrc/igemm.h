@@ -143,7 +143,13 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 
 // What a result is raised to before it is stored: 0 under ReLU, else NaN, which a maximum passes over (it returns the operand
 // that is a number), so that every value stays as it is, NaN among them; -inf in its place would turn a NaN into -inf.
-__device__ __forceinline__ float relu_floor(bool relu) { return relu ? 0.f : __builtin_nanf(""); }
+// (The empty asm hides the NaN: knowing it, the compiler replaces each maximum by one with zero and a select.)
+__device__ __forceinline__ float relu_floor(bool relu)
+{
+    float f = relu ? 0.f : __builtin_nanf("");
+    asm("" : "+v"(f));
+    return f;
+}
 
 // Two fp32 -> bf16 conversions (round to nearest even, NaN kept quiet) packed into one
 // dword, lo in the low half: one hardware conversion instruction on gfx950.
