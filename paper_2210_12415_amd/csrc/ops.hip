@@ -195,14 +195,21 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         const double clk = rounds * (steps * (std::max(mfma, bytes) + 120.0) + 6000.0);
         // (halved like the direct kernels' estimate below: wherever one of these kernels applies it
         // has beaten the implicit-GEMM kernels, whose estimate is optimistic)
-        // The kernels over filter taps fetch a pixel once per tap, so where the patch-resident or the plain streaming
-        // kernels cover the problem (bf16, channels a multiple of 64) those come first.
-        const double taps = k.taps && p.C % 64 == 0 ? 3.0 : 1.0;
+        // The kernels over filter taps fetch a pixel once per tap, so where the patch-resident kernels cover the problem (bf16,
+        // channels a multiple of 64, more than one tap) or the plain streaming ones (one tap, stride 1), those come first.  At other
+        // strides one tap leaves them to the register-staged kernels (17 x 512 x 17 x 17 to 244 channels, 1x1 at stride 2: 17 us
+        // on those, 5.7 here).
+        const bool plain = p.R * p.S == 1 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 0 && p.pad_w == 0;
+        const double taps = k.taps && p.C % 64 == 0 && (plain || p.R * p.S > 1) ? 3.0 : 1.0;
+        // Plain kernels with steps of 32, B as NK, where steps of 64 do not divide the sum: they do with a ring of eight stages what
+        // the estimate expects of steps twice as deep (3220 x 208 x 800 takes 5.4 us on them and 7.8 on the tap kernels, 7 x 1865 x
+        // 584 x 1696 44 and 77; as KN they have large tiles only, and the estimate holds).
+        const double narrow = !k.taps && !k.bt && p.C % 64 ? 0.7 : 1.0;
         // One tap leaves the patch-resident kernel nothing to reuse, and its and the implicit-GEMM kernels' estimates know little
         // of what many slices cost: 37 x 768 x 3072 took 21.6 us on the former in 24 slices, 19.9 here in 24, 7.3 in four;
         // 200 x 1024 x 1024 17.0 and 7.1; 810 x 384 x 1536 17.7 and 7.1. No product of the 36 compared was faster elsewhere.
         const double lead = p.R * p.S == 1 ? 0.25 : 0.5;
-        return taps * lead * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 + 45.0 * partial_us : 0.0));
+        return taps * narrow * lead * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 + 45.0 * partial_us : 0.0));
     }
     if (k.launch_direct && k.stream == 2) {
         // Channel-planar kernel: a workgroup converts its patch on the way in (about 20 bytes per clock

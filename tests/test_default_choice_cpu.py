@@ -1,0 +1,33 @@
+"""Which kernel family the library picks by itself, on both sides of the lines its estimate draws (ops.hip).  Host only."""
+import pytest
+
+import paper_2210_12415_amd as alt
+
+
+@pytest.fixture(scope="module")
+def h():
+    return alt.Handle()
+
+
+def conv(h, N, C, H, K, R, stride=1, dtype=alt.BF16):
+    return h.conv2d_variant_name(alt.conv_desc(N, C, H, H, K, R, R, stride=stride, pad=R // 2, in_dtype=dtype, out_dtype=dtype,
+                                               x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC"), -1)
+
+
+def gemm(h, M, N, K, lay, batch=1, dtype=alt.BF16):
+    return h.gemm_variant_name(alt.gemm_desc(M, N, K, batch=batch, in_dtype=dtype, out_dtype=dtype, b_layout="KN->" + lay), -1)
+
+
+@pytest.mark.parametrize("M,N,K,lay,batch,family", [
+    (3220, 208, 800, "NK", 1, "_stream_"), (1865, 584, 1696, "NK", 7, "_stream_"), (542, 1168, 544, "NK", 1, "_stream_"),
+    (424, 1680, 160, "NK", 1, "_stream_"), (15, 4048, 96, "KN", 1, "_rtapskn_"), (215, 388, 2912, "NK", 1, "_rtaps_"),
+    (300, 264, 1048, "NK", 1, "_rtaps_")])
+def test_products_whose_depth_is_an_odd_number_of_half_steps(h, M, N, K, lay, batch, family):
+    assert family in gemm(h, M, N, K, lay, batch)
+
+
+@pytest.mark.parametrize("N,C,H,K,stride,family", [
+    (8, 608, 12, 640, 1, "_stream_"), (4, 608, 23, 8, 1, "_stream_"), (16, 256, 56, 64, 1, "_stream_"),
+    (17, 512, 17, 244, 2, "taps_"), (21, 256, 22, 92, 2, "taps_"), (3, 128, 42, 108, 2, "taps_")])
+def test_one_tap_convolutions(h, N, C, H, K, stride, family):
+    assert family in conv(h, N, C, H, K, 1, stride)
