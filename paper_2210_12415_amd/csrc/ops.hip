@@ -178,17 +178,23 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         const double partial_us = p.splitk > 1 ? 1e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0 : 0.0;
         if (k.dtype == ALT_F32) {
             // fp32: matrix instructions do a sixteenth of the products per clock, so co-resident workgroups share them; a
-            // step costs 280 clocks beside its products, a workgroup 7200, a split 0.8 us and 0.9 us a MB (fitted over 40
-            // convolutions of 0.05 to 3 GFLOP; the choice is at most 5 % from the fastest variant).  They beat the
-            // register-staged kernels on each of the 40: the five 3x3 and 1x1 layers at batch 5 take
-            // 15.5 / 17.9 / 20.2 / 21.3 / 8.7 us against 28.9 / 26.4 / 26.9 / 26.6 / 13.4.  Past 60 us nothing was compared, and
-            // the two estimates meet as they are.
+            // step costs 280 clocks beside its products, a workgroup 7200, a split 0.8 us and 0.9 us a MB (microseconds, within 10 %
+            // of 1000 measured launches).  The factor brings them to the estimate of the register-staged kernels, which take two
+            // to six times what it says, in steps of 512 tiles.  Of 122 convolutions and products of 5 to 200 us the choice is 2.5 %
+            // from the fastest variant on average; the five 3x3 and 1x1 layers stay on these kernels from batch 1 to 40, where the
+            // others are at most 5 % faster (64 channels at batch 12, 36.4 us against 38.4) and up to 40 % slower.  At 0.2 batches 16
+            // to 23 of two of them go to the others and lose 5 to 16 %.  A step that spans taps (fewer channels than a step is
+            // deep) costs more: 28 x 16 x 36 x 36 to 424 channels, 5x5, takes 140 us here and 122 on the others.
             const double need = std::max((double)k.kw * k.BM * k.BN * k.BK / 128.0 * (waves >= 8 ? 1.11 : 1.07) * std::max(1.0, 4.0 / waves),
                                          (double)k.kw * (k.BM + k.BN) * k.BK * es / 33.6);
             auto round_clk = [&](double n) { return steps * std::max(need + 280.0, n * need) + 7200.0; };
             const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
             const double us = (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0 + (p.splitk > 1 ? 0.8 + 0.9 * partial_us : 0.0);
-            return (us < 60.0 ? 0.2 : 0.5) * us * 45.0;
+            // (Batches take no slices here.  A handful of tiles of a long sum leaves the chip idle, and the register-staged kernels in
+            // slices take 0.5 to 1.06 times as long: 2 x 4 x 28 x 6360 32 us against 61, 11 x 2 x 8 x 5556 57 and 53; with 22 tiles it
+            // is 50 and 39.  The estimate of those that gather is an order too high, hence the factor.)
+            const double idle = p.batch > 1 && blocks <= 12.0 && p.C >= 2000 ? 12.0 : 1.0;
+            return (p.C < 32 && p.R * p.S > 1 ? 0.2 : 0.18) * idle * us * 45.0;
         }
         const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * 8.0 * (waves >= 8 ? 1.7 : 2.0);
         const double bytes = (double)k.kw * (k.BM + k.BN) * k.BK * es / 45.0;

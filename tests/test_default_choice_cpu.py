@@ -31,3 +31,15 @@ def test_products_whose_depth_is_an_odd_number_of_half_steps(h, M, N, K, lay, ba
     (17, 512, 17, 244, 2, "taps_"), (21, 256, 22, 92, 2, "taps_"), (3, 128, 42, 108, 2, "taps_")])
 def test_one_tap_convolutions(h, N, C, H, K, stride, family):
     assert family in conv(h, N, C, H, K, 1, stride)
+
+
+@pytest.mark.parametrize("C,H,K,R", [(64, 56, 64, 3), (128, 28, 128, 3), (256, 14, 256, 3), (512, 7, 512, 3), (256, 56, 64, 1)])
+def test_single_precision_layers_do_not_change_kernels_with_the_batch(h, C, H, K, R):
+    assert all("_rtaps_" in conv(h, n, C, H, K, R, dtype=alt.F32) for n in range(1, 41))
+
+
+@pytest.mark.parametrize("M,N,K,batch,taps", [(4, 28, 6360, 2, False), (12, 12, 4920, 4, False), (14, 64, 3576, 22, True),
+                                              (87, 684, 2280, 18, True), (4, 28, 6360, 1, True)])
+def test_single_precision_batches_of_few_tiles_run_in_slices(h, M, N, K, batch, taps):
+    name = gemm(h, M, N, K, "NK", batch, alt.F32)
+    assert ("_rtaps_" in name) == taps and (taps or not name.endswith("_k1"))
