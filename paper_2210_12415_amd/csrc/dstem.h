@@ -12,9 +12,11 @@
 // rows of each channel comes in through registers while the previous tile computes.  A row tile of the matrix
 // instruction is 2 x 16 pixels.  Results are rounded, transposed through LDS, and stored 16 bytes per lane.
 //
-// 16 images of 3 x 224 x 224, 64 channels of 7 x 7 at stride 2 (30 MB, 3.8 GFLOP): 14.7 us, 2.1 TB/s, against 118 us on the
-// element-gather kernel; 64 images 42 us, 2.9 TB/s. What bounds it is instruction issue: per row tile 22 matrix instructions
-// stand beside about 150 others (window reads and masks, rounding, the transpose, store addresses) on two waves per SIMD.
+// 16 images of 3 x 224 x 224, 64 channels of 7 x 7 at stride 2 (30 MB, 3.8 GFLOP): 14.6 us, 2.1 TB/s, against 118 us on the
+// element-gather kernel; 64 images 42 us, 2.9 TB/s. What bounds it is what two waves per SIMD cannot hide: per matrix
+// instruction 18 vector instructions (window masks, rounding, the transpose, addresses, the filter's way into registers) keep
+// the vector units busy a third of the time, LDS is active another third with two of five cycles lost to bank conflicts
+// (windows start at any even column), and a wave waits 55 % of its life; the matrix cores are busy 8 %.
 #pragma once
 
 #include "dconv.h"

@@ -35,8 +35,8 @@
 //     of few K steps: 115 x 1872 x 2344 12.7 us against 11.4.)
 // The depth of a 3-D convolution is one more direction of taps, so that its input is read where it lies.  A transposed
 // convolution in its sub-pixel form is one such launch with the output phases along blockIdx.y: each phase walks the taps of
-// the merged filter that are its own (the others are zeros: three of four in a 4x4 filter at stride 2, seven of eight
-// in 4x4x4 of the 27 x 8 of the common window) and stores its pixels into the interleaved output.
+// the merged filter that are its own (the others are zeros: five of nine for a 4x4 filter at stride 2, whose phases have
+// four taps each in a common window of 3x3, and nineteen of 27 for 4x4x4) and stores its pixels into the interleaved output.
 // T = float runs on the fp32 matrix instructions: a K step is BK floats, a 16-byte chunk four.
 #pragma once
 
