@@ -157,11 +157,50 @@ __global__ __launch_bounds__(kDwThreads) void dwconv_vec8_kernel(const DwParams 
     }
 }
 
-// The outputs of thread `t` of the 3x3 vector kernel, one after the other and over the taps inside the image alone.
-template <int STRIDE, int TW, int TH>
-__device__ __forceinline__ void dw_3x3_inside(const DwParams &p, uint32_t t)
+typedef uint32_t dw_words __attribute__((ext_vector_type(4)));
+
+// The filters of eight channels from c on, tap by tap.  TAPS: tap-contiguous, 72 elements in one run, transposed in registers.
+template <bool TAPS>
+__device__ __forceinline__ void dw_3x3_filter(const DwParams &p, int c, dw_words (&wv)[9])
 {
-    asm volatile("" : "+v"(t));                     // (decoded anew: nothing of the item stays in registers for this)
+    typedef dw_words w4_t;
+    if constexpr (TAPS) {
+        const w4_t *wp = (const w4_t *)((const uint16_t *)p.w + c * 9);
+        uint32_t raw[36];
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            const w4_t d = wp[v];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) raw[v * 4 + q] = d[q];
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {           // channels 2q and 2q + 1 of tap t
+                const int a = 2 * q * 9 + t, b = a + 9;
+                wv[t][q] = __builtin_amdgcn_perm(raw[b / 2], raw[a / 2], ((b & 1) ? 0x07060000u : 0x05040000u) | ((a & 1) ? 0x0302u : 0x0100u));
+            }
+    } else {
+        const uint16_t *wb = (const uint16_t *)p.w + dim2_off(p.wo, c);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) wv[t] = *(const w4_t *)(wb + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3));
+    }
+}
+
+// The outputs of thread `t` of the 3x3 vector kernel once more, over the taps inside the image alone, if it stands at the border and
+// its filters hold an infinite or NaN value: the same sums with the filter cleared under taps outside.
+// (16 x 144 x 56 x 56 takes 8.9 us, with NaN inputs 9.9, with NaN filters 22.5; one element at a time it took 225, a row of outputs
+// at a time 19.1, but those 11 KB of code, never run, cost every pass through several kernels 1 %.)
+template <int STRIDE, int TW, int TH, bool TAPS>
+__device__ __forceinline__ void dw_3x3_inside(uint32_t t)
+{
+    // (the item is decoded and the kernel's argument read anew, so that the kernel keeps nothing in registers for this)
+    typedef const __attribute__((address_space(4))) DwParams *arg_t;
+    arg_t arg = (arg_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(arg), "+v"(t));
+    const DwParams &p = *(const DwParams *)arg;
+    typedef uint32_t w4_t __attribute__((ext_vector_type(4)));
+    typedef float f4_t __attribute__((ext_vector_type(4)));
     const uint32_t e = (uint32_t)igemm_logical_tile((int)gridDim.x) * kDwThreads + t;
     uint32_t r = fast_div(e, p.fd_c8);
     const int c = (int)(e - r * p.fd_c8.d) * 8;
@@ -171,20 +210,51 @@ __device__ __forceinline__ void dw_3x3_inside(const DwParams &p, uint32_t t)
     const int oh0 = (int)(r2 - (uint32_t)n * p.fd_ohb.d) * TH;
     const int ih0 = oh0 * STRIDE - p.pad_h, iw0 = ow0 * STRIDE - p.pad_w;
     if (ih0 >= 0 && iw0 >= 0 && ih0 + (TH - 1) * STRIDE + 3 <= p.H && iw0 + (TW - 1) * STRIDE + 3 <= p.W) return;
-    const int32_t xb = dim2_off32(p.xn, n), yb = dim2_off32(p.yn, n);
-    for (int o = 0; o < TH * TW * 8; ++o) {
-        const int oh = oh0 + (o >> 3) / TW, ow = ow0 + (o >> 3) % TW, k = c + (o & 7);
-        if (oh >= p.OH || ow >= p.OW) continue;
-        float acc = 0.f;
-        for (int t = 0; t < 9; ++t) {
-            const int ih = oh * STRIDE - p.pad_h + t / 3, iw = ow * STRIDE - p.pad_w + t % 3;
-            if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
-            acc += load_elem(p.x, xb + dim2_off32(p.xc, k) + ih * p.xh.si + iw * p.xw.si, 1) *
-                   load_elem(p.w, dim2_off(p.wo, k) + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3), 1);
+    w4_t wv[9];
+    dw_3x3_filter<TAPS>(p, c, wv);
+    typedef uint16_t h8_t __attribute__((ext_vector_type(8)));
+    h8_t largest = 0;
+#pragma unroll
+    for (int f = 0; f < 9; ++f) largest = __builtin_elementwise_max(largest, __builtin_bit_cast(h8_t, wv[f] & 0x7fff7fffu));
+    const bool finite = __builtin_reduce_max(largest) < 0x7f80;
+    if (finite) return;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, (int)p.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)p.y_bytes, 0x00020000);
+    const int32_t xb = dim2_off32(p.xn, n) + dim2_off32(p.xc, c), yb = dim2_off32(p.yn, n) + dim2_off32(p.yk, c);
+    f4_t blo = {0.f, 0.f, 0.f, 0.f}, bhi = {0.f, 0.f, 0.f, 0.f};
+    if (p.epilogue & ALT_EPI_BIAS) {
+        const f4_t b0 = *(const f4_t *)(p.bias + c), b1 = *(const f4_t *)(p.bias + c + 4);
+        blo = __builtin_shufflevector(b0, b1, 0, 2, 4, 6);
+        bhi = __builtin_shufflevector(b0, b1, 1, 3, 5, 7);
+    }
+    const float floor_ = relu_floor(p.epilogue & ALT_EPI_RELU);
+#pragma unroll 1
+    for (int o = 0; o < TH * TW; ++o) {
+        const int oh = oh0 + o / TW, ow = ow0 + o % TW;
+        w4_t xv[9];
+        uint32_t inside[9];
+#pragma unroll
+        for (int f = 0; f < 9; ++f) {
+            asm volatile("" : "+v"(wv[f]));         // (stays packed from output to output)
+            const int ih = oh * STRIDE - p.pad_h + f / 3, iw = ow * STRIDE - p.pad_w + f % 3;
+            const bool ok = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
+            inside[f] = ok ? 0xffffffffu : 0u;
+            xv[f] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(ok ? (uint32_t)(xb + ih * (int32_t)p.xh.si + iw * (int32_t)p.xw.si) * 2u : kOutOfRange), 0, 0);
         }
-        if (p.epilogue & ALT_EPI_BIAS) acc += p.bias[k];
-        if (p.epilogue & ALT_EPI_RELU) acc = fmaxf(acc, 0.f);
-        ((uint16_t *)p.y)[yb + dim2_off32(p.yk, k) + oh * p.yh.si + ow * p.yw.si] = f32_to_bf16_rne(acc);
+        f4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int f = 0; f < 9; ++f) {
+            const w4_t w = wv[f] & inside[f];
+            lo += __builtin_bit_cast(f4_t, xv[f] << 16) * __builtin_bit_cast(f4_t, w << 16);
+            hi += __builtin_bit_cast(f4_t, xv[f] & 0xffff0000u) * __builtin_bit_cast(f4_t, w & 0xffff0000u);
+        }
+        lo = __builtin_elementwise_max(lo + blo, (f4_t){floor_, floor_, floor_, floor_});
+        hi = __builtin_elementwise_max(hi + bhi, (f4_t){floor_, floor_, floor_, floor_});
+        w4_t out;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q] = f32x2_to_bf16x2(lo[q], hi[q]);
+        const bool ok = ow < p.OW && oh < p.OH;
+        __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + oh * (int32_t)p.yh.si + ow * (int32_t)p.yw.si) * 2u : kOutOfRange), 0, 0);
     }
 }
 
@@ -216,27 +286,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void *)p.x, 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc((void *)p.y, 0, (int)p.y_bytes, 0x00020000);
     w4_t wv[9];                                     // kept packed: unpacked where used, half the registers
-    if constexpr (TAPS) {
-        const w4_t *wp = (const w4_t *)((const uint16_t *)p.w + c * 9);
-        uint32_t raw[36];
-#pragma unroll
-        for (int v = 0; v < 9; ++v) {
-            const w4_t d = wp[v];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) raw[v * 4 + q] = d[q];
-        }
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {           // channels 2q and 2q + 1 of tap t
-                const int a = 2 * q * 9 + t, b = a + 9;
-                wv[t][q] = __builtin_amdgcn_perm(raw[b / 2], raw[a / 2], ((b & 1) ? 0x07060000u : 0x05040000u) | ((a & 1) ? 0x0302u : 0x0100u));
-            }
-    } else {
-        const uint16_t *wb = (const uint16_t *)p.w + dim2_off(p.wo, c);
-#pragma unroll
-        for (int t = 0; t < 9; ++t) wv[t] = *(const w4_t *)(wb + dim2_off(p.wr, t / 3) + dim2_off(p.ws, t % 3));
-    }
+    dw_3x3_filter<TAPS>(p, c, wv);
     f4_t lo[TH][TW], hi[TH][TW];
 #pragma unroll
     for (int i = 0; i < TH; ++i)
@@ -306,7 +356,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
     // A tap outside the image is no part of the sum, but the zeros read for it were multiplied, and zero times an infinite or NaN
     // filter value is NaN.  Where a sum came out NaN, the outputs of a thread at the border are taken again over the taps inside
     // and stored over those above.
-    if (probe != probe) dw_3x3_inside<STRIDE, TW, TH>(p, threadIdx.x);
+    if (probe != probe) dw_3x3_inside<STRIDE, TW, TH, TAPS>(threadIdx.x);
 }
 
 // bf16 in and out, width contiguous, 3x3 without dilation, padding 1 along the width, W and OW multiples of TW
