@@ -366,7 +366,7 @@ alt_status_t alt_conv2d_transpose_weight_shape(const alt_conv_desc_t *d, int64_t
  * (extents, padding and layouts of the form it takes; epilogue, dtypes and variant as given):
  * tune(op, shape) for the transposed operator is alt_tune_conv2d on it, after which the call
  * finds the winning variant in the cache.  The tuner times the 2-D problem alone, so compare the calls where the
- * untuned one runs in place: 128 -> 64 channels, 4x4 at stride 2, 28x28, batch 16 takes 10.5 us in place, 18.3 tuned. */
+ * untuned one runs in place: 128 -> 64 channels, 4x4 at stride 2, 28x28, batch 16 takes 9.7 us in place, 17.0 tuned. */
 alt_status_t alt_conv2d_transpose_problem(alt_handle_t h, const alt_conv_desc_t *d, alt_conv_desc_t *out);
 alt_status_t alt_pack_weights_transpose(alt_handle_t h, const alt_conv_desc_t *d, const void *w_ckrs,
                                         void *w_packed, void *stream);
@@ -392,7 +392,7 @@ alt_status_t alt_pack_weights_transpose(alt_handle_t h, const alt_conv_desc_t *d
  * must divide T*C as they would C.  T = 1 with stride_d = 1 and pad_d = 0 is alt_conv2d on x itself.
  * In place: over dense NHWC slices with an OHWI filter, C a multiple of 16 bytes and K of 4, the depth is one more
  * direction of taps and x is read where it lies, in one launch, unless the 2-D problem has a tuned variant (that fits)
- * or the descriptor names one (128 channels, 3x3x3, 8x28x28, batch 2: 24.3 us in place, 38.0 tuned).
+ * or the descriptor names one (128 channels, 3x3x3, 8x28x28, batch 2: 23.5 us in place, 35.2 tuned).
  * `workspace` (device, 16-byte aligned) holds x' followed by what alt_conv2d wants;
  * alt_conv3d_workspace_size reports the sum, less than x' fails with ALT_WORKSPACE_TOO_SMALL.
  * groups > 1 is ALT_UNSUPPORTED.  alt_conv3d_output_shape writes (N, K, OD, OH, OW).
@@ -436,7 +436,7 @@ alt_status_t alt_conv3d_problem(alt_handle_t h, const alt_conv3d_desc_t *d, alt_
  * one.  alt_conv3d_transpose_weight_shape reports the logical shape (K', T'*C, R', S') of the packed
  * filter of the form the descriptor takes (so its size).
  * Both forms run in place under the conditions stated for alt_conv2d_transpose and alt_conv3d (4x4x4 at stride 2,
- * 128 -> 64 channels on 4x14x14, batch 2: 8.4 us in place, 25.1 tuned); zero insertion does not.
+ * 128 -> 64 channels on 4x14x14, batch 2: 8.0 us in place, 23.8 tuned); zero insertion does not.
  * Workspace and errors as for alt_conv3d.  Asynchronous on `stream`. */
 alt_status_t alt_conv3d_transpose(alt_handle_t h, const alt_conv3d_desc_t *d, const void *x, const void *w_packed,
                                   const float *bias, void *y, void *workspace, size_t ws_bytes, void *stream);
