@@ -112,6 +112,7 @@ struct DconvParams {
 };
 constexpr int kOutPhases = -1;    // y_blk of an output written phase by phase
 constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
+enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2, kTapsDense = 3, kTapsOne = 4 };   // which of them (dstream.h)
 
 // Element offset of channel `ch` of input pixel g (= img * H*W + hw) under the activations' layout.
 __device__ __forceinline__ uint32_t dconv_in_elem(const DconvParams &p, int g, int ch)

@@ -172,6 +172,7 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
     if (splitk > 1 && (int64_t)tiles_m * tiles_n > kDconvMaxTiles) return no("too many output tiles for the split-K counters");
     if ((int64_t)tiles_m * tiles_n * splitk > 0x7fffffff) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
     DconvParams d;
     std::memset(&d, 0, sizeof d);
@@ -194,7 +195,6 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     d.d_ihw = make_div32((uint32_t)(p.H * p.W));
     d.x_bstride = p.x_bstride * 2; d.w_bstride = p.w_bstride * 2; d.y_bstride = p.y_bstride * osz;
     *out = d;
-    *lds_bytes = lds;
     return true;
 }
 
@@ -249,6 +249,7 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
     if (splitk > 1 && (int64_t)tiles_m * tiles_n > kDconvMaxTiles) return no("too many output tiles for the split-K counters");
     if ((int64_t)tiles_m * tiles_n * splitk > 0x7fffffff) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
     DconvParams d;
     std::memset(&d, 0, sizeof d);
@@ -304,7 +305,6 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     d.d_ihw = make_div32((uint32_t)(H * W));
     d.x_bstride = p.x_bstride * es; d.w_bstride = p.w_bstride * es; d.y_bstride = p.y_bstride * osz;
     *out = d;
-    *lds_bytes = lds;
     return true;
 }
 
@@ -346,6 +346,7 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     if (lds > 160 * 1024) return no("patch and weight stages do not fit LDS");
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
     if ((int64_t)tiles_m * tiles_n > 0x7fffffff) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
     DconvParams d;
     std::memset(&d, 0, sizeof d);
@@ -365,7 +366,6 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     d.d_sk = make_div32(1);
     d.bk = 64;
     *out = d;
-    *lds_bytes = lds;
     return true;
 }
 
@@ -395,6 +395,7 @@ static bool dstem_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     if (lds > 64 * 1024) return no("patch does not fit LDS");
     const int64_t tw = (OW + kStemTile - 1) / kStemTile, th = (OH + kStemTile - 1) / kStemTile;
     if (tw * th * N > 0x7fffffff - 4096 || (K + k.BN - 1) / k.BN > 65535) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
     DconvParams d;
     std::memset(&d, 0, sizeof d);
@@ -414,7 +415,6 @@ static bool dstem_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     d.wst_o = (int32_t)(C * R * S); d.wst_i = (int32_t)p.wi.si; d.wst_r = (int32_t)p.wr.si; d.wst_s = (int32_t)p.ws.si;
     d.y_blk = y_blk;
     *out = d;
-    *lds_bytes = lds;
     return true;
 }
 
@@ -465,6 +465,7 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
     if (splitk > 1 && (int64_t)tiles_m * tiles_n > kDconvMaxTiles) return no("too many output tiles for the split-K counters");
     if ((int64_t)tiles_m * tiles_n * splitk > 0x7fffffff) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
     DconvParams d;
     std::memset(&d, 0, sizeof d);
@@ -492,7 +493,6 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
     d.x_blk = x_blk; d.y_blk = y_blk;
     d.d_ihw = make_div32((uint32_t)(H * W));
     *out = d;
-    *lds_bytes = lds;
     return true;
 }
 

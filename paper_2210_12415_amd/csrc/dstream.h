@@ -44,8 +44,6 @@
 
 namespace alt {
 
-enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2, kTapsDense = 3, kTapsOne = 4 };
-
 // KW groups of WGM x WGN waves; group kg handles channels [kg, kg + 1) * Cs / KW of the
 // workgroup's slice in steps of BK (64 or 32; half of that for float), through a ring of NS stages of its own.
 // While a step computes, NS - 2 later stages are in flight: deep rings of small stages

@@ -40,9 +40,10 @@ int igemm_num_splits();
 int igemm_variant_count();
 std::string igemm_variant_name(int variant);
 void igemm_analyse(Problem *pb);
-bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why);
+// (*lds_bytes: of a workgroup of a tile kernel; untouched for the others)
+bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why, size_t *lds_bytes = nullptr);
 size_t igemm_workspace(const Problem &pb, int splitk);
-double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p);
+double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds);
 // (counters = false: among the variants that need no arrival counters)
 int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters = true);
 // (*no_counters: the variant's slices need arrival counters and no set of them is free for the stream)

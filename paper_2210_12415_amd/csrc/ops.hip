@@ -2,6 +2,7 @@
 // the implicit-GEMM kernel's addressing, variant table, split-K reduction,
 // weight packing.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "igemm.h"
@@ -96,7 +97,7 @@ static bool nests(int64_t f, int64_t C, int bk) { return f >= C ? true : (f % bk
 
 // Can kernel `k` with split factor `splitk` run this problem?  Fills the
 // launch-dependent fields of a copy of the parameters.
-bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why)
+bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why, size_t *lds_bytes)
 {
     auto no = [&](const char *m) { if (why) *why = m; return false; };
     const IgemmParams &p0 = pb.p;
@@ -104,7 +105,7 @@ bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igemm
     if (pb.v.T && !k.taps) return no("depth taps and output phases are built into the kernels over filter taps only");
     if (p0.addend && !k.launch_direct) return no("the fused sum is built into the tile kernels only");
     if (k.launch_direct) {
-        if (!dconv_setup(pb, k, splitk, nullptr, nullptr, why)) return false;
+        if (!dconv_setup(pb, k, splitk, nullptr, lds_bytes, why)) return false;
         if (out) {
             IgemmParams p = p0;
             p.splitk = splitk;
@@ -152,70 +153,90 @@ size_t igemm_workspace(const Problem &pb, int splitk)
     return (size_t)splitk * pb.p.batch * pb.p.M * pb.p.Nc * sizeof(float);
 }
 
-// Rough relative time of one variant: rounds of workgroups over the chip x
-// (K steps x per-step cost), gather/transposing loaders penalised.  Only used
-// to pick a default and to order the tuner's trials best-first.
-double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p)
+// Microseconds of a bf16 tile kernel (patch-resident, streaming, over filter taps).  A workgroup opens (latency of its first loads,
+// and the patch), walks its K steps and stores its tile; as many share a compute unit as LDS and registers allow, and a round of
+// them takes what they ask of the unit together (matrix cores, operand bytes into LDS and out of it), but no less than one alone,
+// which waits at every step.  Clocks at 2.2 GHz.  Fitted over 43000 launches (740 layers and products of 4 to 500 us under 60 to 100
+// variants each): the choice takes 3 % longer than the fastest variant on average.  (The estimate before priced slices and patches
+// too low: 30 % on the 3x3 and 1x1 layers among them; 16 x 128 x 28 x 28, 3x3, ran in 19.5 us where 7.7 were to be had, 256 x
+// 512 x 7 x 7 in 122 where 69 were.)  What it does not know: how often an L2 line is fetched again, which matters for few output channels
+// (86 x 512 x 43 x 43 to 8, 5x5: 468 us on the choice, 249 on the fastest).
+static double tile_estimate_us(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds)
 {
-    (void)pb;
+    const bool patch = k.stream == 0;
+    const int waves = k.kw * k.wgm * k.wgn;
+    const double wtm = (double)k.BM / k.wgm, wtn = (double)k.BN / k.wgn, acc = wtm * wtn / 64;
+    const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), std::floor((acc <= 32 ? 16.0 : 8.0) / waves)));
+    const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
+    const double steps = k.taps ? std::ceil((double)p.ksteps_per_split / k.kw) : (double)p.R * p.S * p.C / p.splitk / k.kw / k.BK;
+    // (what bounds a step overlaps with the rest of it only in part: the parts are added in a norm between sum and maximum)
+    auto norm = [](std::initializer_list<double> parts, double e) {
+        double sum = 0;
+        for (double v : parts) sum += std::pow(v, e);
+        return std::pow(sum, 1.0 / e);
+    };
+    const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 2048.0;                  // clocks of a step's products on four SIMDs
+    const double in = (double)k.kw * ((patch ? 0 : k.BM) + k.BN) * k.BK * 2 / 46.6;   // ... of its operands' way into LDS
+    const double out = waves * (wtm + wtn) * k.BK * 2 / 400.0;                        // ... and out of it
+    // (the patch-resident kernels' loop over taps and channels is unrolled for up to two steps a tap, and of one tap)
+    const bool walks = patch && p.R * p.S > 1 && !(p.R == 3 && p.S == 3 && steps <= 2 * 9);
+    const double alone = std::max(mfma * (waves >= 8 ? 1.0 : 1.47) * std::max(1.0, 4.0 / waves), in) + (patch ? 86.0 : 0.0) +
+                         (walks ? 417.0 : 0.0) + (k.taps == kTapsRagged ? 97.0 : 0.0);
+    const double np = patch ? (double)k.BM * p.stride_h * p.stride_h + 2.0 * (p.pad_h * p.W + p.pad_w) : 0.0;
+    const double ends = 4970.0 - (patch ? 180.0 : !k.taps ? 1600.0 : 0.0) - (k.bt ? 1080.0 : 0.0) + (patch ? 0.0 : 9.6 * k.BM) +
+                        (waves < 8 && acc >= 64 ? 1420.0 : 0.0) + (k.kw > 1 ? 700.0 + (double)k.kw * k.BM * k.BN / 74.0 : 0.0);
+    // (half steps beside whole ones of the same tile: 128 x 128 x 32 takes 10 to 25 % longer than 128 x 128 x 64 where both apply)
+    const double begin = !patch && k.BK == 32 ? 15.0 : 0.0;
+    auto round_clk = [&](double n) {
+        const double rate = acc >= 128 ? 1.0 : waves * n >= 8 ? 1.34 : 1.04;
+        const double step = norm({n * mfma * rate * std::max(1.0, 4.0 / (waves * n)), n * in, n * out, alone}, 3.11) + begin;
+        return steps * step + ends + n * (k.BM * k.BN / 6.67 + np * p.C / p.splitk * 2 / 83.0);
+    };
+    const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
+    double us = 1.18 + (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0;
+    // (a split's partial sums are written, fetched and added by whoever comes last)
+    if (p.splitk > 1) us += 1.11 + 0.47 * p.splitk + 0.67e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0;
+    const int entries = pb.v.T ? 1 : p.batch;
+    const double mem = 1.18 + 2.0 * ((double)(pb.x_elems + pb.w_elems) * entries + (double)p.M * p.Nc * p.batch) / 4.64e6;   // the tensors' way from and to memory
+    return norm({us, mem}, 6.0);
+}
+
+// Rough relative time of one variant, about 45 to the microsecond.  lds: bytes of a workgroup of a tile kernel.
+double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds)
+{
+    if (k.launch_direct && k.stream <= 1 && k.dtype == ALT_BF16) {
+        // (a small factor: wherever one of these kernels applies it has been faster than the register-staged ones, whose estimate below
+        // knows little of slices and short sums: at half, 4 x 128 x 5 x 5, 3x3, went there in 36 slices and took 15.6 us, not 7.8.
+        // A 1x1 filter leaves a patch nothing to reuse: the streaming kernels run it without staging one first.)
+        return 0.05 * 45.0 * (k.stream == 0 && p.R * p.S == 1 ? 1.5 : 1.0) * tile_estimate_us(pb, k, p, lds);
+    }
     if (k.launch_direct && k.stream == 1) {
-        // Streaming kernel: all K groups take one K step each in the larger of their matrix-core
-        // time (at the efficiency these kernels reach: less with fewer than eight waves) and the
-        // time to bring their operand tiles into LDS (about 45 bytes per clock per CU), plus a
-        // fixed part; a workgroup adds a prologue and an epilogue; as many workgroups share a CU
-        // as their LDS allows.  Clocks at 2.2 GHz, scaled to the unit of the estimate below
-        // (about 45 per microsecond).
         const int waves = k.kw * k.wgm * k.wgn;
-        const double es = k.dtype == ALT_BF16 ? 2.0 : 4.0;
-        const double lds = (double)k.kw * (k.prefetch + 1) * (k.BM + k.BN) * k.BK * es;
-        const double stage = (double)k.kw * k.BM * (k.BN + 8.0 * k.wgn) * 4;
-        const int per_cu = std::max(1, (int)(160.0 * 1024 / std::max(lds, stage)));
+        const double es = 4.0;
+        const int per_cu = std::max(1, (int)(160.0 * 1024 / lds));
         const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
-        const double rounds = std::ceil(blocks / (256.0 * per_cu));
         const double steps = k.taps ? std::ceil((double)p.ksteps_per_split / k.kw) : (double)p.C / p.splitk / k.kw / k.BK;
         // (a split's partial sums are written, fetched and added by whoever comes last: fitted over products of 37 to 10000 rows,
         // 1 us a MB of them; 1536 x 512 x 2048 in eight slices of 256x128 tiles took 38 us, unsplit on 64x64 tiles 10.8)
         const double partial_us = p.splitk > 1 ? 1e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0 : 0.0;
-        if (k.dtype == ALT_F32) {
-            // fp32: matrix instructions do a sixteenth of the products per clock, so co-resident workgroups share them; a
-            // step costs 280 clocks beside its products, a workgroup 7200, a split 0.8 us and 0.9 us a MB (microseconds, within 10 %
-            // of 1000 measured launches).  The factor brings them to the estimate of the register-staged kernels, which take two
-            // to six times what it says, in steps of 512 tiles.  Of 122 convolutions and products of 5 to 200 us the choice is 2.5 %
-            // from the fastest variant on average; the five 3x3 and 1x1 layers stay on these kernels from batch 1 to 40, where the
-            // others are at most 5 % faster (64 channels at batch 12, 36.4 us against 38.4) and up to 40 % slower.  At 0.2 batches 16
-            // to 23 of two of them go to the others and lose 5 to 16 %.  A step that spans taps (fewer channels than a step is
-            // deep) costs more: 28 x 16 x 36 x 36 to 424 channels, 5x5, takes 140 us here and 122 on the others.
-            const double need = std::max((double)k.kw * k.BM * k.BN * k.BK / 128.0 * (waves >= 8 ? 1.11 : 1.07) * std::max(1.0, 4.0 / waves),
-                                         (double)k.kw * (k.BM + k.BN) * k.BK * es / 33.6);
-            auto round_clk = [&](double n) { return steps * std::max(need + 280.0, n * need) + 7200.0; };
-            const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
-            const double us = (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0 + (p.splitk > 1 ? 0.8 + 0.9 * partial_us : 0.0);
-            // (Batches take no slices here.  A handful of tiles of a long sum leaves the chip idle, and the register-staged kernels in
-            // slices take 0.5 to 1.06 times as long: 2 x 4 x 28 x 6360 32 us against 61, 11 x 2 x 8 x 5556 57 and 53; with 22 tiles it
-            // is 50 and 39.  The estimate of those that gather is an order too high, hence the factor.)
-            const double idle = p.batch > 1 && blocks <= 12.0 && p.C >= 2000 ? 12.0 : 1.0;
-            return (p.C < 32 && p.R * p.S > 1 ? 0.2 : 0.18) * idle * us * 45.0;
-        }
-        const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 16384.0 * 8.0 * (waves >= 8 ? 1.7 : 2.0);
-        const double bytes = (double)k.kw * (k.BM + k.BN) * k.BK * es / 45.0;
-        const double clk = rounds * (steps * (std::max(mfma, bytes) + 120.0) + 6000.0);
-        // (halved like the direct kernels' estimate below: wherever one of these kernels applies it
-        // has beaten the implicit-GEMM kernels, whose estimate is optimistic)
-        // The kernels over filter taps fetch a pixel once per tap, so where the patch-resident kernels cover the problem (bf16,
-        // channels a multiple of 64, more than one tap) or the plain streaming ones (one tap, stride 1), those come first.  At other
-        // strides one tap leaves them to the register-staged kernels (17 x 512 x 17 x 17 to 244 channels, 1x1 at stride 2: 17 us
-        // on those, 5.7 here).
-        const bool plain = p.R * p.S == 1 && p.stride_h == 1 && p.stride_w == 1 && p.pad_h == 0 && p.pad_w == 0;
-        const double taps = k.taps && p.C % 64 == 0 && (plain || p.R * p.S > 1) ? 3.0 : 1.0;
-        // Plain kernels with steps of 32, B as NK, where steps of 64 do not divide the sum: they do with a ring of eight stages what
-        // the estimate expects of steps twice as deep (3220 x 208 x 800 takes 5.4 us on them and 7.8 on the tap kernels, 7 x 1865 x
-        // 584 x 1696 44 and 77; as KN they have large tiles only, and the estimate holds).
-        const double narrow = !k.taps && !k.bt && p.C % 64 ? 0.7 : 1.0;
-        // One tap leaves the patch-resident kernel nothing to reuse, and its and the implicit-GEMM kernels' estimates know little
-        // of what many slices cost: 37 x 768 x 3072 took 21.6 us on the former in 24 slices, 19.9 here in 24, 7.3 in four;
-        // 200 x 1024 x 1024 17.0 and 7.1; 810 x 384 x 1536 17.7 and 7.1. No product of the 36 compared was faster elsewhere.
-        const double lead = p.R * p.S == 1 ? 0.25 : 0.5;
-        return taps * narrow * lead * (clk / 2200.0 * 45.0 + (p.splitk > 1 ? 140.0 + 45.0 * partial_us : 0.0));
+        // fp32: matrix instructions do a sixteenth of the products per clock, so co-resident workgroups share them; a
+        // step costs 280 clocks beside its products, a workgroup 7200, a split 0.8 us and 0.9 us a MB (microseconds, within 10 %
+        // of 1000 measured launches).  The factor brings them to the estimate of the register-staged kernels, which take two
+        // to six times what it says, in steps of 512 tiles.  Of 122 convolutions and products of 5 to 200 us the choice is 2.5 %
+        // from the fastest variant on average; the five 3x3 and 1x1 layers stay on these kernels from batch 1 to 40, where the
+        // others are at most 5 % faster (64 channels at batch 12, 36.4 us against 38.4) and up to 40 % slower.  At 0.2 batches 16
+        // to 23 of two of them go to the others and lose 5 to 16 %.  A step that spans taps (fewer channels than a step is
+        // deep) costs more: 28 x 16 x 36 x 36 to 424 channels, 5x5, takes 140 us here and 122 on the others.
+        const double need = std::max((double)k.kw * k.BM * k.BN * k.BK / 128.0 * (waves >= 8 ? 1.11 : 1.07) * std::max(1.0, 4.0 / waves),
+                                     (double)k.kw * (k.BM + k.BN) * k.BK * es / 33.6);
+        auto round_clk = [&](double n) { return steps * std::max(need + 280.0, n * need) + 7200.0; };
+        const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
+        const double us = (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0 + (p.splitk > 1 ? 0.8 + 0.9 * partial_us : 0.0);
+        // (Batches take no slices here.  A handful of tiles of a long sum leaves the chip idle, and the register-staged kernels in
+        // slices take 0.5 to 1.06 times as long: 2 x 4 x 28 x 6360 32 us against 61, 11 x 2 x 8 x 5556 57 and 53; with 22 tiles it
+        // is 50 and 39.  The estimate of those that gather is an order too high, hence the factor.)
+        const double idle = p.batch > 1 && blocks <= 12.0 && p.C >= 2000 ? 12.0 : 1.0;
+        return (p.C < 32 && p.R * p.S > 1 ? 0.2 : 0.18) * idle * us * 45.0;
     }
     if (k.launch_direct && k.stream == 2) {
         // Channel-planar kernel: a workgroup converts its patch on the way in (about 20 bytes per clock
@@ -273,10 +294,11 @@ int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters)
     for (int ki = 0; ki < (int)tab.size(); ++ki)
         for (int si = 0; si < kNumSplits; ++si) {
             IgemmParams p;
+            size_t lds = 0;
             if (!counters && tab[ki].launch_direct && kSplits[si] > 1) continue;
-            if (!igemm_applicable(pb, tab[ki], kSplits[si], &p, nullptr)) continue;
+            if (!igemm_applicable(pb, tab[ki], kSplits[si], &p, nullptr, &lds)) continue;
             if (igemm_workspace(pb, kSplits[si]) > ws_limit) continue;
-            const double est = igemm_estimate(pb, tab[ki], p);
+            const double est = igemm_estimate(pb, tab[ki], p, lds);
             if (est < best) { best = est; best_v = ki * kNumSplits + si; }
         }
     return best_v;

@@ -128,9 +128,10 @@ std::vector<Trial> ordered_variants(const Problem &pb, size_t ws_limit)
     for (int ki = 0; ki < (int)tab.size(); ++ki)
         for (int si = 0; si < ns; ++si) {
             IgemmParams p;
-            if (!igemm_applicable(pb, tab[ki], kSplitFactors[si], &p, nullptr)) continue;
+            size_t lds = 0;
+            if (!igemm_applicable(pb, tab[ki], kSplitFactors[si], &p, nullptr, &lds)) continue;
             if (igemm_workspace(pb, kSplitFactors[si]) > ws_limit) continue;
-            v.push_back({ki * ns + si, igemm_estimate(pb, tab[ki], p)});
+            v.push_back({ki * ns + si, igemm_estimate(pb, tab[ki], p, lds)});
         }
     std::sort(v.begin(), v.end(), [](const Trial &a, const Trial &b) { return a.est < b.est; });
     return v;

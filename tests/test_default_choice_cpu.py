@@ -43,3 +43,11 @@ def test_single_precision_layers_do_not_change_kernels_with_the_batch(h, C, H, K
 def test_single_precision_batches_of_few_tiles_run_in_slices(h, M, N, K, batch, taps):
     name = gemm(h, M, N, K, "NK", batch, alt.F32)
     assert ("_rtaps_" in name) == taps and (taps or not name.endswith("_k1"))
+
+
+@pytest.mark.parametrize("N,C,H,K,family", [
+    (16, 64, 56, 64, "_direct_"), (16, 128, 28, 128, "_direct_"), (16, 512, 7, 512, "_direct_"), (1, 256, 14, 256, "_direct_"),
+    (256, 256, 14, 256, "taps_"), (256, 512, 7, 512, "taps_"), (4, 128, 5, 128, "_direct_")])
+def test_layers_run_unsliced(h, N, C, H, K, family):
+    name = conv(h, N, C, H, K, 3)
+    assert family in name and name.endswith("_k1")
