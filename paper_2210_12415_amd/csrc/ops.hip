@@ -169,12 +169,8 @@ static double tile_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), std::floor((acc <= 32 ? 16.0 : 8.0) / waves)));
     const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
     const double steps = k.taps ? std::ceil((double)p.ksteps_per_split / k.kw) : (double)p.R * p.S * p.C / p.splitk / k.kw / k.BK;
-    // (what bounds a step overlaps with the rest of it only in part: the parts are added in a norm between sum and maximum)
-    auto norm = [](std::initializer_list<double> parts, double e) {
-        double sum = 0;
-        for (double v : parts) sum += std::pow(v, e);
-        return std::pow(sum, 1.0 / e);
-    };
+    // (what bounds a step overlaps with the rest of it only in part: the parts' cubes are added, between sum and maximum)
+    auto cube = [](double v) { return v * v * v; };
     const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 2048.0;                  // clocks of a step's products on four SIMDs
     const double in = (double)k.kw * ((patch ? 0 : k.BM) + k.BN) * k.BK * 2 / 46.6;   // ... of its operands' way into LDS
     const double out = waves * (wtm + wtn) * k.BK * 2 / 400.0;                        // ... and out of it
@@ -189,7 +185,8 @@ static double tile_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     const double begin = !patch && k.BK == 32 ? 15.0 : 0.0;
     auto round_clk = [&](double n) {
         const double rate = acc >= 128 ? 1.0 : waves * n >= 8 ? 1.34 : 1.04;
-        const double step = norm({n * mfma * rate * std::max(1.0, 4.0 / (waves * n)), n * in, n * out, alone}, 3.11) + begin;
+        const double products = n * mfma * rate * std::max(1.0, 4.0 / (waves * n));
+        const double step = std::cbrt(cube(products) + cube(n * in) + cube(n * out) + cube(alone)) + begin;
         return steps * step + ends + n * (k.BM * k.BN / 6.67 + np * p.C / p.splitk * 2 / 83.0);
     };
     const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
@@ -198,7 +195,7 @@ static double tile_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     if (p.splitk > 1) us += 1.11 + 0.47 * p.splitk + 0.67e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0;
     const int entries = pb.v.T ? 1 : p.batch;
     const double mem = 1.18 + 2.0 * ((double)(pb.x_elems + pb.w_elems) * entries + (double)p.M * p.Nc * p.batch) / 4.64e6;   // the tensors' way from and to memory
-    return norm({us, mem}, 6.0);
+    return std::sqrt(std::cbrt(cube(us * us) + cube(mem * mem)));
 }
 
 // Rough relative time of one variant, about 45 to the microsecond.  lds: bytes of a workgroup of a tile kernel.
