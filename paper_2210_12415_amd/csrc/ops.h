@@ -46,9 +46,16 @@ size_t igemm_workspace(const Problem &pb, int splitk);
 double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds);
 // (counters = false: among the variants that need no arrival counters)
 int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters = true);
-// (*no_counters: the variant's slices need arrival counters and no set of them is free for the stream)
+// A tile kernel's launch worked out for one problem; the operands' addresses are filled in by every call.
+struct TileLaunch {
+    int variant = -1;                      // -1: nothing yet
+    size_t lds = 0;
+    DconvParams d;
+};
+// (*no_counters: the variant's slices need arrival counters and no set of them is free for the stream; kept: where the same
+// problem's launch is kept between calls)
 alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *workspace, size_t ws_bytes,
-                       hipStream_t st, bool *no_counters = nullptr);
+                       hipStream_t st, bool *no_counters = nullptr, TileLaunch *kept = nullptr);
 
 // dconv.hip
 bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes,

@@ -302,7 +302,7 @@ int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters)
 }
 
 alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *workspace, size_t ws_bytes,
-                       hipStream_t st, bool *no_counters)
+                       hipStream_t st, bool *no_counters, TileLaunch *kept)
 {
     if (!h->has_gpu) return fail(h, ALT_HIP_ERROR, "no GPU device available");
     const auto &tab = igemm_table();
@@ -310,19 +310,20 @@ alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *wor
         return fail(h, ALT_INVALID_ARG, "variant %d out of range", variant);
     const IgemmLaunch &k = tab[variant / kNumSplits];
     const int splitk = kSplits[variant % kNumSplits];
-    IgemmParams p;
-    std::string why;
-    if (!igemm_applicable(pb, k, splitk, &p, &why))
-        return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
     const size_t need = igemm_workspace(pb, splitk);
+    std::string why;
     if (k.launch_direct) {
+        TileLaunch once;
+        TileLaunch &t = kept ? *kept : once;
+        if (t.variant != variant) {
+            if (!igemm_applicable(pb, k, splitk, nullptr, &why) || !dconv_setup(pb, k, splitk, &t.d, &t.lds, &why))
+                return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
+            t.variant = variant;
+        }
         if (need > 0 && (!workspace || ws_bytes < need))
             return fail(h, ALT_WORKSPACE_TOO_SMALL, "split-K needs %zu workspace bytes, got %zu", need, ws_bytes);
-        DconvParams dp;
-        size_t lds = 0;
-        if (!dconv_setup(pb, k, splitk, &dp, &lds, &why))
-            return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
-        hipError_t e = dconv_run(k, dp, lds, (float *)workspace, st);
+        t.d.x = pb.p.x; t.d.w = pb.p.w; t.d.bias = pb.p.bias; t.d.y = pb.p.y; t.d.addend = pb.p.addend;
+        hipError_t e = dconv_run(k, t.d, t.lds, (float *)workspace, st);
         if (e == hipErrorNotReady && no_counters) *no_counters = true;
         if (e == hipErrorNotReady)
             return fail(h, ALT_UNSUPPORTED, "%s: no split-K counter set is free for this stream (%d streams hold one; sets "
@@ -330,6 +331,9 @@ alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *wor
         if (e != hipSuccess) return fail(h, ALT_HIP_ERROR, "launch of %s failed: %s", k.name, hipGetErrorString(e));
         return ALT_OK;
     }
+    IgemmParams p;
+    if (!igemm_applicable(pb, k, splitk, &p, &why))
+        return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
     if (need > 0) {
         if (!workspace || ws_bytes < need)
             return fail(h, ALT_WORKSPACE_TOO_SMALL, "split-K needs %zu workspace bytes, got %zu", need, ws_bytes);
@@ -510,6 +514,7 @@ struct MemoEntry {
     size_t ws_limit;
     Problem pb;
     int variant;
+    TileLaunch tile;      // a tile kernel's launch, made by the first call
 };
 
 }  // extern "C"
@@ -584,10 +589,10 @@ static int pick_variant(alt_handle_t h, const Problem &pb, int requested, const 
 // Runs variant v.  Where it was the library's own choice and no set of arrival counters is free for its slices (more streams than
 // sets, under capture), the best variant that needs none takes its place.
 static alt_status_t run_chosen(alt_handle_t h, const Problem &pb, int v, bool own_choice, void *workspace, size_t ws_bytes,
-                               hipStream_t st)
+                               hipStream_t st, TileLaunch *kept = nullptr)
 {
     bool no_counters = false;
-    const alt_status_t s = igemm_run(h, pb, v, workspace, ws_bytes, st, &no_counters);
+    const alt_status_t s = igemm_run(h, pb, v, workspace, ws_bytes, st, &no_counters, kept);
     if (!no_counters || !own_choice) return s;
     v = igemm_default_variant(pb, workspace ? ws_bytes : 0, false);
     return v < 0 ? s : igemm_run(h, pb, v, workspace, ws_bytes, st);
@@ -603,7 +608,8 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
     const unsigned sig = align_sig(x, w, bias, y) | (addend ? 1u << 17 : 0u) | ((unsigned)((uintptr_t)addend & 15) << 18);
     if (MemoEntry *m = memo_find(h, d, sizeof *d, sig, ws_limit)) {
         m->pb.p.x = x; m->pb.p.w = w; m->pb.p.bias = bias; m->pb.p.y = y; m->pb.p.addend = addend;
-        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
+        if (m->pb.depthwise) return depthwise_run(h, m->pb, d->N, d->C, (hipStream_t)stream);
+        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream, &m->tile);
     }
     Problem pb;
     alt_status_t s = conv_problem(h, d, x, w, bias, y, &pb);
@@ -613,7 +619,10 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
         if ((uintptr_t)addend % 16) return fail(h, ALT_INVALID_ARG, "%s: the addend must be 16-byte aligned", who);
         pb.p.addend = addend;
     }
-    if (pb.depthwise) return depthwise_run(h, pb, d->N, d->C, (hipStream_t)stream);
+    if (pb.depthwise) {
+        memo_store(h, d, sizeof *d, sig, ws_limit, pb, -1);
+        return depthwise_run(h, pb, d->N, d->C, (hipStream_t)stream);
+    }
     // (a tuned choice for the same problem without the sum is a good one with it, if it applies)
     int v = pick_variant(h, pb, d->variant, d->variant >= 0 ? std::string() : conv_key(h, d), ws_limit);
     if (v < 0) return fail(h, ALT_UNSUPPORTED, "%s: no kernel variant applies", who);
@@ -638,8 +647,10 @@ alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const vo
     Problem pb;
     int v = -1;
     if (MemoEntry *m = memo_find(h, &c, sizeof c, sig, ws_limit)) {
-        pb = m->pb;
-        v = m->variant;
+        if (m->variant < 0) return ALT_OK;
+        *done = true;
+        m->pb.p.x = x; m->pb.p.w = w; m->pb.p.bias = bias; m->pb.p.y = y;
+        return run_chosen(h, m->pb, m->variant, true, workspace, ws_bytes, st, &m->tile);
     } else {
         BoundLayout bx, by;
         Dim2 dx[4], dy[4];
@@ -819,7 +830,7 @@ alt_status_t alt_gemm(alt_handle_t h, const alt_gemm_desc_t *d, const void *A, c
     const unsigned sig = align_sig(A, B, nullptr, C);
     if (MemoEntry *m = memo_find(h, d, sizeof *d, sig, ws_limit)) {
         m->pb.p.x = A; m->pb.p.w = B; m->pb.p.y = C;
-        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream);
+        return run_chosen(h, m->pb, m->variant, d->variant < 0, workspace, ws_bytes, (hipStream_t)stream, &m->tile);
     }
     Problem pb;
     alt_status_t s = gemm_problem(h, d, A, B, C, &pb);

@@ -241,3 +241,37 @@ def test_product_default_choice(h, M, N, K, lay):
     h.gemm(d, dev(A), dev(B if lay == "KN" else np.ascontiguousarray(B.T)), C, workspace=dev(np.zeros(max(1, ws_bytes // 4), np.float32)),
            ws_bytes=ws_bytes)
     assert canary_ok(whole, M * N) and np.array_equal(host(C, np.float32).reshape(M, N), oracle.gemm(A, B))
+
+
+@pytest.mark.parametrize("kind", ["tile", "sliced", "depthwise", "product", "volume"])
+def test_later_calls_use_their_own_buffers(h, kind):
+    """A launch kept from the first call takes its operands' addresses, stream and workspace from the call."""
+    lay = dict(x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC", out_dtype=alt.BF16)
+    if kind == "product":
+        d, call, size, sizes = alt.gemm_desc(100, 96, 128, out_dtype=alt.BF16, b_layout="KN->NK"), h.gemm, h.gemm_workspace_size, (12800, 12288, 9600)
+    elif kind == "volume":
+        d, call, size = alt.conv3d_desc(1, 16, 3, 6, 6, 16, 3, 3, 3, pad=1, **lay), h.conv3d, h.conv3d_workspace_size
+        sizes = (1728, 6912, 1728)
+    else:
+        C, H, g = (64, 9, 64) if kind == "depthwise" else (64, 9, 1)
+        d = alt.conv_desc(2, C, H, H, C, 3, 3, pad=1, groups=g, **lay)
+        if kind == "sliced":
+            names = applicable_variants(h, d)
+            d.variant = next(v for v, n in names if "_64x64x64_taps_" in n and n.endswith("_k3"))
+        call, size, sizes = h.conv2d, h.conv2d_workspace_size, (2 * H * H * C, C * C * 9 // g, 2 * H * H * C)
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    outs = []
+    for s in streams:
+        gen = torch.Generator(device="cuda").manual_seed(len(outs))
+        x, w = (torch.randint(-4, 5, (n,), generator=gen, device="cuda").to(torch.bfloat16) for n in sizes[:2])
+        nb = size(d)
+        for _ in range(2):
+            y, ws = torch.zeros(sizes[2], dtype=torch.bfloat16, device="cuda"), torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()
+            call(d, x, w, y, workspace=ws, ws_bytes=nb, stream=s)
+            torch.cuda.synchronize()
+            outs.append(y)
+        fresh, y = alt.Handle(), torch.zeros_like(y)
+        getattr(fresh, call.__name__)(d, x, w, y, workspace=ws, ws_bytes=nb)
+        torch.cuda.synchronize()
+        assert torch.equal(outs[-1], y) and torch.equal(outs[-2], y) and bool(y.any())
