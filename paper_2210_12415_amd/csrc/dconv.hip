@@ -334,15 +334,25 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     const bool y_nhwc = dense(p.yk, K, 1) && dense(p.yw, OW, K) && dense(p.yh, OH, OW * K) && dense(p.yn, N, OH * OW * K);
     if (!y_nchw && !y_nhwc) return no("output is neither dense NCHW nor dense NHWC");
     if (!y_nchw && (K % 8 || (uintptr_t)p.y % 16)) return no("NHWC output is stored eight channels at a time");
-    if (C % 64) return no("channels must be a multiple of 64");
+    if (C % 8) return no("channels must be a multiple of eight");
+    if (!k.ragged && C % 64) return no("channels are no multiple of 64");
     if (H * W < 8) return no("images of fewer than eight pixels");
     if ((uintptr_t)p.w % 16 || (uintptr_t)p.x % 2) return no("weights are not 16-byte aligned");
     if ((p.epilogue & ALT_EPI_BIAS) && (uintptr_t)p.bias % 4) return no("bias is not aligned");
     if (pb.x_elems * 2 >= 0x7fffffff || pb.w_elems * 2 >= 0x7fffffff || p.y_bytes == 0 || (int64_t)p.M * K * 4 >= 0x7fffffff)
         return no("operand of 2 GiB or more");
     if (N * H * W > 0x7fffffff) return no("input too large for 32-bit pixel indices");
-    const size_t lds = dplanar_lds_bytes(k.BM, k.BN, k.kw, (int)(R * S), (int)C,
-                                         dconv_patch_pixels(k.BM, p.M, p.H, p.W, p.OH, p.OW, p.R, p.S, p.pad_h, p.pad_w, st_, p.dil_h));
+    // (as few slabs of channels as fit, about equal: at each slab's end the next one's patch is waited for)
+    const size_t np = dconv_patch_pixels(k.BM, p.M, p.H, p.W, p.OH, p.OW, p.R, p.S, p.pad_h, p.pad_w, st_, p.dil_h);
+    const int64_t nsb = (C + 63) / 64;
+    int64_t slab = 0;
+    size_t lds = 0;
+    for (int64_t n = 1; n <= nsb; ++n) {
+        slab = (n == 1 ? nsb : (nsb + 2 * n - 1) / (2 * n) * 2) * 64;      // (an even number: the kernel walks them in pairs)
+        lds = dplanar_lds_bytes(k.BM, k.BN, k.kw, (int)(R * S), (int)slab, np);
+        if (lds <= 160 * 1024 || !k.ragged) break;
+    }
+    if (k.ragged && C % 64 == 0 && slab == C && lds <= 160 * 1024) return no("channels fit LDS in whole steps");
     if (lds > 160 * 1024) return no("patch and weight stages do not fit LDS");
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;
     if ((int64_t)tiles_m * tiles_n > 0x7fffffff) return no("grid too large");
@@ -352,7 +362,7 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     std::memset(&d, 0, sizeof d);
     d.x = p.x; d.w = p.w; d.bias = p.bias; d.y = p.y;
     d.x_bytes = p.x_bytes; d.w_bytes = p.w_bytes; d.y_bytes = p.y_bytes;
-    d.M = p.M; d.Nc = p.Nc; d.C = p.C; d.Cs = p.C;
+    d.M = p.M; d.Nc = p.Nc; d.C = p.C; d.Cs = (int32_t)slab;
     d.H = p.H; d.W = p.W; d.R = p.R; d.S = p.S; d.pad_h = p.pad_h; d.pad_w = p.pad_w;
     d.tiles_m = tiles_m; d.tiles_n = tiles_n; d.splitk = 1;
     d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | (p.out_bf16 ? kDconvOutBf16 : 0) | (y_nchw ? 0 : kPlanarOutNhwc);

@@ -26,13 +26,15 @@
                                     &dstream_launch<BM, BN, WGM, WGN, KW, NS, BK>, WGM, WGN, KW, 1}),            \
          true)
 
-// channel-planar kernel (dplanar.h): BM x BN tile, KW K groups of WGM x WGN waves
-#define ALT_DPLANAR(BM, BN, WGM, WGN, KW)                                                                        \
-    const bool reg_dplanar_##BM##x##BN##_w##WGM##x##WGN##x##KW =                                                 \
-        (igemm_register(IgemmLaunch{"bf16_" #BM "x" #BN "x64_planar_w" #WGM "x" #WGN "x" #KW, ALT_BF16, BM, BN,   \
+// channel-planar kernel (dplanar.h): BM x BN tile, KW K groups of WGM x WGN waves; named rplanar for channels that are no multiple
+// of 64 or more than LDS holds at once
+#define ALT_DPLANAR_(BM, BN, WGM, WGN, KW, RAGGED, MNAME)                                                        \
+    const bool reg_d##MNAME##_##BM##x##BN##_w##WGM##x##WGN##x##KW =                                              \
+        (igemm_register(IgemmLaunch{"bf16_" #BM "x" #BN "x64_" #MNAME "_w" #WGM "x" #WGN "x" #KW, ALT_BF16, BM, BN, \
                                     64, LOAD_VEC, LOAD_VEC, 0, 0, 0, nullptr,                                    \
-                                    &dplanar_launch<BM, BN, WGM, WGN, KW>, WGM, WGN, KW, 2}),                    \
+                                    &dplanar_launch<BM, BN, WGM, WGN, KW>, WGM, WGN, KW, 2, 0, 0, RAGGED}),      \
          true)
+#define ALT_DPLANAR(BM, BN, WGM, WGN, KW) ALT_DPLANAR_(BM, BN, WGM, WGN, KW, 0, planar); ALT_DPLANAR_(BM, BN, WGM, WGN, KW, 1, rplanar)
 
 // the streaming kernel for B stored [K][N] (row-major): the same tiles, B read through LDS transpose reads
 #define ALT_DSTREAM_KN(BM, BN, WGM, WGN, KW, NS, BK)                                                             \

@@ -13,8 +13,9 @@
 //    [pixel][channel], exactly what dconv.h holds;
 //  * weights: a filter row is contiguous over (channel, tap), so the 64 channels x all taps
 //    of a "super-step" are read as one contiguous run per output channel and scattered
-//    element by element into one [row][64 channels] stage per tap; the loads of the next
-//    super-step are in registers while the present one computes;
+//    element by element into one [row][64 channels] stage per tap; the loads of the next two
+//    super-steps are in registers while the present one computes (of one only: 6 % slower over
+//    layers of 32 to 1024 channels; coalesced and turned over in LDS first: 5 to 10 % slower);
 //  * output: the accumulators (pixels along the MFMA rows, so a lane holds four consecutive
 //    pixels of one channel) go through LDS as [channel][pixel] and are stored with
 //    consecutive lanes on consecutive pixels of a plane.
@@ -26,8 +27,15 @@
 // layout for an NHWC consumer by itself, which is how layout propagation (Section 4.2) lets a
 // chain that starts in NCHW do without a conversion operator.
 //
+// The last super-step is filled up with zero channels, and the patch holds the channels in
+// slabs (p.Cs each, one after the other) where all of them do not fit LDS.
+//
+// (Channels that are no multiple of 64 ran on the element-gather kernels before: 26 x 104 x
+// 60 x 60, 3x3, took 567 us there and 67 here, 9 x 40 x 34 x 34 35 and 8.0; so did patches larger than
+// LDS: 26 x 832 x 8 x 8, 232 and 70.  Two 8-plane sets of the patch in flight per wave: spills, 20-36 % slower.)
+//
 // Covers: bf16, 1x1 and 3x3 filters, stride 1 or 2, any dilation, padding from none to
-// same-size, channels a multiple of 64, images of at least eight pixels, fp32 or bf16
+// same-size, channels a multiple of eight, images of at least eight pixels, fp32 or bf16
 // output, bias and ReLU.  No split-K and no fused addend.
 #pragma once
 
@@ -57,6 +65,7 @@ constexpr int kPlanarWP = 144;                   // bytes of a weight row in LDS
 // LDS bytes of one tap's weight stage: BN rows, then 16 bytes that skew consecutive taps over the banks.
 constexpr int planar_stage_bytes(int BN) { return BN * kPlanarWP + 16; }
 
+// (C: channels of a slab)
 inline size_t dplanar_lds_bytes(int BM, int BN, int kw, int taps, int C, size_t np)
 {
     const size_t npr = (np + 7) / 8 * 8;
@@ -96,7 +105,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     }
     const int m0 = mt * BM, n0 = nt * BN;
     const uint16_t *xg = (const uint16_t *)p.x;
-    const uint16_t *wg = (const uint16_t *)p.w;
     const int HW = p.H * p.W;
 
     // ---- weights of super-step sb (channels 64*sb ..): global -> registers -> the taps' stages ----------
@@ -105,21 +113,24 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     // writes them as one 16-byte chunk of that tap's stage.
     static_assert(NT >= BN * 8, "one thread per (row, eight channels)");
     const int w_row = t >> 3, w_cg = t & 7;
-    const bool w_live = t < BN * 8 && n0 + w_row < p.Nc;
-    uint4 wreg[RS];
-    auto load_w = [&](int sb) {
-        const uint16_t *src = wg + ((size_t)(n0 + w_row) * p.C + (size_t)sb * 64 + w_cg * 8) * RS;
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)p.w, 0, (int)p.w_bytes, 0x00020000);
+    const uint32_t w_voff = t < BN * 8 && n0 + w_row < p.Nc ? (uint32_t)((n0 + w_row) * p.C + w_cg * 8) * (uint32_t)(RS * 2) : kOutOfRange;
+    u32x4_t wreg[2][RS];
+    auto load_w = [&](auto SET, int sb) {
+        constexpr int set = decltype(SET)::value;
+        const uint32_t voff = sb * 64 + w_cg * 8 < p.C ? w_voff : kOutOfRange;   // (behind the last channel: zeros)
 #pragma unroll
-        for (int i = 0; i < RS; ++i) {
-            const uint4 v = *(const uint4 *)(w_live ? src + i * 8 : wg);
-            wreg[i] = w_live ? v : make_uint4(0, 0, 0, 0);
-        }
+        for (int i = 0; i < RS; ++i)
+            wreg[set][i] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, (int)voff, sb * (64 * RS * 2) + i * 16, 0);
     };
-    auto scatter_w = [&]() {
+    auto scatter_w = [&](auto SET) {
+        constexpr int set = decltype(SET)::value;
         if (t < BN * 8) {
             uint32_t d[RS * 4];
 #pragma unroll
-            for (int i = 0; i < RS; ++i) { d[4 * i] = wreg[i].x; d[4 * i + 1] = wreg[i].y; d[4 * i + 2] = wreg[i].z; d[4 * i + 3] = wreg[i].w; }
+            for (int i = 0; i < RS; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) d[4 * i + k] = wreg[set][i][k];
 #pragma unroll
             for (int tap = 0; tap < RS; ++tap) {
                 uint32_t o[4];
@@ -133,9 +144,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
             }
         }
     };
-    load_w(0);
+    const std::integral_constant<int, 0> set0{};
+    const std::integral_constant<int, 1> set1{};
+    const int nsb = (p.C + 63) >> 6;
+    load_w(set0, 0);
+    if (nsb > 1) load_w(set1, 1);
 
-    // ---- the patch: input pixels [a0 - halo, a0 - halo + np), all C channels, as [pixel][channel] ----------
+    // ---- the patch: input pixels [a0 - halo, a0 - halo + np), a slab's Cs channels, as [pixel][channel] ----------
     const int halo = p.pad_h * p.W + p.pad_w;
     const int halo_hi = ((p.R - 1) * p.dil - p.pad_h) * p.W + ((p.S - 1) * p.dil - p.pad_w);
     const int ohw = p.OH * p.OW;
@@ -147,13 +162,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     const int a0 = anchor(m0);
     const int np = anchor(min(m0 + BM, p.M) - 1) - a0 + 1 + halo + halo_hi;
     const int npr = (np + 7) & ~7;                         // whole blocks of eight pixels
-    const int pitch_b = p.C * 2 + 16;
+    const int pitch_b = p.Cs * 2 + 16;
     char *patch = smem + RS * WST;
     // behind the patch, at a multiple of 256 bytes: the zero area that taps outside the image read, each lane at
     // the offset modulo 256 (i.e. on the banks) of the pixel it would have read (see dconv.h)
     const uint32_t patch_a = (uint32_t)(uintptr_t)patch;
     const uint32_t zero0 = (patch_a + (uint32_t)(npr * pitch_b) + 255u) & ~255u;
-    {
+    auto load_patch = [&](int c0) {                        // channels c0 .. c0 + Cs - 1 (behind the last channel: zeros)
         // Work items: (pixel block of eight, channel block of eight), one per lane: the lane loads its eight
         // planes' runs, transposes them 8x8 in registers and writes eight 16-byte channel chunks.  A set of 64
         // items is eight pixel blocks (lane % 8) x eight channel blocks (lane / 8): its loads cover 128
@@ -161,11 +176,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
         // least a 16-byte-per-lane write takes.
         const int g0 = a0 - halo;
         const int npb = npr >> 3;                          // pixel blocks
-        const int npbg = (npb + 7) >> 3;                   // sets along the pixels; C / 64 along the channels
-        const int nitems = npbg * (p.C >> 6) * 64;
+        const int npbg = (npb + 7) >> 3;                   // sets along the pixels; Cs / 64 along the channels
+        const int nitems = npbg * (p.Cs >> 6) * 64;
         struct Item {
             int px0, cb, q;
-            bool live, inside, straddle;
+            bool live, real, inside, straddle;             // real: channels of the tensor
             size_t e0;
         };
         auto item_of = [&](int first) {
@@ -178,12 +193,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
             const int cb = it.cb;
             const int g = g0 + it.px0;                     // first input pixel of the block
             it.live = first < nitems && pb < npb;
-            it.inside = it.live && g >= 0 && g + 7 < p.in_px;
+            it.real = it.live && c0 + it.cb * 8 < p.C;
+            it.inside = it.real && g >= 0 && g + 7 < p.in_px;
             const int img = it.inside ? (int)div32((uint32_t)g, p.d_ihw) : 0;
             it.q = (img + 1) * HW - g;                     // pixels of the block that lie in image `img`
             it.straddle = it.inside && it.q < 8;
             // element index of pixel g + e, channel c: g + e + (img * (C - 1) + c) * HW
-            it.e0 = (size_t)g + ((size_t)img * (p.C - 1) + (size_t)cb * 8) * HW;
+            it.e0 = (size_t)g + ((size_t)img * (p.C - 1) + (size_t)(c0 + cb * 8)) * HW;
             return it;
         };
         auto item_load = [&](const Item &it, uint4 (&blk)[8], uint4 (&nx)[8], bool any_straddle) {
@@ -232,10 +248,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int ge = g + e;
-                eok[e] = it.live && ge >= 0 && ge < p.in_px;
+                eok[e] = it.real && ge >= 0 && ge < p.in_px;
                 const int gs = eok[e] ? ge : 0;
                 const int im = (int)div32((uint32_t)gs, p.d_ihw);
-                eb[e] = (size_t)gs + ((size_t)im * (p.C - 1) + (size_t)it.cb * 8) * HW;
+                eb[e] = (size_t)gs + ((size_t)im * (p.C - 1) + (size_t)(c0 + it.cb * 8)) * HW;
             }
             uint4 blk[8];
 #pragma unroll
@@ -252,7 +268,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
         };
         for (int first = wave * 64; first < nitems; first += NW * 64) {
             const Item a = item_of(first);
-            if (__builtin_amdgcn_ballot_w64(a.live && !a.inside) != 0) {
+            if (__builtin_amdgcn_ballot_w64(a.real && !a.inside) != 0) {
                 item_slow(a);
             } else {
                 const bool str_a = __builtin_amdgcn_ballot_w64(a.straddle) != 0;
@@ -261,13 +277,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
                 item_store(a, blk, nx, str_a);
             }
         }
-        for (int i = t; i < 16 + (p.C >> 3) + 2; i += NT)
-            *(uint4 *)(patch + (zero0 - patch_a) + i * 16) = make_uint4(0, 0, 0, 0);
-    }
-    scatter_w();
-    const int nsb = p.C >> 6;
-    if (nsb > 1) load_w(1);
-    __syncthreads();
+    };
+    for (int i = t; i < 16 + (p.Cs >> 3) + 2; i += NT)
+        *(uint4 *)(patch + (zero0 - patch_a) + i * 16) = make_uint4(0, 0, 0, 0);
 
     // ---- per-lane rows of the MFMA tiles -----------------------------------------------------------------
     int32_t row_px[TM], row_oh[TM], row_ow[TM];
@@ -330,7 +342,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
         static_for<TM>([&](auto ic) { lds_read16_async_at<kc * KW * 32>(af[buf][decltype(ic)::value], t_row[tap][decltype(ic)::value]); });
         static_for<TN>([&](auto jc) { lds_read16_async_at<tap * WST + kc * KW * 32>(bf[buf][decltype(jc)::value], b_rd[decltype(jc)::value]); });
     };
-    for (int sb = 0; sb < nsb; ++sb) {
+    auto compute = [&]() {
         static_for<D>([&](auto gc) { reads(gc); });
         static_for<NG>([&](auto gc) {
             constexpr int g = decltype(gc)::value, buf = g % NBUF;
@@ -344,14 +356,40 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, af[buf][i]),
                                                                         __builtin_bit_cast(bf16x8_t, bf[buf][j]), acc[i][j], 0, 0, 0);
         });
-        if (sb + 1 < nsb) {
+    };
+    auto move_on = [&](uint32_t bytes) {                   // every patch pixel's next channels
+#pragma unroll
+        for (int tap = 0; tap < RS; ++tap)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) t_row[tap][i] += bytes;
+    };
+    // weights of super-step sb (register set sb % 2) into the stages, those of sb + 2 on their way
+    auto next_w = [&](auto SET, int sb) {
+        scatter_w(SET);
+        if (sb + 2 < nsb) load_w(SET, sb + 2);
+    };
+    const int slab = p.Cs >> 6;                            // super-steps of a slab (an even number, if there are several slabs)
+    for (int s0 = 0; s0 < nsb; s0 += slab) {
+        const int end = min(s0 + slab, nsb);
+        if (s0 > 0) {
+            __syncthreads();                               // every wave is done with the patch and the stages
+            move_on(128u - (uint32_t)p.Cs * 2u);
+        }
+        load_patch(s0 << 6);
+        next_w(set0, s0);
+        __syncthreads();
+        for (int sb = s0; sb < end; sb += 2) {
+            compute();
+            if (sb + 1 >= end) break;
             __syncthreads();                               // every wave is done with this super-step's stages
-            scatter_w();
-            if (sb + 2 < nsb) load_w(sb + 2);
-#pragma unroll
-            for (int tap = 0; tap < RS; ++tap)
-#pragma unroll
-                for (int i = 0; i < TM; ++i) t_row[tap][i] += 128;             // the next 64 channels of every patch pixel
+            next_w(set1, sb + 1);
+            move_on(128);
+            __syncthreads();
+            compute();
+            if (sb + 2 >= end) break;
+            __syncthreads();
+            next_w(set0, sb + 2);
+            move_on(128);
             __syncthreads();
         }
     }

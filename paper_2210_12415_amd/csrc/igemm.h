@@ -671,6 +671,7 @@ struct IgemmLaunch {
                               // 2: channel-planar operands converted on the way into LDS (dplanar.h)
     int bt = 0;               // streaming kernel: 1 = B stored [K][N] (row-major), read through LDS transpose reads
     int taps = 0;             // streaming kernel over filter taps: kTapsUniform or kTapsRagged
+    int ragged = 0;           // channel-planar kernel: 0 = whole 64-channel steps that fit LDS at once, 1 = the other channel counts
 };
 
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, int AMODE, int BMODE, int PF>

@@ -32,6 +32,12 @@ PLANAR_CASES = [
     dict(N=3, C=64, H=12, W=11, K=64, R=3, S=3, pad=0),              # no padding: the output is smaller than the input
     dict(N=2, C=64, H=13, W=12, K=64, R=3, S=3, pad=2, dil=2),       # dilated, same-size
     dict(N=1, C=192, H=14, W=14, K=40, R=3, S=3, pad=1),             # three super-steps, K below one tile
+    dict(N=3, C=8, H=9, W=11, K=24, R=3, S=3, pad=1),                # one chunk of eight channels, the rest of the step zeros
+    dict(N=2, C=72, H=10, W=9, K=72, R=3, S=3, pad=1),               # eight channels in the second super-step
+    dict(N=2, C=120, H=8, W=5, K=40, R=1, S=1, pad=0),               # the last chunk of a row's run missing, 1x1
+    dict(N=2, C=200, H=12, W=7, K=40, R=3, S=3, pad=1, stride=2),    # four super-steps, ragged, strided
+    dict(N=1, C=1096, H=9, W=8, K=64, R=3, S=3, pad=1),              # channels in slabs, the last of them eight wide
+    dict(N=2, C=1024, H=7, W=13, K=32, R=3, S=3, pad=1),             # slabs of whole super-steps
 ]
 
 
