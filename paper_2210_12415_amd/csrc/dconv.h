@@ -75,7 +75,7 @@ struct DconvParams {
     Div32 d_slots;                // division by Cs / 8 + 1, the 16-byte slots of a patch pixel in LDS
     int32_t ncc;                  // K steps per tap: (Cs / K groups) / channels per K step
     int32_t bk;                   // channels per K step: 64, or 32 for narrow K groups
-    int32_t pad0_;
+    int32_t patch_bytes;          // bytes of a patch buffer (dslab.h)
     Div32 d_sk;                   // division by splitk
     // streaming kernel (dstream.h) only: batch entries and the byte strides between them
     int32_t batch, pad1_;
@@ -159,6 +159,20 @@ __device__ __forceinline__ void dma_load16_s(i32x4_t rsrc, uint32_t voff, uint32
                  :
                  : "s"(lds_s), "v"(voff), "s"(rsrc), "s"(soff_s)
                  : "memory");
+}
+
+// The same to LDS address `base` (wave-uniform) + AT.
+template <int AT>
+__device__ __forceinline__ void dma_load16_at(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t base)
+{
+    const uint32_t base_s = __builtin_amdgcn_readfirstlane(base);
+    const uint32_t soff_s = __builtin_amdgcn_readfirstlane(soff);
+    asm volatile("s_add_u32 m0, %0, %4\n\t"
+                 "s_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(base_s), "v"(voff), "s"(rsrc), "s"(soff_s), "n"(AT)
+                 : "memory", "scc");
 }
 
 // LDS operand read whose completion the compiler does not track: the data is

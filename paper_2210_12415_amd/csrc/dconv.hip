@@ -4,6 +4,7 @@
 #include <mutex>
 
 #include "dplanar.h"
+#include "dslab.h"
 #include "dstem.h"
 #include "dstream.h"
 #include "ops.h"
@@ -308,6 +309,50 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     return true;
 }
 
+// The same for a patch-resident kernel over slabs of channels (dslab.h): what the kernels over filter taps take, with 3x3 filters
+// or output phases of 2x2 taps at stride 1 and an output no larger than the input.
+static bool dslab_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
+{
+    auto no = [&](const char *m) { if (why) *why = m; return false; };
+    const IgemmParams &p = pb.p;
+    const Volume &v = pb.v;
+    if (pb.dtype != ALT_BF16) return no("slab kernel is bf16 only");
+    if (splitk != 1) return no("slab kernel takes no split-K");
+    const int phases = v.T ? v.sd * v.sh * v.sw : 1;
+    if (p.batch != phases) return no("slab kernel takes no batch");
+    const int kr = phases > 1 ? v.taps[1] : p.R, ks = phases > 1 ? v.taps[2] : p.S;
+    if (kr != ks || (kr != 2 && kr != 3)) return no("slab kernel is built for 2x2 and 3x3 taps");
+    if (p.stride_h != 1 || p.stride_w != 1 || (v.T && v.stride_d != 1)) return no("slab kernel needs stride 1");
+    if (p.dil_h != p.dil_w) return no("slab kernel needs one dilation for rows and columns");
+    // (then the input pixel under an output pixel never moves backwards, and a depth tap is a whole number of planes)
+    if (p.OH > p.H || p.OW > p.W || (v.T && v.OD != v.D)) return no("output larger than the input, or of another depth");
+    if (phases > 1 && (p.OH != p.H || p.OW != p.W)) return no("output phases of another size than the input");
+    // (a volume this small is a handful of tiles either way: 64 channels on 4x9x9, 9.4 and 7.0 us over taps, 8.2 and 6.4 here, where 2028
+    // positions of 48 take 10.3 and 8.5; the tests hold small ones to the kernels over taps)
+    if (v.T && p.M < 1024) return no("volume of fewer than 1024 positions");
+    IgemmLaunch t = k;
+    t.kw = 1; t.prefetch = 2;
+    DconvParams d;
+    size_t lds = 0;
+    if (!dtaps_setup(pb, t, 1, &d, &lds, why)) return false;
+    const int64_t planes = (int64_t)p.M / ((int64_t)p.OH * p.OW), in_px = planes * p.H * p.W;
+    if (in_px > 0x7fffffff) return no("input too large for 32-bit pixel indices");
+    const size_t np = dconv_patch_pixels(k.BM, p.M, p.H, p.W, p.OH, p.OW, kr, ks, 0, 0, 1, p.dil_h);
+    const int nwg = k.wgm * k.wgn;
+    if (np > 8192 || (slab_patch_bytes((int)np, k.BK) - kSlabZero) / 1024 > (uint32_t)(nwg * kSlabLoads[2]))
+        return no("patch takes more loads than a slab's steps issue");
+    const int64_t slabs = (int64_t)((d.c16 + k.BK / 8 - 1) / (k.BK / 8)) * d.T;
+    lds = dslab_lds_bytes(k.BM, k.BN, k.BK, kr, k.wgn, k.kw, (int)np, slabs > k.kw ? 2 : 1);
+    if (lds > 160 * 1024) return no("patches and weight stages do not fit LDS");
+    if (lds_bytes) *lds_bytes = lds;
+    if (!out) return true;
+    d.in_px = (int32_t)in_px;
+    d.patch_bytes = (int32_t)slab_patch_bytes((int)np, k.BK);
+    d.d_c16 = make_div32((uint32_t)((d.c16 + k.BK / 8 - 1) / (k.BK / 8)));
+    *out = d;
+    return true;
+}
+
 // The same for a channel-planar kernel (dplanar.h): NCHW activations, OIHW weights, NCHW output, all dense.
 static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes,
                           std::string *why)
@@ -434,6 +479,7 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
 {
     if (k.stream == 2) return dplanar_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream == 3) return dstem_setup(pb, k, splitk, out, lds_bytes, why);
+    if (k.stream == 4) return dslab_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.taps) return dtaps_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream) return dstream_setup(pb, k, splitk, out, lds_bytes, why);
     auto no = [&](const char *m) { if (why) *why = m; return false; };

@@ -1,5 +1,6 @@
 // Registration of one direct-convolution tile configuration with the kernel table.
 #pragma once
+#include "dslab.h"
 #include "dstream.h"
 
 // BM x BN output tile, WGM x WGN waves, NS weight stages
@@ -60,4 +61,12 @@
         (igemm_register(IgemmLaunch{"bf16_" #BM "x" #BN "x" #BK "_rtapskn_w" #WGM "x" #WGN "x" #KW "_s" #NS,      \
                                     ALT_BF16, BM, BN, BK, LOAD_VEC, LOAD_VEC, NS - 1, 1, 0, nullptr,             \
                                     &dstream_launch<BM, BN, WGM, WGN, KW, NS, BK, true, kTapsRagged>, WGM, WGN, KW, 1, 1, kTapsRagged}), \
+         true)
+
+// patch-resident kernel over slabs of BK channels (dslab.h): BM x BN tile, KW K groups of WGM x WGN waves
+#define ALT_DSLAB(BM, BN, WGM, WGN, KW, BK)                                                                      \
+    const bool reg_dslab_##BM##x##BN##x##BK##_w##WGM##x##WGN##x##KW =                                            \
+        (igemm_register(IgemmLaunch{"bf16_" #BM "x" #BN "x" #BK "_slab_w" #WGM "x" #WGN "x" #KW, ALT_BF16, BM, BN, \
+                                    BK, LOAD_VEC, LOAD_VEC, 2, 1, 0, nullptr,                                    \
+                                    &dslab_launch<BM, BN, WGM, WGN, KW, BK>, WGM, WGN, KW, 4, 0, kTapsRagged}),  \
          true)

@@ -198,9 +198,38 @@ static double tile_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     return std::sqrt(std::cbrt(cube(us * us) + cube(mem * mem)));
 }
 
+// The same for the patch-resident kernels over slabs of channels, fitted over 640 launches (100 3x3 layers of 5 to 400 us): a slab costs
+// 400 clocks beside its steps, since no operand read is in flight where two meet, and each slab's patch adds to what its steps load.
+static double slab_estimate_us(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds)
+{
+    const int nwg = k.wgm * k.wgn, waves = k.kw * nwg;
+    const int taps = pb.v.T && p.batch > 1 ? pb.v.taps[1] * pb.v.taps[2] : p.R * p.S;
+    const int depth = pb.v.T ? p.batch > 1 ? pb.v.taps[0] : pb.v.T : 1;
+    const double wtm = (double)k.BM / k.wgm, wtn = (double)k.BN / k.wgn, acc = wtm * wtn / 64;
+    const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), std::floor((acc <= 32 ? 16.0 : 8.0) / waves)));
+    const double blocks = (double)p.tiles_m * p.tiles_n * p.batch;
+    const double slabs = std::ceil(std::ceil((double)p.C / k.BK) * depth / k.kw), steps = slabs * taps;
+    const double np = k.BM + 2.0 * p.dil_h * (p.W + 1);
+    const double mfma = (double)k.kw * k.BM * k.BN * k.BK / 2048.0;
+    const double in = (double)k.kw * (k.BN * k.BK * 2 + np * (k.BK * 2 + 16) / taps) / 63.0;
+    const double out = waves * (wtm + wtn) * k.BK * 2 / 400.0;
+    const double alone = std::max(mfma * (waves >= 8 ? 1.0 : 1.34) * std::max(1.0, 4.0 / waves), in);
+    auto cube = [](double v) { return v * v * v; };
+    auto round_clk = [&](double n) {
+        const double products = n * mfma * (waves * n >= 8 ? 1.3 : 1.0) * std::max(1.0, 4.0 / (waves * n));
+        return steps * std::cbrt(cube(products) + cube(n * in) + cube(n * out) + cube(alone)) + slabs * 408.0 + 5340.0 -
+               (waves >= 8 ? 1475.0 : 0.0) + n * k.BM * k.BN / 3.36 + (k.kw > 1 ? 2950.0 + (double)k.kw * k.BM * k.BN / 74.0 : 0.0);
+    };
+    const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
+    const double us = 1.18 + (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0;
+    const double mem = 1.18 + 2.0 * ((double)pb.x_elems + pb.w_elems + (double)p.M * p.Nc * p.batch) / 4.64e6;
+    return std::sqrt(std::cbrt(cube(us * us) + cube(mem * mem)));
+}
+
 // Rough relative time of one variant, about 45 to the microsecond.  lds: bytes of a workgroup of a tile kernel.
 double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds)
 {
+    if (k.launch_direct && k.stream == 4) return 0.05 * 45.0 * slab_estimate_us(pb, k, p, lds);
     if (k.launch_direct && k.stream <= 1 && k.dtype == ALT_BF16) {
         // (a small factor: wherever one of these kernels applies it has been faster than the register-staged ones, whose estimate below
         // knows little of slices and short sums: at half, 4 x 128 x 5 x 5, 3x3, went there in 36 slices and took 15.6 us, not 7.8.

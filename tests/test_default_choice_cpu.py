@@ -47,7 +47,7 @@ def test_single_precision_batches_of_few_tiles_run_in_slices(h, M, N, K, batch, 
 
 @pytest.mark.parametrize("N,C,H,K,family", [
     (16, 64, 56, 64, "_direct_"), (16, 128, 28, 128, "_direct_"), (16, 512, 7, 512, "_direct_"), (1, 256, 14, 256, "_direct_"),
-    (256, 256, 14, 256, "taps_"), (256, 512, 7, 512, "taps_"), (4, 128, 5, 128, "_direct_")])
+    (256, 256, 14, 256, "taps_"), (256, 512, 7, 512, "_slab_"), (40, 96, 39, 96, "_slab_"), (6, 208, 15, 208, "_slab_"), (4, 128, 5, 128, "_direct_")])
 def test_layers_run_unsliced(h, N, C, H, K, family):
     name = conv(h, N, C, H, K, 3)
     assert family in name and name.endswith("_k1")

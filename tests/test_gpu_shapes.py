@@ -166,6 +166,26 @@ def test_few_channel_kernels_every_variant(h, N, C, H, W, K, R, S, stride, pad, 
         check_conv(h, N, C, H, W, K, R, stride, pad, S=S, layouts=("NCHW", wl, yl), variant=v)
 
 
+@pytest.mark.parametrize("N,C,H,W,K,R,pad,dil,yl", [
+    (2, 8, 9, 7, 12, 3, 1, 1, "NHWC"),         # one chunk of one slab, narrow output
+    (3, 40, 10, 11, 72, 3, 1, 1, "NHWC"),      # a slab of eight channels behind a whole one
+    (1, 104, 13, 12, 40, 3, 1, 1, "NCHW8c"),   # four slabs (two of 64), blocked output
+    (2, 64, 17, 15, 132, 3, 0, 1, "NHWC"),     # no padding: patches of several images' ends
+    (1, 72, 19, 18, 64, 3, 2, 2, "NHWC"),      # dilated, same-size
+    (5, 96, 4, 4, 32, 3, 1, 1, "NHWC"),        # images smaller than a tile
+    (2, 200, 8, 9, 36, 2, 0, 1, "NHWC"),       # 2x2 taps, seven slabs
+    (1, 24, 3, 70, 20, 3, 1, 1, "NHWC"),       # long rows
+    (1, 16, 1, 1, 16, 3, 1, 1, "NHWC")])       # one pixel, eight of nine taps outside
+def test_slab_kernels_every_variant(h, N, C, H, W, K, R, pad, dil, yl):
+    d = alt.conv_desc(N, C, H, W, K, R, R, pad=pad, dil=dil, in_dtype=alt.BF16, out_dtype=alt.BF16, x_layout="NCHW->NHWC",
+                      w_layout="OIHW->OHWI", y_layout="NCHW->" + yl)
+    slab = [(v, n) for v, n in applicable_variants(h, d) if "_slab_" in n]
+    assert len(slab) >= 3
+    for v, name in slab:
+        print(name, flush=True)
+        check_conv(h, N, C, H, W, K, R, 1, pad, dil, layouts=("NHWC", "OHWI", yl), variant=v)
+
+
 # 3-D and transposed convolutions on the kernels over filter taps: channel counts of whole and of broken K steps (and of one
 # chunk), depth taps beside the channels, output phases of one to four taps per direction, tiles that end inside a phase;
 # the last two have taps that these kernels leave to the copying path (a dilated one, phases of unequal taps): several launches
@@ -215,6 +235,38 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     got = np.moveaxis(host(y, np_out).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1)
     assert canary_ok(whole, ref.size), "wrote outside y"
     assert np.array_equal(got, ref)
+
+
+# volumes and output phases large enough for the slab kernels: depth taps outside the volume, a last slab of eight channels, tiles that end
+# inside a plane, a phase and an image
+@pytest.mark.parametrize("op,N,C,D,H,W,K,T,R,stride,pad,dil", [
+    ("c3d", 2, 40, 12, 13, 11, 72, 3, 3, 1, 1, 1), ("c3d", 1, 104, 7, 23, 21, 20, 5, 3, 1, (2, 1, 1), 1),
+    ("c3d", 3, 32, 9, 15, 14, 64, 3, 3, 1, (2, 2, 2), 2), ("c3d", 1, 64, 9, 20, 19, 136, 3, 3, 1, (1, 0, 0), 1),
+    ("t3d", 2, 24, 8, 24, 23, 20, 4, 4, 2, 1, 1), ("t3d", 3, 72, 7, 19, 21, 64, 4, 4, 2, 1, 1),
+    ("t2d", 6, 48, 1, 44, 41, 36, 1, 4, 2, 1, 1), ("t2d", 5, 136, 1, 34, 51, 64, 1, 4, 2, 1, 1)])
+def test_larger_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, stride, pad, dil):
+    x, b = small_ints_f32(71, (N, C, D, H, W), -3, 3), small_ints_f32(73, (K,), -20, 20)
+    w = small_ints_f32(72, ((K, C) if op == "c3d" else (C, K)) + (T, R, R), -3, 3)
+    each = lambda v, first: (first, v, v) if op == "t2d" else v
+    fn = oracle.conv3d if op == "c3d" else oracle.conv3d_transpose
+    ref = np.maximum(fn(x, w, stride=each(stride, 1), pad=each(pad, 0), dil=each(dil, 1)) + b[None, :, None, None, None], np.float32(0))
+    lay = dict(in_dtype=alt.BF16, out_dtype=alt.BF16, epilogue=alt.EPI_BIAS | alt.EPI_RELU, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI",
+               y_layout="NCHW->NHWC", stride=stride, pad=pad, dil=dil)
+    d = alt.conv_desc(N, C, H, W, K, R, R, **lay) if op == "t2d" else alt.conv3d_desc(N, C, D, H, W, K, T, R, R, **lay)
+    name, pack = {"c3d": ("conv3d", h.pack_weights3d), "t3d": ("conv3d_transpose", h.pack_weights3d_transpose),
+                  "t2d": ("conv2d_transpose", h.pack_weights_transpose)}[op]
+    wshape = (K, C * T, R, R) if op == "c3d" else getattr(h, name + "_weight_shape")(d)
+    wd = dev(np.zeros(int(np.prod(wshape)), np.uint16))
+    pack(d, dev(f32_to_bf16_bits(w.reshape(-1))), wd)
+    whole, y = canary_dev(ref.size, np.uint16)
+    ws_bytes = getattr(h, name + "_workspace_size")(d)
+    ws = dev(np.zeros(max(4, ws_bytes // 4), np.float32))
+    xd, bd = dev(f32_to_bf16_bits(np.ascontiguousarray(np.moveaxis(x, 1, -1)).reshape(-1))), dev(b)
+    print(op, N, C, D, H, W, K, T, R, flush=True)
+    ran = kernels_run(lambda: getattr(h, name)(d, xd, wd, y, bias=bd, workspace=ws, ws_bytes=ws_bytes))
+    assert len(ran) == 1 and "dslab_kernel" in ran[0], ran
+    assert canary_ok(whole, ref.size), "wrote outside y"
+    assert np.array_equal(np.moveaxis(host(y, np.uint16).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1), f32_to_bf16_bits(ref))
 
 
 # single precision: the library's own choice among tiles, K groups and slices (remainders in all of them), with the workspace that
