@@ -70,13 +70,15 @@ struct DconvParams {
     int32_t M, Nc, C, Cs;         // Cs = C / splitk channels per slice
     int32_t H, W, R, S, pad_h, pad_w;
     int32_t tiles_m, tiles_n, splitk, flags;             // flags: ALT_EPI_BIAS | ALT_EPI_RELU | 4 (bf16 output)
-    Div32 d_hw, d_w, d_tm, d_tn;  // divisions by OH*OW, OW, tiles_m, tiles_n
+    Div32 d_hw, d_w;              // divisions by OH*OW, OW
+    // order of the tiles (dconv_tile): rows of tiles per panel (a divisor of tiles_m; with slices all of them), panels or slices
+    int32_t panel_m, outer;
+    Div32 d_pm, d_tn;             // divisions by panel_m, tiles_n
     int32_t log2_cpp;             // log2(Cs / 8): 16-byte chunks per patch pixel
     Div32 d_slots;                // division by Cs / 8 + 1, the 16-byte slots of a patch pixel in LDS
     int32_t ncc;                  // K steps per tap: (Cs / K groups) / channels per K step
     int32_t bk;                   // channels per K step: 64, or 32 for narrow K groups
     int32_t patch_bytes;          // bytes of a patch buffer (dslab.h)
-    Div32 d_sk;                   // division by splitk
     // streaming kernel (dstream.h) only: batch entries and the byte strides between them
     int32_t batch, pad1_;
     int64_t x_bstride, w_bstride, y_bstride;
@@ -110,6 +112,27 @@ struct DconvParams {
     // a channel's patch rows and R
     int32_t wst_o, wst_i, wst_r, wst_s;
 };
+// The tile and the slice of channels of this workgroup.  Consecutive logical numbers share an XCD and its L2 and run at
+// about the same time; they walk down a panel's rows of tiles and then across, so that they cover a block of rows and columns of
+// the output and the operands come into that L2 once for many tiles.  (In columns of all rows, the order before, each of the eight
+// XCDs fetched all of the activations: 2048 x 768 x 3072 in 128x64 tiles, 106 MB instead of 44, 19.4 us and now 17.0; 1000 x 640 x
+// 2560 12.7 and now 8.1; 4096^3 111.6 and now 104.2.)  Panels are equal, so that this takes no more divisions and kernel arguments than plain columns: a last
+// panel of fewer rows took two of each more and cost launches of 5 us 0.1 to 0.3.
+// fp32 tiles stay in columns (PANELS = false): their matrix instructions take far longer than their operands.
+template <bool PANELS = true>
+__device__ __forceinline__ void dconv_tile(const DconvParams &p, int &mt, int &nt, int &split)
+{
+    const int logical = igemm_logical_tile(PANELS ? p.panel_m * p.tiles_n * p.outer : p.tiles_m * p.tiles_n * p.splitk);
+    const int rest = (int)div32((uint32_t)logical, p.d_pm), o = (int)div32((uint32_t)rest, p.d_tn);
+    nt = rest - o * p.tiles_n;
+    if constexpr (PANELS) {
+        split = p.splitk > 1 ? o : 0;
+        mt = logical - rest * p.panel_m + (o - split) * p.panel_m;
+    } else {
+        split = o;
+        mt = logical - rest * p.tiles_m;
+    }
+}
 constexpr int kOutPhases = -1;    // y_blk of an output written phase by phase
 constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
 enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2, kTapsDense = 3, kTapsOne = 4 };   // which of them (dstream.h)
@@ -629,15 +652,7 @@ void dconv_kernel(const DconvParams p)
 
     // workgroup -> (m tile, n tile, channel slice)
     int mt, nt, split;
-    {
-        // consecutive logical ids share an XCD
-        const int ntot = p.tiles_m * p.tiles_n * p.splitk;
-        const int logical = igemm_logical_tile(ntot);
-        const int rest = (int)div32((uint32_t)logical, p.d_tm);
-        mt = logical - rest * p.tiles_m;
-        split = (int)div32((uint32_t)rest, p.d_tn);
-        nt = rest - split * p.tiles_n;
-    }
+    dconv_tile(p, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
 
     const i32x4_t x_rsrc = make_rsrc(p.x, p.x_bytes);

@@ -132,6 +132,31 @@ static hipError_t counter_slot(DeviceState *ds, hipStream_t st, int *slot)
     return hipSuccess;
 }
 
+// The order in which a launch's tiles are numbered (dconv_tile): rows of tiles per panel.  An XCD works on a window of at most 64
+// consecutive tiles at a time (32 compute units of one or two), which covers rows and columns of tiles; the panel is the one whose window
+// reads least.  a, b: bytes that a row and a column of tiles read.  All rows are one panel where that reads no more than an eighth
+// above the least, or no more than half of an XCD's L2 (4 MB), where it comes in once in any order; and fp32 tiles (dconv_tile).
+static void order_tiles(DconvParams *d, double a, double b, bool panels = true)
+{
+    const int64_t tiles = (int64_t)d->tiles_m * d->tiles_n, share = (tiles * d->splitk + 7) / 8;
+    const int window = (int)std::min<int64_t>(std::min<int64_t>(share, tiles), 64);
+    auto reads = [&](int pm) {
+        const int64_t panel = (int64_t)pm * d->tiles_n;
+        const int rows = panel >= window ? std::min(pm, window) : (int)std::min<int64_t>((int64_t)pm * ((window + panel - 1) / panel), d->tiles_m);
+        const int cols = panel >= window ? (window + pm - 1) / pm : d->tiles_n;
+        return rows * a + cols * b;
+    };
+    int best = d->tiles_m;
+    double least = reads(best) / 1.125;
+    if (panels && d->splitk == 1 && reads(best) > 2e6)
+        for (int pm = 1; pm <= window && 2 * pm <= d->tiles_m; ++pm)
+            if (d->tiles_m % pm == 0 && reads(pm) < least) { least = reads(pm); best = pm; }
+    d->panel_m = best;
+    d->outer = d->splitk > 1 ? d->splitk : d->tiles_m / best;
+    d->d_pm = make_div32((uint32_t)best);
+    d->d_tn = make_div32((uint32_t)d->tiles_n);
+}
+
 // The same for a streaming kernel (dstream.h): 1x1 filters, stride 1, no padding (a GEMM
 // is lowered to that), any number of channels that splits into 64-channel steps.
 static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes,
@@ -186,11 +211,9 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | (p.out_bf16 ? kDconvOutBf16 : 0);
     d.d_hw = make_div32((uint32_t)(p.H * p.W));
     d.d_w = make_div32((uint32_t)p.W);
-    d.d_tm = make_div32((uint32_t)tiles_m);
-    d.d_tn = make_div32((uint32_t)tiles_n);
+    order_tiles(&d, 2.0 * C / splitk * k.BM, 2.0 * C / splitk * k.BN);
     d.ncc = (int32_t)(C / splitk / k.kw / k.BK);
     d.bk = k.BK;
-    d.d_sk = make_div32((uint32_t)splitk);
     d.batch = p.batch;
     d.OH = p.H; d.OW = p.W; d.x_blk = x_blk; d.y_blk = y_blk;
     d.d_ihw = make_div32((uint32_t)(p.H * p.W));
@@ -266,9 +289,7 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | (p.out_bf16 ? kDconvOutBf16 : 0);
     d.d_hw = make_div32((uint32_t)(OH * OW));
     d.d_w = make_div32((uint32_t)OW);
-    d.d_tm = make_div32((uint32_t)tiles_m);
-    d.d_tn = make_div32((uint32_t)tiles_n);
-    d.d_sk = make_div32((uint32_t)splitk);
+    order_tiles(&d, (double)es * C / splitk * T * k.BM * p.stride_h * p.stride_w, (double)es * C / splitk * T * R * S * k.BN, es == 2);
     d.d_od = make_div32((uint32_t)OD);
     d.ncc = (int32_t)nk;
     d.bk = k.BK;
@@ -415,10 +436,8 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     d.in_px = (int32_t)(N * H * W);
     d.d_hw = make_div32((uint32_t)(p.OH * p.OW));
     d.d_w = make_div32((uint32_t)p.OW);
-    d.d_tm = make_div32((uint32_t)tiles_m);
-    d.d_tn = make_div32((uint32_t)tiles_n);
+    order_tiles(&d, 2.0 * C * k.BM * st_ * st_, 2.0 * C * p.R * p.S * k.BN);
     d.d_ihw = make_div32((uint32_t)(H * W));
-    d.d_sk = make_div32(1);
     d.bk = 64;
     *out = d;
     return true;
@@ -537,15 +556,13 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
     d.in_px = (int32_t)(N * H * W);
     d.d_hw = make_div32((uint32_t)(p.OH * p.OW));
     d.d_w = make_div32((uint32_t)p.OW);
-    d.d_tm = make_div32((uint32_t)tiles_m);
-    d.d_tn = make_div32((uint32_t)tiles_n);
+    order_tiles(&d, 2.0 * Cs * k.BM * st_ * st_, 2.0 * Cs * p.R * p.S * k.BN);
     int l2 = 0;
     while ((8 << l2) < Cs) ++l2;
     d.log2_cpp = l2;
     d.d_slots = make_div32((uint32_t)(Cs / 8 + 1));
     d.ncc = (int32_t)(Csg / bk);
     d.bk = bk;
-    d.d_sk = make_div32((uint32_t)splitk);
     d.x_blk = x_blk; d.y_blk = y_blk;
     d.d_ihw = make_div32((uint32_t)(H * W));
     *out = d;

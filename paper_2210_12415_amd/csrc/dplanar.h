@@ -96,13 +96,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     const int kg = wave / NWG, wq = wave % NWG;
     const int wm = wq / WGN, wn = wq % WGN;
 
-    int mt, nt;
-    {
-        const int ntot = p.tiles_m * p.tiles_n;
-        const int logical = igemm_logical_tile(ntot);
-        nt = (int)div32((uint32_t)logical, p.d_tm);
-        mt = logical - nt * p.tiles_m;
-    }
+    int mt, nt, split;                                     // (one slice)
+    dconv_tile(p, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
     const uint16_t *xg = (const uint16_t *)p.x;
     const int HW = p.H * p.W;

@@ -89,12 +89,8 @@ void dslab_kernel(const DconvParams p)
     const int kg = wave / NWG, wq = wave % NWG;
     const int wm = wq / WGN, wn = wq % WGN;
 
-    int mt, nt;
-    {
-        const int logical = igemm_logical_tile(p.tiles_m * p.tiles_n);
-        nt = (int)div32((uint32_t)logical, p.d_tm);
-        mt = logical - nt * p.tiles_m;
-    }
+    int mt, nt, split;                                     // (one slice)
+    dconv_tile(p, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
     int f_d = 0, f_h = 0, f_w = 0;                         // the phase's first tap in the common window
     int64_t y_phase = 0;

@@ -92,14 +92,7 @@ void dstream_kernel(const DconvParams p)
 
     // workgroup -> (m tile, n tile, channel slice), as in the direct convolution
     int mt, nt, split;
-    {
-        const int ntot = p.tiles_m * p.tiles_n * p.splitk;
-        const int logical = igemm_logical_tile(ntot);
-        const int rest = (int)div32((uint32_t)logical, p.d_tm);
-        mt = logical - rest * p.tiles_m;
-        split = (int)div32((uint32_t)rest, p.d_tn);
-        nt = rest - split * p.tiles_n;
-    }
+    dconv_tile<ES == 2>(p, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
     const int bz = blockIdx.y;                             // batch entry, or output phase
     // the phase's first tap in the common window (depth, row, column) and the offset of its first output
