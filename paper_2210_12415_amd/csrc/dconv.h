@@ -36,6 +36,7 @@
 // second kernel is launched.
 #pragma once
 
+#include <cstddef>
 #include <utility>
 
 #include "igemm_dma.h"
@@ -69,16 +70,15 @@ struct DconvParams {
     uint32_t x_bytes, w_bytes, y_bytes, partial_bytes;   // partial_bytes: one slice
     int32_t M, Nc, C, Cs;         // Cs = C / splitk channels per slice
     int32_t H, W, R, S, pad_h, pad_w;
-    int32_t tiles_m, tiles_n, splitk, flags;             // flags: ALT_EPI_BIAS | ALT_EPI_RELU | 4 (bf16 output)
-    Div32 d_hw, d_w;              // divisions by OH*OW, OW
-    // order of the tiles (dconv_tile): rows of tiles per panel (a divisor of tiles_m; with slices all of them), panels or slices
-    int32_t panel_m, outer;
-    Div32 d_pm, d_tn;             // divisions by panel_m, tiles_n
+    // flags: ALT_EPI_BIAS | ALT_EPI_RELU | kDconvOutBf16 | kPlanarOutNhwc | rows of tiles per panel (dconv_tile) << kPanelShift
+    int32_t tiles_m, tiles_n, splitk, flags;
+    Div32 d_hw, d_w, d_pm, d_tn;  // divisions by OH*OW, OW, rows of tiles per panel, tiles_n
     int32_t log2_cpp;             // log2(Cs / 8): 16-byte chunks per patch pixel
     Div32 d_slots;                // division by Cs / 8 + 1, the 16-byte slots of a patch pixel in LDS
     int32_t ncc;                  // K steps per tap: (Cs / K groups) / channels per K step
     int32_t bk;                   // channels per K step: 64, or 32 for narrow K groups
     int32_t patch_bytes;          // bytes of a patch buffer (dslab.h)
+    int32_t pad0_[2];             // (what lies behind stays where the fp32 kernels read it, see below)
     // streaming kernel (dstream.h) only: batch entries and the byte strides between them
     int32_t batch, pad1_;
     int64_t x_bstride, w_bstride, y_bstride;
@@ -112,6 +112,12 @@ struct DconvParams {
     // a channel's patch rows and R
     int32_t wst_o, wst_i, wst_r, wst_s;
 };
+// Where the arguments lie decides how they are loaded, and so what the fp32 kernels over filter taps keep in scalar registers: with the
+// fields from log2_cpp to patch_bytes eight bytes further on, six of the eighteen spilled 2 to 8 scalars more, and five layers of 5 images took
+// 81.7 us, not 80.3 (same tiles in the same order).  Hence fixed places, and the panel in the flags' upper bits.
+static_assert(offsetof(DconvParams, d_hw) == 120 && offsetof(DconvParams, log2_cpp) == 152 && offsetof(DconvParams, batch) == 184,
+              "kernel arguments where the fp32 kernels were measured with them");
+constexpr int kPanelShift = 4;    // (rows of tiles: at most 2^31 / 64)
 // The tile and the slice of channels of this workgroup.  Consecutive logical numbers share an XCD and its L2 and run at
 // about the same time; they walk down a panel's rows of tiles and then across, so that they cover a block of rows and columns of
 // the output and the operands come into that L2 once for many tiles.  (In columns of all rows, the order before, each of the eight
@@ -122,12 +128,13 @@ struct DconvParams {
 template <bool PANELS = true>
 __device__ __forceinline__ void dconv_tile(const DconvParams &p, int &mt, int &nt, int &split)
 {
-    const int logical = igemm_logical_tile(PANELS ? p.panel_m * p.tiles_n * p.outer : p.tiles_m * p.tiles_n * p.splitk);
+    const int logical = igemm_logical_tile(p.tiles_m * p.tiles_n * p.splitk);
     const int rest = (int)div32((uint32_t)logical, p.d_pm), o = (int)div32((uint32_t)rest, p.d_tn);
     nt = rest - o * p.tiles_n;
     if constexpr (PANELS) {
+        const int panel_m = (int)((uint32_t)p.flags >> kPanelShift);
         split = p.splitk > 1 ? o : 0;
-        mt = logical - rest * p.panel_m + (o - split) * p.panel_m;
+        mt = logical - rest * panel_m + (o - split) * panel_m;
     } else {
         split = o;
         mt = logical - rest * p.tiles_m;

@@ -151,8 +151,7 @@ static void order_tiles(DconvParams *d, double a, double b, bool panels = true)
     if (panels && d->splitk == 1 && reads(best) > 2e6)
         for (int pm = 1; pm <= window && 2 * pm <= d->tiles_m; ++pm)
             if (d->tiles_m % pm == 0 && reads(pm) < least) { least = reads(pm); best = pm; }
-    d->panel_m = best;
-    d->outer = d->splitk > 1 ? d->splitk : d->tiles_m / best;
+    d->flags |= (int32_t)((uint32_t)best << kPanelShift);
     d->d_pm = make_div32((uint32_t)best);
     d->d_tn = make_div32((uint32_t)d->tiles_n);
 }
