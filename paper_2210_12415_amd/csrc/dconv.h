@@ -37,6 +37,7 @@
 #pragma once
 
 #include <cstddef>
+#include <numeric>
 #include <utility>
 
 #include "igemm_dma.h"
@@ -982,12 +983,16 @@ inline size_t dconv_patch_pixels(int BM, int64_t M, int H, int W, int OH, int OW
     };
     int64_t span = 1;
     if (stride == 1 && OH == H && OW == W) span = BM;      // output and input indices coincide
-    else
-        for (int64_t m0 = 0; m0 < M; m0 += BM) {
-            const int64_t m1 = (m0 + BM < M ? m0 + BM : M) - 1;
+    else {
+        // (a tile's span depends on where in an image it starts, which repeats; the last tile may be shorter)
+        const int64_t ohw = (int64_t)OH * OW, tiles = (M + BM - 1) / BM, period = ohw / std::gcd(ohw, (int64_t)BM);
+        for (int64_t i = 0; i < tiles; ++i) {
+            if (i == period && i < tiles - 1) i = tiles - 1;
+            const int64_t m0 = i * BM, m1 = (m0 + BM < M ? m0 + BM : M) - 1;
             const int64_t d = anchor(m1) - anchor(m0) + 1;
             if (d > span) span = d;
         }
+    }
     return (size_t)span + (size_t)pad_h * W + pad_w + (size_t)((R - 1) * dil - pad_h) * W + ((S - 1) * dil - pad_w);
 }
 

@@ -168,15 +168,16 @@ static bool dstream_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
         return no("streaming kernel needs a 1x1 filter, stride 1, no padding");
     if (p.OH != p.H || p.OW != p.W) return no("streaming kernel needs output size = input size");
     const int64_t C = p.C, H = p.H, W = p.W, K = p.Nc, N = p.M / (H * W);
-    int x_blk = 0, y_blk = 0;
-    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, N, &x_blk)) return no("A is not dense with K contiguous (whole or in blocks)");
-    if (x_blk && k.BK % (1 << x_blk)) return no("channel blocks larger than a K step");
+    // (B first: half of these kernels read the other layout of it)
     if (k.bt) {
         if (!(dense(p.wo, K, 1) && dense(p.wi, C, K))) return no("B is not dense with N contiguous");
         if (K % 8) return no("row-major B is loaded eight columns at a time");
     } else if (!(dense(p.wi, C, 1) && dense(p.wo, K, C))) {
         return no("B is not dense with K contiguous");
     }
+    int x_blk = 0, y_blk = 0;
+    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, N, &x_blk)) return no("A is not dense with K contiguous (whole or in blocks)");
+    if (x_blk && k.BK % (1 << x_blk)) return no("channel blocks larger than a K step");
     if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, H, W, N, &y_blk)) return no("output is not dense with N contiguous (whole or in blocks)");
     if ((x_blk || y_blk) && p.batch > 1) return no("blocked tensors are not built for batched problems");
     const int64_t osz = p.out_bf16 ? 2 : 4;
@@ -237,15 +238,15 @@ static bool dtaps_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     const int64_t nT = phases > 1 ? v.taps[0] : T, nR = phases > 1 ? v.taps[1] : R, nS = phases > 1 ? v.taps[2] : S;
     if (T > kTapBits || R > kTapBits || S > kTapBits) return no("filters of more than ten taps in one direction");
     if (C % epc) return no("a pixel's channels are not a whole number of 16-byte chunks");
-    int x_blk = 0, y_blk = 0;
-    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, NX, &x_blk) || x_blk) return no("activations are not dense NHWC");
-    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH * sh, OW * sw, NY * sd, &y_blk) || (y_blk && p.batch > 1)) return no("output is not dense NHWC or N K/b H W b");
     if (k.bt) {
         if (v.T || R * S != 1 || !(dense(p.wo, K, 1) && dense(p.wi, C, K))) return no("B is not dense with N contiguous");
         if (K % 8) return no("row-major B is loaded eight columns at a time");
     } else if (!(dense(p.wi, T * C, 1) && dense(p.ws, S, T * C) && dense(p.wr, R, S * T * C) && dense(p.wo, phases * K, R * S * T * C))) {
         return no("weights are not dense OHWI");
     }
+    int x_blk = 0, y_blk = 0;
+    if (!nhwc_or_blocked(p.xc, p.xw, p.xh, p.xn, C, H, W, NX, &x_blk) || x_blk) return no("activations are not dense NHWC");
+    if (!nhwc_or_blocked(p.yk, p.yw, p.yh, p.yn, K, OH * sh, OW * sw, NY * sd, &y_blk) || (y_blk && p.batch > 1)) return no("output is not dense NHWC or N K/b H W b");
     const int64_t osz = p.out_bf16 ? 2 : 4;
     if ((uintptr_t)p.x % 16 || (uintptr_t)p.w % 16 || (uintptr_t)p.y % 16) return no("operands are not 16-byte aligned");
     if (p.batch > 1 && ((p.x_bstride * es) % 16 || (p.w_bstride * es) % 16 || (p.y_bstride * osz) % 16))
@@ -350,25 +351,26 @@ static bool dslab_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     // (a volume this small is a handful of tiles either way: 64 channels on 4x9x9, 9.4 and 7.0 us over taps, 8.2 and 6.4 here, where 2028
     // positions of 48 take 10.3 and 8.5; the tests hold small ones to the kernels over taps)
     if (v.T && p.M < 1024) return no("volume of fewer than 1024 positions");
+    // (the parameters are built for a launch alone: choosing a kernel asks about seven of these)
     IgemmLaunch t = k;
     t.kw = 1; t.prefetch = 2;
-    DconvParams d;
-    size_t lds = 0;
-    if (!dtaps_setup(pb, t, 1, &d, &lds, why)) return false;
+    if (!dtaps_setup(pb, t, 1, nullptr, nullptr, why)) return false;
     const int64_t planes = (int64_t)p.M / ((int64_t)p.OH * p.OW), in_px = planes * p.H * p.W;
     if (in_px > 0x7fffffff) return no("input too large for 32-bit pixel indices");
     const size_t np = dconv_patch_pixels(k.BM, p.M, p.H, p.W, p.OH, p.OW, kr, ks, 0, 0, 1, p.dil_h);
     const int nwg = k.wgm * k.wgn;
     if (np > 8192 || (slab_patch_bytes((int)np, k.BK) - kSlabZero) / 1024 > (uint32_t)(nwg * kSlabLoads[2]))
         return no("patch takes more loads than a slab's steps issue");
-    const int64_t slabs = (int64_t)((d.c16 + k.BK / 8 - 1) / (k.BK / 8)) * d.T;
-    lds = dslab_lds_bytes(k.BM, k.BN, k.BK, kr, k.wgn, k.kw, (int)np, slabs > k.kw ? 2 : 1);
+    const int64_t ncs = ((int64_t)p.C + k.BK - 1) / k.BK, slabs = ncs * (phases > 1 ? v.taps[0] : v.T ? v.T : 1);
+    const size_t lds = dslab_lds_bytes(k.BM, k.BN, k.BK, kr, k.wgn, k.kw, (int)np, slabs > k.kw ? 2 : 1);
     if (lds > 160 * 1024) return no("patches and weight stages do not fit LDS");
     if (lds_bytes) *lds_bytes = lds;
     if (!out) return true;
+    DconvParams d;
+    if (!dtaps_setup(pb, t, 1, &d, nullptr, why)) return false;
     d.in_px = (int32_t)in_px;
     d.patch_bytes = (int32_t)slab_patch_bytes((int)np, k.BK);
-    d.d_c16 = make_div32((uint32_t)((d.c16 + k.BK / 8 - 1) / (k.BK / 8)));
+    d.d_c16 = make_div32((uint32_t)ncs);
     *out = d;
     return true;
 }

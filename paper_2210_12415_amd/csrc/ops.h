@@ -1,6 +1,8 @@
 // Shared between ops.hip (conv/gemm entry points) and tune.cpp.
 #pragma once
 
+#include <functional>
+
 #include "dconv.h"
 
 namespace alt {
@@ -40,11 +42,11 @@ int igemm_num_splits();
 int igemm_variant_count();
 std::string igemm_variant_name(int variant);
 void igemm_analyse(Problem *pb);
-// (*lds_bytes: of a workgroup of a tile kernel; untouched for the others)
-bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why, size_t *lds_bytes = nullptr);
+bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, std::string *why);
 size_t igemm_workspace(const Problem &pb, int splitk);
 double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds);
-// (counters = false: among the variants that need no arrival counters)
+// Every variant that runs the problem within the workspace, with its estimate (counters = false: those that need no arrival counters)
+void igemm_for_each(const Problem &pb, size_t ws_limit, bool counters, const std::function<void(int variant, double estimate)> &seen);
 int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters = true);
 // A tile kernel's launch worked out for one problem; the operands' addresses are filled in by every call.
 struct TileLaunch {

@@ -95,9 +95,9 @@ void igemm_analyse(Problem *pb)
 
 static bool nests(int64_t f, int64_t C, int bk) { return f >= C ? true : (f % bk == 0 || bk % f == 0); }
 
-// Can kernel `k` with split factor `splitk` run this problem?  Fills the
-// launch-dependent fields of a copy of the parameters.
-bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *out, std::string *why, size_t *lds_bytes)
+// Can kernel `k` with split factor `splitk` run this problem?  `p`: a copy of the parameters, or null; its launch-dependent fields but
+// the divisors (igemm_divisors) are filled in.  Choosing a kernel asks this a thousand times, so no copy is made here.
+static bool applicable(const Problem &pb, const IgemmLaunch &k, int splitk, IgemmParams *p, std::string *why, size_t *lds_bytes)
 {
     auto no = [&](const char *m) { if (why) *why = m; return false; };
     const IgemmParams &p0 = pb.p;
@@ -106,15 +106,13 @@ bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igemm
     if (p0.addend && !k.launch_direct) return no("the fused sum is built into the tile kernels only");
     if (k.launch_direct) {
         if (!dconv_setup(pb, k, splitk, nullptr, lds_bytes, why)) return false;
-        if (out) {
-            IgemmParams p = p0;
-            p.splitk = splitk;
-            const int64_t taps = pb.v.T ? (int64_t)pb.v.taps[0] * pb.v.taps[1] * pb.v.taps[2] : (int64_t)p.R * p.S;
-            p.ksteps_total = (int32_t)(k.taps ? (taps * p.C + k.BK - 1) / k.BK : p.R * p.S * (p.C / 64));
-            p.ksteps_per_split = (p.ksteps_total + splitk - 1) / splitk;
-            p.tiles_m = (p.M + k.BM - 1) / k.BM;
-            p.tiles_n = (p.Nc + k.BN - 1) / k.BN;
-            *out = p;
+        if (p) {
+            p->splitk = splitk;
+            const int64_t taps = pb.v.T ? (int64_t)pb.v.taps[0] * pb.v.taps[1] * pb.v.taps[2] : (int64_t)p0.R * p0.S;
+            p->ksteps_total = (int32_t)(k.taps ? (taps * p0.C + k.BK - 1) / k.BK : p0.R * p0.S * (p0.C / 64));
+            p->ksteps_per_split = (p->ksteps_total + splitk - 1) / splitk;
+            p->tiles_m = (p0.M + k.BM - 1) / k.BM;
+            p->tiles_n = (p0.Nc + k.BN - 1) / k.BN;
         }
         return true;
     }
@@ -126,25 +124,36 @@ bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igemm
     if (k.bmode == LOAD_TRANS && !pb.b_trans) return no("B rows are not contiguous");
     if (pb.spatial_split && k.amode == LOAD_GATHER && !(p0.R == 1 && p0.S == 1 && p0.pad_h == 0 && p0.pad_w == 0))
         return no("blocked H/W with a sliding window");
-    IgemmParams p = p0;
-    p.fd_ohow = make_fastdiv((uint32_t)(p.OH * p.OW));
-    p.fd_ow = make_fastdiv((uint32_t)p.OW);
-    p.fd_c = make_fastdiv((uint32_t)p.C);
-    p.fd_s = make_fastdiv((uint32_t)p.S);
-    p.fd_nc = make_fastdiv((uint32_t)p.Nc);
-    p.uniform_rs = uniform ? 1 : 0;
-    p.spatial_split = pb.spatial_split ? 1 : 0;
-    p.ksteps_total = (p.Kg + k.BK - 1) / k.BK;
-    if (splitk < 1 || splitk > p.ksteps_total) return no("split-K factor exceeds the K steps");
-    if (splitk > 1 && (int64_t)p.M * p.Nc * 4 >= 0x7fffffff) return no("output too large for the split-K reduction");
-    p.splitk = splitk;
-    p.ksteps_per_split = (p.ksteps_total + splitk - 1) / splitk;
-    if ((int64_t)(splitk - 1) * p.ksteps_per_split >= p.ksteps_total) return no("split-K factor leaves an empty slice");
-    p.tiles_m = (p.M + k.BM - 1) / k.BM;
-    p.tiles_n = (p.Nc + k.BN - 1) / k.BN;
-    if ((int64_t)p.batch * splitk > 65535) return no("batch x split-K exceeds the grid");
-    if (out) *out = p;
+    const int32_t steps = (p0.Kg + k.BK - 1) / k.BK, per_split = splitk < 1 ? 0 : (steps + splitk - 1) / splitk;
+    if (splitk < 1 || splitk > steps) return no("split-K factor exceeds the K steps");
+    if (splitk > 1 && (int64_t)p0.M * p0.Nc * 4 >= 0x7fffffff) return no("output too large for the split-K reduction");
+    if ((int64_t)(splitk - 1) * per_split >= steps) return no("split-K factor leaves an empty slice");
+    if ((int64_t)p0.batch * splitk > 65535) return no("batch x split-K exceeds the grid");
+    if (p) {
+        p->uniform_rs = uniform ? 1 : 0;
+        p->spatial_split = pb.spatial_split ? 1 : 0;
+        p->ksteps_total = steps;
+        p->splitk = splitk;
+        p->ksteps_per_split = per_split;
+        p->tiles_m = (p0.M + k.BM - 1) / k.BM;
+        p->tiles_n = (p0.Nc + k.BN - 1) / k.BN;
+    }
     return true;
+}
+
+// What only a launch of a register-staged kernel needs beside that.
+static void igemm_divisors(IgemmParams *p)
+{
+    p->fd_ohow = make_fastdiv((uint32_t)(p->OH * p->OW));
+    p->fd_ow = make_fastdiv((uint32_t)p->OW);
+    p->fd_c = make_fastdiv((uint32_t)p->C);
+    p->fd_s = make_fastdiv((uint32_t)p->S);
+    p->fd_nc = make_fastdiv((uint32_t)p->Nc);
+}
+
+bool igemm_applicable(const Problem &pb, const IgemmLaunch &k, int splitk, std::string *why)
+{
+    return applicable(pb, k, splitk, nullptr, why, nullptr);
 }
 
 size_t igemm_workspace(const Problem &pb, int splitk)
@@ -312,21 +321,28 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
     return est;
 }
 
-int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters)
+void igemm_for_each(const Problem &pb, size_t ws_limit, bool counters, const std::function<void(int, double)> &seen)
 {
     const auto &tab = igemm_table();
+    IgemmParams p = pb.p;
+    for (int ki = 0; ki < (int)tab.size(); ++ki) {
+        const IgemmLaunch &k = tab[ki];
+        if (k.dtype != pb.dtype || (pb.v.T && !k.taps)) continue;
+        // (the first factor is 1; the channel-planar, few-channel and slab kernels take no other)
+        const int splits = k.launch_direct && (!counters || k.stream >= 2) ? 1 : kNumSplits;
+        for (int si = 0; si < splits; ++si) {
+            size_t lds = 0;
+            if (igemm_workspace(pb, kSplits[si]) > ws_limit) continue;
+            if (applicable(pb, k, kSplits[si], &p, nullptr, &lds)) seen(ki * kNumSplits + si, igemm_estimate(pb, k, p, lds));
+        }
+    }
+}
+
+int igemm_default_variant(const Problem &pb, size_t ws_limit, bool counters)
+{
     double best = 1e300;
     int best_v = -1;
-    for (int ki = 0; ki < (int)tab.size(); ++ki)
-        for (int si = 0; si < kNumSplits; ++si) {
-            IgemmParams p;
-            size_t lds = 0;
-            if (!counters && tab[ki].launch_direct && kSplits[si] > 1) continue;
-            if (!igemm_applicable(pb, tab[ki], kSplits[si], &p, nullptr, &lds)) continue;
-            if (igemm_workspace(pb, kSplits[si]) > ws_limit) continue;
-            const double est = igemm_estimate(pb, tab[ki], p, lds);
-            if (est < best) { best = est; best_v = ki * kNumSplits + si; }
-        }
+    igemm_for_each(pb, ws_limit, counters, [&](int v, double est) { if (est < best) { best = est; best_v = v; } });
     return best_v;
 }
 
@@ -345,7 +361,7 @@ alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *wor
         TileLaunch once;
         TileLaunch &t = kept ? *kept : once;
         if (t.variant != variant) {
-            if (!igemm_applicable(pb, k, splitk, nullptr, &why) || !dconv_setup(pb, k, splitk, &t.d, &t.lds, &why))
+            if (!igemm_applicable(pb, k, splitk, &why) || !dconv_setup(pb, k, splitk, &t.d, &t.lds, &why))
                 return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
             t.variant = variant;
         }
@@ -360,14 +376,15 @@ alt_status_t igemm_run(alt_handle_t h, const Problem &pb, int variant, void *wor
         if (e != hipSuccess) return fail(h, ALT_HIP_ERROR, "launch of %s failed: %s", k.name, hipGetErrorString(e));
         return ALT_OK;
     }
-    IgemmParams p;
-    if (!igemm_applicable(pb, k, splitk, &p, &why))
+    IgemmParams p = pb.p;
+    if (!applicable(pb, k, splitk, &p, &why, nullptr))
         return fail(h, ALT_UNSUPPORTED, "variant %s/splitk%d not applicable: %s", k.name, splitk, why.c_str());
     if (need > 0) {
         if (!workspace || ws_bytes < need)
             return fail(h, ALT_WORKSPACE_TOO_SMALL, "split-K needs %zu workspace bytes, got %zu", need, ws_bytes);
         p.partial = (float *)workspace;
     }
+    igemm_divisors(&p);
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)(p.batch * p.splitk));
     hipError_t e = k.launch(p, grid, st);
     if (e != hipSuccess) return fail(h, ALT_HIP_ERROR, "launch of %s failed: %s", k.name, hipGetErrorString(e));
@@ -601,7 +618,7 @@ static int tuned_variant(alt_handle_t h, const Problem &pb, const std::string &k
     const auto &tab = igemm_table();
     const int v = it->second.variant;
     return v >= 0 && v < (int)tab.size() * kNumSplits &&
-                   igemm_applicable(pb, tab[v / kNumSplits], kSplits[v % kNumSplits], nullptr, nullptr) &&
+                   igemm_applicable(pb, tab[v / kNumSplits], kSplits[v % kNumSplits], nullptr) &&
                    igemm_workspace(pb, kSplits[v % kNumSplits]) <= ws_limit ? v : -1;
 }
 
@@ -828,7 +845,7 @@ alt_status_t alt_conv2d_variant_name(alt_handle_t h, const alt_conv_desc_t *d, i
     std::snprintf(buf, buflen, "%s", n.c_str());
     std::string why;
     const auto &tab = igemm_table();
-    if (!igemm_applicable(pb, tab[variant / kNumSplits], kSplits[variant % kNumSplits], nullptr, &why))
+    if (!igemm_applicable(pb, tab[variant / kNumSplits], kSplits[variant % kNumSplits], &why))
         return fail(h, ALT_UNSUPPORTED, "%s: %s", n.c_str(), why.c_str());
     return ALT_OK;
 }
@@ -921,7 +938,7 @@ alt_status_t alt_gemm_variant_name(alt_handle_t h, const alt_gemm_desc_t *d, int
     std::snprintf(buf, buflen, "%s", n.c_str());
     std::string why;
     const auto &tab = igemm_table();
-    if (!igemm_applicable(pb, tab[variant / kNumSplits], kSplits[variant % kNumSplits], nullptr, &why))
+    if (!igemm_applicable(pb, tab[variant / kNumSplits], kSplits[variant % kNumSplits], &why))
         return fail(h, ALT_UNSUPPORTED, "%s: %s", n.c_str(), why.c_str());
     return ALT_OK;
 }

@@ -123,16 +123,7 @@ struct Trial {
 std::vector<Trial> ordered_variants(const Problem &pb, size_t ws_limit)
 {
     std::vector<Trial> v;
-    const auto &tab = igemm_table();
-    const int ns = igemm_num_splits();
-    for (int ki = 0; ki < (int)tab.size(); ++ki)
-        for (int si = 0; si < ns; ++si) {
-            IgemmParams p;
-            size_t lds = 0;
-            if (!igemm_applicable(pb, tab[ki], kSplitFactors[si], &p, nullptr, &lds)) continue;
-            if (igemm_workspace(pb, kSplitFactors[si]) > ws_limit) continue;
-            v.push_back({ki * ns + si, igemm_estimate(pb, tab[ki], p, lds)});
-        }
+    igemm_for_each(pb, ws_limit, true, [&](int variant, double est) { v.push_back({variant, est}); });
     std::sort(v.begin(), v.end(), [](const Trial &a, const Trial &b) { return a.est < b.est; });
     return v;
 }
