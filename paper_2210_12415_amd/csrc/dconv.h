@@ -141,6 +141,14 @@ __device__ __forceinline__ void dconv_tile(const DconvParams &p, int &mt, int &n
         mt = logical - rest * p.tiles_m;
     }
 }
+// The same for a kernel that takes no slices, out of `tiles` tiles.
+__device__ __forceinline__ void dconv_tile_unsliced(const DconvParams &p, int tiles, int &mt, int &nt)
+{
+    const int logical = igemm_logical_tile(tiles);
+    const int rest = (int)div32((uint32_t)logical, p.d_pm), o = (int)div32((uint32_t)rest, p.d_tn);
+    nt = rest - o * p.tiles_n;
+    mt = logical - (rest - o) * (int)((uint32_t)p.flags >> kPanelShift);
+}
 constexpr int kOutPhases = -1;    // y_blk of an output written phase by phase
 constexpr int kTapBits = 10;      // most taps per direction of those kernels (three fields of a 32-bit mask)
 enum { kNoTaps = 0, kTapsUniform = 1, kTapsRagged = 2, kTapsDense = 3, kTapsOne = 4 };   // which of them (dstream.h)

@@ -96,8 +96,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     const int kg = wave / NWG, wq = wave % NWG;
     const int wm = wq / WGN, wn = wq % WGN;
 
-    int mt, nt, split;                                     // (one slice)
-    dconv_tile(p, mt, nt, split);
+    int mt, nt;
+    dconv_tile_unsliced(p, p.tiles_m * p.tiles_n, mt, nt);
     const int m0 = mt * BM, n0 = nt * BN;
     const uint16_t *xg = (const uint16_t *)p.x;
     const int HW = p.H * p.W;
