@@ -1,6 +1,7 @@
 """ctypes marshalling for libalt.so.  Function names follow include/alt.h."""
 import ctypes
 import os
+import struct
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBPATH = os.environ.get("ALT_LIBRARY", os.path.join(_HERE, "libalt.so"))   # ALT_LIBRARY: developer builds
@@ -257,19 +258,24 @@ def _stream_address(s):
         return int(s)
 
 
-_array_types = {}
+_packers = {}
 
 
 def _extents(a):
-    """_i64 with its array type kept; sequences of other integers than int are converted."""
+    """_i64 as packed bytes, which take half as long to make; what is no whole number of 64 bits is converted there."""
     n = len(a)
-    t = _array_types.get(n)
-    if t is None:
-        t = _array_types[n] = ctypes.c_int64 * n
+    pack = _packers.get(n)
+    if pack is None:
+        pack = _packers[n] = struct.Struct("=%dq" % n).pack
     try:
-        return t(*a)
-    except TypeError:
-        return t(*[int(x) for x in a])
+        return pack(*a)
+    except struct.error:
+        return _i64(a)
+
+
+# What a prototype is given: an int goes through as it is; anything else (a numpy integer, None, an object of ctypes, what is no number at all)
+# takes the call without prototypes, which decides as ever what it accepts and what it raises.
+_CODES = frozenset(range(256))
 
 
 # ------------------------------------------------------------- layouts (host) ----
@@ -402,9 +408,14 @@ class Handle:
         return lib().alt_last_error(self._h).decode()
 
     def layout_transform(self, dtype, shape, src_layout, src, dst_layout, dst, stream=None):
-        status = _call("alt_layout_transform")(self._h, dtype, len(shape), _extents(shape),
-                                               ctypes.byref(_as_layout(src_layout)), _address(src),
-                                               ctypes.byref(_as_layout(dst_layout)), _address(dst), _stream_address(stream))
+        if dtype.__class__ is int and dtype in _CODES:
+            status = _call("alt_layout_transform")(self._h, dtype, len(shape), _extents(shape),
+                                                   ctypes.byref(_as_layout(src_layout)), _address(src),
+                                                   ctypes.byref(_as_layout(dst_layout)), _address(dst), _stream_address(stream))
+        else:
+            status = lib().alt_layout_transform(self._h, dtype, len(shape), _i64(shape),
+                                                ctypes.byref(_as_layout(src_layout)), _ptr(src),
+                                                ctypes.byref(_as_layout(dst_layout)), _ptr(dst), _stream(stream))
         if status != 0:
             _ck(status, self._h)
 
@@ -416,6 +427,8 @@ class Handle:
         return out
 
     def _operator(self, name, d, x, w, bias, y, workspace, ws_bytes, stream):
+        if ws_bytes.__class__ is not int:
+            ws_bytes = ctypes.c_size_t(ws_bytes).value
         status = _call(name)(self._h, ctypes.byref(d), _address(x), _address(w), _address(bias), _address(y), _address(workspace),
                              ws_bytes, _stream_address(stream))
         if status != 0:
@@ -436,6 +449,7 @@ class Handle:
         """The same call as conv2d with its arguments marshalled once: returns a
         function of no arguments that launches it (for loops that repeat one call)."""
         fn = _call("alt_conv2d")
+        ws_bytes = ctypes.c_size_t(ws_bytes).value
         args = (self._h, ctypes.byref(d), _address(x), _address(w), _address(bias), _address(y), _address(workspace),
                 ws_bytes, _stream_address(stream))
         keep = (d, x, w, y, bias, workspace)
@@ -585,6 +599,8 @@ class Handle:
 
     # gemm
     def gemm(self, d, A, B, C, workspace=None, ws_bytes=0, stream=None):
+        if ws_bytes.__class__ is not int:
+            ws_bytes = ctypes.c_size_t(ws_bytes).value
         status = _call("alt_gemm")(self._h, ctypes.byref(d), _address(A), _address(B), _address(C), _address(workspace),
                                    ws_bytes, _stream_address(stream))
         if status != 0:
@@ -665,8 +681,12 @@ class Handle:
                              _ptr(src), _ptr(dst), _stream(stream)), self._h)
 
     def eltwise_add(self, dtype, numel, a, b, y, relu=False, stream=None):
-        status = _call("alt_eltwise_add")(self._h, dtype, numel, _address(a), _address(b), _address(y), int(bool(relu)),
-                                          _stream_address(stream))
+        if dtype.__class__ is int and dtype in _CODES and numel.__class__ is int:
+            status = _call("alt_eltwise_add")(self._h, dtype, numel, _address(a), _address(b), _address(y), int(bool(relu)),
+                                              _stream_address(stream))
+        else:
+            status = lib().alt_eltwise_add(self._h, dtype, ctypes.c_int64(numel), _ptr(a), _ptr(b), _ptr(y), int(bool(relu)),
+                                           _stream(stream))
         if status != 0:
             _ck(status, self._h)
 

@@ -2,6 +2,7 @@
 header declares, its layout index math agrees with the oracle bit for bit, its
 chain planner finds known shortest paths, and argument errors come back as
 status codes.  No kernel is launched."""
+import ctypes
 import itertools
 import os
 import re
@@ -518,3 +519,21 @@ def test_kernel_families_follow_the_layouts():
     assert families(gemm("KN", N=772), "gemm") == set()               # row-major B is loaded eight columns at a time
     assert "_streamkn_" in h.gemm_variant_name(gemm("KN"), -1)
     assert "_stream_" in h.gemm_variant_name(gemm("NK"), -1)
+
+
+@pytest.mark.parametrize("call,error", [
+    (lambda h: h.eltwise_add(ctypes.c_int64(7), 64, 16, 32, 48, stream=0), alt.AltError),             # an object of ctypes reaches the library
+    (lambda h: h.layout_transform(ctypes.c_int64(7), (1, 8), "NC->NC", 16, "NC->CN", 32, stream=0), alt.AltError),
+    (lambda h: h.eltwise_add(np.int64(0), 64, 16, 32, 48, stream=0), ctypes.ArgumentError),
+    (lambda h: h.layout_transform(1 << 64, (1, 8), "NC->NC", 16, "NC->CN", 32, stream=0), ctypes.ArgumentError),
+    (lambda h: h.layout_transform(alt.F32, (1, ctypes.c_int64(8)), "NC->NC", 16, "NC->CN", 32, stream=0), ValueError),
+    (lambda h: h.eltwise_add(alt.F32, 64.0, 16, 32, 48, stream=0), TypeError),
+    (lambda h: h.eltwise_add(alt.F32, None, 16, 32, 48, stream=0), TypeError),
+    (lambda h: h.eltwise_add(alt.F32, ctypes.c_int64(64), 16, 32, 48, stream=0), TypeError),
+    (lambda h: h.gemm(alt.gemm_desc(8, 8, 8), None, 32, 48, ws_bytes=64.0, stream=0), TypeError),
+    (lambda h: h.conv2d(alt.conv_desc(1, 8, 8, 8, 8, 3, 3), None, 32, 48, ws_bytes=ctypes.c_size_t(0), stream=0), TypeError),
+    (lambda h: h.conv2d_prepared(alt.conv_desc(1, 8, 8, 8, 8, 3, 3), None, 32, 48, ws_bytes="0", stream=0), TypeError)])
+def test_arguments_of_other_kinds(call, error):
+    """What short calls hand to the library without wrapping it is refused, or taken, as with wrapping."""
+    with pytest.raises(error):
+        call(alt.Handle())
