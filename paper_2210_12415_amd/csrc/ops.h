@@ -80,6 +80,8 @@ alt_status_t eltwise_add(alt_handle_t h, int dtype, int64_t numel, const void *a
 // the 2-D problem would have for itself, negative if its operands do not fit.
 alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
                       size_t ws_bytes, int64_t ws_2d, hipStream_t st, bool *done);
+// Bytes of workspace that the kernel taps_run would choose wants for itself (0 where it would leave the call alone).
+size_t taps_workspace(alt_handle_t h, const TapsCall &c);
 
 alt_status_t conv_problem(alt_handle_t h, const alt_conv_desc_t *d, const void *x, const void *w,
                           const float *bias, void *y, Problem *pb);

@@ -683,6 +683,43 @@ namespace alt {
 // that are not zeros for 4x4 at stride 2 and 27/8 for 4x4x4, and its result one more pass into place: 128 channels, 3x3x3 on
 // 8x28x28 at batch 2 took 48 us that way and 26 here, T3D 128 -> 64, 4x4x4 at stride 2 on the same volume 128 us and 34; so these
 // kernels run whatever they cover, unless the problem's 2-D form has been tuned to a variant of its own)
+static bool taps_problem(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, int64_t ws_2d, Problem *out)
+{
+    BoundLayout bx, by;
+    Dim2 dx[4], dy[4];
+    std::string err;
+    Problem &pb = *out;
+    if (!(conv_problem(h, &c.f, x, w, bias, y, &pb) == ALT_OK && pb.groups <= 1 &&
+          bind_layout(&c.f.x_layout, 4, c.xs, &bx, &err) == ALT_OK && bind_layout(&c.f.y_layout, 4, c.ys, &by, &err) == ALT_OK &&
+          layout_to_dim2(bx, dx) && layout_to_dim2(by, dy)))
+        return false;
+    // (tuning an operator is tuning its 2-D problem: the winner runs, by the copying path)
+    if (ws_2d >= 0 && tuned_variant(h, pb, conv_key(h, &c.f), (size_t)ws_2d) >= 0) return false;
+    const int64_t es = (int64_t)dtype_size(c.f.in_dtype), os = (int64_t)dtype_size(c.f.out_dtype);
+    IgemmParams &p = pb.p;
+    pb.v = c.v;
+    p.xn = dx[0]; p.xc = dx[1]; p.xh = dx[2]; p.xw = dx[3];
+    p.yn = dy[0]; p.yk = dy[1]; p.yh = dy[2]; p.yw = dy[3];
+    p.C = (int32_t)c.C;
+    p.Nc = (int32_t)c.K;
+    p.batch = c.v.sd * c.v.sh * c.v.sw;
+    pb.x_elems = bx.numel;
+    pb.w_elems = (int64_t)c.K * c.f.C * c.f.R * c.f.S;
+    p.x_bstride = 0; p.w_bstride = pb.w_elems; p.y_bstride = 0;
+    p.x_bytes = (uint32_t)std::min<int64_t>(pb.x_elems * es, 0x7fffffff);
+    p.w_bytes = (uint32_t)std::min<int64_t>(pb.w_elems * es, 0x7fffffff);
+    p.y_bytes = by.numel * 4 < 0x7fffffff ? (uint32_t)(by.numel * os) : 0;
+    return true;
+}
+
+size_t taps_workspace(alt_handle_t h, const TapsCall &c)
+{
+    Problem pb;
+    if (c.f.variant >= 0 || !taps_problem(h, c, nullptr, nullptr, nullptr, nullptr, INT64_MAX, &pb)) return 0;
+    const int v = igemm_default_variant(pb, (size_t)-1);
+    return v < 0 ? 0 : igemm_workspace(pb, kSplits[v % kNumSplits]);
+}
+
 alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, void *workspace,
                       size_t ws_bytes, int64_t ws_2d, hipStream_t st, bool *done)
 {
@@ -690,44 +727,17 @@ alt_status_t taps_run(alt_handle_t h, const TapsCall &c, const void *x, const vo
     if (c.f.variant >= 0 || !x || !w || !y || ((c.f.epilogue & ALT_EPI_BIAS) && !bias)) return ALT_OK;
     const size_t ws_limit = workspace ? ws_bytes : 0;
     const unsigned sig = align_sig(x, w, bias, y) | 1u << 31;
-    Problem pb;
-    int v = -1;
     if (MemoEntry *m = memo_find(h, &c, sizeof c, sig, ws_limit)) {
         if (m->variant < 0) return ALT_OK;
         *done = true;
         m->pb.p.x = x; m->pb.p.w = w; m->pb.p.bias = bias; m->pb.p.y = y;
         return run_chosen(h, m->pb, m->variant, true, workspace, ws_bytes, st, &m->tile);
-    } else {
-        BoundLayout bx, by;
-        Dim2 dx[4], dy[4];
-        std::string err;
-        bool ok = conv_problem(h, &c.f, x, w, bias, y, &pb) == ALT_OK && pb.groups <= 1 &&
-                  bind_layout(&c.f.x_layout, 4, c.xs, &bx, &err) == ALT_OK && bind_layout(&c.f.y_layout, 4, c.ys, &by, &err) == ALT_OK &&
-                  layout_to_dim2(bx, dx) && layout_to_dim2(by, dy);
-        // (tuning an operator is tuning its 2-D problem: the winner runs, by the copying path)
-        if (ok && ws_2d >= 0 && tuned_variant(h, pb, conv_key(h, &c.f), (size_t)ws_2d) >= 0) ok = false;
-        if (ok) {
-            const int64_t es = (int64_t)dtype_size(c.f.in_dtype), os = (int64_t)dtype_size(c.f.out_dtype);
-            IgemmParams &p = pb.p;
-            pb.v = c.v;
-            p.xn = dx[0]; p.xc = dx[1]; p.xh = dx[2]; p.xw = dx[3];
-            p.yn = dy[0]; p.yk = dy[1]; p.yh = dy[2]; p.yw = dy[3];
-            p.C = (int32_t)c.C;
-            p.Nc = (int32_t)c.K;
-            p.batch = c.v.sd * c.v.sh * c.v.sw;
-            pb.x_elems = bx.numel;
-            pb.w_elems = (int64_t)c.K * c.f.C * c.f.R * c.f.S;
-            p.x_bstride = 0; p.w_bstride = pb.w_elems; p.y_bstride = 0;
-            p.x_bytes = (uint32_t)std::min<int64_t>(pb.x_elems * es, 0x7fffffff);
-            p.w_bytes = (uint32_t)std::min<int64_t>(pb.w_elems * es, 0x7fffffff);
-            p.y_bytes = by.numel * 4 < 0x7fffffff ? (uint32_t)(by.numel * os) : 0;
-            v = igemm_default_variant(pb, ws_limit);
-        }
-        memo_store(h, &c, sizeof c, sig, ws_limit, pb, v);
     }
+    Problem pb;
+    const int v = taps_problem(h, c, x, w, bias, y, ws_2d, &pb) ? igemm_default_variant(pb, ws_limit) : -1;
+    memo_store(h, &c, sizeof c, sig, ws_limit, pb, v);
     if (v < 0) return ALT_OK;
     *done = true;
-    pb.p.x = x; pb.p.w = w; pb.p.bias = bias; pb.p.y = y;
     return run_chosen(h, pb, v, true, workspace, ws_bytes, st);
 }
 }  // namespace alt

@@ -67,3 +67,12 @@ def test_choosing_a_kernel_takes_no_longer_for_large_batches(h):
             times.append(time.perf_counter() - t)
         return min(times)
     assert us(512) < 5 * us(8)
+
+
+@pytest.mark.parametrize("N,C,D,H,W,K", [(1, 96, 7, 23, 6, 136), (1, 128, 2, 25, 2, 152), (3, 144, 3, 17, 6, 128)])
+def test_a_volumes_workspace_holds_the_slices_of_the_kernel_that_runs(h, N, C, D, H, W, K):
+    """The kernels over filter taps read the volume in place, in more slices than the depth-unfolded problem takes."""
+    d = alt.conv3d_desc(N, C, D, H, W, K, 3, 3, 3, stride=(2, 1, 1), pad=1, in_dtype=alt.BF16, out_dtype=alt.BF16,
+                        x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+    n, k, od, oh, ow = h.conv3d_output_shape(d)
+    assert h.conv3d_workspace_size(d) >= 3 * n * k * od * oh * ow * 4
