@@ -348,9 +348,6 @@ static bool dslab_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     // (then the input pixel under an output pixel never moves backwards, and a depth tap is a whole number of planes)
     if (p.OH > p.H || p.OW > p.W || (v.T && v.OD != v.D)) return no("output larger than the input, or of another depth");
     if (phases > 1 && (p.OH != p.H || p.OW != p.W)) return no("output phases of another size than the input");
-    // (a volume this small is a handful of tiles either way: 64 channels on 4x9x9, 9.4 and 7.0 us over taps, 8.2 and 6.4 here, where 2028
-    // positions of 48 take 10.3 and 8.5; the tests hold small ones to the kernels over taps)
-    if (v.T && p.M < 1024) return no("volume of fewer than 1024 positions");
     // (the parameters are built for a launch alone: choosing a kernel asks about seven of these)
     IgemmLaunch t = k;
     t.kw = 1; t.prefetch = 2;

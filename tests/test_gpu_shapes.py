@@ -186,7 +186,7 @@ def test_slab_kernels_every_variant(h, N, C, H, W, K, R, pad, dil, yl):
         check_conv(h, N, C, H, W, K, R, 1, pad, dil, layouts=("NHWC", "OHWI", yl), variant=v)
 
 
-# 3-D and transposed convolutions on the kernels over filter taps: channel counts of whole and of broken K steps (and of one
+# 3-D and transposed convolutions on the kernels over filter taps and over slabs: channel counts of whole and of broken K steps (and of one
 # chunk), depth taps beside the channels, output phases of one to four taps per direction, tiles that end inside a phase;
 # the last two have taps that these kernels leave to the copying path (a dilated one, phases of unequal taps): several launches
 @pytest.mark.parametrize("dtype,out_dtype", [(alt.BF16, alt.F32), (alt.BF16, alt.BF16), (alt.F32, alt.F32)])
@@ -231,7 +231,7 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     if dil == 3 or (op, R, stride) == ("t3d", 3, 2):
         assert len(ran) > 1, ran
     else:
-        assert len(ran) == 1 and "dstream_kernel" in ran[0], ran
+        assert len(ran) == 1 and ("dstream_kernel" in ran[0] or "dslab_kernel" in ran[0]), ran
     got = np.moveaxis(host(y, np_out).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1)
     assert canary_ok(whole, ref.size), "wrote outside y"
     assert np.array_equal(got, ref)

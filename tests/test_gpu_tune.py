@@ -385,7 +385,7 @@ def test_a_tuned_problem_is_what_its_operator_runs(h):
             ws = torch.empty(need // 4 + 4, dtype=torch.float32, device="cuda")
             return kernels_run(lambda: getattr(h, name)(d, x, w, y, workspace=ws, ws_bytes=need))
 
-        assert [("dstream_kernel" in k) for k in call(ys[0])] == [True]
+        assert [("dstream_kernel" in k or "dslab_kernel" in k) for k in call(ys[0])] == [True]
         h.tune_conv2d_variants(f, arena, arena.numel(), max_trials=6, warmup=1, reps=2)
         assert f.variant >= 0 and h.conv2d_variant_name(f, -1) == h.conv2d_variant_name(f, f.variant)
         ran = call(ys[1])
