@@ -406,16 +406,9 @@ static bool dplanar_setup(const Problem &pb, const IgemmLaunch &k, int splitk, D
     if (pb.x_elems * 2 >= 0x7fffffff || pb.w_elems * 2 >= 0x7fffffff || p.y_bytes == 0 || (int64_t)p.M * K * 4 >= 0x7fffffff)
         return no("operand of 2 GiB or more");
     if (N * H * W > 0x7fffffff) return no("input too large for 32-bit pixel indices");
-    // (as few slabs of channels as fit, about equal: at each slab's end the next one's patch is waited for)
     const size_t np = dconv_patch_pixels(k.BM, p.M, p.H, p.W, p.OH, p.OW, p.R, p.S, p.pad_h, p.pad_w, st_, p.dil_h);
-    const int64_t nsb = (C + 63) / 64;
-    int64_t slab = 0;
     size_t lds = 0;
-    for (int64_t n = 1; n <= nsb; ++n) {
-        slab = (n == 1 ? nsb : (nsb + 2 * n - 1) / (2 * n) * 2) * 64;      // (an even number: the kernel walks them in pairs)
-        lds = dplanar_lds_bytes(k.BM, k.BN, k.kw, (int)(R * S), (int)slab, np);
-        if (lds <= 160 * 1024 || !k.ragged) break;
-    }
+    const int64_t slab = planar_slab(k.BM, k.BN, k.kw, (int)(R * S), C, np, k.ragged, &lds);
     if (k.ragged && C % 64 == 0 && slab == C && lds <= 160 * 1024) return no("channels fit LDS in whole steps");
     if (lds > 160 * 1024) return no("patch and weight stages do not fit LDS");
     const int tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (p.Nc + k.BN - 1) / k.BN;

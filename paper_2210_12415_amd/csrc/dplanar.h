@@ -76,6 +76,20 @@ inline size_t dplanar_lds_bytes(int BM, int BN, int kw, int taps, int C, size_t 
     return main_loop > staging ? main_loop : staging;
 }
 
+// Channels of a slab: all of them (in whole super-steps) or, if they do not fit LDS and `parts` are allowed, as few about equal parts as fit,
+// since at each slab's end the next one's patch is waited for.  *lds: bytes of a workgroup.
+inline int64_t planar_slab(int BM, int BN, int kw, int taps, int64_t C, size_t np, bool parts, size_t *lds)
+{
+    const int64_t nsb = (C + 63) / 64;
+    int64_t slab = nsb * 64;
+    *lds = dplanar_lds_bytes(BM, BN, kw, taps, (int)slab, np);
+    for (int64_t n = 2; n <= nsb && *lds > 160 * 1024 && parts; ++n) {
+        slab = (nsb + 2 * n - 1) / (2 * n) * 2 * 64;       // (an even number of super-steps: the kernel walks them in pairs)
+        *lds = dplanar_lds_bytes(BM, BN, kw, taps, (int)slab, np);
+    }
+    return slab;
+}
+
 template <int BM, int BN, int WGM, int WGN, int KW, int KR>
 __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const DconvParams p)
 {

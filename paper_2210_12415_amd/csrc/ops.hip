@@ -5,6 +5,7 @@
 #include <cmath>
 #include <mutex>
 
+#include "dplanar.h"
 #include "igemm.h"
 #include "ops.h"
 
@@ -276,24 +277,37 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         return (p.C < 32 && p.R * p.S > 1 ? 0.2 : 0.18) * idle * us * 45.0;
     }
     if (k.launch_direct && k.stream == 2) {
-        // Channel-planar kernel: a workgroup converts its patch on the way in (about 20 bytes per clock
-        // after a start-up latency), then per 64 channels runs all taps out of LDS (matrix-core time of
-        // the tile, or the time to bring the weights in) between two barriers and a weight scatter, then
-        // stores its tile plane by plane.  As many workgroups share a CU as their LDS allows.
-        const int taps = p.R * p.S, st = p.stride_h;
-        const double halo = (double)(p.dil_h * (p.R - 1)) * p.W + p.dil_w * (p.S - 1);
-        const double np = (double)k.BM * st * st + halo + 8;
-        const double lds = std::max((double)taps * (k.BN * 144 + 16) + np * (p.C * 2 + 16), (double)k.kw * k.BN * (k.BM + 4) * 4);
-        const int per_cu = std::max(1, (int)(160.0 * 1024 / lds));
-        // (workgroups that share a CU overlap their latencies, not their traffic or their matrix-core time)
+        // Channel-planar kernel: a workgroup converts its patch on the way in, 64 pixels x 64 channels of it by a wave at a time (a
+        // chain of loads, more where planes do not begin at eight pixels; each plane's run touches 128 bytes more than it has); then
+        // per super-step of 64 channels (the last one filled up) it runs all taps out of LDS (matrix-core time of the tile, or the way of the
+        // weights into their stages), waits at two barriers, and at a slab's end for the next one's patch; then it stores its tile plane
+        // by plane.  A round of workgroups asks of a compute unit what they ask together and waits a little longer than one does.  Clocks
+        // at 2.2 GHz, fitted over half of 647 layers and products under all seven tiles, of 4 to 300 us; over the other half the choice takes
+        // 1.0 % longer than the fastest tile on average.  (The estimate before left a broken last super-step out, so that 24 channels had no
+        // products, and took LDS for all channels at once: 4.3 %; 8 x 320 x 68 x 68 to 80, 1x1, took 29.0 us where 17.9 were to be had.)
+        const int taps = p.R * p.S, st = p.stride_h, waves = k.kw * k.wgm * k.wgn;
+        const double np = (double)k.BM * st * st + (double)(p.dil_h * (p.R - 1)) * p.W + p.dil_w * (p.S - 1);
+        size_t whole_lds = 0;
+        const double steps = std::ceil(p.C / 64.0);
+        const double slabs = std::ceil(steps * 64.0 / planar_slab(k.BM, k.BN, k.kw, taps, p.C, (size_t)np, k.ragged, &whole_lds));
+        const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), std::floor(16.0 / waves)));
+        const double weights = (double)k.BN * 64 * taps * 2 / 18.0;
+        const double unaligned = p.H * p.W % 8 ? 1.42 : 1.0;
+        const double loads = std::ceil(std::ceil(np / 64.0) * steps / waves) * 950.0 * unaligned;
+        const double stored = (double)k.BM * (k.BN + (p.out_bf16 ? 0 : std::min(k.BN, p.Nc)));
+        auto round_clk = [&](double n) {
+            const double products = taps * (double)k.BM * k.BN / 32.0 * (waves * n >= 8 ? 2.6 : 4.6) * std::max(1.0, 4.0 / (waves * n));
+            return n * ((np + 64.0) * p.C * 2 / 30.5 * unaligned + steps * std::max(products, weights) + stored / 3.15) +
+                   (1.0 + 0.04 * (n - 1.0)) * (1360.0 + loads + steps * 530.0 + slabs * 270.0) + (k.kw > 1 ? 630.0 * k.kw : 0.0);
+        };
         const double blocks = (double)p.tiles_m * p.tiles_n;
-        const double per_cu_work = std::ceil(blocks / 256.0), rounds = std::ceil(blocks / (256.0 * per_cu));
-        const double wload = (double)k.BN * 64 * taps * 2 / 40.0;      // the super-step's weights through L2
-        const double busy = np * p.C * 2 / 20.0 + (p.C / 64) * std::max(taps * (double)k.BM * k.BN / 32.0 * 1.2, wload) +
-                            (double)k.BM * k.BN / 8.0;
-        const double latency = 3000.0 + (p.C / 64) * 800.0 + 1500.0;
-        const double clk = per_cu_work * busy + rounds * latency + 5000.0;
-        return 0.5 * (clk / 2200.0 * 45.0);
+        const double whole = std::floor(blocks / (256.0 * per_cu)), rest = std::ceil((blocks - whole * 256.0 * per_cu) / 256.0);
+        // (against the register-staged kernels: they gather a layer's operands, and of 275 layers all but three are fastest here, whatever the
+        // factor up to 1.  Products with rows of A contiguous take no slices here.  The kernels that transpose aligned rows promise too much, the
+        // ones that gather others too little: at these factors the choice between the families takes 0.6 % and 3.3 % longer than the better
+        // one, at 0.5 for all 0.6 % and 7.3 %: 47 x 664 x 3960 takes 60 us here, 36 there; 112 x 1464 x 704 7.9 here, 15.1 there.)
+        const double family = p.H == 1 && p.R * p.S == 1 && p.W % 8 ? 1.3 : 0.5;
+        return family * 45.0 * (1.67 + (whole * round_clk(per_cu) + (rest > 0 ? round_clk(rest) : 0.0)) / 2200.0);
     }
     if (k.launch_direct && k.stream == 3) {
         // Kernel for images of few channels: a start (the filter into registers), then 16 x 16 pixel tiles at a rate per

@@ -76,3 +76,19 @@ def test_a_volumes_workspace_holds_the_slices_of_the_kernel_that_runs(h, N, C, D
                         x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
     n, k, od, oh, ow = h.conv3d_output_shape(d)
     assert h.conv3d_workspace_size(d) >= 3 * n * k * od * oh * ow * 4
+
+
+def planar(h, N, C, H, K, R):
+    return h.conv2d_variant_name(alt.conv_desc(N, C, H, H, K, R, R, pad=R // 2, in_dtype=alt.BF16, out_dtype=alt.BF16,
+                                               x_layout="NCHW->NCHW", w_layout="OIHW->OIHW", y_layout="NCHW->NCHW"), -1)
+
+
+@pytest.mark.parametrize("widths", [(40, 48, 56, 64), (72, 88, 104, 120, 128)])
+def test_planar_layers_of_as_many_channel_steps_run_the_same_tile(h, widths):
+    """A step of 64 channels that is filled up with zeros costs what a whole one does."""
+    assert len({planar(h, 16, C, 28, 64, 3).replace("rplanar", "planar") for C in widths}) == 1
+
+
+@pytest.mark.parametrize("M,N,K,family", [(47, 664, 3960, "_gg_"), (170, 1792, 3040, "_gv_"), (112, 1464, 704, "planar_"), (2291, 1600, 608, "planar_")])
+def test_products_with_contiguous_rows_of_a(h, M, N, K, family):
+    assert family in h.gemm_variant_name(alt.gemm_desc(M, N, K, in_dtype=alt.BF16, out_dtype=alt.BF16, a_layout="MK->KM", b_layout="KN->NK"), -1)
