@@ -109,9 +109,11 @@ static bool applicable(const Problem &pb, const IgemmLaunch &k, int splitk, Igem
         if (!dconv_setup(pb, k, splitk, nullptr, lds_bytes, why)) return false;
         if (p) {
             p->splitk = splitk;
-            const int64_t taps = pb.v.T ? (int64_t)pb.v.taps[0] * pb.v.taps[1] * pb.v.taps[2] : (int64_t)p0.R * p0.S;
-            p->ksteps_total = (int32_t)(k.taps ? (taps * p0.C + k.BK - 1) / k.BK : p0.R * p0.S * (p0.C / 64));
-            p->ksteps_per_split = (p->ksteps_total + splitk - 1) / splitk;
+            if (k.taps) {
+                const int64_t taps = pb.v.T ? (int64_t)pb.v.taps[0] * pb.v.taps[1] * pb.v.taps[2] : (int64_t)p0.R * p0.S;
+                p->ksteps_total = (int32_t)((taps * p0.C + k.BK - 1) / k.BK);
+                p->ksteps_per_split = (p->ksteps_total + splitk - 1) / splitk;
+            }
             p->tiles_m = (p0.M + k.BM - 1) / k.BM;
             p->tiles_n = (p0.Nc + k.BN - 1) / k.BN;
         }
@@ -317,23 +319,18 @@ double igemm_estimate(const Problem &pb, const IgemmLaunch &k, const IgemmParams
         const double us = k.BN == 32 ? 4.5 + std::max(tiles, 0.5) * (1.4 + 0.07 * k.prefetch) : 6.5 + std::max(tiles, 0.5) * (1.4 + 0.1 * k.prefetch);
         return 0.5 * us * 45.0;
     }
+    // Register-staged kernels: rounds of workgroups over the chip, their K steps, gathering and transposing loaders penalised.
     double mode_cost = 1.0;
     if (k.amode == LOAD_GATHER) mode_cost *= 6.0;
     if (k.bmode == LOAD_GATHER) mode_cost *= 3.0;
     if (k.amode == LOAD_TRANS) mode_cost *= 1.5;
     if (k.bmode == LOAD_TRANS) mode_cost *= 1.5;
     if (k.prefetch > 1) mode_cost *= 0.8;
-    if (k.launch_direct) mode_cost *= 0.5;
-    // (a 1x1 filter leaves the patch-resident kernel nothing to reuse: the streaming kernel runs the same
-    // problem without staging the patch first, and has measured faster wherever both apply)
-    if (k.launch_direct && p.R == 1 && p.S == 1) mode_cost *= 1.5;
     const double blocks = (double)p.tiles_m * p.tiles_n * p.splitk * p.batch;
     const double rounds = std::ceil(blocks / 512.0);
     const double step = (double)k.BM * k.BN * k.BK / 16384.0 + 3.0 * (k.BM + k.BN) * k.BK / 8192.0 + 2.0;
     double est = rounds * (p.ksteps_per_split * step + 60.0) * mode_cost;
-    if (p.splitk > 1) est += (k.launch_direct ? 5.0 : 30.0) + 0.00002 * p.splitk * (double)p.M * p.Nc * p.batch;
-    // (of one tap: what a split costs the streaming kernel, whose tail it shares)
-    if (p.splitk > 1 && k.launch_direct && p.R * p.S == 1) est += 70.0 + 22.5e-6 * p.splitk * p.M * (double)p.Nc * p.batch * 4.0;
+    if (p.splitk > 1) est += 30.0 + 0.00002 * p.splitk * (double)p.M * p.Nc * p.batch;
     return est;
 }
 
