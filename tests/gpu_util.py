@@ -117,3 +117,27 @@ def applicable_variants(h, d, kind="conv"):
             continue
         out.append((v, name))
     return out
+
+
+def panel_rows(M, N, BM, BN, a, b):
+    """Rows of tiles per panel in which an unsliced launch of bf16 tiles is numbered (order_tiles in dconv.hip): the divisor of all rows whose
+    window of consecutive tiles reads least, a and b bytes per row and column of tiles; all rows where that reads little or hardly less."""
+    tm, tn = -(-M // BM), -(-N // BN)
+    window = min((tm * tn + 7) // 8, tm * tn, 64)
+
+    def reads(pm):
+        panel = pm * tn
+        if panel >= window:
+            return min(pm, window) * a + -(-window // pm) * b
+        return min(pm * -(-window // panel), tm) * a + tn * b
+    best, least = tm, reads(tm) / 1.125
+    if reads(tm) > 2e6:
+        for pm in range(1, min(window, tm // 2) + 1):
+            if tm % pm == 0 and reads(pm) < least:
+                best, least = pm, reads(pm)
+    return best
+
+
+def tile_of(name):
+    """(BM, BN) of a variant name."""
+    return tuple(int(v) for v in name.split("_")[1].split("x")[:2])

@@ -941,7 +941,7 @@ def test_conv3d_transpose_gaussian_within_tolerance_and_errors(h):
 @pytest.mark.parametrize("out_dtype", [alt.F32, alt.BF16])
 def test_conv2d_add_fused_sum_exact_integers(h, out_dtype):
     """alt_conv2d_add: y = relu(conv + bias + addend) in one launch, every tile-kernel variant
-    (direct, streaming, K groups, split-K), ragged tiles; integers, so bit for bit the oracle's
+    (direct, streaming, over filter taps, over slabs, K groups, split-K), ragged tiles; integers, so bit for bit the oracle's
     convolution followed by its element-wise sum.  Descriptors the tile kernels do not cover fail."""
     for (N, C, H, W, K, R, cfg) in [(2, 64, 11, 9, 72, 3, dict(stride=1, pad=1)), (2, 128, 10, 7, 64, 1, dict(stride=1, pad=0)),
                                     (3, 64, 12, 10, 96, 3, dict(stride=2, pad=1))]:
@@ -960,8 +960,9 @@ def test_conv2d_add_fused_sum_exact_integers(h, out_dtype):
         xd, wd = dev(to_layout(f32_to_bf16_bits(x), "NCHW", "NHWC")), dev(to_layout(f32_to_bf16_bits(w), "OIHW", "OHWI"))
         ad, bd = dev(a_l), dev(b)
         ws = torch.empty(36 * n_out, dtype=torch.float32, device="cuda")
-        variants = [(v, n) for v, n in applicable_variants(h, d0) if "direct" in n or "stream" in n]
-        assert len(variants) >= 6
+        tile = lambda n: any(f in n for f in ("direct", "stream", "taps", "slab"))
+        variants = [(v, n) for v, n in applicable_variants(h, d0) if tile(n)]
+        assert len(variants) >= 6 and any("taps" in n for _, n in variants) and (R == 1 or cfg["stride"] == 2 or any("slab" in n for _, n in variants))
         for v, name in variants:
             import copy
             d = copy.copy(d0)
@@ -972,13 +973,14 @@ def test_conv2d_add_fused_sum_exact_integers(h, out_dtype):
             assert canary_ok(whole, n_out), name
             want = ref if out_dtype == alt.F32 else f32_to_bf16_bits(ref)
             assert np.array_equal(got, want), name
-        generic = [v for v, n in applicable_variants(h, d0) if "direct" not in n and "stream" not in n]
-        d = copy.copy(d0)
-        d.variant = generic[0]
-        whole, yd = canary_dev(n_out, ydt)
-        with pytest.raises(alt.AltError) as e:
-            h.conv2d_add(d, xd, wd, ad, yd, bias=bd, workspace=ws, ws_bytes=ws.numel() * 4)
-        assert e.value.status == 4
+        generic = [v for v, n in applicable_variants(h, d0) if not tile(n)]
+        assert generic
+        for v in generic:
+            d = copy.copy(d0)
+            d.variant = v
+            with pytest.raises(alt.AltError) as e:
+                h.conv2d_add(d, xd, wd, ad, yd, bias=bd, workspace=ws, ws_bytes=ws.numel() * 4)
+            assert e.value.status == 4
     # a layout only the implicit-GEMM kernels take: no variant applies
     d = alt.conv_desc(1, 32, 8, 8, 32, 3, 3, pad=1, in_dtype=alt.BF16)
     z = torch.zeros(1 << 14, dtype=torch.float32, device="cuda")

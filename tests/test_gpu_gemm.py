@@ -7,7 +7,7 @@ import oracle
 import paper_2210_12415_amd as alt
 from workloads import BERT_GEMMS, BERT_QKT, f32_to_bf16_bits, normal_f32, small_ints_f32
 
-from gpu_util import TOL, applicable_variants, canary_dev, canary_ok, dev, from_layout, host, rel_err, to_layout
+from gpu_util import TOL, applicable_variants, canary_dev, canary_ok, dev, from_layout, host, panel_rows, rel_err, tile_of, to_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -211,17 +211,20 @@ def test_kernels_over_filter_taps_every_step_count(h, dtype, bl):
     assert len(seen) >= 4
 
 
-@pytest.mark.parametrize("shape", [(1024, 1024, 840), (2560, 512, 328), (200, 64, 4104)], ids=lambda s: "%dx%dx%d" % s)
+@pytest.mark.parametrize("shape", [(1, 1024, 1024, 840), (1, 2560, 512, 328), (1, 1024, 896, 2056), (2, 2560, 512, 328)],
+                         ids=lambda s: "%dx%dx%dx%d" % s)
 @pytest.mark.parametrize("bl", ["NK", "KN"])
 def test_every_tile_of_a_panel_order(h, shape, bl):
-    """Enough tiles and bytes that tiles are numbered in panels of rows, and more columns of tiles than rows: every tile once, bit for bit."""
-    M, K, N = shape
-    A, B = small_ints_f32(81, (1, M, K), -3, 3), small_ints_f32(82, (1, K, N), -3, 3)
+    """Enough tiles and bytes that tiles are numbered in panels of rows, more rows of tiles than columns and fewer, one entry and two: every
+    tile once, bit for bit."""
+    batch, M, K, N = shape
+    A, B = small_ints_f32(81, (batch, M, K), -3, 3), small_ints_f32(82, (batch, K, N), -3, 3)
     ref = oracle.gemm(A, B)
     Ab, Bb = f32_to_bf16_bits(A), f32_to_bf16_bits(B)
-    d0 = alt.gemm_desc(M, N, K, in_dtype=alt.BF16, a_layout="MK->MK", b_layout="KN->" + bl, c_layout="MN->MN")
+    d0 = alt.gemm_desc(M, N, K, batch=batch, in_dtype=alt.BF16, a_layout="MK->MK", b_layout="KN->" + bl, c_layout="MN->MN")
     variants = [(v, n) for v, n in applicable_variants(h, d0, "gemm") if ("stream" in n or "rtaps" in n) and n.endswith("_k1")]
-    assert any("64x64" in n for _, n in variants)
+    panels = [panel_rows(M, N, *tile_of(n), 2 * K * tile_of(n)[0], 2 * K * tile_of(n)[1]) < -(-M // tile_of(n)[0]) for _, n in variants]
+    assert sum(panels) >= 5
     for v, name in variants:
         got, _ = run_gemm(h, Ab, Bb, "MK", bl, "MN", alt.BF16, variant=v)
         assert np.array_equal(got, ref), name

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2210_12415_amd as alt
-from gpu_util import applicable_variants, canary_dev, canary_ok, dev, from_layout, host, kernels_run, to_layout
+from gpu_util import applicable_variants, canary_dev, canary_ok, dev, from_layout, host, kernels_run, panel_rows, tile_of, to_layout
 from workloads import f32_to_bf16_bits, small_ints_f32
 
 pytestmark = pytest.mark.gpu
@@ -237,6 +237,30 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     assert np.array_equal(got, ref)
 
 
+# 3x3 layers whose tiles are numbered in panels of rows (order_tiles): patch-resident kernels over all channels, over slabs and for planar
+# operands, and those over filter taps; the last column of tiles is eight channels wide
+@pytest.mark.parametrize("layouts,families", [(("NHWC", "OHWI", "NHWC"), ("_direct_", "_slab_", "taps_")), (("NCHW", "OIHW", "NCHW"), ("planar_",))])
+def test_every_tile_of_a_panel_order_of_layers(h, layouts, families):
+    N, C, H, K, R = 40, 512, 16, 72, 3
+    x, w = small_ints_f32(61, (N, C, H, H), -3, 3), small_ints_f32(62, (K, C, R, R), -3, 3)
+    ref = oracle.conv2d(x, w, stride=1, pad=1)
+    xl, wl, yl = layouts
+    lay = dict(pad=1, in_dtype=alt.BF16, out_dtype=alt.F32, x_layout="NCHW->" + xl, w_layout="OIHW->" + wl, y_layout="NCHW->" + yl)
+    xd, wd = dev(to_layout(f32_to_bf16_bits(x), "NCHW", xl)), dev(to_layout(f32_to_bf16_bits(w), "OIHW", wl))
+    seen = set()
+    for v, name in applicable_variants(h, alt.conv_desc(N, C, H, H, K, R, R, **lay)):
+        family = next((f for f in families if f in name), None)
+        bm, bn = tile_of(name)
+        if not family or not name.endswith("_k1") or panel_rows(N * H * H, K, bm, bn, 2 * C * bm, 2 * C * 9 * bn) == -(-N * H * H // bm):
+            continue
+        print(name, flush=True)
+        whole, y = canary_dev(ref.size, np.float32)
+        h.conv2d(alt.conv_desc(N, C, H, H, K, R, R, variant=v, **lay), xd, wd, y)
+        assert canary_ok(whole, ref.size) and np.array_equal(from_layout(host(y, np.float32), ref.shape, "NCHW", yl), ref), name
+        seen.add(family)
+    assert seen == set(families)
+
+
 # volumes and output phases large enough for the slab kernels: depth taps outside the volume, a last slab of eight channels, tiles that end
 # inside a plane, a phase and an image
 @pytest.mark.parametrize("op,N,C,D,H,W,K,T,R,stride,pad,dil", [
@@ -244,13 +268,14 @@ def test_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, S, stride, pad
     ("c3d", 3, 32, 9, 15, 14, 64, 3, 3, 1, (2, 2, 2), 2), ("c3d", 1, 64, 9, 20, 19, 136, 3, 3, 1, (1, 0, 0), 1),
     ("t3d", 2, 24, 8, 24, 23, 20, 4, 4, 2, 1, 1), ("t3d", 3, 72, 7, 19, 21, 64, 4, 4, 2, 1, 1),
     ("t2d", 6, 48, 1, 44, 41, 36, 1, 4, 2, 1, 1), ("t2d", 5, 136, 1, 34, 51, 64, 1, 4, 2, 1, 1)])
-def test_larger_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, stride, pad, dil):
+@pytest.mark.parametrize("out_dtype", [alt.BF16, alt.F32])
+def test_larger_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, stride, pad, dil, out_dtype):
     x, b = small_ints_f32(71, (N, C, D, H, W), -3, 3), small_ints_f32(73, (K,), -20, 20)
     w = small_ints_f32(72, ((K, C) if op == "c3d" else (C, K)) + (T, R, R), -3, 3)
     each = lambda v, first: (first, v, v) if op == "t2d" else v
     fn = oracle.conv3d if op == "c3d" else oracle.conv3d_transpose
     ref = np.maximum(fn(x, w, stride=each(stride, 1), pad=each(pad, 0), dil=each(dil, 1)) + b[None, :, None, None, None], np.float32(0))
-    lay = dict(in_dtype=alt.BF16, out_dtype=alt.BF16, epilogue=alt.EPI_BIAS | alt.EPI_RELU, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI",
+    lay = dict(in_dtype=alt.BF16, out_dtype=out_dtype, epilogue=alt.EPI_BIAS | alt.EPI_RELU, x_layout="NCHW->NHWC", w_layout="OIHW->OHWI",
                y_layout="NCHW->NHWC", stride=stride, pad=pad, dil=dil)
     d = alt.conv_desc(N, C, H, W, K, R, R, **lay) if op == "t2d" else alt.conv3d_desc(N, C, D, H, W, K, T, R, R, **lay)
     name, pack = {"c3d": ("conv3d", h.pack_weights3d), "t3d": ("conv3d_transpose", h.pack_weights3d_transpose),
@@ -258,7 +283,9 @@ def test_larger_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, stride,
     wshape = (K, C * T, R, R) if op == "c3d" else getattr(h, name + "_weight_shape")(d)
     wd = dev(np.zeros(int(np.prod(wshape)), np.uint16))
     pack(d, dev(f32_to_bf16_bits(w.reshape(-1))), wd)
-    whole, y = canary_dev(ref.size, np.uint16)
+    np_out = np.uint16 if out_dtype == alt.BF16 else np.float32
+    ref = f32_to_bf16_bits(ref) if out_dtype == alt.BF16 else ref
+    whole, y = canary_dev(ref.size, np_out)
     ws_bytes = getattr(h, name + "_workspace_size")(d)
     ws = dev(np.zeros(max(4, ws_bytes // 4), np.float32))
     xd, bd = dev(f32_to_bf16_bits(np.ascontiguousarray(np.moveaxis(x, 1, -1)).reshape(-1))), dev(b)
@@ -266,7 +293,7 @@ def test_larger_volumes_and_output_phases(h, op, N, C, D, H, W, K, T, R, stride,
     ran = kernels_run(lambda: getattr(h, name)(d, xd, wd, y, bias=bd, workspace=ws, ws_bytes=ws_bytes))
     assert len(ran) == 1 and "dslab_kernel" in ran[0], ran
     assert canary_ok(whole, ref.size), "wrote outside y"
-    assert np.array_equal(np.moveaxis(host(y, np.uint16).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1), f32_to_bf16_bits(ref))
+    assert np.array_equal(np.moveaxis(host(y, np_out).reshape(ref.shape[:1] + ref.shape[2:] + (K,)), -1, 1), ref)
 
 
 # single precision: the library's own choice among tiles, K groups and slices (remainders in all of them), with the workspace that

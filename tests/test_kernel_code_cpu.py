@@ -1,7 +1,7 @@
-"""Branches of the built streaming kernels (dstream.h), read from their machine code.  Their operand reads from LDS complete behind
-the compiler's back, and the compiler copies registers where paths join: a copy of a register whose read is in flight copies stale
-data.  So the kernels with row-major B may not branch at all between such a read and its wait, and the others not more often
-than the loop over the stages needs."""
+"""Branches of the built tile kernels (dstream.h, dslab.h, dplanar.h), read from their machine code.  Their operand reads from LDS
+complete behind the compiler's back, and the compiler copies registers where paths join: a copy of a register whose read is in flight
+copies stale data.  So the streaming kernels with row-major B, the slab and the planar kernels may not branch at all between such a
+read and its wait, and the other streaming kernels not more often than the loop over the stages needs."""
 import os
 import re
 import subprocess
@@ -13,23 +13,26 @@ import paper_2210_12415_amd as alt
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
-def streaming_kernels(folder):
-    """name -> [(address, operation, operands)] of every streaming kernel in the library."""
+FAMILIES = ("dstream_kernel", "dslab_kernel", "dplanar_kernel")
+
+
+def tile_kernels(folder):
+    """family -> template arguments -> [(address, operation, operands)] of every kernel of these families in the library."""
     lib = os.path.join(os.path.dirname(alt.__file__), "libalt.so")
     os.symlink(lib, os.path.join(folder, "lib.so"))
     subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=folder, check=True, capture_output=True)
-    out = {}
+    out = {k: {} for k in FAMILIES}
     for f in sorted(os.listdir(folder)):
         path = os.path.join(folder, f)
-        if "gfx950" not in f or b"dstream_kernel" not in open(path, "rb").read():
+        if "gfx950" not in f or not any(k.encode() in open(path, "rb").read() for k in FAMILIES):
             continue
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--demangle", path], check=True, capture_output=True, text=True).stdout
         code = None
         for line in text.splitlines():
             head = re.match(r"^[0-9a-f]+ <(.*)>:$", line)
             if head:
-                name = re.search(r"dstream_kernel<(.*)>\(", head.group(1))
-                code = out.setdefault(name.group(1), []) if name else None
+                name = re.search(r"(%s)<(.*)>\(" % "|".join(FAMILIES), head.group(1))
+                code = out[name.group(1)].setdefault(name.group(2), []) if name else None
             elif code is not None:
                 m = re.match(r"^\s+(\S+)\s*(.*?)\s*//\s*([0-9A-F]+)", line)
                 if m:
@@ -37,19 +40,21 @@ def streaming_kernels(folder):
     return out
 
 
-def branches_with_reads_in_flight(code):
+def branches_with_reads_in_flight(code, writes_end=True, most=None):
     """Indices of the branches of the main loop that some path reaches with operand reads in flight.  (It ends with the last matrix
-    instruction, and a write to LDS opens the epilogue: the compiler keeps the waits of its own reads there.)"""
+    instruction; in the streaming kernels, which write nothing to LDS themselves before, also with the write that opens the epilogue: the
+    compiler keeps the waits of its own reads there.)  most: filled with the instructions reached and the reads in flight there."""
     at = {a: i for i, (a, _, _) in enumerate(code)}
     end = max(i for i, (_, op, _) in enumerate(code) if "mfma" in op)
-    most, todo, found = {}, [(0, 0)], set()
+    most = {} if most is None else most
+    todo, found = [(0, 0)], set()
     while todo:
         i, reads = todo.pop()
         if most.get(i, -1) >= reads:
             continue
         most[i] = reads
         address, op, text = code[i]
-        if op == "s_endpgm" or op.startswith("ds_write") or i > end:
+        if op == "s_endpgm" or (writes_end and op.startswith("ds_write")) or i > end:
             continue
         if op.startswith("ds_read"):
             reads += 1
@@ -70,21 +75,30 @@ def branches_with_reads_in_flight(code):
 def kernels(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
-    found = streaming_kernels(str(tmp_path_factory.mktemp("code")))
-    assert len(found) > 40
+    found = tile_kernels(str(tmp_path_factory.mktemp("code")))
+    assert len(found["dstream_kernel"]) > 40
     return found
 
 
 def test_row_major_b_kernels_do_not_branch_with_reads_in_flight(kernels):
-    row_major = {n: c for n, c in kernels.items() if n.split(", ")[7] == "true"}
+    row_major = {n: c for n, c in kernels["dstream_kernel"].items() if n.split(", ")[7] == "true"}
     assert {n.split(", ")[8] for n in row_major} == {"0", "4"}
     for name, code in row_major.items():
         assert not branches_with_reads_in_flight(code), name
 
 
 def test_kernels_over_filter_taps_branch_for_the_stages_alone(kernels):
-    taps = {n: c for n, c in kernels.items() if n.split(", ")[8] != "0"}
+    taps = {n: c for n, c in kernels["dstream_kernel"].items() if n.split(", ")[8] != "0"}
     assert len(taps) >= 20
     for name, code in taps.items():
         # the loop over whole rounds, and each step of the last one is entered or left out
         assert len(branches_with_reads_in_flight(code)) <= 2 * int(name.split(", ")[5]) + 1, name
+
+
+@pytest.mark.parametrize("family,count", [("dslab_kernel", 42), ("dplanar_kernel", 14)])
+def test_slab_and_planar_kernels_do_not_branch_with_reads_in_flight(kernels, family, count):
+    assert len(kernels[family]) >= count
+    for name, code in kernels[family].items():
+        most = {}
+        assert not branches_with_reads_in_flight(code, writes_end=False, most=most), name
+        assert max(i for i, (_, op, _) in enumerate(code) if "mfma" in op) in most and max(most.values()) >= 2, name    # the loop was walked, with reads in flight
