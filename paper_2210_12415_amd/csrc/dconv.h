@@ -122,8 +122,8 @@ constexpr int kPanelShift = 4;    // (rows of tiles: at most 2^31 / 64)
 // The tile and the slice of channels of this workgroup.  Consecutive logical numbers share an XCD and its L2 and run at
 // about the same time; they walk down a panel's rows of tiles and then across, so that they cover a block of rows and columns of
 // the output and the operands come into that L2 once for many tiles.  (In columns of all rows, the order before, each of the eight
-// XCDs fetched all of the activations: 2048 x 768 x 3072 in 128x64 tiles, 106 MB instead of 44, 19.4 us and now 17.0; 1000 x 640 x
-// 2560 12.7 and now 8.1; 4096^3 111.6 and now 104.2.)  Panels are equal, so that this takes no more divisions and kernel arguments than plain columns: a last
+// XCDs fetched all of the activations: 2048 x 768 x 3072 in 128x64 tiles, 107 MB instead of 44, 19.4 us and now 17.0; 1000 x 640 x
+// 2560 12.7 and now 8.1; 4096^3 111 to 113 and now 104 to 108.)  Panels are equal, so that this takes no more divisions and kernel arguments than plain columns: a last
 // panel of fewer rows took two of each more and cost launches of 5 us 0.1 to 0.3.
 // fp32 tiles stay in columns (PANELS = false): their matrix instructions take far longer than their operands.
 template <bool PANELS = true>
