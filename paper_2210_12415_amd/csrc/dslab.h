@@ -90,9 +90,9 @@ void dslab_kernel(const DconvParams p)
     const int wm = wq / WGN, wn = wq % WGN;
 
     int mt, nt;
-    // (the number of tiles as the grid has it costs a load and saves scalar registers: with K groups, whose kernels spill up to twenty of
-    // them, a 3x3x3 layer of 128 channels takes 16.9 us so and 17.1 with the product; the others take 0.5 % longer so)
-    dconv_tile_unsliced(p, KW > 1 ? (int)gridDim.x : p.tiles_m * p.tiles_n, mt, nt);
+    // (the number of tiles as the grid has it costs a load and saves up to 17 spilled scalar registers: 3x3x3 over 128 channels 16.9 us, 17.1 with
+    // the product; 62 x 80 x 17 x 17, 3x3, 11.4 and 11.9.  Layers of 256 images that run 256x128 tiles take 0.5 % longer so.)
+    dconv_tile_unsliced(p, BN < 128 ? (int)gridDim.x : p.tiles_m * p.tiles_n, mt, nt);
     const int m0 = mt * BM, n0 = nt * BN;
     int f_d = 0, f_h = 0, f_w = 0;                         // the phase's first tap in the common window
     int64_t y_phase = 0;
