@@ -392,7 +392,7 @@ alt_status_t alt_pack_weights_transpose(alt_handle_t h, const alt_conv_desc_t *d
  * must divide T*C as they would C.  T = 1 with stride_d = 1 and pad_d = 0 is alt_conv2d on x itself.
  * In place: over dense NHWC slices with an OHWI filter, C a multiple of 16 bytes and K of 4, the depth is one more
  * direction of taps and x is read where it lies, in one launch, unless the 2-D problem has a tuned variant (that fits)
- * or the descriptor names one (128 channels, 3x3x3, 8x28x28, batch 2: 23.5 us in place, 35.2 tuned).
+ * or the descriptor names one (128 channels, 3x3x3, 8x28x28, batch 2: 16.7 us in place, 35.2 tuned).
  * `workspace` (device, 16-byte aligned) holds x' followed by what alt_conv2d wants, or the partial sums of the one launch;
  * alt_conv3d_workspace_size reports the larger, less than x' fails with ALT_WORKSPACE_TOO_SMALL.
  * groups > 1 is ALT_UNSUPPORTED.  alt_conv3d_output_shape writes (N, K, OD, OH, OW).

@@ -694,7 +694,7 @@ static alt_status_t conv2d_impl(alt_handle_t h, const alt_conv_desc_t *d, const 
 namespace alt {
 // (a depth-unfolded copy of the input costs T times its traffic, a merged filter all products of the common window, 9/4 of those
 // that are not zeros for 4x4 at stride 2 and 27/8 for 4x4x4, and its result one more pass into place: 128 channels, 3x3x3 on
-// 8x28x28 at batch 2 took 48 us that way and 26 here, T3D 128 -> 64, 4x4x4 at stride 2 on the same volume 128 us and 34; so these
+// 8x28x28 at batch 2 took 48 us that way and 16.7 here, T3D 128 -> 64, 4x4x4 at stride 2 on the same volume 128 us and 21; so these
 // kernels run whatever they cover, unless the problem's 2-D form has been tuned to a variant of its own)
 static bool taps_problem(alt_handle_t h, const TapsCall &c, const void *x, const void *w, const float *bias, void *y, int64_t ws_2d, Problem *out)
 {
