@@ -309,12 +309,15 @@ typedef struct {
 
 /* Issues n convolutions that do not depend on one another (operators of a computational
  * graph with no path between them, Section 2.2's graph view; e.g. a residual block's
- * projection shortcut beside its main branch), the i-th exactly as
+ * projection shortcut beside its main branch), the i-th as
  * alt_conv2d(h, calls[i].d, ...) on calls[i].stream.  Calls given different streams may
  * run on the GPU at the same time, so a kernel that cannot fill the chip alone shares it
  * and one call's start-up overlaps another's tail; ordering between the streams is the
- * caller's (events or stream synchronisation).  The outputs and workspaces must not
- * overlap.  Stops at the first call that fails and returns its status; the calls before
+ * caller's (events or stream synchronisation).  Consecutive calls on one stream with
+ * variant = -1 and no tuned kernel may go out as one launch (up to eight; bf16 NHWC or NCHW,
+ * or fp32 NHWC, 3x3 and 1x1 filters among others): then the library chooses their tiles together, within
+ * the workspaces given, and calls whose buffers overlap still run one after the other.
+ * The outputs and workspaces must not overlap.  Stops at the first call that fails and returns its status; the calls before
  * it stay issued. */
 alt_status_t alt_conv2d_multi(alt_handle_t h, const alt_conv_call_t *calls, int32_t n);
 alt_status_t alt_conv2d_output_shape(const alt_conv_desc_t *d, int64_t *out_nkhw);

@@ -127,9 +127,9 @@ constexpr int kPanelShift = 4;    // (rows of tiles: at most 2^31 / 64)
 // panel of fewer rows took two of each more and cost launches of 5 us 0.1 to 0.3.
 // fp32 tiles stay in columns (PANELS = false): their matrix instructions take far longer than their operands.
 template <bool PANELS = true>
-__device__ __forceinline__ void dconv_tile(const DconvParams &p, int &mt, int &nt, int &split)
+__device__ __forceinline__ void dconv_tile(const DconvParams &p, int bx, int &mt, int &nt, int &split)
 {
-    const int logical = igemm_logical_tile(p.tiles_m * p.tiles_n * p.splitk);
+    const int logical = igemm_logical_tile(p.tiles_m * p.tiles_n * p.splitk, bx);
     const int rest = (int)div32((uint32_t)logical, p.d_pm), o = (int)div32((uint32_t)rest, p.d_tn);
     nt = rest - o * p.tiles_n;
     if constexpr (PANELS) {
@@ -142,9 +142,9 @@ __device__ __forceinline__ void dconv_tile(const DconvParams &p, int &mt, int &n
     }
 }
 // The same for a kernel that takes no slices, out of `tiles` tiles.
-__device__ __forceinline__ void dconv_tile_unsliced(const DconvParams &p, int tiles, int &mt, int &nt)
+__device__ __forceinline__ void dconv_tile_unsliced(const DconvParams &p, int tiles, int bx, int &mt, int &nt)
 {
-    const int logical = igemm_logical_tile(tiles);
+    const int logical = igemm_logical_tile(tiles, bx);
     const int rest = (int)div32((uint32_t)logical, p.d_pm), o = (int)div32((uint32_t)rest, p.d_tn);
     nt = rest - o * p.tiles_n;
     mt = logical - (rest - o) * (int)((uint32_t)p.flags >> kPanelShift);
@@ -668,7 +668,7 @@ void dconv_kernel(const DconvParams p)
 
     // workgroup -> (m tile, n tile, channel slice)
     int mt, nt, split;
-    dconv_tile(p, mt, nt, split);
+    dconv_tile(p, (int)blockIdx.x, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
 
     const i32x4_t x_rsrc = make_rsrc(p.x, p.x_bytes);

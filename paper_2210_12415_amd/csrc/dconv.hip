@@ -7,6 +7,7 @@
 #include "dslab.h"
 #include "dstem.h"
 #include "dstream.h"
+#include "group.h"
 #include "ops.h"
 
 namespace alt {
@@ -560,20 +561,43 @@ bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParam
     return true;
 }
 
+// The arrival counters of launches on `st`.
+static hipError_t stream_counters(hipStream_t st, uint32_t **out)
+{
+    uint32_t *base = nullptr;
+    hipError_t e = dconv_counters(&base);
+    if (e != hipSuccess) return e;
+    int slot = 0;
+    e = counter_slot(device_state(), st, &slot);
+    if (e != hipSuccess) return e;
+    *out = base + (size_t)slot * kDconvMaxTiles;
+    return hipSuccess;
+}
+
 hipError_t dconv_run(const IgemmLaunch &k, DconvParams d, size_t lds, float *partial, hipStream_t st)
 {
     if (d.splitk > 1 && k.stream != 3) {
-        uint32_t *base = nullptr;
-        hipError_t e = dconv_counters(&base);
+        hipError_t e = stream_counters(st, &d.counters);
         if (e != hipSuccess) return e;
-        DeviceState *ds = device_state();
-        int slot = 0;
-        e = counter_slot(ds, st, &slot);
-        if (e != hipSuccess) return e;
-        d.counters = base + (size_t)slot * kDconvMaxTiles;
         d.partial = partial;
     }
     return k.launch_direct(d, lds, st);
+}
+
+// A problem's sliced tiles in a launch of several have counters of their own.
+hipError_t group_run(const GroupFamily &f, GroupParams *g, unsigned workgroups, size_t lds, hipStream_t st)
+{
+    uint32_t *counters = nullptr;
+    for (int i = 0; i < g->n; ++i) {
+        if (g->p[i].splitk <= 1) continue;
+        if (!counters) {
+            const hipError_t e = stream_counters(st, &counters);
+            if (e != hipSuccess) return e;
+        }
+        g->p[i].counters = counters;
+        counters += g->p[i].tiles_m * g->p[i].tiles_n;
+    }
+    return f.launch(*g, workgroups, lds, st);
 }
 
 }  // namespace alt

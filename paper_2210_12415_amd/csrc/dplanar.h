@@ -91,7 +91,7 @@ inline int64_t planar_slab(int BM, int BN, int kw, int taps, int64_t C, size_t n
 }
 
 template <int BM, int BN, int WGM, int WGN, int KW, int KR>
-__global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const DconvParams p)
+__device__ __forceinline__ void dplanar_body(const DconvParams &p, int bx)
 {
     constexpr int NWG = WGM * WGN, NW = NWG * KW, NT = 64 * NW;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
     const int wm = wq / WGN, wn = wq % WGN;
 
     int mt, nt;
-    dconv_tile_unsliced(p, p.tiles_m * p.tiles_n, mt, nt);
+    dconv_tile_unsliced(p, p.tiles_m * p.tiles_n, bx, mt, nt);
     const int m0 = mt * BM, n0 = nt * BN;
     const uint16_t *xg = (const uint16_t *)p.x;
     const int HW = p.H * p.W;
@@ -522,6 +522,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const Dcon
             }
         }
     }
+}
+
+template <int BM, int BN, int WGM, int WGN, int KW, int KR>
+__global__ __launch_bounds__(64 * WGM * WGN * KW) void dplanar_kernel(const DconvParams p)
+{
+    dplanar_body<BM, BN, WGM, WGN, KW, KR>(p, (int)blockIdx.x);
 }
 
 template <int BM, int BN, int WGM, int WGN, int KW, int KR>

@@ -65,8 +65,7 @@ constexpr int slab_loads_behind(int tap)
 }
 
 template <int BM, int BN, int WGM, int WGN, int KW, int BK, int KR, int PN>
-__global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM) * (BN / WGN) / 64, WGM * WGN * KW))
-void dslab_kernel(const DconvParams p)
+__device__ __forceinline__ void dslab_body(const DconvParams &p, int tiles, int bx, int by)
 {
     constexpr int NWG = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
@@ -90,14 +89,12 @@ void dslab_kernel(const DconvParams p)
     const int wm = wq / WGN, wn = wq % WGN;
 
     int mt, nt;
-    // (the number of tiles as the grid has it costs a load and saves up to 17 spilled scalar registers: 3x3x3 over 128 channels 16.9 us, 17.1 with
-    // the product; 62 x 80 x 17 x 17, 3x3, 11.4 and 11.9.  Layers of 256 images that run 256x128 tiles take 0.5 % longer so.)
-    dconv_tile_unsliced(p, BN < 128 ? (int)gridDim.x : p.tiles_m * p.tiles_n, mt, nt);
+    dconv_tile_unsliced(p, tiles, bx, mt, nt);
     const int m0 = mt * BM, n0 = nt * BN;
     int f_d = 0, f_h = 0, f_w = 0;                         // the phase's first tap in the common window
     int64_t y_phase = 0;
     if (p.phases > 1) {
-        const uint32_t bz = blockIdx.y;
+        const uint32_t bz = (uint32_t)by;
         const uint32_t pd = div32(bz, p.d_phw), phw = bz - pd * (uint32_t)(p.ph_sh * p.ph_sw);
         const uint32_t ph = div32(phw, p.d_phs), pw = phw - ph * (uint32_t)p.ph_sw;
         f_d = (int)div32(pd + (uint32_t)p.ph_pad_d, p.d_phd) + p.ph_first_d;
@@ -106,7 +103,7 @@ void dslab_kernel(const DconvParams p)
         y_phase = (int64_t)(pd * p.y_pd + ph * p.y_ph + pw * p.y_pw) * (p.flags & kDconvOutBf16 ? 2 : 4);
     }
     const i32x4_t x_rsrc = make_rsrc(p.x, p.x_bytes);
-    const i32x4_t w_rsrc = make_rsrc((const char *)p.w + (int64_t)blockIdx.y * p.w_bstride, p.w_bytes);
+    const i32x4_t w_rsrc = make_rsrc((const char *)p.w + (int64_t)by * p.w_bstride, p.w_bytes);
 
     // ---- the patch: pixels a0 + s_min .. of the planes the tile's outputs lie in (before the depth tap's shift) -----------
     const int HW = p.H * p.W, ohw = p.OH * p.OW;
@@ -291,6 +288,15 @@ void dslab_kernel(const DconvParams p)
     wait_vmcnt<0>();                                       // the loads past the last slab
 
     dconv_epilogue<BM, BN, WGM, WGN, KW>(p, acc, smem_u4, t, lane, wave, kg, wq, wm, wn, m0, n0, mt, nt, 0, (char *)p.y + y_phase);
+}
+
+template <int BM, int BN, int WGM, int WGN, int KW, int BK, int KR, int PN>
+__global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM) * (BN / WGN) / 64, WGM * WGN * KW))
+void dslab_kernel(const DconvParams p)
+{
+    // (the number of tiles as the grid has it costs a load and saves up to 17 spilled scalar registers: 3x3x3 over 128 channels 16.9 us, 17.1 with
+    // the product; 62 x 80 x 17 x 17, 3x3, 11.4 and 11.9.  Layers of 256 images that run 256x128 tiles take 0.5 % longer so.)
+    dslab_body<BM, BN, WGM, WGN, KW, BK, KR, PN>(p, BN < 128 ? (int)gridDim.x : p.tiles_m * p.tiles_n, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 template <int BM, int BN, int WGM, int WGN, int KW, int BK, int KR, int PN>

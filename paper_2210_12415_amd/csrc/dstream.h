@@ -48,9 +48,11 @@ namespace alt {
 // workgroup's slice in steps of BK (64 or 32; half of that for float), through a ring of NS stages of its own.
 // While a step computes, NS - 2 later stages are in flight: deep rings of small stages
 // (BK = 32) cover the load latency with the same LDS as shallow rings of large ones.
-template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false, int TAPS = kNoTaps, typename T = bf16_tag>
-__global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM) * (BN / WGN) / 64, WGM * WGN * KW))
-void dstream_kernel(const DconvParams p)
+// NACC = 4 (fp32 wave tiles of one matrix tile): four sums, each over every fourth product, added at the end.  They make up for the K groups
+// that a launch of several problems (group.h) does without: layers of 32 to 128 channels are 2.0e-7 from 64 bits in the 2-norm so, 3.3e-7 with
+// one sum, 3.4e-7 in launches of their own.  (Those keep one: four cost them 0.5 to 2 %.)
+template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false, int TAPS = kNoTaps, typename T = bf16_tag, int NACC = 1>
+__device__ __forceinline__ void dstream_body(const DconvParams &p, int bx, int bz)
 {
     constexpr int ES = ElemTraits<T>::SIZE;                // bytes per element
     constexpr bool kRagged = TAPS >= kTapsRagged;
@@ -92,9 +94,8 @@ void dstream_kernel(const DconvParams p)
 
     // workgroup -> (m tile, n tile, channel slice), as in the direct convolution
     int mt, nt, split;
-    dconv_tile<ES == 2>(p, mt, nt, split);
+    dconv_tile<ES == 2>(p, bx, mt, nt, split);
     const int m0 = mt * BM, n0 = nt * BN;
-    const int bz = blockIdx.y;                             // batch entry, or output phase
     // the phase's first tap in the common window (depth, row, column) and the offset of its first output
     int f_d = 0, f_h = 0, f_w = 0;
     int64_t y_phase = 0;
@@ -292,13 +293,18 @@ void dstream_kernel(const DconvParams p)
         }
     }
 
-    floatx16_t acc[TM][TN];
+    static_assert(NACC == 1 || (NACC == 4 && ES == 4 && TM * TN == 1), "sums");
+    floatx16_t acc[TM][TN], more[NACC];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+#pragma unroll
+    for (int a = 1; a < NACC; ++a)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) more[a][e] = 0.f;
 
     // Operand reads run D k-chunks ahead of the MFMAs that use them; k chunk g (counted
     // from the start of a round over the stages) uses register buffer g % NBUF.
@@ -377,7 +383,8 @@ void dstream_kernel(const DconvParams p)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const f32x4_t fb = __builtin_bit_cast(f32x4_t, b), fa = __builtin_bit_cast(f32x4_t, a);
-                c = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[j], c, 0, 0, 0);
+                floatx16_t &sum = NACC == 1 || j % NACC == 0 ? c : more[j % NACC];
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[j], sum, 0, 0, 0);
             }
         }
     };
@@ -453,6 +460,10 @@ void dstream_kernel(const DconvParams p)
         });
     }
 
+    if constexpr (NACC > 1) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[0][0][e] = (acc[0][0][e] + more[1][e]) + (more[2][e] + more[3][e]);
+    }
     wait_vmcnt<0>();                                       // the repeated loads past the last step
     // the look-ahead reads past the last step still land in their registers: tie them to a wait (with BT every read is consumed, and
     // the ties would only keep registers: 100 bytes a lane spilled in the largest tile)
@@ -475,6 +486,13 @@ void dstream_kernel(const DconvParams p)
         dconv_epilogue<BM, BN, WGM, WGN, KW>(p, acc, smem_u4, t, lane, wave, kg, wq, wm, wn, m0, n0, mt, nt, split,
                                              (char *)p.y + (int64_t)bz * p.y_bstride + y_phase);
     }
+}
+
+template <int BM, int BN, int WGM, int WGN, int KW, int NS, int BK, bool BT = false, int TAPS = kNoTaps, typename T = bf16_tag>
+__global__ __launch_bounds__(64 * WGM * WGN * KW, ALT_DCONV_MIN_WAVES((BM / WGM) * (BN / WGN) / 64, WGM * WGN * KW))
+void dstream_kernel(const DconvParams p)
+{
+    dstream_body<BM, BN, WGM, WGN, KW, NS, BK, BT, TAPS, T>(p, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // LDS bytes of one workgroup: the K groups' operand rings, or the output staging.

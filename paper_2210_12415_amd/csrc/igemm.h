@@ -318,12 +318,13 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams &p, floatx16_t 
 // Consecutive logical tiles stay on one XCD (workgroup ids are dealt round-robin
 // to the 8 XCDs), n-tiles of one m-tile adjacent, so the activation rows they
 // share are served by the same L2.
-__device__ __forceinline__ int igemm_logical_tile(int ntiles)
+__device__ __forceinline__ int igemm_logical_tile(int ntiles, int id)
 {
-    const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
+    const int xcd = id & 7, slot = id >> 3;
     const int q = ntiles >> 3, rem = ntiles & 7;
     return xcd * q + min(xcd, rem) + slot;
 }
+__device__ __forceinline__ int igemm_logical_tile(int ntiles) { return igemm_logical_tile(ntiles, (int)blockIdx.x); }
 
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, int AMODE, int BMODE, int PF>
 __global__ __launch_bounds__(kIgemmThreads) void igemm_kernel(const IgemmParams p)

@@ -1,4 +1,4 @@
-"""Branches of the built tile kernels (dstream.h, dslab.h, dplanar.h), read from their machine code.  Their operand reads from LDS
+"""Branches of the built tile kernels (dstream.h, dslab.h, dplanar.h, and group.h, which holds bodies of all three), read from their machine code.  Their operand reads from LDS
 complete behind the compiler's back, and the compiler copies registers where paths join: a copy of a register whose read is in flight
 copies stale data.  So the streaming kernels with row-major B, the slab and the planar kernels may not branch at all between such a
 read and its wait, and the other streaming kernels not more often than the loop over the stages needs."""
@@ -13,7 +13,7 @@ import paper_2210_12415_amd as alt
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
-FAMILIES = ("dstream_kernel", "dslab_kernel", "dplanar_kernel")
+FAMILIES = ("dstream_kernel", "dslab_kernel", "dplanar_kernel", "group_kernel")
 
 
 def tile_kernels(folder):
@@ -102,3 +102,21 @@ def test_slab_and_planar_kernels_do_not_branch_with_reads_in_flight(kernels, fam
         most = {}
         assert not branches_with_reads_in_flight(code, writes_end=False, most=most), name
         assert max(i for i, (_, op, _) in enumerate(code) if "mfma" in op) in most and max(most.values()) >= 2, name    # the loop was walked, with reads in flight
+
+
+@pytest.mark.parametrize("family,mfma_bodies,branching", [("F32", 4, 2 * 7 + 2 * 9), ("Slab", 9, 2 * 7), ("Planar", 8, 0)])
+def test_kernels_of_several_bodies_branch_for_the_stages_alone(kernels, family, mfma_bodies, branching):
+    """The same for every body of a kernel that holds several: its streaming bodies branch for the stages, the others not at all.  (A
+    body's epilogue lies between its last matrix instruction and the next one's; there the compiler keeps the waits of its own reads.)"""
+    name, code = next((n, c) for n, c in kernels["group_kernel"].items() if n.endswith("::" + family))
+    store = [op.startswith(("buffer_store", "global_store")) for _, op, _ in code]
+    mfma = ["mfma" in op for _, op, _ in code]
+    most, found = {}, []
+    for i in branches_with_reads_in_flight(code, writes_end=False, most=most):
+        ahead = next(j for j in range(i, len(code)) if mfma[j] or store[j])
+        if mfma[ahead]:
+            found.append(i)
+    assert len(found) <= branching, name
+    assert max(i for i, m in enumerate(mfma) if m) in most and max(most.values()) >= 2, name
+    bodies = 1 + sum(1 for i in range(1, len(code)) if mfma[i] and any(store[j] for j in range(max(j for j in range(i) if mfma[j] or j == 0), i)))
+    assert bodies >= mfma_bodies, (name, bodies)
