@@ -1,7 +1,12 @@
-"""ctypes marshalling for libalt.so.  Function names follow include/alt.h."""
+"""ctypes marshalling for libalt.so, with a native module for the calls that programs repeat.  Function names follow include/alt.h."""
 import ctypes
 import os
 import struct
+
+try:
+    from . import _altcall as _native
+except ImportError:                       # built where Python's headers are (build.py)
+    _native = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBPATH = os.environ.get("ALT_LIBRARY", os.path.join(_HERE, "libalt.so"))   # ALT_LIBRARY: developer builds
@@ -154,6 +159,9 @@ def lib():
         L.alt_last_error.restype = ctypes.c_char_p
         L.alt_status_string.restype = ctypes.c_char_p
         L.alt_version.restype = ctypes.c_char_p
+        if _native is not None:
+            _native.setup(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _REPEATED],
+                          ctypes.c_void_p, ConvDesc, Conv3dDesc, GemmDesc, Layout)
         _lib = L
     return _lib
 
@@ -167,6 +175,23 @@ _PROTOTYPES = {"alt_layout_transform": (_V, _I, _I, _V, _V, _V, _V, _V, _V), "al
                "alt_gemm": (_V, _V, _V, _V, _V, _V, ctypes.c_size_t, _V), "alt_conv2d": _OPERATOR, "alt_conv3d": _OPERATOR,
                "alt_conv2d_transpose": _OPERATOR, "alt_conv3d_transpose": _OPERATOR}
 _calls = {}
+
+# The same calls by the native module (native/altcall.c), for arguments of plain types; it answers None to others, and without the module
+# everything is another.  (A conversion's arguments took 1.8 us through ctypes, beside 3.5 for the launch.)
+_REPEATED = ("alt_conv2d", "alt_conv3d", "alt_conv2d_transpose", "alt_conv3d_transpose", "alt_gemm", "alt_layout_transform", "alt_eltwise_add")
+
+
+def _not_taken(*_):
+    return None
+
+
+def _quick(name):
+    return getattr(_native, name) if _native is not None else _not_taken
+
+
+_quick_conv2d, _quick_conv3d = _quick("conv2d"), _quick("conv3d")
+_quick_conv2d_transpose, _quick_conv3d_transpose = _quick("conv2d_transpose"), _quick("conv3d_transpose")
+_quick_gemm, _quick_transform, _quick_add, _quick_prepare = _quick("gemm"), _quick("layout_transform"), _quick("eltwise_add"), _quick("prepare_conv2d")
 
 
 def _call(name):
@@ -249,6 +274,8 @@ def _stream_address(s):
             c = torch._C
             if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice"):
                 _raw_stream = lambda: c._cuda_getCurrentRawStream(c._cuda_getDevice())
+                if _native is not None:
+                    _native.streams(c._cuda_getCurrentRawStream, c._cuda_getDevice)
             else:
                 _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
         return _raw_stream()
@@ -408,7 +435,10 @@ class Handle:
         return lib().alt_last_error(self._h).decode()
 
     def layout_transform(self, dtype, shape, src_layout, src, dst_layout, dst, stream=None):
-        if dtype.__class__ is int and dtype in _CODES:
+        status = _quick_transform(self._h, dtype, shape, src_layout, src, dst_layout, dst, stream)
+        if status is not None:
+            pass
+        elif dtype.__class__ is int and dtype in _CODES:
             status = _call("alt_layout_transform")(self._h, dtype, len(shape), _extents(shape),
                                                    ctypes.byref(_as_layout(src_layout)), _address(src),
                                                    ctypes.byref(_as_layout(dst_layout)), _address(dst), _stream_address(stream))
@@ -436,7 +466,11 @@ class Handle:
 
     # conv
     def conv2d(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
-        self._operator("alt_conv2d", d, x, w, bias, y, workspace, ws_bytes, stream)
+        status = _quick_conv2d(self._h, d, x, w, bias, y, workspace, ws_bytes, stream)
+        if status is None:
+            self._operator("alt_conv2d", d, x, w, bias, y, workspace, ws_bytes, stream)
+        elif status != 0:
+            _ck(status, self._h)
 
     def conv2d_static(self, d, x, w, y, bias=None, stream=None):
         _ck(lib().alt_conv2d_static(self._h, ctypes.byref(d), _ptr(x), _ptr(w), _ptr(bias), _ptr(y), _stream(stream)), self._h)
@@ -448,6 +482,9 @@ class Handle:
     def conv2d_prepared(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
         """The same call as conv2d with its arguments marshalled once: returns a
         function of no arguments that launches it (for loops that repeat one call)."""
+        call = _quick_prepare(self._h, d, x, w, bias, y, workspace, ws_bytes, stream, _ck)
+        if call is not None:
+            return call
         fn = _call("alt_conv2d")
         ws_bytes = ctypes.c_size_t(ws_bytes).value
         args = (self._h, ctypes.byref(d), _address(x), _address(w), _address(bias), _address(y), _address(workspace),
@@ -508,7 +545,11 @@ class Handle:
         return tuple(out)
 
     def conv2d_transpose(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
-        self._operator("alt_conv2d_transpose", d, x, w, bias, y, workspace, ws_bytes, stream)
+        status = _quick_conv2d_transpose(self._h, d, x, w, bias, y, workspace, ws_bytes, stream)
+        if status is None:
+            self._operator("alt_conv2d_transpose", d, x, w, bias, y, workspace, ws_bytes, stream)
+        elif status != 0:
+            _ck(status, self._h)
 
     def conv2d_transpose_workspace_size(self, d):
         n = ctypes.c_size_t()
@@ -550,7 +591,11 @@ class Handle:
                                              _stream(stream)), self._h)
 
     def conv3d(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
-        self._operator("alt_conv3d", d, x, w, bias, y, workspace, ws_bytes, stream)
+        status = _quick_conv3d(self._h, d, x, w, bias, y, workspace, ws_bytes, stream)
+        if status is None:
+            self._operator("alt_conv3d", d, x, w, bias, y, workspace, ws_bytes, stream)
+        elif status != 0:
+            _ck(status, self._h)
 
     def conv3d_workspace_size(self, d):
         n = ctypes.c_size_t()
@@ -567,7 +612,11 @@ class Handle:
                                      _stream(stream)), self._h)
 
     def conv3d_transpose(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
-        self._operator("alt_conv3d_transpose", d, x, w, bias, y, workspace, ws_bytes, stream)
+        status = _quick_conv3d_transpose(self._h, d, x, w, bias, y, workspace, ws_bytes, stream)
+        if status is None:
+            self._operator("alt_conv3d_transpose", d, x, w, bias, y, workspace, ws_bytes, stream)
+        elif status != 0:
+            _ck(status, self._h)
 
     def conv3d_transpose_workspace_size(self, d):
         n = ctypes.c_size_t()
@@ -599,6 +648,11 @@ class Handle:
 
     # gemm
     def gemm(self, d, A, B, C, workspace=None, ws_bytes=0, stream=None):
+        status = _quick_gemm(self._h, d, A, B, C, workspace, ws_bytes, stream)
+        if status is not None:
+            if status != 0:
+                _ck(status, self._h)
+            return
         if ws_bytes.__class__ is not int:
             ws_bytes = ctypes.c_size_t(ws_bytes).value
         status = _call("alt_gemm")(self._h, ctypes.byref(d), _address(A), _address(B), _address(C), _address(workspace),
@@ -681,7 +735,10 @@ class Handle:
                              _ptr(src), _ptr(dst), _stream(stream)), self._h)
 
     def eltwise_add(self, dtype, numel, a, b, y, relu=False, stream=None):
-        if dtype.__class__ is int and dtype in _CODES and numel.__class__ is int:
+        status = _quick_add(self._h, dtype, numel, a, b, y, relu, stream)
+        if status is not None:
+            pass
+        elif dtype.__class__ is int and dtype in _CODES and numel.__class__ is int:
             status = _call("alt_eltwise_add")(self._h, dtype, numel, _address(a), _address(b), _address(y), int(bool(relu)),
                                               _stream_address(stream))
         else:

@@ -1,4 +1,4 @@
-"""Builds libalt.so (HIP, gfx950 only) next to this file.
+"""Builds libalt.so (HIP, gfx950 only) and the binding's call module (C) next to this file.
 
     python -m paper_2210_12415_amd.build [-j N] [--force]
 
@@ -10,6 +10,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -46,8 +47,29 @@ def _compile(src, force, hdr_time):
     return obj, True, warn
 
 
+def build_calls(force=False, verbose=True):
+    """The marshalling of repeated calls (native/altcall.c).  Where Python's headers are missing the binding goes through ctypes alone."""
+    src = os.path.join(HERE, "native", "altcall.c")
+    out = os.path.join(HERE, "_altcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        if verbose:
+            print("[build] no Python.h: calls go through ctypes", flush=True)
+        return None
+    if force or not os.path.exists(out) or os.path.getmtime(out) < os.path.getmtime(src):
+        tmp = out + ".tmp%d" % os.getpid()
+        r = subprocess.run([os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-Wall", "-I" + include, src, "-o", tmp], capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError("compile failed: %s\n%s" % (src, r.stderr[-4000:]))
+        os.replace(tmp, out)
+        if verbose:
+            print("[build] %s" % os.path.basename(out), flush=True)
+    return out
+
+
 def build(jobs=8, force=False, verbose=True):
     os.makedirs(OBJ, exist_ok=True)
+    build_calls(force, verbose)
     hdr = _newest_header()
     objs, rebuilt = [], False
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
