@@ -4,6 +4,7 @@
 #include <mutex>
 
 #include "dplanar.h"
+#include "dshort.h"
 #include "dslab.h"
 #include "dstem.h"
 #include "dstream.h"
@@ -484,12 +485,57 @@ static bool dstem_setup(const Problem &pb, const IgemmLaunch &k, int splitk, Dco
     return true;
 }
 
+// The same for a kernel over a short reduction (dshort.h): 1x1 filters at stride 1 over dense NHWC, and products of contiguous rows.
+static bool dshort_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
+{
+    auto no = [&](const char *m) { if (why) *why = m; return false; };
+    const IgemmParams &p = pb.p;
+    if (pb.dtype != ALT_BF16 || !p.out_bf16) return no("kernel for short reductions is bf16 in and out");
+    if (splitk != 1 || pb.groups > 1 || p.addend) return no("kernel for short reductions takes no split-K, groups or fused sum");
+    if (p.R != 1 || p.S != 1 || p.stride_h != 1 || p.stride_w != 1 || p.pad_h != 0 || p.pad_w != 0 || p.OH != p.H || p.OW != p.W)
+        return no("kernel for short reductions needs a 1x1 filter, stride 1, no padding");
+    const int64_t C = p.C, H = p.H, W = p.W, K = p.Nc, N = p.M / (H * W), stages = (C + 63) / 64;
+    if (C % 8) return no("a row's reduction is not a whole number of 16-byte chunks");
+    if (stages > (k.BN <= 64 ? kShortStages : 2)) return no("reduction does not fit LDS at once");
+    if (!(dense(p.xc, C, 1) && dense(p.xw, W, C) && dense(p.xh, H, W * C) && dense(p.xn, N, H * W * C))) return no("A is not dense with K contiguous");
+    if (!(dense(p.wi, C, 1) && dense(p.wo, K, C))) return no("B is not dense with K contiguous");
+    if (!(dense(p.yk, K, 1) && dense(p.yw, W, K) && dense(p.yh, H, W * K) && dense(p.yn, N, H * W * K))) return no("output is not dense with N contiguous");
+    if ((uintptr_t)p.x % 16 || (uintptr_t)p.w % 16 || (uintptr_t)p.y % 2) return no("operands are not 16-byte aligned");
+    if (p.batch > 1 && ((p.x_bstride * 2) % 16 || (p.w_bstride * 2) % 16)) return no("batch entries are not 16-byte aligned");
+    if ((p.epilogue & ALT_EPI_BIAS) && (K % 4 || (uintptr_t)p.bias % 16)) return no("bias is loaded four columns at a time");
+    if (pb.x_elems * 2 >= 0x7fffffff || pb.w_elems * 2 >= 0x7fffffff || p.y_bytes == 0 || ((int64_t)p.M + k.BM) * C * 2 >= 0x7fffffff ||
+        (K + k.BN) * C * 2 >= 0x7fffffff)
+        return no("operand of 2 GiB or more");
+    const size_t lds = dshort_lds_bytes(k.BN, C);
+    const int64_t tiles_m = (p.M + k.BM - 1) / k.BM, tiles_n = (K + k.BN - 1) / k.BN;
+    if (tiles_m * tiles_n * p.batch > 0x7fffffff) return no("grid too large");
+    if (lds_bytes) *lds_bytes = lds;
+    if (!out) return true;
+    DconvParams d;
+    std::memset(&d, 0, sizeof d);
+    d.x = p.x; d.w = p.w; d.bias = p.bias; d.y = p.y;
+    d.x_bytes = p.x_bytes; d.w_bytes = p.w_bytes; d.y_bytes = p.y_bytes;
+    d.M = p.M; d.Nc = p.Nc; d.C = p.C;
+    d.tiles_m = (int32_t)tiles_m; d.tiles_n = (int32_t)tiles_n; d.splitk = 1;
+    d.flags = (p.epilogue & (ALT_EPI_BIAS | ALT_EPI_RELU)) | kDconvOutBf16;
+    d.d_tn = make_div32((uint32_t)tiles_n);
+    d.d_od = make_div32((uint32_t)(tiles_m * tiles_n));
+    d.c16 = (int32_t)(C / 8);
+    d.x_pix = (uint32_t)(C * 2);
+    d.bk = 64;
+    d.batch = p.batch;
+    d.x_bstride = p.x_bstride * 2; d.w_bstride = p.w_bstride * 2; d.y_bstride = p.y_bstride * 2;
+    *out = d;
+    return true;
+}
+
 // Fills the launch parameters of direct kernel `k` for `pb` split into `splitk`
 // channel slices, or says why the kernel does not cover the problem.
 bool dconv_setup(const Problem &pb, const IgemmLaunch &k, int splitk, DconvParams *out, size_t *lds_bytes, std::string *why)
 {
     if (k.stream == 2) return dplanar_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream == 3) return dstem_setup(pb, k, splitk, out, lds_bytes, why);
+    if (k.stream == 5) return dshort_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream == 4) return dslab_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.taps) return dtaps_setup(pb, k, splitk, out, lds_bytes, why);
     if (k.stream) return dstream_setup(pb, k, splitk, out, lds_bytes, why);

@@ -670,7 +670,8 @@ struct IgemmLaunch {
     int kw = 1;               // its K groups (each a wave grid of its own over a share of the channels)
     int stream = 0;           // 1: both operands stream through LDS (dstream.h: 1x1 filters and GEMMs of any depth);
                               // 2: channel-planar operands converted on the way into LDS (dplanar.h);
-                              // 3: images of few channels (dstem.h); 4: patches of slabs of channels (dslab.h)
+                              // 3: images of few channels (dstem.h); 4: patches of slabs of channels (dslab.h);
+                              // 5: the whole of a short reduction in LDS at once (dshort.h)
     int bt = 0;               // streaming kernel: 1 = B stored [K][N] (row-major), read through LDS transpose reads
     int taps = 0;             // streaming kernel over filter taps: kTapsUniform or kTapsRagged
     int ragged = 0;           // channel-planar kernel: 0 = whole 64-channel steps that fit LDS at once, 1 = the other channel counts

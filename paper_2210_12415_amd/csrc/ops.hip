@@ -253,11 +253,30 @@ static double slab_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     return std::sqrt(std::cbrt(cube(us * us) + cube(mem * mem)));
 }
 
+// The same for the kernels of a short reduction: what a workgroup's loads (those past the operands' ends cost as much), products and stores take of
+// a compute unit, the chain that it is, rounds of as many as share one, and the tensors' way from and to memory.  Fitted over 9400 products
+// (K up to 256, batches of 1 to 900, 4 to 400 us) under all three tiles, rms 9.5 %; the choice among them takes 3.1 % longer than the best.
+static double short_estimate_us(const IgemmLaunch &k, const IgemmParams &p, size_t lds)
+{
+    const double rows = (double)p.M / p.tiles_m, cols = (double)p.Nc / p.tiles_n, stages = std::ceil(p.C / 64.0);
+    const double rounds = (double)p.tiles_m * p.tiles_n * p.batch / 256.0;
+    const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), k.BN <= 64 ? 4.0 : 3.0));
+    const double busy = ((rows + cols) * p.C * 2 + 0.94 * stages * (k.BM + k.BN) * 128) / 183.0 + rows * cols * 2 / 54.0 + stages * k.BN / 32 * 70.0;
+    const double work = busy * std::max(1.0, rounds) / 2200.0, chain = (4770.0 + busy) * std::max(1.0, rounds / per_cu) / 2200.0;
+    const double mem = 2.0 * p.batch * ((double)p.M * p.C + (double)p.Nc * p.C + (double)p.M * p.Nc) / 5.33e6;
+    return 3.45 + std::cbrt(work * work * work + chain * chain * chain + mem * mem * mem);
+}
+
 // Microseconds of a tile kernel.  *family: what the choice between families multiplies them with.
 static double direct_estimate_us(const Problem &pb, const IgemmLaunch &k, const IgemmParams &p, size_t lds, double *family, TileClocks *one = nullptr)
 {
     *family = 0.05;
     if (k.stream == 4) return slab_estimate_us(pb, k, p, lds, one);
+    if (k.stream == 5) {
+        // (a little before the others, whose estimates are low for few columns: 144 channels to 24 at 16 x 56 x 56 take 4.8 us here, 6.6 there)
+        *family = 0.047;
+        return short_estimate_us(k, p, lds);
+    }
     if (k.stream <= 1 && k.dtype == ALT_BF16) {
         // (a small factor: wherever one of these kernels applies it has been faster than the register-staged ones, whose estimate below
         // knows little of slices and short sums: at half, 4 x 128 x 5 x 5, 3x3, went there in 36 slices and took 15.6 us, not 7.8.
