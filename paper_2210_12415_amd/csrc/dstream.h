@@ -72,7 +72,7 @@ __device__ __forceinline__ void dstream_body(const DconvParams &p, int bx, int b
     static_assert(A_STAGE % (1024 * NWG) == 0 && B_STAGE % (1024 * NWG) == 0 && NLA >= 1 && NLB >= 1,
                   "a stage is a whole number of wave-loads per wave");
     static_assert(BKB == 128 || BKB == 64, "K step");
-    static_assert(ES == 2 || (!BT && kRagged), "fp32: built for ragged taps, which cover the rest");
+    static_assert(ES == 2 || (!BT && TAPS), "fp32: built over taps, which cover the rest");
     static_assert(NS >= 3 && (NS - 1) * LPS < 60, "pipeline depth against the vmcnt range");
     static_assert((NS * NKC) % 4 == 0, "a round over the stages is a whole number of fragment-buffer cycles");
     constexpr int RB = BT ? 2 : 1;                         // LDS reads per B fragment

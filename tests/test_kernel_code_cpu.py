@@ -104,7 +104,7 @@ def test_slab_and_planar_kernels_do_not_branch_with_reads_in_flight(kernels, fam
         assert max(i for i, (_, op, _) in enumerate(code) if "mfma" in op) in most and max(most.values()) >= 2, name    # the loop was walked, with reads in flight
 
 
-@pytest.mark.parametrize("family,mfma_bodies,branching", [("F32", 4, 2 * 7 + 2 * 9), ("Slab", 9, 2 * 7), ("Planar", 8, 0)])
+@pytest.mark.parametrize("family,mfma_bodies,branching", [("F32", 6, 3 * 7 + 3 * 9), ("Slab", 9, 2 * 7), ("Planar", 8, 0)])
 def test_kernels_of_several_bodies_branch_for_the_stages_alone(kernels, family, mfma_bodies, branching):
     """The same for every body of a kernel that holds several: its streaming bodies branch for the stages, the others not at all.  (A
     body's epilogue lies between its last matrix instruction and the next one's; there the compiler keeps the waits of its own reads.)"""
