@@ -191,7 +191,7 @@ __device__ __forceinline__ void dw_3x3_filter(const DwParams &p, int c, dw_words
 // its filters hold an infinite or NaN value: the same sums with the filter cleared under taps outside.
 // (16 x 144 x 56 x 56 takes 8.9 us, with NaN inputs 9.9, with NaN filters 22.5; one element at a time it took 225, a row of outputs
 // at a time 19.1, but those 11 KB of code, never run, cost every pass through several kernels 1 %.)
-template <int STRIDE, int TW, int TH, bool TAPS>
+template <int STRIDE, int TW, int TH, bool TAPS, int POLICY>
 __device__ __forceinline__ void dw_3x3_inside(uint32_t t)
 {
     // (the item is decoded and the kernel's argument read anew, so that the kernel keeps nothing in registers for this)
@@ -254,7 +254,7 @@ __device__ __forceinline__ void dw_3x3_inside(uint32_t t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) out[q] = f32x2_to_bf16x2(lo[q], hi[q]);
         const bool ok = ow < p.OW && oh < p.OH;
-        __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + oh * (int32_t)p.yh.si + ow * (int32_t)p.yw.si) * 2u : kOutOfRange), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + oh * (int32_t)p.yh.si + ow * (int32_t)p.yw.si) * 2u : kOutOfRange), 0, POLICY);
     }
 }
 
@@ -268,7 +268,10 @@ __device__ __forceinline__ void dw_3x3_inside(uint32_t t)
 // Consecutive blocks run on one XCD, so that the rows two blocks share come out of one L2.
 // Measured on 16 x 144 x 56 x 56 (29 MB): 10.0 us, 2.9 TB/s; OHWI filters took the element kernel before, 137 us, and
 // filters with the channel innermost a version of this one with a branch per load and one row per thread, 13.0 us.
-template <int STRIDE, int TW, int TH, bool TAPS>
+// POLICY: of the stores.  Outputs that the L2s could keep (32 MB) go through to memory as they are written, which leaves nothing to write back
+// between this kernel and the next: a block of 16 x 144 x 56 x 56 26.6 us before and 25.3 so, of 15 x 384 x 29 x 29 24.1 and 23.1; larger ones leave
+// the L2s anyway (32 x 528 x 43 x 43 102.0 us, through 103.8).
+template <int STRIDE, int TW, int TH, bool TAPS, int POLICY>
 __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const DwParams p)
 {
     typedef uint32_t w4_t __attribute__((ext_vector_type(4)));
@@ -351,12 +354,12 @@ __global__ __launch_bounds__(kDwThreads, 2) void dwconv_vec8_3x3_kernel(const Dw
             w4_t out;
 #pragma unroll
             for (int q = 0; q < 4; ++q) out[q] = f32x2_to_bf16x2(a[q], b[q]);
-            __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + (oh0 + i) * syh + (ow0 + j) * syw) * 2u : kOutOfRange), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(out, yr, (int)(ok ? (uint32_t)(yb + (oh0 + i) * syh + (ow0 + j) * syw) * 2u : kOutOfRange), 0, POLICY);
         }
     // A tap outside the image is no part of the sum, but the zeros read for it were multiplied, and zero times an infinite or NaN
     // filter value is NaN.  Where a sum came out NaN, the outputs of a thread at the border are taken again over the taps inside
     // and stored over those above.
-    if (probe != probe) dw_3x3_inside<STRIDE, TW, TH, TAPS>(threadIdx.x);
+    if (probe != probe) dw_3x3_inside<STRIDE, TW, TH, TAPS, POLICY>(threadIdx.x);
 }
 
 // bf16 in and out, width contiguous, 3x3 without dilation, padding 1 along the width, W and OW multiples of TW
@@ -496,9 +499,13 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
         p.fd_c8 = make_fastdiv((uint32_t)C / 8);
         p.fd_owb = make_fastdiv(owb);
         p.fd_ohb = make_fastdiv(ohb);
-        auto kern = th == 2            ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 2, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 2, false>)
-                    : q.stride_h == 1 ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<1, kDwCols, 1, false>)
-                                      : (taps ? dwconv_vec8_3x3_kernel<2, kDwCols, 1, true> : dwconv_vec8_3x3_kernel<2, kDwCols, 1, false>);
+        auto kernel = [&](auto policy) {
+            constexpr int P = decltype(policy)::value;
+            return th == 2             ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 2, true, P> : dwconv_vec8_3x3_kernel<1, kDwCols, 2, false, P>)
+                 : q.stride_h == 1 ? (taps ? dwconv_vec8_3x3_kernel<1, kDwCols, 1, true, P> : dwconv_vec8_3x3_kernel<1, kDwCols, 1, false, P>)
+                                   : (taps ? dwconv_vec8_3x3_kernel<2, kDwCols, 1, true, P> : dwconv_vec8_3x3_kernel<2, kDwCols, 1, false, P>);
+        };
+        auto kern = N * y_image * 2 <= 32 << 20 ? kernel(std::integral_constant<int, kWriteThrough>{}) : kernel(std::integral_constant<int, 0>{});
         for (int64_t n = 0; n < N; n += images) {
             const int64_t here = std::min(images, N - n);
             p.x = (const uint16_t *)q.x + n * x_image;
