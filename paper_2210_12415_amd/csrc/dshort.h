@@ -4,7 +4,7 @@
 // Such a product is bound by its output's and its left operand's way from and to memory, not by matrix instructions, and has no loop worth
 // a pipeline.  A workgroup of four waves brings the whole reduction of its 128 x 32 TN tile into LDS at once (direct-to-LDS loads, all in flight
 // together), waits once, multiplies, and stores through LDS; what covers the waiting are the other three or so workgroups on the compute
-// unit: 35 KB of LDS each for 64 channels and 128 columns.
+// unit: 20 to 28 KB of LDS each for 64 channels and 32 to 96 columns.
 //
 // Output rows may have any length: a lane stores eight columns at once, at any even address, and the last ones of a row one by one.
 // (The tile kernels of dstream.h store four aligned columns at least; other products ran on register-staged kernels.)
