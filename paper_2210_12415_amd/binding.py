@@ -422,8 +422,9 @@ class Handle:
 
     def close(self):
         if self._h:
-            lib().alt_destroy(self._h)
-            self._h = ctypes.c_void_p()
+            h = ctypes.c_void_p(self._h.value)
+            self._h.value = None              # in place: calls prepared with it find no handle
+            lib().alt_destroy(h)
 
     def __del__(self):
         try:
@@ -482,14 +483,14 @@ class Handle:
     def conv2d_prepared(self, d, x, w, y, bias=None, workspace=None, ws_bytes=0, stream=None):
         """The same call as conv2d with its arguments marshalled once: returns a
         function of no arguments that launches it (for loops that repeat one call)."""
-        call = _quick_prepare(self._h, d, x, w, bias, y, workspace, ws_bytes, stream, _ck)
+        call = _quick_prepare(self._h, d, x, w, bias, y, workspace, ws_bytes, stream, _ck, self)
         if call is not None:
             return call
         fn = _call("alt_conv2d")
         ws_bytes = ctypes.c_size_t(ws_bytes).value
         args = (self._h, ctypes.byref(d), _address(x), _address(w), _address(bias), _address(y), _address(workspace),
                 ws_bytes, _stream_address(stream))
-        keep = (d, x, w, y, bias, workspace)
+        keep = (self, d, x, w, y, bias, workspace)
 
         def run():
             status = fn(*args)
@@ -516,7 +517,7 @@ class Handle:
         once: returns a function of no arguments that issues them all."""
         n = len(calls)
         arr = self._call_array(calls)
-        keep = list(calls)
+        keep = (self, [tuple(c.values()) for c in calls])
         fn, hh, nn = lib().alt_conv2d_multi, self._h, ctypes.c_int32(n)
 
         def run():

@@ -173,7 +173,7 @@ static PyObject *py_eltwise_add(PyObject *m, PyObject *const *a, Py_ssize_t n)
     return PyLong_FromLong(status);
 }
 
-/* A call of conv2d with its arguments marshalled once.  It keeps what they came from. */
+/* A call of conv2d with its arguments marshalled once.  It keeps what they came from, the owner of the handle among them. */
 typedef struct {
     PyObject_HEAD
     vectorcallfunc vectorcall;
@@ -226,12 +226,12 @@ static PyTypeObject prepared_type = {
     .tp_call = PyVectorcall_Call, .tp_traverse = prepared_traverse, .tp_clear = prepared_clear, .tp_dealloc = prepared_dealloc,
 };
 
-/* (h, d, x, w, bias, y, workspace, ws_bytes, stream, failed) */
+/* (h, d, x, w, bias, y, workspace, ws_bytes, stream, failed, the owner of h) */
 static PyObject *py_prepare_conv2d(PyObject *m, PyObject *const *a, Py_ssize_t n)
 {
     operator_args r;
-    if (n != 10 || !entry[CONV2D] || handle_of(a[0], &r.h) || operator_args_of(a, conv_type, &r)) Py_RETURN_NONE;
-    PyObject *keep = PyTuple_Pack(6, a[1], a[2], a[3], a[4], a[5], a[6]);
+    if (n != 11 || !entry[CONV2D] || handle_of(a[0], &r.h) || operator_args_of(a, conv_type, &r)) Py_RETURN_NONE;
+    PyObject *keep = PyTuple_Pack(7, a[10], a[1], a[2], a[3], a[4], a[5], a[6]);
     if (!keep) return NULL;
     Prepared *p = PyObject_GC_New(Prepared, &prepared_type);
     if (!p) { Py_DECREF(keep); return NULL; }

@@ -94,3 +94,35 @@ def test_prepared_call_keeps_its_arguments():
     del run
     gc.collect()
     assert alive() is None
+
+
+@pytest.mark.parametrize("native", [True, False], ids=["native", "ctypes"])
+@pytest.mark.parametrize("several", [False, True], ids=["one", "several"])
+def test_prepared_call_keeps_its_handle(native, several, monkeypatch):
+    """A prepared call outlives the caller's reference to the Handle and to its tensors; after close() it finds no handle."""
+    if not native:
+        monkeypatch.setattr(binding, "_quick_prepare", binding._not_taken)
+
+    def prepare(h, x):
+        kw = dict(d=alt.conv_desc(1, 8, 8, 8, 8, 1, 1), x=x, w=Tensor(128), y=Tensor(192), stream=0)
+        run = h.conv2d_multi_prepared([kw, kw]) if several else h.conv2d_prepared(**kw)
+        kw["x"] = None
+        return run
+
+    h, x = alt.Handle(), Tensor(64)
+    alive = weakref.ref(h), weakref.ref(x)
+    run = prepare(h, x)
+    del h, x
+    gc.collect()
+    assert all(a() is not None for a in alive)
+    with pytest.raises(alt.AltError, match="no GPU"):
+        run()
+    del run
+    gc.collect()
+    assert all(a() is None for a in alive)
+
+    h = alt.Handle()
+    run = prepare(h, Tensor(64))
+    h.close()
+    with pytest.raises(alt.AltError, match="invalid argument"):
+        run()
