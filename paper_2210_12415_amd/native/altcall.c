@@ -1,6 +1,7 @@
 /* The calls a program repeats, marshalled natively: descriptors and layouts by the address of their ctypes object, tensors by data_ptr(), the
  * current stream by its number.  A function returns the library's status, or None where an argument is not of the plain types below; the
- * caller then takes the call through ctypes, which decides as ever what it accepts and what it raises. */
+ * caller then takes the call through ctypes, which decides as ever what it accepts and what it raises.  (An interrupt, or whatever else is no
+ * Exception, that ends an argument's own code is raised at once: the second attempt would not see it again.) */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>
@@ -20,12 +21,26 @@ static PyObject *raw_stream, *get_device;                  /* torch's, once it h
 static pid_t stream_pid;
 static PyObject *s_data_ptr, *s_cuda_stream;
 
-/* 0, or -1 for an object of another type (no exception is left). */
+/* An argument is not taken: its exception goes, for ctypes to raise.  -1 */
+static int refused(void)
+{
+    if (PyErr_Occurred() && PyErr_ExceptionMatches(PyExc_Exception)) PyErr_Clear();
+    return -1;
+}
+
+/* The answer for arguments that are not taken. */
+static PyObject *not_taken(void)
+{
+    if (PyErr_Occurred()) return NULL;
+    Py_RETURN_NONE;
+}
+
+/* 0, or -1 for an object of another type. */
 static int object_at(PyObject *o, PyObject *type, void **out)
 {
     Py_buffer b;
     if ((PyObject *)Py_TYPE(o) != type) return -1;
-    if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return -1; }
+    if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return refused();
     *out = b.buf;
     PyBuffer_Release(&b);
     return 0;
@@ -35,14 +50,14 @@ static int number(PyObject *o, unsigned long long most, unsigned long long *out)
 {
     if (!PyLong_CheckExact(o)) return -1;
     *out = PyLong_AsUnsignedLongLong(o);
-    if (*out == (unsigned long long)-1 && PyErr_Occurred()) { PyErr_Clear(); return -1; }
+    if (*out == (unsigned long long)-1 && PyErr_Occurred()) return refused();
     return *out <= most ? 0 : -1;
 }
 
 static int number_of(PyObject *r, void **out)              /* takes the reference; NULL: an exception is set */
 {
     unsigned long long v;
-    if (!r) { PyErr_Clear(); return -1; }
+    if (!r) return refused();
     const int bad = number(r, UINT64_MAX, &v);
     Py_DECREF(r);
     *out = (void *)(uintptr_t)v;
@@ -66,7 +81,7 @@ static int stream_of(PyObject *o, void **out)
     if (o == Py_None) {
         if (!raw_stream || getpid() != stream_pid) return -1;
         PyObject *d = PyObject_CallNoArgs(get_device);
-        if (!d) { PyErr_Clear(); return -1; }
+        if (!d) return refused();
         PyObject *r = PyObject_CallOneArg(raw_stream, d);
         Py_DECREF(d);
         return number_of(r, out);
@@ -111,7 +126,7 @@ static int call_operator(int which, const operator_args *r)
 static PyObject *operator_call(int which, PyObject *type, PyObject *const *a, Py_ssize_t n)
 {
     operator_args r;
-    if (n != 9 || !entry[which] || handle_of(a[0], &r.h) || operator_args_of(a, type, &r)) Py_RETURN_NONE;
+    if (n != 9 || !entry[which] || handle_of(a[0], &r.h) || operator_args_of(a, type, &r)) return not_taken();
     return PyLong_FromLong(call_operator(which, &r));
 }
 
@@ -128,7 +143,7 @@ static PyObject *py_gemm(PyObject *m, PyObject *const *a, Py_ssize_t n)
     int status;
     if (n != 8 || !entry[GEMM] || handle_of(a[0], &h) || object_at(a[1], gemm_type, &d) || address(a[2], &A) || address(a[3], &B) ||
         address(a[4], &C) || address(a[5], &ws) || number(a[6], SIZE_MAX, &bytes) || stream_of(a[7], &st))
-        Py_RETURN_NONE;
+        return not_taken();
     Py_BEGIN_ALLOW_THREADS
     status = ((gemm_fn)entry[GEMM])(h, d, A, B, C, ws, (size_t)bytes, st);
     Py_END_ALLOW_THREADS
@@ -142,15 +157,15 @@ static PyObject *py_layout_transform(PyObject *m, PyObject *const *a, Py_ssize_t
     unsigned long long dtype, v;
     int64_t shape[16];
     int status;
-    if (n != 8 || !entry[TRANSFORM] || handle_of(a[0], &h) || number(a[1], 255, &dtype) || !PyTuple_CheckExact(a[2])) Py_RETURN_NONE;
+    if (n != 8 || !entry[TRANSFORM] || handle_of(a[0], &h) || number(a[1], 255, &dtype) || !PyTuple_CheckExact(a[2])) return not_taken();
     const Py_ssize_t nd = PyTuple_GET_SIZE(a[2]);
-    if (nd > 16) Py_RETURN_NONE;
+    if (nd > 16) return not_taken();
     for (Py_ssize_t i = 0; i < nd; ++i) {
-        if (number(PyTuple_GET_ITEM(a[2], i), INT64_MAX, &v)) Py_RETURN_NONE;
+        if (number(PyTuple_GET_ITEM(a[2], i), INT64_MAX, &v)) return not_taken();
         shape[i] = (int64_t)v;
     }
     if (object_at(a[3], layout_type, &ls) || address(a[4], &src) || object_at(a[5], layout_type, &ld) || address(a[6], &dst) || stream_of(a[7], &st))
-        Py_RETURN_NONE;
+        return not_taken();
     Py_BEGIN_ALLOW_THREADS
     status = ((transform_fn)entry[TRANSFORM])(h, (int)dtype, (int)nd, shape, ls, src, ld, dst, st);
     Py_END_ALLOW_THREADS
@@ -165,7 +180,7 @@ static PyObject *py_eltwise_add(PyObject *m, PyObject *const *a, Py_ssize_t n)
     int status;
     if (n != 8 || !entry[ADD] || handle_of(a[0], &h) || number(a[1], 255, &dtype) || number(a[2], INT64_MAX, &numel) || address(a[3], &x) ||
         address(a[4], &y) || address(a[5], &z) || !PyBool_Check(a[6]) || stream_of(a[7], &st))
-        Py_RETURN_NONE;
+        return not_taken();
     const int relu = a[6] == Py_True;
     Py_BEGIN_ALLOW_THREADS
     status = ((add_fn)entry[ADD])(h, (int)dtype, (int64_t)numel, x, y, z, relu, st);
@@ -230,7 +245,7 @@ static PyTypeObject prepared_type = {
 static PyObject *py_prepare_conv2d(PyObject *m, PyObject *const *a, Py_ssize_t n)
 {
     operator_args r;
-    if (n != 11 || !entry[CONV2D] || handle_of(a[0], &r.h) || operator_args_of(a, conv_type, &r)) Py_RETURN_NONE;
+    if (n != 11 || !entry[CONV2D] || handle_of(a[0], &r.h) || operator_args_of(a, conv_type, &r)) return not_taken();
     PyObject *keep = PyTuple_Pack(7, a[10], a[1], a[2], a[3], a[4], a[5], a[6]);
     if (!keep) return NULL;
     Prepared *p = PyObject_GC_New(Prepared, &prepared_type);

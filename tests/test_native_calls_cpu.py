@@ -126,3 +126,22 @@ def test_prepared_call_keeps_its_handle(native, several, monkeypatch):
     h.close()
     with pytest.raises(alt.AltError, match="invalid argument"):
         run()
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_interrupts_are_raised_at_once(name):
+    """An interrupt inside an argument's own code ends the call; ctypes does not ask the argument again."""
+    asked = []
+
+    class Interrupted:
+        def data_ptr(self):
+            asked.append(1)
+            if len(asked) == 1:
+                raise KeyboardInterrupt
+            return 64
+
+    base = CALLS[name][0]
+    kw = dict(base, **{next(k for k in ("x", "A", "a", "src") if k in base): Interrupted()})
+    with pytest.raises(KeyboardInterrupt):
+        getattr(alt.Handle(), name)(**kw)
+    assert len(asked) == 1
