@@ -48,22 +48,30 @@ def _compile(src, force, hdr_time):
 
 
 def build_calls(force=False, verbose=True):
-    """The marshalling of repeated calls (native/altcall.c).  Where Python's headers are missing the binding goes through ctypes alone."""
+    """The marshalling of repeated calls (native/altcall.c), which nothing needs: without Python's headers or a C compiler that takes it
+    there is none, and the binding goes through ctypes alone.  Returns the module's path or None."""
     src = os.path.join(HERE, "native", "altcall.c")
     out = os.path.join(HERE, "_altcall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    if not force and os.path.exists(out) and os.path.getmtime(out) >= os.path.getmtime(src):
+        return out
     include = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(include, "Python.h")):
-        if verbose:
-            print("[build] no Python.h: calls go through ctypes", flush=True)
-        return None
-    if force or not os.path.exists(out) or os.path.getmtime(out) < os.path.getmtime(src):
-        tmp = out + ".tmp%d" % os.getpid()
+    tmp = out + ".tmp%d" % os.getpid()
+    try:
+        if not os.path.exists(os.path.join(include, "Python.h")):
+            raise RuntimeError("no Python.h")
         r = subprocess.run([os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-Wall", "-I" + include, src, "-o", tmp], capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("compile failed: %s\n%s" % (src, r.stderr[-4000:]))
-        os.replace(tmp, out)
+    except (OSError, RuntimeError) as e:
+        for stale in (tmp, out):              # (an older module would be loaded still)
+            if os.path.exists(stale):
+                os.remove(stale)
         if verbose:
-            print("[build] %s" % os.path.basename(out), flush=True)
+            print("[build] calls go through ctypes: %s" % e, flush=True)
+        return None
+    os.replace(tmp, out)
+    if verbose:
+        print("[build] %s" % os.path.basename(out), flush=True)
     return out
 
 
