@@ -320,6 +320,15 @@ typedef struct {
  * The outputs and workspaces must not overlap.  Stops at the first call that fails and returns its status; the calls before
  * it stay issued. */
 alt_status_t alt_conv2d_multi(alt_handle_t h, const alt_conv_call_t *calls, int32_t n);
+
+/* How alt_conv2d_multi issues these calls, for each of them (host only: nothing is launched, no buffer is read, and it works
+ * without a GPU).  launch: the list's launch that it belongs to, 0, 1, ...; family: the kernel of several problems that runs it
+ * (1 fp32 NHWC, 2 bf16 NHWC, 3 bf16 NCHW), 0 where it goes out as alt_conv2d; body and slices: its tile body in that kernel and
+ * the slices of its sum (-1 and 0 where family is 0); kept: this call had nothing to plan. */
+typedef struct {
+    int32_t launch, family, body, slices, kept;
+} alt_multi_plan_t;
+alt_status_t alt_conv2d_multi_plan(alt_handle_t h, const alt_conv_call_t *calls, int32_t n, alt_multi_plan_t *out);
 alt_status_t alt_conv2d_output_shape(const alt_conv_desc_t *d, int64_t *out_nkhw);
 
 /* Offline weight transformation (Section 4.2: the weight tensor is a constant,

@@ -123,6 +123,10 @@ class GraphPlan(ctypes.Structure):
                 ("fused_into", ctypes.c_int32 * MAX_GRAPH)]
 
 
+class MultiPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("launch", "family", "body", "slices", "kept")]
+
+
 class TransformPlan(ctypes.Structure):
     _fields_ = [("kind", ctypes.c_int32), ("src_flat", ctypes.c_int32), ("dst_flat", ctypes.c_int32),
                 ("load_bytes", ctypes.c_int32), ("store_bytes", ctypes.c_int32),
@@ -206,7 +210,7 @@ def exported_symbols():
     return ["alt_create", "alt_destroy", "alt_last_error", "alt_status_string", "alt_version",
             "alt_layout_parse", "alt_layout_from_prims", "alt_layout_physical_shape",
             "alt_layout_offset", "alt_layout_index_of", "alt_layout_transform",
-            "alt_conv2d", "alt_conv2d_add", "alt_conv2d_multi", "alt_conv2d_transpose", "alt_conv2d_transpose_workspace_size",
+            "alt_conv2d", "alt_conv2d_add", "alt_conv2d_multi", "alt_conv2d_multi_plan", "alt_conv2d_transpose", "alt_conv2d_transpose_workspace_size",
             "alt_conv2d_transpose_output_shape", "alt_conv2d_transpose_weight_shape", "alt_pack_weights_transpose",
             "alt_conv3d", "alt_conv3d_workspace_size", "alt_conv3d_output_shape", "alt_pack_weights3d",
             "alt_conv3d_transpose", "alt_conv3d_transpose_workspace_size", "alt_conv3d_transpose_output_shape",
@@ -534,6 +538,12 @@ class Handle:
 
     def conv2d_multi(self, calls):
         self.conv2d_multi_prepared(calls)()
+
+    def conv2d_multi_plan(self, calls):
+        """How conv2d_multi issues `calls`: a MultiPlan for each (host only)."""
+        out = (MultiPlan * len(calls))()
+        _ck(lib().alt_conv2d_multi_plan(self._h, self._call_array(calls), ctypes.c_int32(len(calls)), out), self._h)
+        return list(out)
 
     def conv2d_workspace_size(self, d):
         n = ctypes.c_size_t()

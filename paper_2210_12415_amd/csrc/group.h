@@ -34,6 +34,7 @@ struct GroupTile {
 };
 
 struct GroupFamily {
+    int code;                             // in alt_multi_plan_t
     const GroupTile *tiles;
     int ntiles, threads;
     hipError_t (*launch)(const GroupParams &g, unsigned workgroups, size_t lds, hipStream_t st);

@@ -41,7 +41,7 @@ const GroupTile kTiles[] = {{tile(64, 64, 2, 2, 1, 3, 32), body<0, 32, 1>}, {til
 
 const GroupFamily &group_f32()
 {
-    static const GroupFamily f = {kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), F32::kThreads, &group_launch<F32>};
+    static const GroupFamily f = {1, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), F32::kThreads, &group_launch<F32>};
     return f;
 }
 

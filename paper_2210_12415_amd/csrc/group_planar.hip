@@ -40,7 +40,7 @@ const GroupTile kTiles[] = {
 
 const GroupFamily &group_planar()
 {
-    static const GroupFamily f = {kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Planar::kThreads, &group_launch<Planar>};
+    static const GroupFamily f = {3, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Planar::kThreads, &group_launch<Planar>};
     return f;
 }
 

@@ -53,7 +53,7 @@ const GroupTile kTiles[] = {
 
 const GroupFamily &group_slab()
 {
-    static const GroupFamily f = {kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Slab::kThreads, &group_launch<Slab>};
+    static const GroupFamily f = {2, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Slab::kThreads, &group_launch<Slab>};
     return f;
 }
 

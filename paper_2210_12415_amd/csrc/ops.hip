@@ -624,11 +624,11 @@ struct MemoEntry {
 
 }  // extern "C"
 
-// The same for the calls of one alt_conv2d_multi that go out as one launch, or (family null) do not.
+// The same for the calls of one alt_conv2d_multi that go out as one launch.
 struct GroupEntry {
+    uint64_t tag;
     std::vector<unsigned char> key;
-    unsigned gen;
-    const GroupFamily *family = nullptr;
+    const GroupFamily *family;
     GroupParams g;
     int order[kGroupMax];             // the call behind each problem of the launch
     size_t ws_need[kGroupMax], x_bytes[kGroupMax], w_bytes[kGroupMax], y_bytes[kGroupMax];
@@ -636,10 +636,17 @@ struct GroupEntry {
     size_t lds;
 };
 
+// Lists kept, the oldest replaced: 64 launches (5 KB each, and 1 KB a call for the key), and 1024 lists of the calls that go out one by one,
+// which are remembered by a hash alone: one mistaken for another would run as its calls do by themselves.  (With eight places for both kinds, nine lists
+// of three layers in turn were planned on every call: 38 us of host time a list, 3.2 so.)
+constexpr size_t kGroupLaunches = 64, kGroupSingles = 1024;
+
 struct alt_launch_memo {
     std::vector<MemoEntry> entries;
     std::vector<GroupEntry> groups;
-    size_t next = 0, next_group = 0;
+    std::vector<std::pair<uint64_t, uint64_t>> singles;    // tag, hash of the key
+    size_t next = 0, next_group = 0, next_single = 0;
+    unsigned group_gen = 0;           // the tune cache's generation that both belong to
 };
 
 namespace alt {
@@ -902,26 +909,28 @@ static double group_us(const GroupPick *const *pick, int n, int threads)
     return 2.5 + std::max(longest, busy / 256.0 + 0.5 * longest);
 }
 
-// The launch of the calls' problems, or e->family = null where launches of their own are better or needed.
-static void group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, GroupEntry *e)
+// The launch of the calls' problems, or false where launches of their own are better or needed.
+static bool group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, GroupEntry *e)
 {
     const auto &tab = igemm_table();
     Problem pb[kGroupMax];
+    int own[kGroupMax];               // the variant that runs a call by itself, -1: not known
     size_t limit[kGroupMax];
-    double one_by_one = 0;
+    unsigned sig[kGroupMax];
     for (int i = 0; i < n; ++i) {
         const alt_conv_call_t &c = calls[i];
         limit[i] = c.workspace ? c.ws_bytes : 0;
-        if (conv_problem(h, c.d, c.x, c.w, c.bias, c.y, &pb[i]) != ALT_OK || pb[i].groups > 1 || pb[i].dtype != pb[0].dtype) return;
-        // (a tuned kernel runs; and the register-staged kernels' estimate is no time)
-        if (tuned_variant(h, pb[i], conv_key(h, c.d), limit[i]) >= 0) return;
-        const int v = igemm_default_variant(pb[i], limit[i]);
-        if (v < 0 || !tab[v / kNumSplits].launch_direct) return;
-        IgemmParams p = pb[i].p;
-        size_t lds = 0;
-        double family;
-        if (!applicable(pb[i], tab[v / kNumSplits], kSplits[v % kNumSplits], &p, nullptr, &lds)) return;
-        one_by_one += direct_estimate_us(pb[i], tab[v / kNumSplits], p, lds, &family);
+        sig[i] = align_sig(c.x, c.w, c.bias, c.y);
+        own[i] = -1;
+        if (const MemoEntry *m = memo_find(h, c.d, sizeof *c.d, sig[i], limit[i])) {
+            pb[i] = m->pb;
+            pb[i].p.x = c.x; pb[i].p.w = c.w; pb[i].p.bias = c.bias; pb[i].p.y = c.y;
+            own[i] = m->variant;
+        } else if (conv_problem(h, c.d, c.x, c.w, c.bias, c.y, &pb[i]) != ALT_OK) {
+            return false;
+        }
+        // (a tuned kernel runs)
+        if (pb[i].depthwise || pb[i].groups > 1 || pb[i].dtype != pb[0].dtype || tuned_variant(h, pb[i], conv_key(h, c.d), limit[i]) >= 0) return false;
     }
     const GroupFamily &f = pb[0].dtype == ALT_F32 ? group_f32() : pb[0].p.xc.si == 1 ? group_slab() : group_planar();
     std::vector<GroupPick> all[kGroupMax];
@@ -943,7 +952,25 @@ static void group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, Grou
                 all[i].push_back({c.alone / 2200.0, c.beside / 2200.0, (double)d.tiles_m * d.tiles_n * d.splitk, lds, t, kSplits[si], body});
             }
         }
-        if (all[i].empty()) return;
+        if (all[i].empty()) return false;
+    }
+    // What the calls take one by one.  Where that is the answer, the choices made for it are the calls' own.
+    auto singly = [&] {
+        for (int i = 0; i < n; ++i)
+            if (own[i] >= 0 && !memo_find(h, calls[i].d, sizeof *calls[i].d, sig[i], limit[i]))
+                memo_store(h, calls[i].d, sizeof *calls[i].d, sig[i], limit[i], pb[i], own[i]);
+        return false;
+    };
+    double one_by_one = 0;
+    for (int i = 0; i < n; ++i) {
+        if (own[i] < 0) own[i] = igemm_default_variant(pb[i], limit[i]);
+        // (the register-staged kernels' estimate is no time)
+        if (own[i] < 0 || !tab[own[i] / kNumSplits].launch_direct) return singly();
+        IgemmParams p = pb[i].p;
+        size_t lds = 0;
+        double family;
+        if (!applicable(pb[i], tab[own[i] / kNumSplits], kSplits[own[i] % kNumSplits], &p, nullptr, &lds)) return singly();
+        one_by_one += direct_estimate_us(pb[i], tab[own[i] / kNumSplits], p, lds, &family);
     }
     // For every bound on a workgroup's length, and on its LDS for one to four on a compute unit: of each problem the tile of least work.
     const GroupPick *best[kGroupMax];
@@ -966,7 +993,7 @@ static void group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, Grou
     // (launches of their own have all tiles to choose from and win for large layers: of 62 sets of five layers those predicted within 4 % took
     // 0.91 to 1.1 times as long one by one, and the rest, predicted faster together, 0.99 to 3.4 times; 256 images of 64 channels 371 us
     // one by one and 398 together, 128 of them 220 and 213, 16 of them 47 and 30, one 28 and 10.6)
-    if (best_us > 0.96 * one_by_one) return;
+    if (best_us > 0.96 * one_by_one) return singly();
     // the longest workgroups first
     for (int i = 0; i < n; ++i) e->order[i] = i;
     std::sort(e->order, e->order + n, [&](int a, int b) { return best[a]->alone > best[b]->alone; });
@@ -977,7 +1004,7 @@ static void group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, Grou
     for (int j = 0; j < n; ++j) {
         const int i = e->order[j];
         DconvParams &d = e->g.p[j];
-        if (at > 0x3fffffff || !dconv_setup(pb[i], f.tiles[best[i]->tile].k, best[i]->splitk, &d, nullptr, nullptr)) return;
+        if (at > 0x3fffffff || !dconv_setup(pb[i], f.tiles[best[i]->tile].k, best[i]->splitk, &d, nullptr, nullptr)) return singly();
         e->g.first[j] = (int32_t)at;
         e->g.body[j] = best[i]->body;
         const int64_t tiles = (int64_t)d.tiles_m * d.tiles_n;
@@ -987,9 +1014,105 @@ static void group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, Grou
         e->ws_need[i] = igemm_workspace(pb[i], d.splitk);
         e->x_bytes[i] = d.x_bytes; e->w_bytes[i] = d.w_bytes; e->y_bytes[i] = d.y_bytes;
     }
-    if (at > 0x7fffffff || sliced > kDconvMaxTiles) return;
+    if (at > 0x7fffffff || sliced > kDconvMaxTiles) return singly();
     e->workgroups = (unsigned)at;
     e->family = &f;
+    return true;
+}
+
+// The list's kept launch, or the one planned for it now; null: its calls go out one by one.  *kept: the answer was there.
+static GroupEntry *group_entry(alt_handle_t h, const alt_conv_call_t *calls, int n, bool *kept)
+{
+    // the descriptors without their layouts' primitives, which no convolution reads
+    constexpr size_t kPlain = offsetof(alt_conv_desc_t, x_layout), kLayout = offsetof(alt_layout_t, prims);
+    unsigned char key[kGroupMax * (kPlain + 3 * kLayout + sizeof(alt_conv_desc_t::groups) + sizeof(uint64_t) + sizeof(size_t))];
+    size_t len = 0;
+    auto put = [&](const void *p, size_t bytes) { std::memcpy(key + len, p, bytes); len += bytes; };
+    uint64_t tag = (uint64_t)n;       // of what differs most often
+    auto mix = [](uint64_t t, uint64_t v) { t = (t ^ v) * 0x9e3779b97f4a7c15ull; return t ^ (t >> 29); };
+    *kept = true;
+    for (int i = 0; i < n; ++i) {
+        const alt_conv_call_t &c = calls[i];
+        if (!c.d || !c.x || !c.w || !c.y || ((c.d->epilogue & ALT_EPI_BIAS) && !c.bias)) return nullptr;
+        if (c.d->variant >= 0) return nullptr;
+        const uint64_t sig = align_sig(c.x, c.w, c.bias, c.y);
+        const size_t limit = c.workspace ? c.ws_bytes : 0;
+        put(c.d, kPlain);
+        for (const alt_layout_t *l : {&c.d->x_layout, &c.d->w_layout, &c.d->y_layout}) put(l, kLayout);
+        put(&c.d->groups, sizeof c.d->groups);
+        put(&sig, sizeof sig);
+        put(&limit, sizeof limit);
+        tag = mix(mix(tag, (uint64_t)c.d->N << 32 ^ (uint64_t)c.d->H << 16 ^ (uint64_t)c.d->W), (uint64_t)c.d->C << 32 ^ (uint64_t)c.d->K << 8 ^ (uint64_t)c.d->R);
+        tag = mix(mix(tag, sig), limit);
+    }
+    if (!h->memo) h->memo = new alt_launch_memo();
+    alt_launch_memo &memo = *h->memo;
+    if (memo.group_gen != h->cache_gen) {
+        memo.groups.clear();
+        memo.singles.clear();
+        memo.next_group = memo.next_single = 0;
+        memo.group_gen = h->cache_gen;
+    }
+    for (GroupEntry &c : memo.groups)
+        if (c.tag == tag && c.key.size() == len && std::memcmp(c.key.data(), key, len) == 0) return &c;
+    uint64_t hash = 0;                // of the whole key, where it is asked for
+    auto whole = [&] {
+        if (hash) return hash;
+        uint64_t lane[4] = {1, 2, 3, 4}, word[4] = {0, 0, 0, 0};
+        for (size_t at = 0; at < len; at += sizeof word) {
+            std::memcpy(word, key + at, std::min(sizeof word, len - at));
+            for (int l = 0; l < 4; ++l) lane[l] = mix(lane[l], word[l]);
+        }
+        for (uint64_t l : lane) hash = mix(hash, l);
+        return hash;
+    };
+    for (const auto &c : memo.singles)
+        if (c.first == tag && c.second == whole()) return nullptr;
+    *kept = false;
+    GroupEntry e;
+    if (!group_plan(h, calls, n, &e)) {
+        const std::pair<uint64_t, uint64_t> single(tag, whole());
+        if (memo.singles.size() < kGroupSingles) memo.singles.push_back(single);
+        else { memo.singles[memo.next_single] = single; memo.next_single = (memo.next_single + 1) % kGroupSingles; }
+        return nullptr;
+    }
+    e.tag = tag;
+    e.key.assign(key, key + len);
+    if (memo.groups.size() < kGroupLaunches) { memo.groups.push_back(std::move(e)); return &memo.groups.back(); }
+    GroupEntry &place = memo.groups[memo.next_group];
+    memo.next_group = (memo.next_group + 1) % kGroupLaunches;
+    place = std::move(e);
+    return &place;
+}
+
+// (a call that writes what another reads or writes has to wait for it, as on the stream)
+static bool calls_meet(const GroupEntry &e, const alt_conv_call_t *calls, int n)
+{
+    struct Range { uintptr_t at; size_t bytes; };
+    auto meet = [](Range a, Range b) { return a.at < b.at + b.bytes && b.at < a.at + a.bytes; };
+    for (int i = 0; i < n; ++i) {
+        const alt_conv_call_t &c = calls[i];
+        const Range out[2] = {{(uintptr_t)c.y, e.y_bytes[i]}, {(uintptr_t)c.workspace, e.ws_need[i]}};
+        for (int j = 0; j < n; ++j) {
+            if (j == i) continue;
+            const alt_conv_call_t &o = calls[j];
+            const Range other[5] = {{(uintptr_t)o.x, e.x_bytes[j]}, {(uintptr_t)o.w, e.w_bytes[j]},
+                                    {(uintptr_t)o.bias, o.bias ? (size_t)o.d->K * 4 : 0}, {(uintptr_t)o.y, e.y_bytes[j]},
+                                    {(uintptr_t)o.workspace, e.ws_need[j]}};
+            for (const Range &a : out)
+                for (const Range &b : other)
+                    if (a.bytes && b.bytes && meet(a, b)) return true;
+        }
+    }
+    return false;
+}
+
+// The calls from the first on that may go out together: on one stream, as many as a launch takes.
+static int calls_together(const alt_conv_call_t *calls, int n)
+{
+    int m = 1;
+    while (m < kGroupMax && m < n && calls[m].stream == calls[0].stream) ++m;
+    return m;
 }
 
 // Issues the calls, all on one stream, as one launch and says so in *done, or leaves them alone.
@@ -997,49 +1120,9 @@ static alt_status_t multi_as_one(alt_handle_t h, const alt_conv_call_t *calls, i
 {
     *done = false;
     if (n < 2 || !h->has_gpu) return ALT_OK;
-    unsigned char key[kGroupMax * (sizeof(alt_conv_desc_t) + sizeof(unsigned) + sizeof(size_t))];
-    size_t len = 0;
-    for (int i = 0; i < n; ++i) {
-        const alt_conv_call_t &c = calls[i];
-        if (!c.d || !c.x || !c.w || !c.y || ((c.d->epilogue & ALT_EPI_BIAS) && !c.bias)) return ALT_OK;
-        if (c.d->variant >= 0) return ALT_OK;
-        const unsigned sig = align_sig(c.x, c.w, c.bias, c.y);
-        const size_t limit = c.workspace ? c.ws_bytes : 0;
-        std::memcpy(key + len, c.d, sizeof *c.d); len += sizeof *c.d;
-        std::memcpy(key + len, &sig, sizeof sig); len += sizeof sig;
-        std::memcpy(key + len, &limit, sizeof limit); len += sizeof limit;
-    }
-    if (!h->memo) h->memo = new alt_launch_memo();
-    GroupEntry *e = nullptr;
-    for (GroupEntry &c : h->memo->groups)
-        if (c.gen == h->cache_gen && c.key.size() == len && std::memcmp(c.key.data(), key, len) == 0) { e = &c; break; }
-    if (!e) {
-        constexpr size_t kGroups = 8;
-        auto &v = h->memo->groups;
-        if (v.size() < kGroups) { v.emplace_back(); e = &v.back(); }
-        else { e = &v[h->memo->next_group]; *e = GroupEntry(); h->memo->next_group = (h->memo->next_group + 1) % kGroups; }
-        group_plan(h, calls, n, e);
-        e->key.assign(key, key + len);
-        e->gen = h->cache_gen;
-    }
-    if (!e->family) return ALT_OK;
-    // (a call that writes what another reads or writes has to wait for it, as on the stream)
-    struct Range { uintptr_t at; size_t bytes; };
-    auto meet = [](Range a, Range b) { return a.at < b.at + b.bytes && b.at < a.at + a.bytes; };
-    for (int i = 0; i < n; ++i) {
-        const alt_conv_call_t &c = calls[i];
-        const Range out[2] = {{(uintptr_t)c.y, e->y_bytes[i]}, {(uintptr_t)c.workspace, e->ws_need[i]}};
-        for (int j = 0; j < n; ++j) {
-            if (j == i) continue;
-            const alt_conv_call_t &o = calls[j];
-            const Range other[5] = {{(uintptr_t)o.x, e->x_bytes[j]}, {(uintptr_t)o.w, e->w_bytes[j]},
-                                    {(uintptr_t)o.bias, o.bias ? (size_t)o.d->K * 4 : 0}, {(uintptr_t)o.y, e->y_bytes[j]},
-                                    {(uintptr_t)o.workspace, e->ws_need[j]}};
-            for (const Range &a : out)
-                for (const Range &b : other)
-                    if (a.bytes && b.bytes && meet(a, b)) return ALT_OK;
-        }
-    }
+    bool kept;
+    GroupEntry *e = group_entry(h, calls, n, &kept);
+    if (!e || calls_meet(*e, calls, n)) return ALT_OK;
     for (int j = 0; j < n; ++j) {
         const alt_conv_call_t &c = calls[e->order[j]];
         DconvParams &p = e->g.p[j];
@@ -1057,8 +1140,7 @@ alt_status_t alt_conv2d_multi(alt_handle_t h, const alt_conv_call_t *calls, int3
     if (!h) return ALT_INVALID_ARG;
     if (n < 0 || (n > 0 && !calls)) return fail(h, ALT_INVALID_ARG, "alt_conv2d_multi: bad call list");
     for (int32_t i = 0; i < n;) {
-        int32_t m = 1;                                     // calls on one stream
-        while (m < kGroupMax && i + m < n && calls[i + m].stream == calls[i].stream) ++m;
+        const int m = calls_together(calls + i, n - i);
         bool done = false;
         alt_status_t s = multi_as_one(h, calls + i, m, &done);
         for (int32_t j = i; j < i + m && !done; ++j) {
@@ -1067,6 +1149,27 @@ alt_status_t alt_conv2d_multi(alt_handle_t h, const alt_conv_call_t *calls, int3
             if (s != ALT_OK) return s;
         }
         if (s != ALT_OK) return s;
+        i += m;
+    }
+    return ALT_OK;
+}
+
+alt_status_t alt_conv2d_multi_plan(alt_handle_t h, const alt_conv_call_t *calls, int32_t n, alt_multi_plan_t *out)
+{
+    if (!h) return ALT_INVALID_ARG;
+    if (n < 0 || (n > 0 && (!calls || !out))) return fail(h, ALT_INVALID_ARG, "alt_conv2d_multi_plan: bad call list");
+    int32_t launch = 0;
+    for (int32_t i = 0; i < n;) {
+        const int m = calls_together(calls + i, n - i);
+        bool kept = false;
+        const GroupEntry *e = m > 1 ? group_entry(h, calls + i, m, &kept) : nullptr;
+        if (e && calls_meet(*e, calls + i, m)) e = nullptr;
+        for (int j = 0; j < m; ++j) out[i + j] = alt_multi_plan_t{e ? launch : launch + j, e ? e->family->code : 0, -1, 0, kept};
+        for (int j = 0; j < m && e; ++j) {
+            out[i + e->order[j]].body = e->g.body[j];
+            out[i + e->order[j]].slices = e->g.p[j].splitk;
+        }
+        launch += e ? 1 : m;
         i += m;
     }
     return ALT_OK;
