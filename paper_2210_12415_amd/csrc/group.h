@@ -37,6 +37,7 @@ struct GroupFamily {
     int code;                             // in alt_multi_plan_t
     const GroupTile *tiles;
     int ntiles, threads;
+    double line;                          // together up to this part of the time that the calls take one by one, both as estimated
     hipError_t (*launch)(const GroupParams &g, unsigned workgroups, size_t lds, hipStream_t st);
 };
 const GroupFamily &group_f32();           // fp32, NHWC

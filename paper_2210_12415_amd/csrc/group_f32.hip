@@ -37,11 +37,14 @@ int body(const DconvParams &p)
 }
 const GroupTile kTiles[] = {{tile(64, 64, 2, 2, 1, 3, 32), body<0, 32, 1>}, {tile(64, 32, 2, 1, 2, 4, 16), body<3, 16, 2>}};
 
+// (98 lists: together takes 0.56 to 0.91 up to here)
+constexpr double kLine = 0.96;
+
 }  // namespace
 
 const GroupFamily &group_f32()
 {
-    static const GroupFamily f = {1, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), F32::kThreads, &group_launch<F32>};
+    static const GroupFamily f = {1, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), F32::kThreads, kLine, &group_launch<F32>};
     return f;
 }
 

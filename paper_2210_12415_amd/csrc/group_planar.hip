@@ -36,11 +36,14 @@ const GroupTile kTiles[] = {
     {tile(64, 32, 2, 1, 4, 0), body<6>},  {tile(64, 32, 2, 1, 4, 1), body<6>},
 };
 
+// (64 random lists of two to eight: the few predicted above take 0.79 to 1.6 of the time one by one)
+constexpr double kLine = 0.96;
+
 }  // namespace
 
 const GroupFamily &group_planar()
 {
-    static const GroupFamily f = {3, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Planar::kThreads, &group_launch<Planar>};
+    static const GroupFamily f = {3, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Planar::kThreads, kLine, &group_launch<Planar>};
     return f;
 }
 

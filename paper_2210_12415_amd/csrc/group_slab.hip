@@ -49,11 +49,17 @@ const GroupTile kTiles[] = {
     {stream(64, 64, 2, 2), one_tap<7>}, {stream(128, 64, 4, 1), one_tap<8>},
 };
 
+// 90 sets of five layers and 136 random lists of two to eight, predicted at 0.7 to 1.4 of the time one by one: up to this line together takes 0.56 to 1.07 of it
+// (five layers of 172 images of 64 channels at 54 x 54 266 us, 288 one by one), beyond 0.72 to 1.3 (256 images at 56 x 56, predicted 1.03: 408 and 383).  The choice
+// takes 3.0 and 1.5 % longer than the better of both, at 0.96 4.1 and 3.0.  (The line goes with the estimate of the kernels for short reductions: it was
+// 0.96 while that was up to a third higher.)
+constexpr double kLine = 1.0;
+
 }  // namespace
 
 const GroupFamily &group_slab()
 {
-    static const GroupFamily f = {2, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Slab::kThreads, &group_launch<Slab>};
+    static const GroupFamily f = {2, kTiles, (int)(sizeof kTiles / sizeof kTiles[0]), Slab::kThreads, kLine, &group_launch<Slab>};
     return f;
 }
 

@@ -253,18 +253,20 @@ static double slab_estimate_us(const Problem &pb, const IgemmLaunch &k, const Ig
     return std::sqrt(std::cbrt(cube(us * us) + cube(mem * mem)));
 }
 
-// The same for the kernels of a short reduction: what a workgroup's loads (those past the operands' ends cost as much), products and stores take of
-// a compute unit, the chain that it is, rounds of as many as share one, and the tensors' way from and to memory.  Fitted over 9400 products
-// (K up to 256, batches of 1 to 900, 4 to 400 us) under all three tiles, rms 9.5 %; the choice among them takes 3.1 % longer than the best.
+// The same for the kernels of a short reduction: what a workgroup's loads (those past the operands' ends cost too), products, bias and stores (rows that
+// do not begin at 16 bytes cost nearly twice) take of a compute unit, the chain that it is, rounds of as many as share one, and the tensors' way from and
+// to memory.  Fitted over 5600 products and 1x1 layers (K up to 256, with and without bias, batches, 4 to 400 us) under all three tiles, rms 12 %.
+// (The fit before was over products without bias and large K alone, 30 % too high for 32 columns and as much too low for 96 with a bias: 238 of
+// the 5600 took over 5 % longer than without these kernels, 46 x 248 x 76 x 76 to 296 209 us instead of 144.)
 static double short_estimate_us(const IgemmLaunch &k, const IgemmParams &p, size_t lds)
 {
     const double rows = (double)p.M / p.tiles_m, cols = (double)p.Nc / p.tiles_n, stages = std::ceil(p.C / 64.0);
     const double rounds = (double)p.tiles_m * p.tiles_n * p.batch / 256.0;
     const double per_cu = std::max(1.0, std::min(std::floor(160.0 * 1024 / lds), k.BN <= 64 ? 4.0 : 3.0));
-    const double busy = ((rows + cols) * p.C * 2 + 0.94 * stages * (k.BM + k.BN) * 128) / 183.0 + rows * cols * 2 / 54.0 + stages * k.BN / 32 * 70.0;
-    const double work = busy * std::max(1.0, rounds) / 2200.0, chain = (4770.0 + busy) * std::max(1.0, rounds / per_cu) / 2200.0;
-    const double mem = 2.0 * p.batch * ((double)p.M * p.C + (double)p.Nc * p.C + (double)p.M * p.Nc) / 5.33e6;
-    return 3.45 + std::cbrt(work * work * work + chain * chain * chain + mem * mem * mem);
+    const double busy = (rows + cols) * p.C * 2 / 353.0 + stages * (k.BM + k.BN) * 128 / 127.0 + rows * cols * 2 / 35.7 * (p.Nc % 8 ? 1.85 : 1.0) +
+                        k.BN / 32 * (stages * 170.0 + (p.epilogue & ALT_EPI_BIAS ? 152.0 : 0.0));
+    const double work = busy * std::max(1.0, rounds), chain = (455.0 + 1.195 * busy) * std::max(1.0, rounds / per_cu);
+    return 2.49 + (work + chain) / 2200.0 + 2.0 * p.batch * ((double)p.M * p.C + (double)p.Nc * p.C + (double)p.M * p.Nc) / 17.7e6;
 }
 
 // Microseconds of a tile kernel.  *family: what the choice between families multiplies them with.
@@ -273,8 +275,9 @@ static double direct_estimate_us(const Problem &pb, const IgemmLaunch &k, const 
     *family = 0.05;
     if (k.stream == 4) return slab_estimate_us(pb, k, p, lds, one);
     if (k.stream == 5) {
-        // (a little before the others, whose estimates are low for few columns: 144 channels to 24 at 16 x 56 x 56 take 4.8 us here, 6.6 there)
-        *family = 0.047;
+        // (a little behind the others, whose estimates are 9 % high in the median over the same problems: at this factor the choice takes 2.3 % longer than
+        // the fastest, 0.736 of the time without these kernels, and 81 of 5600 problems take more than 5 % longer, at 0.05 1.7 %, 0.732 and 162)
+        *family = 0.054;
         return short_estimate_us(k, p, lds);
     }
     if (k.stream <= 1 && k.dtype == ALT_BF16) {
@@ -990,10 +993,8 @@ static bool group_plan(alt_handle_t h, const alt_conv_call_t *calls, int n, Grou
                 const double us = fits ? group_us(pick, n, f.threads) : 1e300;
                 if (us < best_us) { best_us = us; std::copy(pick, pick + n, best); }
             }
-    // (launches of their own have all tiles to choose from and win for large layers: of 62 sets of five layers those predicted within 4 % took
-    // 0.91 to 1.1 times as long one by one, and the rest, predicted faster together, 0.99 to 3.4 times; 256 images of 64 channels 371 us
-    // one by one and 398 together, 128 of them 220 and 213, 16 of them 47 and 30, one 28 and 10.6)
-    if (best_us > 0.96 * one_by_one) return singly();
+    // (launches of their own have all tiles to choose from and win for large layers)
+    if (best_us > f.line * one_by_one) return singly();
     // the longest workgroups first
     for (int i = 0; i < n; ++i) e->order[i] = i;
     std::sort(e->order, e->order + n, [&](int a, int b) { return best[a]->alone > best[b]->alone; });

@@ -92,3 +92,15 @@ def test_planar_layers_of_as_many_channel_steps_run_the_same_tile(h, widths):
 @pytest.mark.parametrize("M,N,K,family", [(47, 664, 3960, "_gg_"), (170, 1792, 3040, "_gv_"), (112, 1464, 704, "planar_"), (2291, 1600, 608, "planar_")])
 def test_products_with_contiguous_rows_of_a(h, M, N, K, family):
     assert family in h.gemm_variant_name(alt.gemm_desc(M, N, K, in_dtype=alt.BF16, out_dtype=alt.BF16, a_layout="MK->KM", b_layout="KN->NK"), -1)
+
+
+@pytest.mark.parametrize("N,C,H,K,epilogue,short", [
+    (46, 248, 76, 296, 3, False), (41, 176, 76, 224, 1, False), (14, 144, 38, 624, 0, False), (12, 200, 61, 568, 3, False), (44, 168, 72, 544, 1, False),
+    (4, 160, 81, 160, 1, False), (87, 72, 47, 224, 3, False), (42, 248, 73, 272, 1, False), (46, 88, 37, 208, 1, False),
+    (16, 24, 56, 144, 3, True), (16, 144, 56, 24, 1, True), (256, 256, 56, 64, 0, True), (64, 32, 56, 192, 3, True)])
+def test_one_tap_layers_of_few_channels(h, N, C, H, K, epilogue, short):
+    """The kernels for short reductions run layers with a bias and wide outputs only where they are the faster ones (those above took 1.2 to 1.45 times
+    as long as on the tile kernels)."""
+    d = alt.conv_desc(N, C, H, H, K, 1, 1, in_dtype=alt.BF16, out_dtype=alt.BF16, epilogue=epilogue,
+                      x_layout="NCHW->NHWC", w_layout="OIHW->OHWI", y_layout="NCHW->NHWC")
+    assert ("_short_" in h.conv2d_variant_name(d, -1)) == short
