@@ -2,6 +2,7 @@
 import pytest
 
 import paper_2210_12415_amd as alt
+from test_gpu_group import MORE, SETS, describe
 
 
 def call(i, N, C, H, K, R, dtype=alt.BF16, layout="NHWC", ws=1 << 26, W=None, pad=None, **more):
@@ -68,3 +69,24 @@ def test_windows_streams_and_buffers():
     two[1] = dict(two[1], x=nine[1]["x"], d=call(1, 1, 24, 10, 24, 3, variant=0)["d"])
     assert [(p.launch, p.kept) for p in h.conv2d_multi_plan(two)] == [(0, 1), (1, 1)]
     assert h.conv2d_multi_plan([]) == []
+
+
+@pytest.mark.parametrize("kind,family,bodies", [(("f32", "NHWC"), 1, 6), (("bf16", "NHWC"), 2, 9), (("bf16", "NCHW"), 3, 8)])
+def test_the_lists_run_on_the_gpu_reach_every_body(kind, family, bodies):
+    """.. and sums in slices, of one tap and of nine (channel-planar kernels take none)."""
+    h = alt.Handle()
+    dtype, layout = kind
+    reached, sliced = set(), set()
+    for problems in [SETS[kind]] + MORE[kind]:
+        calls = []
+        for i, problem in enumerate(problems):
+            d, ws_elems = describe(dtype, layout, problem, alt.F32 if dtype == "f32" or problems is SETS[kind] else alt.BF16)
+            at = (i + 1) << 40
+            calls.append(dict(d=d, x=at, w=at + (1 << 36), y=at + (2 << 36), bias=at + (5 << 36) if problem[7] else None, workspace=at + (3 << 36),
+                              ws_bytes=4 * ws_elems, stream=0))
+        plan = h.conv2d_multi_plan(calls)
+        assert all((p.launch, p.family) == (0, family) for p in plan)
+        reached |= {p.body for p in plan}
+        sliced |= {problem[5] for p, problem in zip(plan, problems) if p.slices > 1}
+    assert reached == set(range(bodies))
+    assert sliced == {"f32": {1, 3}, "bf16": {1} if layout == "NHWC" else set()}[dtype]

@@ -104,19 +104,39 @@ def test_slab_and_planar_kernels_do_not_branch_with_reads_in_flight(kernels, fam
         assert max(i for i, (_, op, _) in enumerate(code) if "mfma" in op) in most and max(most.values()) >= 2, name    # the loop was walked, with reads in flight
 
 
-@pytest.mark.parametrize("family,mfma_bodies,branching", [("F32", 6, 3 * 7 + 3 * 9), ("Slab", 9, 2 * 7), ("Planar", 8, 0)])
-def test_kernels_of_several_bodies_branch_for_the_stages_alone(kernels, family, mfma_bodies, branching):
-    """The same for every body of a kernel that holds several: its streaming bodies branch for the stages, the others not at all.  (A
-    body's epilogue lies between its last matrix instruction and the next one's; there the compiler keeps the waits of its own reads.)"""
+def bodies(code):
+    """(first, last) instruction of each body of a kernel that holds several, up to its last matrix instruction: what lies between that and the next
+    body's first one is its epilogue, which stores."""
+    last, stored, begin, out = None, False, 0, []
+    for i, (_, op, _) in enumerate(code):
+        if "mfma" in op:
+            if stored and last is not None:
+                out.append((begin, last))
+                begin = last + 1
+            last, stored = i, False
+        elif op.startswith(("buffer_store", "global_store")):
+            stored = True
+    return out + [(begin, last)]
+
+
+@pytest.mark.parametrize("family,most_branches", [("F32", [2 * 3 + 1] * 3 + [2 * 4 + 1] * 3), ("Slab", [0] * 7 + [2 * 3 + 1] * 2), ("Planar", [0] * 8)])
+def test_kernels_of_several_bodies_branch_for_the_stages_alone(kernels, family, most_branches):
+    """The same for every body of a kernel that holds several: a streaming body branches for its stages (3 or 4), the others not at all.  (Those of the
+    slab kernel are told by their products: nine taps.  In an epilogue the compiler keeps the waits of its own reads.)"""
     name, code = next((n, c) for n, c in kernels["group_kernel"].items() if n.endswith("::" + family))
-    store = [op.startswith(("buffer_store", "global_store")) for _, op, _ in code]
-    mfma = ["mfma" in op for _, op, _ in code]
-    most, found = {}, []
+    matters = [i for i, (_, op, _) in enumerate(code) if "mfma" in op or op.startswith(("buffer_store", "global_store"))]
+    most, branches = {}, []
     for i in branches_with_reads_in_flight(code, writes_end=False, most=most):
-        ahead = next(j for j in range(i, len(code)) if mfma[j] or store[j])
-        if mfma[ahead]:
-            found.append(i)
-    assert len(found) <= branching, name
-    assert max(i for i, m in enumerate(mfma) if m) in most and max(most.values()) >= 2, name
-    bodies = 1 + sum(1 for i in range(1, len(code)) if mfma[i] and any(store[j] for j in range(max(j for j in range(i) if mfma[j] or j == 0), i)))
-    assert bodies >= mfma_bodies, (name, bodies)
+        ahead = next(j for j in matters if j >= i)
+        if "mfma" in code[ahead][1]:
+            branches.append(i)
+    found = bodies(code)
+    assert len(found) == len(most_branches), (name, found)
+    counts = []
+    for first, last in found:
+        assert last in most and max(most.get(i, 0) for i in range(first, last)) >= 2, name      # the body was walked, with reads in flight
+        counts.append(sum(first <= i <= last for i in branches))
+        products = sum("mfma" in code[i][1] for i in range(first, last + 1))
+        if family == "Slab" and products % 9 == 0:
+            assert counts[-1] == 0, (name, first, last)
+    assert all(c <= m for c, m in zip(sorted(counts), most_branches)), (name, counts)
