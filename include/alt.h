@@ -316,7 +316,11 @@ typedef struct {
  * caller's (events or stream synchronisation).  Consecutive calls on one stream with
  * variant = -1 and no tuned kernel may go out as one launch (up to eight; bf16 NHWC or NCHW,
  * or fp32 NHWC, 3x3 and 1x1 filters among others): then the library chooses their tiles together, within
- * the workspaces given, and calls whose buffers overlap still run one after the other.
+ * the workspaces given, and calls whose buffers overlap still run one after the other.  Tile and slices
+ * decide the order in which an fp32 sum is taken, so a result is alt_conv2d's to the precision of that
+ * sum and not bit for bit, and its last bits can change with the other calls of the list, their
+ * workspaces and overlaps; the same list on the same buffers gives the same bits each time it goes out as one launch.
+ * A call that names a variant runs that kernel by itself.
  * The outputs and workspaces must not overlap.  Stops at the first call that fails and returns its status; the calls before
  * it stay issued. */
 alt_status_t alt_conv2d_multi(alt_handle_t h, const alt_conv_call_t *calls, int32_t n);

@@ -518,7 +518,7 @@ class Handle:
     def conv2d_multi_prepared(self, calls):
         """alt_conv2d_multi over `calls`, a list of dicts with the keyword arguments of
         conv2d (d, x, w, y and optionally bias, workspace, ws_bytes, stream), marshalled
-        once: returns a function of no arguments that issues them all."""
+        once: returns a function of no arguments that issues them all, and keeps the Handle and the arguments."""
         n = len(calls)
         arr = self._call_array(calls)
         keep = (self, [tuple(c.values()) for c in calls])

@@ -182,7 +182,10 @@ __device__ __forceinline__ void dplanar_body(const DconvParams &p, int bx)
         // planes' runs, transposes them 8x8 in registers and writes eight 16-byte channel chunks.  A set of 64
         // items is eight pixel blocks (lane % 8) x eight channel blocks (lane / 8): its loads cover 128
         // contiguous bytes of each plane, and each of its LDS writes covers every bank four times, which is the
-        // least a 16-byte-per-lane write takes.
+        // least a 16-byte-per-lane write takes where any lanes may go together.  Neighbouring lanes may not: they lie
+        // eight pixels apart, 1152 bytes at 64 channels, so that eight of them meet on two 16-byte slots of the
+        // banks.  (39 % of the LDS-active cycles of five layers of 16 images are conflicts; how many of them
+        // are these writes has not been measured.)
         const int g0 = a0 - halo;
         const int npb = npr >> 3;                          // pixel blocks
         const int npbg = (npb + 7) >> 3;                   // sets along the pixels; Cs / 64 along the channels

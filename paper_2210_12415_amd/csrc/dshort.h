@@ -9,9 +9,10 @@
 // Output rows may have any length: a lane stores eight columns at once, at any even address, and the last ones of a row one by one.
 // (The tile kernels of dstream.h store four aligned columns at least; other products ran on register-staged kernels.)
 //
-// Scores of 12 x 37 x 37 x 64 7.2 us before and 4.9, 120 x 367 x 367 x 64 29.6 and 13.3 (40 MB out: 3 TB/s), 260 x 280 x 280 x 64 36.4 and 14.0; 16 x
-// 56 x 56, 24 channels to 144 9.3 and 7.6 to 8.6, 144 to 24 6.6 and 4.8; 256 x 56 x 56, 256 to 64 118 and 113.5 (514 MB, 4.5 TB/s: every kernel
-// tried there ends between 112 and 120).  Over 3133 random products in its range the choice with this kernel takes 0.72 of the time without.
+// Without this kernel and with it: scores of 12 x 37 x 37 x 64 6.7 us and 3.5, 120 x 367 x 367 x 64 29.8 and 13.0 (40 MB out: 3 TB/s), 260 x 280 x 280 x 64
+// 36.7 and 13.7; 16 x 56 x 56, 24 channels to 144 with bias 8.8 and 7.5, 144 to 24 5.9 and 4.3; 256 x 56 x 56, 256 to 64 118 and 113.5 (411 MB fetched and 103 written, 4.5
+// TB/s: every kernel tried there ends between 112 and 120; two column tiles ask the L2s for 9.6 M lines, 58 % hits).  Over 5600 random products and 1x1
+// layers in its range the choice with this kernel takes 0.74 of the time without.
 #pragma once
 
 #include "dplanar.h"

@@ -189,7 +189,7 @@ __device__ __forceinline__ void dw_3x3_filter(const DwParams &p, int c, dw_words
 
 // The outputs of thread `t` of the 3x3 vector kernel once more, over the taps inside the image alone, if it stands at the border and
 // its filters hold an infinite or NaN value: the same sums with the filter cleared under taps outside.
-// (16 x 144 x 56 x 56 takes 8.9 us, with NaN inputs 9.9, with NaN filters 22.5; one element at a time it took 225, a row of outputs
+// (16 x 144 x 56 x 56 takes 7.5 us, with NaN inputs 8.3, with NaN filters 21.1; one element at a time it took 225, a row of outputs
 // at a time 19.1, but those 11 KB of code, never run, cost every pass through several kernels 1 %.)
 template <int STRIDE, int TW, int TH, bool TAPS, int POLICY>
 __device__ __forceinline__ void dw_3x3_inside(uint32_t t)
@@ -266,7 +266,7 @@ __device__ __forceinline__ void dw_3x3_inside(uint32_t t)
 // TAPS: the filter lies tap-contiguous (OHWI, OIHW: the nine taps of a channel side by side), so that eight
 // channels' taps are one run of 72 elements; they are loaded as nine vectors and transposed in registers.
 // Consecutive blocks run on one XCD, so that the rows two blocks share come out of one L2.
-// Measured on 16 x 144 x 56 x 56 (29 MB): 10.0 us, 2.9 TB/s; OHWI filters took the element kernel before, 137 us, and
+// Measured on 16 x 144 x 56 x 56 (29 MB): 7.5 us, 3.9 TB/s; OHWI filters took the element kernel before, 137 us, and
 // filters with the channel innermost a version of this one with a branch per load and one row per thread, 13.0 us.
 // POLICY: of the stores.  Outputs that the L2s could keep (32 MB) go through to memory as they are written, which leaves nothing to write back
 // between this kernel and the next: a block of 16 x 144 x 56 x 56 26.6 us before and 25.3 so, of 15 x 384 x 29 x 29 24.1 and 23.1; larger ones leave
@@ -490,8 +490,8 @@ alt_status_t depthwise_run(alt_handle_t h, const Problem &pb, int64_t N, int64_t
                       q.yw.f >= q.OW && images > 0;
     if (k3x3) {
         // Rows per thread.  Two share their windows' rows (24 loads for eight outputs against 36) where one row each
-        // would make more threads than the chip holds one wave of per SIMD: 16 x 144 x 56 x 56 takes 10.0 us with two
-        // and 11.5 with one, but 1 x 144 x 56 x 56 4.8 and 3.9.  At stride 2 they share one row of three, and the
+        // would make more threads than the chip holds one wave of per SIMD: 16 x 144 x 56 x 56 took 10.0 us with two
+        // and 11.5 with one (before outputs were written through), but 1 x 144 x 56 x 56 4.8 and 3.9.  At stride 2 they share one row of three, and the
         // registers they take cost more than that (16 x 96 x 112 x 112: 23 us with two, 12.0 with one).
         const int64_t items1 = N * q.OH * ((q.OW + kDwCols - 1) / kDwCols) * (C / 8);
         const int th = q.stride_h == 1 && items1 >= 65536 ? 2 : 1;

@@ -5,7 +5,7 @@
 // of up to kGroupMax problems are one grid: a workgroup finds its problem by its number and runs the body of a tile kernel
 // (dstream.h, dslab.h, dplanar.h) on that problem's parameters, so that all layers are in flight together and one's ends are covered by
 // another's sums.  Five layers of a ResNet in one call (64 channels at 56 x 56 and so on), one launch each before and one for all now: a batch of 1
-// 28.2 us and 10.6, of 16 in NCHW 72 and 48, of 5 in fp32 80 and 52.
+// 35 us and 10.8, of 16 in NCHW 71 and 48, of 5 in fp32 80 and 52.
 //
 // A family is a kernel that holds the bodies its problems choose from, with one number of threads.  Its registers are those of its
 // largest body, its LDS that of the largest problem of the launch.
